@@ -143,6 +143,8 @@ def force_kernel_name(prec: str, shape: dict) -> str:
     # template arguments: (targets per lane, torque, wall, periodic) for the symmetric kernel,
     # (torque, targets per lane, wall, periodic) for the ordered one
     if shape["symmetric"]:
+        if kind == "f64":
+            return "pair_kernel_f64_tiles<1, false, ..., true, false>"
         return f"pair_kernel_{kind}_sym<{shape['tpt']}, false, true, false>"
     return f"pair_kernel_{kind}<false, {shape['tpt']}, true, false>"
 

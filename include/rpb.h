@@ -346,7 +346,8 @@ void rpb_step_graph_destroy(rpb_graph *g);
 /* Launch-shape tuning ---------------------------------------------------------------------
  *
  * One shape per precision.  Single-system products: tpt, targets per lane of the pair kernels
- * (1, 2 or 4; 4 applies to the symmetric kernel, the ordered kernel then takes 2); target_wgs,
+ * (1, 2 or 4; 4 applies to the symmetric kernel, the ordered kernel then takes 2; in float64 the
+ * symmetric kernel takes at most tpt, at most 2, and picks its tile by n); target_wgs,
  * workgroups the ordered kernel aims for when splitting the sources into chunks; symmetric,
  * whole-system products use the symmetric tile-pair kernel (M_ij = M_ji^T: each unordered pair
  * evaluated once, both directions applied; with torques both coupling directions come from the

@@ -25,6 +25,7 @@
 #include <type_traits>
 
 #include "pair_common.h"
+#include "sym64.h"
 
 namespace rpb {
 
@@ -889,22 +890,6 @@ __global__ __launch_bounds__(kBlock) void pair_kernel_mixed_sym(SymArgs a, PartM
                                              int64_t(blockIdx.x) % a.nsplit, L, col);
 }
 
-template <int TPT, bool TORQUE, bool WALL, bool PERIODIC>
-__global__ __launch_bounds__(kBlock) void pair_kernel_f64_sym(SymArgs a, PartMap pm, GeomD g,
-                                                              const double *__restrict__ src,
-                                                              PairConsts<double> k_arg,
-                                                              double *__restrict__ partial) {
-  const PairConsts<double> k = vgpr_consts(k_arg);
-  if (a.skip && *a.skip) return;
-  __shared__ LdsD<TORQUE> L;
-  __shared__ double col[kWaves][kBlock][3];
-  int64_t I, J;
-  const int64_t Lp = pm.L0 + int64_t(blockIdx.x) / a.nsplit;
-  tri_decode(Lp, a.nt, I, J);
-  sym_tile_pair<TPT, TORQUE, WALL, PERIODIC>(a, g, src, k, partial, pm, Lp, I, J,
-                                             int64_t(blockIdx.x) % a.nsplit, L, col);
-}
-
 // kRedGroups threads per (component, row), 64 rows per workgroup (one wavefront per group):
 // the partials of the chunk [pm.L0, L1) dealt over the groups (chunk_row_sum_dealt) and the
 // group sums added in a fixed order, written to vel on the first chunk and added to it on the
@@ -1426,9 +1411,55 @@ void with_sym_variant(bool torque, int tpt, bool wall, bool periodic, Fn &&fn) {
   with_variant(torque, tpt, wall, periodic, fn);
 }
 
+// Tile of the float64 symmetric kernel: targets per lane (at most tpt), wavefronts along the
+// targets and wavefronts per workgroup; tiles of 64 wt tpt spheres.
+struct TileShape {
+  int tpt, wt, waves;
+};
+
+// Small tiles give a small system enough workgroups (n^2 / (2 tile^2) of them); large ones spend
+// less on the rotation (two targets per lane share its moves and LDS reads) and write fewer
+// partial sums (n / tile per row).  Force-only products, us, tiles of 64 / 128 / 256 / 512:
+//   2,100: 18.9 / 23.6 / 66 / 228      4,099: 40.5 / 44 / 68 / 228     8,191: 126 / 115 / 145 / 231
+//   16,384: 472 / 372 / 385 / 508      32,768: 1824 / 1395 / 1377 / 1484
+//   65,536: 6849 / 5620 / 5381 / 5431
+// With one target per lane, 64 / 256: 8,191: 126 / 176, 16,384: 472 / 449.  (Four targets per lane,
+// tiles of 1,024, were slower at every size: 6614 us at 65,536.)
+// Below 1,500 spheres (300 pairs of 64-sphere tiles) a pair's 64 rotation steps are dealt to eight
+// wavefronts instead of four (256: 10.9 -> 9.3 us, 1,024: 11.4 -> 10.1; 2,100: 17.9 and 17.5,
+// with torques 21.6 and 24.4).
+inline TileShape sym64_shape(int64_t n, int tpt) {
+  if (n < 1500) return TileShape{1, 1, 8};
+  if (tpt == 1) return n < 12000 ? TileShape{1, 1, 4} : TileShape{1, 4, 4};
+  if (n < 6000) return TileShape{1, 1, 4};
+  if (n < 24000) return TileShape{2, 1, 4};
+  return n < 96000 ? TileShape{2, 2, 4} : TileShape{2, 4, 4};
+}
+
+// Calls fn(tpt, wt, waves) with the three as std::integral_constant values.
+template <typename Fn>
+void with_tile(TileShape t, Fn &&fn) {
+  using C8 = std::integral_constant<int, 8>;
+  using C1 = std::integral_constant<int, 1>;
+  using C2 = std::integral_constant<int, 2>;
+  using C4 = std::integral_constant<int, 4>;
+  if (t.tpt == 2 && t.wt == 4)
+    fn(C2{}, C4{}, C4{});
+  else if (t.tpt == 2 && t.wt == 2)
+    fn(C2{}, C2{}, C4{});
+  else if (t.tpt == 2)
+    fn(C2{}, C1{}, C4{});
+  else if (t.wt == 4)
+    fn(C1{}, C4{}, C4{});
+  else if (t.waves == 8)
+    fn(C1{}, C1{}, C8{});
+  else
+    fn(C1{}, C1{}, C4{});
+}
+
 // Whole-system product with one evaluation per unordered pair.  The triangle of tile pairs is
 // walked in chunks whose partials fit the context's limit (512 MiB: one chunk up to about
-// 150,000 spheres in mixed precision and 100,000 in float64 at 2 targets per lane), each
+// 150,000 spheres in mixed precision at 2 targets per lane and 75,000 in float64), each
 // chunk's pair kernel followed by its reduction into vel, so the workspace stays bounded
 // whatever n.  The timing record spans the pair kernels of all chunks.
 int matvec_symmetric(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const void *src,
@@ -1436,10 +1467,11 @@ int matvec_symmetric(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const v
                      const int *skip) {
   const int64_t n = g.n;
   const bool f64 = g.precision == RPB_FP64;
-  SymArgs a{n, int64_t(kBlock) * tpt, 0, n};
+  const TileShape tile = sym64_shape(n, tpt);
+  SymArgs a{n, f64 ? int64_t(64) * tile.wt * tile.tpt : int64_t(kBlock) * tpt, 0, n};
   a.skip = skip;
   a.nt = (n + a.ts - 1) / a.ts;
-  a.nsplit = sym_nsplit(n, a.ts);
+  a.nsplit = f64 ? 1 : sym_nsplit(n, a.ts);
   const int64_t pairs = a.nt * (a.nt + 1) / 2;
   const size_t esz = f64 ? sizeof(double) : sizeof(float);
   const int64_t per = chunk_pairs(pairs, a.nsplit, 1, a.ts, esz, ctx->chunk_bytes);
@@ -1451,20 +1483,27 @@ int matvec_symmetric(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const v
   RPB_TRY(timing_begin(ctx, stream, &t0));
   for (int64_t L0 = 0; L0 < pairs; L0 += per) {
     const int64_t L1 = std::min(pairs, L0 + per);
-    const PartMap pm{L0, a.nsplit, a.ts, 1};
+    const PartMap pm{L0, a.nsplit, a.ts, 1, f64 ? 1 : 0};
     const unsigned grid = unsigned((L1 - L0) * a.nsplit);
-    with_sym_variant(torque, tpt, p->wall != 0, periodic(p), [&](auto T, auto P, auto W, auto B) {
-      constexpr bool kT = decltype(T)::value, kW = decltype(W)::value, kB = decltype(B)::value;
-      constexpr int kP = decltype(P)::value;
-      if (f64)
-        pair_kernel_f64_sym<kP, kT, kW, kB><<<grid, kBlock, 0, stream>>>(
-            a, pm, geom_d(g), static_cast<const double *>(src),
-            make_pair_consts<double>(p->lx / p->a, p->ly / p->a), static_cast<double *>(part));
-      else
+    if (f64)
+      with_variant(torque, 1, p->wall != 0, periodic(p), [&](auto T, auto, auto W, auto B) {
+        constexpr bool kT = decltype(T)::value, kW = decltype(W)::value, kB = decltype(B)::value;
+        with_tile(tile, [&](auto P, auto Q, auto N) {
+          constexpr int kP = decltype(P)::value, kQ = decltype(Q)::value;
+          constexpr int kN = decltype(N)::value;
+          pair_kernel_f64_tiles<1, kT, kP, kQ, kN, kW, kB><<<grid, 64 * kN, 0, stream>>>(
+              a, pm, geom_d(g), static_cast<const double *>(src),
+              make_pair_consts<double>(p->lx / p->a, p->ly / p->a), static_cast<double *>(part));
+        });
+      });
+    else
+      with_sym_variant(torque, tpt, p->wall != 0, periodic(p), [&](auto T, auto P, auto W, auto B) {
+        constexpr bool kT = decltype(T)::value, kW = decltype(W)::value, kB = decltype(B)::value;
+        constexpr int kP = decltype(P)::value;
         pair_kernel_mixed_sym<kP, kT, kW, kB><<<grid, kBlock, 0, stream>>>(
             a, pm, geom_f(g), static_cast<const float *>(src),
             make_pair_consts<float>(p->lx / p->a, p->ly / p->a), static_cast<float *>(part));
-    });
+      });
     RPB_LAUNCHED(ctx);
     if (L1 == pairs)
       RPB_TRY(timing_end(ctx, stream, t0, double(n) * double(n),

@@ -105,6 +105,7 @@ struct PartMap {
   int64_t nsplit;   // source parts per tile pair
   int64_t ts;       // rows per tile
   int V;            // vectors per slot
+  int diag = 0;     // 1: the column slot of a diagonal pair (I, I) holds sums of I's rows too
 };
 
 __host__ __device__ __forceinline__ int64_t part_elem(const PartMap &m, int64_t L, int64_t sub,
@@ -131,7 +132,8 @@ __device__ __forceinline__ double chunk_row_sum(const Part *__restrict__ p, cons
   double s[4] = {0.0, 0.0, 0.0, 0.0};
   int k = 0;
   auto Lcol = [&](int64_t I) { return tri_start(I, nt) + T - I; };
-  int64_t lo = 0, hi = T;
+  const int64_t Tc = T + m.diag;   // column slots of pairs (I, T), I < Tc
+  int64_t lo = 0, hi = Tc;
   while (lo < hi) {   // first I with L(I, T) >= L0
     const int64_t mid = (lo + hi) / 2;
     if (Lcol(mid) >= m.L0)
@@ -140,7 +142,7 @@ __device__ __forceinline__ double chunk_row_sum(const Part *__restrict__ p, cons
       lo = mid + 1;
   }
   const int64_t i0 = lo;
-  hi = T;
+  hi = Tc;
   while (lo < hi) {   // first I with L(I, T) >= L1
     const int64_t mid = (lo + hi) / 2;
     if (Lcol(mid) >= L1)
@@ -175,7 +177,8 @@ __device__ __forceinline__ double chunk_row_sum_dealt(const Part *__restrict__ p
                                                       int64_t T, int64_t local, int c, int g,
                                                       int G) {
   auto Lcol = [&](int64_t I) { return tri_start(I, nt) + T - I; };
-  int64_t lo = 0, hi = T;
+  const int64_t Tc = T + m.diag;   // column slots of pairs (I, T), I < Tc
+  int64_t lo = 0, hi = Tc;
   while (lo < hi) {   // first I with L(I, T) >= L0
     const int64_t mid = (lo + hi) / 2;
     if (Lcol(mid) >= m.L0)
@@ -184,7 +187,7 @@ __device__ __forceinline__ double chunk_row_sum_dealt(const Part *__restrict__ p
       lo = mid + 1;
   }
   const int64_t i0 = lo;
-  hi = T;
+  hi = Tc;
   while (lo < hi) {   // first I with L(I, T) >= L1
     const int64_t mid = (lo + hi) / 2;
     if (Lcol(mid) >= L1)
