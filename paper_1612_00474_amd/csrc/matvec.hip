@@ -894,8 +894,6 @@ __global__ __launch_bounds__(kBlock) void pair_kernel_mixed_sym(SymArgs a, PartM
 // the partials of the chunk [pm.L0, L1) dealt over the groups (chunk_row_sum_dealt) and the
 // group sums added in a fixed order, written to vel on the first chunk and added to it on the
 // others; after the last chunk the sum is scaled by H_i / (8 pi eta a).
-constexpr int kRedGroups = 8;
-
 template <typename Part>
 __global__ __launch_bounds__(64 * kRedGroups) void reduce_sym_chunk(
     SymArgs a, PartMap pm, int64_t L1, int first, int last, const Part *__restrict__ partial,
@@ -908,7 +906,7 @@ __global__ __launch_bounds__(64 * kRedGroups) void reduce_sym_chunk(
   const int d = live ? int(e / a.n) : 0;
   const int64_t r = live ? e - int64_t(d) * a.n : 0;
   sh[grp * 64 + lane] =
-      live ? chunk_row_sum_dealt(partial, pm, a.nt, L1, r / a.ts, r % a.ts, d, grp, kRedGroups)
+      live ? chunk_row_sum_dealt(partial, pm, a.nt, L1, r / a.ts, r % a.ts, 0, d, grp, kRedGroups)
            : 0.0;
   __syncthreads();
   if (grp != 0 || !live) return;

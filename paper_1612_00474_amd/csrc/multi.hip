@@ -8,22 +8,23 @@
 // evaluation serves every vector: about half the work of a symmetric pair update is the
 // coefficients, the rest is applying them to a vector.
 //
-// Layout: the symmetric tile-pair scheme of the single-vector product, one target per lane
-// (tile = kBlock spheres), K = 2, 3 or 4 vectors per launch, the first optionally with a torque:
+// Layout: the symmetric tile-pair scheme of the single-vector product, one target per lane, K = 1
+// to 4 vectors per launch, the first optionally with a torque:
 //   pack_multi    O(N K)    AoS float64 vectors -> SoA H-weighted sources src[(k 3 + c) n + i]
-//   pair kernel   O(N^2)    tile pair (I, J), I <= J, per workgroup: M_IJ F_J into the rows of
+//   pair kernel   O(N^2)    float64: pair_kernel_f64_tiles (sym64.h).  Mixed: tile pair (I, J), I <= J, per workgroup: M_IJ F_J into the rows of
 //                           I (lane sums), M_JI F_I into the rows of J (rotating per-source sums
 //                           added across the workgroup's wavefronts in LDS); diagonal tiles as
 //                           ordered pairs.  Each pair's coefficients are computed once.  Batches
 //                           of systems: persistent workgroups map a work-item number to
 //                           (system, I, J).
-//   reduce_multi  O(N^2/256) fixed-order sum of the tile partials, times H_i / (8 pi eta a).
+//   reduce_multi  O(N^2/tile) fixed-order sum of the tile partials, times H_i / (8 pi eta a).
 #include <algorithm>
 #include <cmath>
 #include <type_traits>
 #include <vector>
 
 #include "pair_common.h"
+#include "sym64.h"
 
 namespace rpb {
 
@@ -76,25 +77,12 @@ struct MultiLdsF {
   float f[src_rows<K, TQ>()][kBlock];
   float col[kWaves][3 * K][64];   // per-wavefront sums for one 64-source block
 };
-template <int K, bool TQ>
-struct MultiLdsD {
-  double x[kBlock], y[kBlock], z[kBlock];
-  double f[src_rows<K, TQ>()][kBlock];
-  double col[kWaves][3 * K][64];
-};
-
 struct TgtF {
   float xh, xl, yh, yl, z;
-};
-struct TgtD {
-  double x, y, z;
 };
 
 __device__ __forceinline__ TgtF target_of(const GeomF &g, int64_t i) {
   return {g.xh[i], g.xl[i], g.yh[i], g.yl[i], g.z[i]};
-}
-__device__ __forceinline__ TgtD target_of(const GeomD &g, int64_t i) {
-  return {g.x[i], g.y[i], g.z[i]};
 }
 template <typename Lds>
 __device__ __forceinline__ void stage(Lds &L, const GeomF &g, int64_t j, int s) {
@@ -104,12 +92,6 @@ __device__ __forceinline__ void stage(Lds &L, const GeomF &g, int64_t j, int s) 
   L.yl[s] = g.yl[j];
   L.z[s] = g.z[j];
 }
-template <typename Lds>
-__device__ __forceinline__ void stage(Lds &L, const GeomD &g, int64_t j, int s) {
-  L.x[s] = g.x[j];
-  L.y[s] = g.y[j];
-  L.z[s] = g.z[j];
-}
 // In-plane separation r_i - r_j (mixed: hi and lo parts subtracted separately).
 template <typename Lds>
 __device__ __forceinline__ void separation(const TgtF &t, const Lds &L, int j, float &dx,
@@ -117,13 +99,6 @@ __device__ __forceinline__ void separation(const TgtF &t, const Lds &L, int j, f
   dx = (t.xh - L.xh[j]) + (t.xl - L.xl[j]);
   dy = (t.yh - L.yh[j]) + (t.yl - L.yl[j]);
 }
-template <typename Lds>
-__device__ __forceinline__ void separation(const TgtD &t, const Lds &L, int j, double &dx,
-                                           double &dy) {
-  dx = t.x - L.x[j];
-  dy = t.y - L.y[j];
-}
-
 // Coefficients of pair (i, j): the far-field form alone for pairs at least 2a apart, the
 // complete form for closer ones (including the self pair, r = 0).
 template <bool TQ, bool WALL, typename Real>
@@ -264,39 +239,42 @@ __global__ __launch_bounds__(kBlock) void pair_kernel_mixed_multi(SymArgs a, Par
   multi_tile_pair<K, TQ, WALL>(a, g, src, k, partial, pm, Lp, I, J, L);
 }
 
-template <int K, bool TQ, bool WALL>
-__global__ __launch_bounds__(kBlock) void pair_kernel_f64_multi(SymArgs a, PartMap pm, GeomD g,
-                                                                const double *__restrict__ src,
-                                                                PairConsts<double> k_arg,
-                                                                double *__restrict__ partial) {
-  const PairConsts<double> k = vgpr_consts(k_arg);
-  __shared__ MultiLdsD<K, TQ> L;
-  int64_t I, J;
-  const int64_t Lp = pm.L0 + int64_t(blockIdx.x);
-  tri_decode(Lp, a.nt, I, J);
-  multi_tile_pair<K, TQ, WALL>(a, g, src, k, partial, pm, Lp, I, J, L);
-}
-
-// One thread per (vector slot, component, row): the chunk's partials added in a fixed order
-// (chunk_row_sum), written to out.p[v] ([n][3]) on the first chunk and added on the others,
-// scaled by H_i / (8 pi eta a) after the last.
+// kRedGroups threads per (vector slot, component, row), 64 rows per workgroup: the chunk's
+// partials dealt over the groups (chunk_row_sum_dealt), the group sums added in a fixed order,
+// written to out.p[v] ([n][3]) on the first chunk and added on the others, scaled by H_i / (8 pi
+// eta a) after the last.
 template <int K, typename Part>
-__global__ void reduce_multi(SymArgs a, PartMap pm, int64_t L1, int first, int last,
-                             OutPtrs<K> out, const Part *__restrict__ partial,
-                             const double *__restrict__ h, double scale) {
-  const int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+__global__ __launch_bounds__(64 * kRedGroups) void reduce_multi(
+    SymArgs a, PartMap pm, int64_t L1, int first, int last, OutPtrs<K> out,
+    const Part *__restrict__ partial, const double *__restrict__ h, double scale) {
+  __shared__ double sh[kRedGroups * 64];
+  const int lane = threadIdx.x & 63, grp = threadIdx.x >> 6;
+  const int64_t e = int64_t(blockIdx.x) * 64 + lane;
   const int64_t per = 3 * a.n;
-  if (e >= K * per) return;
-  const int v = int(e / per);
-  const int64_t rem = e - int64_t(v) * per;
+  const bool in = e < K * per;
+  const int v = in ? int(e / per) : 0;
+  const int64_t rem = in ? e - int64_t(v) * per : 0;
   const int d = int(rem / a.n);
   const int64_t r = rem - int64_t(d) * a.n;
   double *dst = out.p[v];
-  if (!dst) return;
-  double x = chunk_row_sum(partial, pm, a.nt, L1, r / kBlock, r % kBlock, v, d);
+  const bool live = in && dst;
+  sh[grp * 64 + lane] =
+      live ? chunk_row_sum_dealt(partial, pm, a.nt, L1, r / a.ts, r % a.ts, v, d, grp, kRedGroups)
+           : 0.0;
+  __syncthreads();
+  if (grp != 0 || !live) return;
+  double x = sh[lane];
+  for (int q = 1; q < kRedGroups; ++q) x += sh[q * 64 + lane];
   if (!first) x += dst[3 * r + d];
   dst[3 * r + d] = last ? scale * h[r] * x : x;
 }
+
+// Wavefronts along the targets of the float64 tiles (64 of them each, one target per lane): small
+// tiles fill the device, large ones write fewer partials.  Four vectors, us, tiles of 64 / 128 /
+// 256:  1,100: 17 / 44 / 135   4,099: 74 / 91 / 141   8,191: 234 / 229 / 296
+//       16,384: 909 / 772 / 813   65,536: 15486 / 12862 / 12021
+// (tiles of 256 on every size before: 110 us at 1,100; one to three vectors cross alike).
+inline int multi_wt(int64_t n) { return n < 7000 ? 1 : n < 28000 ? 2 : 4; }
 
 // One product of K vectors: sources in.p[k] (slot 0 with torque `torque` when TQ), results to
 // out.p[k].  The triangle of tile pairs is walked in chunks whose partials fit the context's
@@ -308,12 +286,14 @@ int multi_launch(rpb_ctx *ctx, const rpb_params *p, const Packed &g, SrcPtrs<K> 
                  const double *torque, OutPtrs<K> out, hipStream_t stream) {
   const int64_t n = g.n;
   const bool f64 = g.precision == RPB_FP64;
-  SymArgs a{n, kBlock, (n + kBlock - 1) / kBlock, n};
+  const int wt = multi_wt(n);
+  const int64_t ts = f64 ? 64 * wt : kBlock;
+  SymArgs a{n, ts, (n + ts - 1) / ts, n};
   const int64_t pairs = a.nt * (a.nt + 1) / 2;
   const size_t esz = f64 ? sizeof(double) : sizeof(float);
-  const int64_t per_chunk = chunk_pairs(pairs, 1, K, kBlock, esz, ctx->chunk_bytes);
+  const int64_t per_chunk = chunk_pairs(pairs, 1, K, ts, esz, ctx->chunk_bytes);
   int st;
-  void *part = workspace(ctx, WS_PART, size_t(part_elems(per_chunk, 1, K, kBlock)) * esz, &st);
+  void *part = workspace(ctx, WS_PART, size_t(part_elems(per_chunk, 1, K, ts)) * esz, &st);
   if (!part) return st;
   void *src = workspace(ctx, WS_SRC, size_t(src_rows<K, TQ>()) * size_t(n) * esz, &st);
   if (!src) return st;
@@ -334,17 +314,30 @@ int multi_launch(rpb_ctx *ctx, const rpb_params *p, const Packed &g, SrcPtrs<K> 
   const bool wall = p->wall != 0;
   for (int64_t L0 = 0; L0 < pairs; L0 += per_chunk) {
     const int64_t L1 = std::min(pairs, L0 + per_chunk);
-    const PartMap pm{L0, 1, kBlock, K};
+    const PartMap pm{L0, 1, ts, K, f64 ? 1 : 0};
     const unsigned grid = unsigned(L1 - L0);
     if (f64) {
       const auto k = make_pair_consts<double>();
       const auto *s = static_cast<const double *>(src);
       auto *pt = static_cast<double *>(part);
+      auto launch = [&](auto W, auto Q) {
+        constexpr bool kW = decltype(W)::value;
+        constexpr int kQ = decltype(Q)::value;
+        pair_kernel_f64_tiles<K, TQ, 1, kQ, kWaves, kW, false><<<grid, kBlock, 0, stream>>>(
+            a, pm, geom_d(g), s, k, pt);
+      };
+      auto by_tile = [&](auto W) {
+        if (wt == 1)
+          launch(W, std::integral_constant<int, 1>{});
+        else if (wt == 2)
+          launch(W, std::integral_constant<int, 2>{});
+        else
+          launch(W, std::integral_constant<int, 4>{});
+      };
       if (wall)
-        pair_kernel_f64_multi<K, TQ, true><<<grid, kBlock, 0, stream>>>(a, pm, geom_d(g), s, k, pt);
+        by_tile(std::true_type{});
       else
-        pair_kernel_f64_multi<K, TQ, false><<<grid, kBlock, 0, stream>>>(a, pm, geom_d(g), s, k,
-                                                                        pt);
+        by_tile(std::false_type{});
     } else {
       const auto k = make_pair_consts<float>();
       const auto *s = static_cast<const float *>(src);
@@ -360,13 +353,13 @@ int multi_launch(rpb_ctx *ctx, const rpb_params *p, const Packed &g, SrcPtrs<K> 
     if (L1 == pairs)
       RPB_TRY(timing_end(ctx, stream, t0, double(n) * double(n) * used, 8 + (f64 ? 0 : 2)));
     const int first = L0 == 0, last = L1 == pairs;
-    const unsigned rgrid = blocks_for(int64_t(K) * 3 * n, 256);
+    const unsigned rgrid = blocks_for(int64_t(K) * 3 * n, 64);
     if (f64)
-      reduce_multi<K, double><<<rgrid, 256, 0, stream>>>(a, pm, L1, first, last, out,
+      reduce_multi<K, double><<<rgrid, 64 * kRedGroups, 0, stream>>>(a, pm, L1, first, last, out,
                                                          static_cast<const double *>(part), h,
                                                          scale);
     else
-      reduce_multi<K, float><<<rgrid, 256, 0, stream>>>(a, pm, L1, first, last, out,
+      reduce_multi<K, float><<<rgrid, 64 * kRedGroups, 0, stream>>>(a, pm, L1, first, last, out,
                                                         static_cast<const float *>(part), h,
                                                         scale);
     RPB_LAUNCHED(ctx);
@@ -482,18 +475,18 @@ __global__ __launch_bounds__(kBlock) void pair_kernel_mixed_multi_batched(
 
 template <int K, bool TQ, bool WALL>
 __global__ __launch_bounds__(kBlock) void pair_kernel_f64_multi_batched(
-    MultiBatchArgs b, GeomD g, const double *__restrict__ src, PairConsts<double> k_arg,
+    MultiBatchArgs b, GeomD g, const double *__restrict__ src, PairConsts<double> k,
     double *__restrict__ partial) {
-  const PairConsts<double> k = vgpr_consts(k_arg);
-  __shared__ MultiLdsD<K, TQ> L;
+  __shared__ Sym64Lds<K, TQ, 1, kWaves, kWaves> L;
   __shared__ int slot[1];
-  const PartMap pm{0, 1, kBlock, K};
+  const PartMap pm{0, 1, kBlock, K, 1};
   int s;
   int64_t Lp, I, J;
   while (next_multi_item(b, slot, s, Lp, I, J)) {
     const int64_t s0 = b.offs[s];
-    multi_tile_pair<K, TQ, WALL>(multi_args_of(b, s), offset_geom(g, s0), src + s0, k,
-                                 partial + b.base[s], pm, Lp, I, J, L);
+    sym64_tile_pair<K, TQ, 1, kWaves, kWaves, WALL, false>(multi_args_of(b, s), offset_geom(g, s0),
+                                                           src + s0, k, partial + b.base[s], pm,
+                                                           Lp, I, J, L);
   }
 }
 
@@ -513,7 +506,7 @@ __global__ void reduce_multi_batched(MultiBatchArgs b, const int *__restrict__ s
   const int s = sys_of[r];
   const SymArgs a = multi_args_of(b, s);
   const int64_t local = r - b.offs[s];
-  const PartMap pm{0, 1, kBlock, K};
+  const PartMap pm{0, 1, kBlock, K, std::is_same<Part, double>::value ? 1 : 0};
   dst[3 * r + d] = scale * h[r] *
                    chunk_row_sum(partial + b.base[s], pm, a.nt, a.nt * (a.nt + 1) / 2,
                                  local / kBlock, local % kBlock, v, d);
@@ -540,18 +533,27 @@ int matvec_multi(rpb_ctx *ctx, const rpb_params *p, const Packed &g, int nvec, c
   std::vector<int> ids;
   for (int v = 0; v < nvec; ++v)
     if (!done || !done[v]) ids.push_back(v);
-  for (size_t g0 = 0; g0 < ids.size(); g0 += kMulti) {
-    SrcPtrs<kMulti> in;
-    OutPtrs<kMulti> out;
-    for (int s = 0; s < kMulti; ++s) {
-      const bool on = g0 + s < ids.size();
-      const size_t off = on ? size_t(ids[g0 + s]) * 3 * n : 0;
-      in.p[s] = on ? force + off : nullptr;
-      out.p[s] = on ? vel + off : nullptr;
+  // four vectors per launch, the rest (one to three) in a launch of its own size
+  auto group = [&](size_t g0, auto C) -> int {
+    constexpr int K = decltype(C)::value;
+    SrcPtrs<K> in;
+    OutPtrs<K> out;
+    for (int s = 0; s < K; ++s) {
+      const size_t off = size_t(ids[g0 + s]) * 3 * n;
+      in.p[s] = force + off;
+      out.p[s] = vel + off;
     }
-    RPB_TRY((multi_launch<kMulti, false>(ctx, p, g, in, nullptr, out, stream)));
+    return multi_launch<K, false>(ctx, p, g, in, nullptr, out, stream);
+  };
+  size_t g0 = 0;
+  for (; g0 + kMulti <= ids.size(); g0 += kMulti)
+    RPB_TRY(group(g0, std::integral_constant<int, kMulti>{}));
+  switch (ids.size() - g0) {
+    case 1: return group(g0, std::integral_constant<int, 1>{});
+    case 2: return group(g0, std::integral_constant<int, 2>{});
+    case 3: return group(g0, std::integral_constant<int, 3>{});
+    default: return RPB_OK;
   }
-  return RPB_OK;
 }
 
 bool matvec_first_supported(const rpb_params *p, int64_t n) { return p->lx <= 0.0 && n > 0; }

@@ -166,7 +166,7 @@ __device__ __forceinline__ double chunk_row_sum(const Part *__restrict__ p, cons
   return (s[0] + s[1]) + (s[2] + s[3]);
 }
 
-// The same partials as chunk_row_sum for one vector, shared by G threads: the slots, in the
+// The same partials as chunk_row_sum, shared by G threads: the slots, in the
 // order of chunk_row_sum (column slots of pairs (I, T) in increasing I, then the parts h of the
 // row slots of pairs (T, J) in increasing J and h), are dealt to the G threads in turn; thread g
 // adds slots g + (4 j + q) G into running sum q, four loads in flight, and returns
@@ -174,8 +174,8 @@ __device__ __forceinline__ double chunk_row_sum(const Part *__restrict__ p, cons
 template <typename Part>
 __device__ __forceinline__ double chunk_row_sum_dealt(const Part *__restrict__ p,
                                                       const PartMap &m, int64_t nt, int64_t L1,
-                                                      int64_t T, int64_t local, int c, int g,
-                                                      int G) {
+                                                      int64_t T, int64_t local, int v, int c,
+                                                      int g, int G) {
   auto Lcol = [&](int64_t I) { return tri_start(I, nt) + T - I; };
   const int64_t Tc = T + m.diag;   // column slots of pairs (I, T), I < Tc
   int64_t lo = 0, hi = Tc;
@@ -202,10 +202,10 @@ __device__ __forceinline__ double chunk_row_sum_dealt(const Part *__restrict__ p
   const int ns = int(m.nsplit);
   const int nslots = ncol + int(j1 - j0) * ns;
   auto slot = [&](int q) -> double {   // value of slot q < nslots
-    if (q < ncol) return double(p[part_elem(m, Lcol(i0 + q), m.nsplit, 0, c, local)]);
+    if (q < ncol) return double(p[part_elem(m, Lcol(i0 + q), m.nsplit, v, c, local)]);
     const int t = q - ncol;
     const int64_t J = j0 + t / ns;
-    return double(p[part_elem(m, st + J - T, t % ns, 0, c, local)]);
+    return double(p[part_elem(m, st + J - T, t % ns, v, c, local)]);
   };
   double s[4] = {0.0, 0.0, 0.0, 0.0};
   for (int q = g; q < nslots; q += 4 * G) {
@@ -229,6 +229,10 @@ inline int64_t chunk_pairs(int64_t pairs, int64_t nsplit, int V, int64_t ts, siz
   const int64_t nchunks = (pairs + fit - 1) / fit;
   return (pairs + nchunks - 1) / nchunks;   // equal chunks
 }
+
+// Threads per (component, row) of the reductions that deal a row's partials (one wavefront each,
+// 64 rows per workgroup).
+constexpr int kRedGroups = 8;
 
 inline unsigned blocks_for(int64_t n, int threads) {
   return unsigned((n + threads - 1) / threads);
