@@ -385,7 +385,7 @@ __device__ __forceinline__ void sym_step(const LdsF<TORQUE> &L, int j, bool vali
   }
 }
 
-template <int TPT, bool TORQUE, bool WALL, bool PERIODIC>
+template <int TPT, bool TORQUE, bool WALL, bool PERIODIC, typename Coef>
 __device__ __forceinline__ void sym_step(const LdsD<TORQUE> &L, int j, bool valid,
                                          const TargetsD<TPT> &T, const double (&own)[TPT][6],
                                          const PairConsts<double> &k, double (&acc)[TPT][3],
@@ -405,12 +405,12 @@ __device__ __forceinline__ void sym_step(const LdsD<TORQUE> &L, int j, bool vali
     for_images<PERIODIC>(T.x[q] - xj, T.y[q] - yj, k, [&](double dx, double dy) {
       const double dz = T.z[q] - zj;
       if (dx * dx + dy * dy + dz * dz < kFourA2)
-        pair_velocity_sym<double, false, TORQUE, WALL>(dx, dy, T.z[q], zj, fx, fy, fz, own[q][0],
+        pair_velocity_sym<double, false, TORQUE, WALL, Coef>(dx, dy, T.z[q], zj, fx, fy, fz, own[q][0],
                                                        own[q][1], own[q][2], k, acc[q][0],
                                                        acc[q][1], acc[q][2], cs[0], cs[1], cs[2],
                                                        tq, own[q] + 3);
       else
-        pair_velocity_sym<double, true, TORQUE, WALL>(dx, dy, T.z[q], zj, fx, fy, fz, own[q][0],
+        pair_velocity_sym<double, true, TORQUE, WALL, Coef>(dx, dy, T.z[q], zj, fx, fy, fz, own[q][0],
                                                       own[q][1], own[q][2], k, acc[q][0],
                                                       acc[q][1], acc[q][2], cs[0], cs[1], cs[2],
                                                       tq, own[q] + 3);
@@ -488,7 +488,7 @@ __device__ __forceinline__ void sym_step_diag(const LdsF<TORQUE> &L, int j, bool
   }
 }
 
-template <int TPT, bool TORQUE, bool WALL, bool PERIODIC>
+template <int TPT, bool TORQUE, bool WALL, bool PERIODIC, typename Coef>
 __device__ __forceinline__ void sym_step_diag(const LdsD<TORQUE> &L, int j, bool valid, int step,
                                               const int (&mode)[TPT], const TargetsD<TPT> &T,
                                               const double (&own)[TPT][6],
@@ -518,11 +518,11 @@ __device__ __forceinline__ void sym_step_diag(const LdsD<TORQUE> &L, int j, bool
     for_images<PERIODIC>(T.x[q] - xj, T.y[q] - yj, k, [&](double dx, double dy) {
       const double dz = T.z[q] - zj;
       if (dx * dx + dy * dy + dz * dz < kFourA2)
-        pair_velocity_sym<double, false, TORQUE, WALL>(dx, dy, T.z[q], zj, fx, fy, fz, g[0],
+        pair_velocity_sym<double, false, TORQUE, WALL, Coef>(dx, dy, T.z[q], zj, fx, fy, fz, g[0],
                                                        g[1], g[2], k, acc[q][0], acc[q][1],
                                                        acc[q][2], cs[0], cs[1], cs[2], tq, g + 3);
       else
-        pair_velocity_sym<double, true, TORQUE, WALL>(dx, dy, T.z[q], zj, fx, fy, fz, g[0], g[1],
+        pair_velocity_sym<double, true, TORQUE, WALL, Coef>(dx, dy, T.z[q], zj, fx, fy, fz, g[0], g[1],
                                                       g[2], k, acc[q][0], acc[q][1], acc[q][2],
                                                       cs[0], cs[1], cs[2], tq, g + 3);
     });
@@ -617,7 +617,7 @@ __device__ __forceinline__ void sym_diag_tile(const SymArgs &a, const GeomF &g,
   }
 }
 
-template <int TPT, bool TORQUE, bool WALL, bool PERIODIC>
+template <int TPT, bool TORQUE, bool WALL, bool PERIODIC, typename Coef>
 __device__ __forceinline__ void sym_diag_tile(const SymArgs &a, const GeomD &g,
                                               const double *__restrict__ src,
                                               const PairConsts<double> &k, int64_t first,
@@ -650,7 +650,7 @@ __device__ __forceinline__ void sym_diag_tile(const SymArgs &a, const GeomD &g,
       double cs[3] = {0.0, 0.0, 0.0};
       for (int step = 0; step < steps; ++step) {
         const int sl = (lane + step) & 63;
-        sym_step_diag<TPT, TORQUE, WALL, PERIODIC>(L, blk + (sl < nb ? sl : 0), sl < nb, step,
+        sym_step_diag<TPT, TORQUE, WALL, PERIODIC, Coef>(L, blk + (sl < nb ? sl : 0), sl < nb, step,
                                                    mode, T, own, k, T.u, cs);
       }
       const int sl = (lane + (steps > 0 ? steps - 1 : 0)) & 63;
@@ -783,7 +783,7 @@ __device__ __forceinline__ void sym_tile_pair(const SymArgs &a, const GeomF &g,
   }
 }
 
-template <int TPT, bool TORQUE, bool WALL, bool PERIODIC>
+template <int TPT, bool TORQUE, bool WALL, bool PERIODIC, typename Coef>
 __device__ __forceinline__ void sym_tile_pair(const SymArgs &a, const GeomD &g,
                                               const double *__restrict__ src,
                                               const PairConsts<double> &k,
@@ -801,7 +801,7 @@ __device__ __forceinline__ void sym_tile_pair(const SymArgs &a, const GeomD &g,
   const int64_t jb = jt + h * part, je = min(n, jb + part);
   if (I == J) {
     if (part % 64 == 0)
-      sym_diag_tile<TPT, TORQUE, WALL, PERIODIC>(a, g, src, k, first, jb, je, L, col, T);
+      sym_diag_tile<TPT, TORQUE, WALL, PERIODIC, Coef>(a, g, src, k, first, jb, je, L, col, T);
     else
       sources_f64<TORQUE, TPT, WALL, PERIODIC>(g, src, a.stride, jb, je, k, L, T);
 #pragma unroll
@@ -836,12 +836,12 @@ __device__ __forceinline__ void sym_tile_pair(const SymArgs &a, const GeomD &g,
       if (nb == 64) {
 #pragma unroll 2
         for (int step = 0; step < 64; ++step)
-          sym_step<TPT, TORQUE, WALL, PERIODIC>(L, blk + ((lane + step) & 63), true, T, own, k,
+          sym_step<TPT, TORQUE, WALL, PERIODIC, Coef>(L, blk + ((lane + step) & 63), true, T, own, k,
                                                 T.u, cs);
       } else {
         for (int step = 0; step < 64; ++step) {
           const int sl = (lane + step) & 63;
-          sym_step<TPT, TORQUE, WALL, PERIODIC>(L, blk + (sl < nb ? sl : 0), sl < nb, T, own, k,
+          sym_step<TPT, TORQUE, WALL, PERIODIC, Coef>(L, blk + (sl < nb ? sl : 0), sl < nb, T, own, k,
                                                 T.u, cs);
         }
       }
@@ -888,6 +888,24 @@ __global__ __launch_bounds__(kBlock) void pair_kernel_mixed_sym(SymArgs a, PartM
   tri_decode(Lp, a.nt, I, J);
   sym_tile_pair<TPT, TORQUE, WALL, PERIODIC>(a, g, src, k, partial, pm, Lp, I, J,
                                              int64_t(blockIdx.x) % a.nsplit, L, col);
+}
+
+// Float64 forces with the expanded coefficients, for the drift of mixed-precision steps only (see
+// expanded_drift); every other float64 whole-system product takes pair_kernel_f64_tiles.
+template <int TPT, bool WALL, bool PERIODIC>
+__global__ __launch_bounds__(kBlock) void pair_kernel_f64_expanded(SymArgs a, PartMap pm, GeomD g,
+                                                                   const double *__restrict__ src,
+                                                                   PairConsts<double> k_arg,
+                                                                   double *__restrict__ partial) {
+  const PairConsts<double> k = vgpr_consts(k_arg);
+  if (a.skip && *a.skip) return;
+  __shared__ LdsD<false> L;
+  __shared__ double col[kWaves][kBlock][3];
+  int64_t I, J;
+  const int64_t Lp = pm.L0 + int64_t(blockIdx.x) / a.nsplit;
+  tri_decode(Lp, a.nt, I, J);
+  sym_tile_pair<TPT, false, WALL, PERIODIC, SymCoefExpanded>(
+      a, g, src, k, partial, pm, Lp, I, J, int64_t(blockIdx.x) % a.nsplit, L, col);
 }
 
 // kRedGroups threads per (component, row), 64 rows per workgroup (one wavefront per group):
@@ -1052,7 +1070,7 @@ __global__ __launch_bounds__(kBlock) void pair_kernel_mixed_sym_batched(
   }
 }
 
-template <int TPT, bool TORQUE, bool WALL>
+template <int TPT, bool TORQUE, bool WALL, typename Coef>
 __global__ __launch_bounds__(kBlock) void pair_kernel_f64_sym_batched(
     SymBatchArgs b, GeomD g, const double *__restrict__ src, PairConsts<double> k_arg,
     double *__restrict__ partial) {
@@ -1067,10 +1085,10 @@ __global__ __launch_bounds__(kBlock) void pair_kernel_f64_sym_batched(
     if (b.done && b.done[w.x]) continue;
     const int64_t s0 = b.offs[w.x];
     const SymArgs a = sym_args_of(b, w.x);
-    sym_tile_pair<TPT, TORQUE, WALL, false>(a, offset_geom(g, s0), src + s0, k,
-                                            partial + b.part_base[w.x], pm,
-                                            tri_start(w.y, a.nt) + w.z - w.y, w.y, w.z, w.w, L,
-                                            col);
+    sym_tile_pair<TPT, TORQUE, WALL, false, Coef>(a, offset_geom(g, s0), src + s0, k,
+                                                  partial + b.part_base[w.x], pm,
+                                                  tri_start(w.y, a.nt) + w.z - w.y, w.y, w.z,
+                                                  w.w, L, col);
   }
 }
 
@@ -1462,14 +1480,15 @@ void with_tile(TileShape t, Fn &&fn) {
 // whatever n.  The timing record spans the pair kernels of all chunks.
 int matvec_symmetric(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const void *src,
                      bool torque, const double *h, int tpt, double *vel, hipStream_t stream,
-                     const int *skip) {
+                     const int *skip, bool expanded) {
   const int64_t n = g.n;
   const bool f64 = g.precision == RPB_FP64;
+  const bool tiles = f64 && !(expanded && !torque);
   const TileShape tile = sym64_shape(n, tpt);
-  SymArgs a{n, f64 ? int64_t(64) * tile.wt * tile.tpt : int64_t(kBlock) * tpt, 0, n};
+  SymArgs a{n, tiles ? int64_t(64) * tile.wt * tile.tpt : int64_t(kBlock) * tpt, 0, n};
   a.skip = skip;
   a.nt = (n + a.ts - 1) / a.ts;
-  a.nsplit = f64 ? 1 : sym_nsplit(n, a.ts);
+  a.nsplit = tiles ? 1 : sym_nsplit(n, a.ts);
   const int64_t pairs = a.nt * (a.nt + 1) / 2;
   const size_t esz = f64 ? sizeof(double) : sizeof(float);
   const int64_t per = chunk_pairs(pairs, a.nsplit, 1, a.ts, esz, ctx->chunk_bytes);
@@ -1481,9 +1500,17 @@ int matvec_symmetric(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const v
   RPB_TRY(timing_begin(ctx, stream, &t0));
   for (int64_t L0 = 0; L0 < pairs; L0 += per) {
     const int64_t L1 = std::min(pairs, L0 + per);
-    const PartMap pm{L0, a.nsplit, a.ts, 1, f64 ? 1 : 0};
+    const PartMap pm{L0, a.nsplit, a.ts, 1, tiles ? 1 : 0};
     const unsigned grid = unsigned((L1 - L0) * a.nsplit);
-    if (f64)
+    if (f64 && !tiles)
+      with_sym_variant(false, tpt, p->wall != 0, periodic(p), [&](auto, auto P, auto W, auto B) {
+        constexpr bool kW = decltype(W)::value, kB = decltype(B)::value;
+        constexpr int kP = decltype(P)::value;
+        pair_kernel_f64_expanded<kP, kW, kB><<<grid, kBlock, 0, stream>>>(
+            a, pm, geom_d(g), static_cast<const double *>(src),
+            make_pair_consts<double>(p->lx / p->a, p->ly / p->a), static_cast<double *>(part));
+      });
+    else if (f64)
       with_variant(torque, 1, p->wall != 0, periodic(p), [&](auto T, auto, auto W, auto B) {
         constexpr bool kT = decltype(T)::value, kW = decltype(W)::value, kB = decltype(B)::value;
         with_tile(tile, [&](auto P, auto Q, auto N) {
@@ -1535,7 +1562,7 @@ int matvec_prepacked(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const v
   const Shape &shape = ctx->tune.s[f64 ? RPB_FP64 : RPB_MIXED];
   if (shape.symmetric)
     return matvec_symmetric(ctx, p, g, src, false, packed_weights(g), shape.tpt, vel, stream,
-                            skip);
+                            skip, false);
   const int tpt = std::min(shape.tpt, 2);
   const int64_t chunk = ordered_chunk(n, tpt, shape.target_wgs, 65535);
   const int64_t nchunks = (n + chunk - 1) / chunk;
@@ -1549,7 +1576,7 @@ int matvec_prepacked(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const v
 
 int matvec_packed(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const double *force,
                   const double *torque, int64_t row0, int64_t nrows, double *vel,
-                  hipStream_t stream, const int *skip) {
+                  hipStream_t stream, const int *skip, bool expanded) {
   const int64_t n = g.n;
   if (nrows <= 0) return RPB_OK;
   const bool has_t = torque != nullptr;
@@ -1560,7 +1587,7 @@ int matvec_packed(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const doub
 
   const Shape &shape = ctx->tune.s[f64 ? RPB_FP64 : RPB_MIXED];
   if (row0 == 0 && nrows == n && shape.symmetric)
-    return matvec_symmetric(ctx, p, g, src, has_t, h, shape.tpt, vel, stream, skip);
+    return matvec_symmetric(ctx, p, g, src, has_t, h, shape.tpt, vel, stream, skip, expanded);
   const int tpt = std::min(shape.tpt, 2);   // the ordered kernel takes 1 or 2 targets per lane
   const int64_t chunk = ordered_chunk(n, tpt, shape.target_wgs, 65535);
   const int64_t nchunks = (n + chunk - 1) / chunk;
@@ -1731,7 +1758,7 @@ namespace {
 
 int matvec_batched_sym(rpb_ctx *ctx, const rpb_params *p, const Batch &b, const Packed &g,
                        const void *src, bool has_t, const int *done, int *counter, void *part,
-                       const double *h, double *vel, hipStream_t stream) {
+                       const double *h, double *vel, hipStream_t stream, bool expanded) {
   const int64_t n = g.n;
   const bool f64 = g.precision == RPB_FP64;
   const int tpt = b.tpt;
@@ -1748,8 +1775,12 @@ int matvec_batched_sym(rpb_ctx *ctx, const rpb_params *p, const Batch &b, const 
   with_variant(has_t, tpt, p->wall != 0, false, [&](auto T, auto P, auto W, auto) {
     constexpr bool kT = decltype(T)::value, kW = decltype(W)::value;
     constexpr int kP = decltype(P)::value;
-    if (f64)
-      pair_kernel_f64_sym_batched<kP, kT, kW><<<grid, kBlock, 0, stream>>>(
+    if (f64 && expanded && !kT)
+      pair_kernel_f64_sym_batched<kP, false, kW, SymCoefExpanded><<<grid, kBlock, 0, stream>>>(
+          args, geom_d(g), static_cast<const double *>(src), make_pair_consts<double>(),
+          static_cast<double *>(part));
+    else if (f64)
+      pair_kernel_f64_sym_batched<kP, kT, kW, SymCoef<double>><<<grid, kBlock, 0, stream>>>(
           args, geom_d(g), static_cast<const double *>(src), make_pair_consts<double>(),
           static_cast<double *>(part));
     else
@@ -1774,7 +1805,7 @@ int matvec_batched_sym(rpb_ctx *ctx, const rpb_params *p, const Batch &b, const 
 
 int matvec_batched(rpb_ctx *ctx, const rpb_params *p, const Batch &b, const Packed &g,
                    const double *force, const double *torque, const int *done, double *vel,
-                   hipStream_t stream) {
+                   hipStream_t stream, bool expanded) {
   const int64_t n = g.n;
   if (n == 0 || b.nitems == 0) return RPB_OK;
   const bool has_t = torque != nullptr;
@@ -1795,7 +1826,7 @@ int matvec_batched(rpb_ctx *ctx, const rpb_params *p, const Batch &b, const Pack
   zero_int<<<1, 1, 0, stream>>>(counter);
   RPB_LAUNCHED(ctx);
   if (b.symmetric) return matvec_batched_sym(ctx, p, b, g, src, has_t, done, counter, part, h,
-                                             vel, stream);
+                                             vel, stream, expanded);
 
   BatchArgs args{b.offs, b.items, b.nitems, counter, n, b.chunk, done,
                  done ? done + b.nsys : nullptr};

@@ -265,6 +265,10 @@ struct SymCoef {
   Real az, al, be[2], ec[2], cz[2];
 };
 
+// Float64 coefficients in the expanded form (the one float32 takes), for the drift of
+// mixed-precision steps: see expanded_drift in rpb_internal.h.
+struct SymCoefExpanded : SymCoef<double> {};
+
 // The float64 coefficients with a wall, in the fewest operations.  The two heights enter only
 // through T = z~_i z~_j, dz and R_z, since R^2 = r^2 + 4 T, h (h - e_z) = -T X, 2 h - e_z =
 // -dz/|R| and e_z^2 = 1 - rho^2 X; each coefficient then is a polynomial of at most second
@@ -337,10 +341,10 @@ __device__ __forceinline__ void sym_coefficients_f64(double dx, double dy, doubl
   }
 }
 
-template <typename Real, bool FAR_ONLY, bool TORQUE, bool WALL>
+template <typename Real, bool FAR_ONLY, bool TORQUE, bool WALL, typename Coef>
 __device__ __forceinline__ void sym_coefficients(Real dx, Real dy, Real zi, Real zj,
-                                                 const PairConsts<Real> &k, SymCoef<Real> &c) {
-  if constexpr (std::is_same<Real, double>::value && WALL) {
+                                                 const PairConsts<Real> &k, Coef &c) {
+  if constexpr (std::is_same<Coef, SymCoef<double>>::value && WALL) {
     sym_coefficients_f64<FAR_ONLY, TORQUE>(dx, dy, zi, zj, k, c);
     return;
   }
@@ -445,13 +449,19 @@ __device__ __forceinline__ void sym_apply_z(const SymCoef<double> &c, double s, 
   oz += c.az * fz;
   oz += zs * s;
 }
+__device__ __forceinline__ void sym_apply_z(const SymCoefExpanded &c, double s, double fz,
+                                            double zs, double &oz) {
+  oz += c.A * fz;
+  oz += zs * s;
+  oz += c.z2 * fz;
+}
 
 // (o) += M_ij f (velocity of i from source j's force f) and (p) += M_ij^T g (velocity of j from
 // target i's force g), 8 pi eta units; M_ij^T swaps the roles of c3 and c4 (e z^T <-> z e^T).
-template <typename Real, bool WALL>
-__device__ __forceinline__ void sym_apply(const SymCoef<Real> &c, Real fx, Real fy, Real fz,
-                                          Real gx, Real gy, Real gz, Real &ox, Real &oy,
-                                          Real &oz, Real &px, Real &py, Real &pz) {
+template <typename Real, bool WALL, typename Coef>
+__device__ __forceinline__ void sym_apply(const Coef &c, Real fx, Real fy, Real fz, Real gx,
+                                          Real gy, Real gz, Real &ox, Real &oy, Real &oz, Real &px,
+                                          Real &py, Real &pz) {
   const Real dx = c.dx, dy = c.dy, dz = c.dz;
   if (!WALL) {   // free space: the unbounded RPY tensors alone (r -> -r for j <- i)
     const Real cr = c.cRR * (dx * fx + dy * fy + dz * fz);
@@ -647,14 +657,15 @@ __device__ __forceinline__ void sym_apply_both(const SymCoef<double> &c, double 
 }
 
 // Both directions of one unordered pair (force and, with TORQUE, torque sources).
-template <typename Real, bool FAR_ONLY = false, bool TORQUE = false, bool WALL = true>
+template <typename Real, bool FAR_ONLY = false, bool TORQUE = false, bool WALL = true,
+          typename Coef = SymCoef<Real>>
 __device__ __forceinline__ void pair_velocity_sym(Real dx, Real dy, Real zi, Real zj, Real fx,
                                                   Real fy, Real fz, Real gx, Real gy, Real gz,
                                                   const PairConsts<Real> &k, Real &ox, Real &oy,
                                                   Real &oz, Real &px, Real &py, Real &pz,
                                                   const Real *tq = nullptr,
                                                   const Real *uq = nullptr) {
-  SymCoef<Real> c;
+  Coef c;
   sym_coefficients<Real, FAR_ONLY, TORQUE, WALL>(dx, dy, zi, zj, k, c);
   if constexpr (std::is_same<Real, double>::value && WALL && TORQUE) {
     sym_apply_both(c, fx, fy, fz, gx, gy, gz, tq, uq, ox, oy, oz, px, py, pz);

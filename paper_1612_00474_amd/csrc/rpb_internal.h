@@ -218,10 +218,21 @@ int noalloc_setup(rpb_ctx *ctx, int device);
 // vel[r] for rows [row0, row0 + nrows) of U = M F + M_C T for packed geometry `g`.
 // force / torque are [n][3] float64 device arrays (nullable, not both).  `skip` (nullable)
 // is a device flag read by every kernel of the product when it runs: while it is nonzero
-// they return at once and `vel` keeps its contents.
+// they return at once and `vel` keeps its contents.  `expanded`: whole-system float64 forces by
+// the expanded coefficients (see expanded_drift).
 int matvec_packed(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const double *force,
                   const double *torque, int64_t row0, int64_t nrows, double *vel,
-                  hipStream_t stream, const int *skip = nullptr);
+                  hipStream_t stream, const int *skip = nullptr, bool expanded = false);
+
+// Whether the float64 drift products of parameters `p` keep the expanded coefficients and the
+// 256-to-1,024-sphere tiles.  Those of a mixed-precision step do: another rounding of the drift
+// moves a position by ~1e-14, and now and then that carries a height across a float32 rounding
+// boundary, after which a velocity of the next mixed step differs by up to 1e-7 of its value
+// (seen in two of ten steps of 282,000 spheres).  Keeping the sums keeps mixed trajectories
+// reproducible to the bit against earlier results, at 7 % (batches) to 15 % of the drift's time.
+inline bool expanded_drift(const rpb_params *p, int rfd_precision) {
+  return p->precision == RPB_MIXED && rfd_precision == RPB_FP64;
+}
 
 // The H weights of packed geometry `g` (n float64 values on the device).
 const double *packed_weights(const Packed &g);
@@ -266,7 +277,7 @@ int prepare_batch(rpb_ctx *ctx, int32_t nsys, const int64_t *offs, int precision
 // done[nsys] != 0 (every system done).  `done` (nsys + 1 flags) may be NULL.
 int matvec_batched(rpb_ctx *ctx, const rpb_params *p, const Batch &b, const Packed &g,
                    const double *force, const double *torque, const int *done, double *vel,
-                   hipStream_t stream);
+                   hipStream_t stream, bool expanded = false);
 
 // ---- multi-vector products (multi.hip) --------------------------------------------------
 

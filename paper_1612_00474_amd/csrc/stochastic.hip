@@ -132,14 +132,15 @@ int rfd_run(rpb_ctx *ctx, const rpb_params *p, int64_t n, const double *pos, con
   shifted_pair<<<nblk(m), 256, 0, stream>>>(m, pos, wt, one_sided ? delta : 0.5 * delta,
                                              one_sided ? 0.0 : 0.5 * delta, qp, qm);
   RPB_LAUNCHED(ctx);
+  const bool ex = expanded_drift(p, rfd_precision);
   rpb_params q = *p;
   q.precision = rfd_precision;
   Packed gp, gm;
   RPB_TRY(pack_geometry(ctx, &q, n, qp, WS_GEOM, &gp, stream));
-  RPB_TRY(matvec_packed(ctx, &q, gp, wt, nullptr, 0, n, up, stream));
+  RPB_TRY(matvec_packed(ctx, &q, gp, wt, nullptr, 0, n, up, stream, nullptr, ex));
   if (!(one_sided && base)) {   // the product at q- (= q when one-sided)
     RPB_TRY(pack_geometry(ctx, &q, n, qm, WS_GEOM2, &gm, stream));
-    RPB_TRY(matvec_packed(ctx, &q, gm, wt, nullptr, 0, n, um, stream));
+    RPB_TRY(matvec_packed(ctx, &q, gm, wt, nullptr, 0, n, um, stream, nullptr, ex));
     base = um;
   }
   scaled_difference<<<nblk(m), 256, 0, stream>>>(m, up, base, p->kT / delta, drift);
@@ -174,13 +175,14 @@ int rfd_batched_run(rpb_ctx *ctx, const rpb_params *p, const Batch &bt, const do
   shifted_pair<<<nblk(m), 256, 0, stream>>>(m, pos, wt, one_sided ? delta : 0.5 * delta,
                                              one_sided ? 0.0 : 0.5 * delta, qp, qm);
   RPB_LAUNCHED(ctx);
+  const bool ex = expanded_drift(p, rfd_precision);
   rpb_params q = *p;
   q.precision = rfd_precision;
   Packed gp, gm;
   RPB_TRY(pack_geometry(ctx, &q, n, qp, WS_GEOM, &gp, stream));
   RPB_TRY(pack_geometry(ctx, &q, n, qm, WS_GEOM2, &gm, stream));
-  RPB_TRY(matvec_batched(ctx, &q, bt, gp, wt, nullptr, nullptr, up, stream));
-  RPB_TRY(matvec_batched(ctx, &q, bt, gm, wt, nullptr, nullptr, um, stream));
+  RPB_TRY(matvec_batched(ctx, &q, bt, gp, wt, nullptr, nullptr, up, stream, ex));
+  RPB_TRY(matvec_batched(ctx, &q, bt, gm, wt, nullptr, nullptr, um, stream, ex));
   scaled_difference<<<nblk(m), 256, 0, stream>>>(m, up, um, p->kT / delta, drift);
   RPB_LAUNCHED(ctx);
   return RPB_OK;
