@@ -5,7 +5,7 @@
 //     u = M v_m;  alpha_m = v_m . u;  u -= alpha_m v_m + beta_{m-1} v_{m-1};
 //     u -= V_m (V_m^T u)                       (full re-orthogonalisation)
 //     beta_m = |u|
-//     T_m = Q L Q^T (updated from T_{m-1}'s), y_m = |w| Q L^{1/2} Q^T e_1
+//     y_m = |w| T_m^{1/2} e_1    (quadrature, or T_m = Q L Q^T updated from T_{m-1}'s)
 //     eps_m = |y_m - (y_{m-1}, 0)| / |y_{m-1}|  (= |g_m - g_{m-1}|/|g_{m-1}| for orthonormal V)
 //     stop if eps_m < tol (m >= 2), or beta_m ~ 0 (invariant Krylov space, exact result)
 //     v_{m+1} = u / beta_m
@@ -41,7 +41,7 @@ struct LzState {
   double h[kMaxKrylov];
   double wnorm;
   int halt;       // set by the vector work once it has seen reason != 0 (read by the products)
-  int pad_;
+  int eig_m;      // order of the eigendecomposition held in LzEig (0: none)
   // status (read by the host every iteration)
   double eps;
   int m;
@@ -159,12 +159,17 @@ __global__ void basis_combine(int64_t m, int nvec, const double *__restrict__ V,
   out[i] = acc;
 }
 
-// Eigendecomposition of T_{m-1} kept from one iteration to the next (the eigensolve of T_m
-// updates it): eigenvalues in increasing order and the eigenvector matrix, row-major.
+// Eigendecomposition of T_m kept from one order to the next (the eigensolve of T_{m+1} updates
+// it): eigenvalues in increasing order and the eigenvector matrix of T_m in Q[m & 1],
+// column-major.
 struct LzEig {
   double lam[kMaxKrylov];
-  double Q[kMaxKrylov * kMaxKrylov];   // Q[col * kMaxKrylov + row] (column-major)
+  double Q[2][kMaxKrylov * kMaxKrylov];   // Q[..][col * kMaxKrylov + row]
 };
+
+// LDS of the root of T_m: the quadrature's transposed sums or the arrowhead's eigenvectors.
+constexpr int kRootPool = 4 * 16 * 65;
+static_assert(kRootPool >= kMaxKrylov * kMaxKrylov, "the eigenvectors fit the pool");
 
 // 1/x: the hardware estimate refined by two Newton steps r <- r + r (1 - x r) (the error is
 // squared by each; the result is within an ulp or two of the rounded quotient), about half the
@@ -340,7 +345,8 @@ __device__ void secular_roots(int p, const double *__restrict__ d, const double 
   }
 }
 
-// Eigendecomposition of T_m from that of T_{m-1} (in eig, replaced by T_m's).  In the basis of
+// Eigendecomposition of T_m from that of T_{m-1} (in eig, replaced by T_m's), for the T_m that
+// root_quadrature does not take.  In the basis of
 // T_{m-1}'s eigenvectors and e_m, T_m is an arrowhead matrix: diagonal lambda, border
 // z = beta_{m-1} (last row of Q), corner alpha_m.  Its eigenproblem is solved as in the
 // divide-and-conquer method (Cuppen 1981; Gu and Eisenstat 1995):
@@ -354,12 +360,12 @@ __device__ void secular_roots(int p, const double *__restrict__ d, const double 
 // Every thread of the workgroup calls this; the first wavefront (one lane per eigenvalue, m <=
 // 64) does the scalar work and the workgroup forms the product.  Returns 1 (every thread)
 // when a root iteration did not stop or an eigenvalue is not finite.
-__device__ int eig_update(int m, const LzState *__restrict__ st, LzEig *__restrict__ eig) {
+__device__ int eig_update(int m, const LzState *__restrict__ st, LzEig *__restrict__ eig,
+                          double *__restrict__ U) {
   // column-major (entry [row or component] fastest), so that the lanes of a wavefront, which
-  // take consecutive rows, touch consecutive LDS words
-  __shared__ double Qs[kMaxKrylov * kMaxKrylov];   // old Q (rows < m - 1), rotated: [col * 64 + row]
-  __shared__ double U[kMaxKrylov * kMaxKrylov];    // eigenvectors of the arrowhead: [j * 64 + i]
-  __shared__ double Qk[kMaxKrylov * kMaxKrylov];   // the kept columns of Qs, in order
+  // take consecutive rows, touch consecutive words; U (LDS, kRootPool): eigenvectors of the
+  // arrowhead, [j * 64 + i].  The old Q is rotated in place, the new one goes to the other buffer.
+  double *Qs = eig->Q[(m - 1) & 1], *Qn = eig->Q[m & 1];
   __shared__ double dd[kMaxKrylov], zz[kMaxKrylov], dn[kMaxKrylov], z2n[kMaxKrylov];
   __shared__ double zh[kMaxKrylov], tau_s[kMaxKrylov], dK_s[kMaxKrylov], val[kMaxKrylov];
   __shared__ double rot_c[kMaxKrylov], rot_s[kMaxKrylov];
@@ -373,21 +379,17 @@ __device__ int eig_update(int m, const LzState *__restrict__ st, LzEig *__restri
   if (m == 1) {
     if (tid == 0) {
       eig->lam[0] = st->alpha[0];
-      eig->Q[0] = 1.0;
+      Qn[0] = 1.0;
     }
     __syncthreads();
     return 0;
   }
   const int n1 = m - 1;
   const double alpha = st->alpha[m - 1], beta = st->beta[m - 2];
-  for (int e = tid; e < n1 * n1; e += nthr) {
-    const int c = e / n1, r = e - c * n1;
-    Qs[c * 64 + r] = eig->Q[c * kMaxKrylov + r];
-  }
   if (w0) {
     if (lane < n1) {
       dd[lane] = eig->lam[lane];
-      zz[lane] = beta * eig->Q[lane * kMaxKrylov + (n1 - 1)];
+      zz[lane] = beta * Qs[lane * kMaxKrylov + (n1 - 1)];
     }
     // deflation tolerance from |T_m| <= max(|lambda|, |alpha|) + |beta|
     double amax = lane < n1 ? fabs(eig->lam[lane]) : 0.0;
@@ -470,11 +472,6 @@ __device__ int eig_update(int m, const LzState *__restrict__ st, LzEig *__restri
     }
     __syncthreads();
   }
-  // the kept columns side by side for the product below (read after the next barrier)
-  for (int x = tid; x < p * n1; x += nthr) {
-    const int jj = x / n1, r = x - jj * n1;
-    Qk[jj * 64 + r] = Qs[nd_s[jj] * 64 + r];
-  }
   // the roots (with p = 0 the arrowhead is alpha alone), by the whole workgroup
   secular_roots(p, dn, z2n, alpha, K_s, tau_s, dK_s, fail_s);
   if (w0) {
@@ -541,13 +538,13 @@ __device__ int eig_update(int m, const LzState *__restrict__ st, LzEig *__restri
     double v;
     if (e <= p) {
       if (r < n1) {
-        // four running sums keep several LDS loads in flight
+        // four running sums keep several loads in flight
         double v4[4] = {0.0, 0.0, 0.0, 0.0};
         int j = 0;
         for (; j + 4 <= p; j += 4)
 #pragma unroll
-          for (int q = 0; q < 4; ++q) v4[q] += Qk[(j + q) * 64 + r] * U[(j + q) * 64 + e];
-        for (; j < p; ++j) v4[0] += Qk[j * 64 + r] * U[j * 64 + e];
+          for (int q = 0; q < 4; ++q) v4[q] += Qs[nd_s[j + q] * 64 + r] * U[(j + q) * 64 + e];
+        for (; j < p; ++j) v4[0] += Qs[nd_s[j] * 64 + r] * U[j * 64 + e];
         v = (v4[0] + v4[1]) + (v4[2] + v4[3]);
       } else {
         v = U[p * 64 + e];
@@ -555,31 +552,171 @@ __device__ int eig_update(int m, const LzState *__restrict__ st, LzEig *__restri
     } else {
       v = r < n1 ? Qs[df_s[e - p - 1] * 64 + r] : 0.0;
     }
-    eig->Q[rank_s[e] * kMaxKrylov + r] = v;
+    Qn[rank_s[e] * kMaxKrylov + r] = v;
   }
   __syncthreads();
   return info[3];
 }
 
-// Eigendecomposition of T_m (eig_update), then y_m = |w| Q L^{1/2} Q^T e_1, eps_m and the stop
-// test.  Every thread of the workgroup calls this; the first wavefront forms y_m and the status.
+// T^{1/2} e_1 without an eigendecomposition, from T^{1/2} = (2/pi) int_0^inf T (T + t^2)^{-1} dt with
+// t = e^x: the trapezoidal rule converges as exp(-pi^2/h) (the integrand's poles lie at
+// distance pi/2 from the real axis), 2e-21 at h = 0.2.  Thread k takes node t_k = sqrt(G) e^{(k -
+// 191.5) h}, G >= |T| by Gershgorin, and solves (T + t_k^2) x = e_1 by elimination from the last
+// row; the solutions are independent chains of m reciprocals.  Nodes below sqrt(G) add t (e_1 -
+// t^2 x) and the others t T x (neither form cancels by more than |T|^{1/2}); what lies below t_0
+// and above t_255 is summed as the geometric series it has become to (t_0^2/lambda_min and
+// |T|/t_255^2 cubed roots of 1e-16).  The error is that of T^{1/2} under a rounding of T,
+// ~eps (|T|/lambda_min)^{1/2} |T|^{1/2}, as with an eigendecomposition.
+// A pivot of T itself below 1e-8 G (T indefinite, singular or nearly so) or a value that is not
+// finite returns 0 on every thread and the caller takes the eigendecomposition.  Else lane r of
+// the first wavefront returns row r of T^{1/2} e_1 in y.
+// One chain of m dependent steps instead of the root searches and the product of the updated
+// eigendecomposition: lanczos_eig over m = 1..26 16.7 -> 6.4 us, beta_eig over m = 1..12 (which
+// also sums beta) 13.2 -> 7.3 us; the 2,100-sphere step 714 -> 677 us.
+constexpr double kRootStep = 0.2;
+constexpr int kRootLow = 192;   // nodes below sqrt(G): the first three wavefronts
+
+struct RootLds {
+  double a[kMaxKrylov], b[kMaxKrylov], b2[kMaxKrylov];
+  double sum[kThreads / 64][kMaxKrylov];   // per wavefront: sum over its nodes of c x_i
+  double z[kMaxKrylov + 2];                // padded, z[i + 1]
+  int ok;
+};
+
+// Orders a wavefront's own LDS writes before its later reads of other lanes' words.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// The weighted solutions of this thread's node for the leading M rows (rows past m are decoupled),
+// summed over each wavefront into L.sum.
+template <int M>
+__device__ __forceinline__ void root_nodes(double G, RootLds &L, double *__restrict__ pool) {
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const double node = sqrt(G) * exp((double(t) - (kRootLow - 0.5)) * kRootStep);
+  const double sh = node * node;
+  const double cw = t < kRootLow ? node * sh : node;
+  double r[M];
+  const double floor_ = 1e-8 * G;
+  double d = L.a[M - 1] + sh;
+  bool ok = d >= floor_;
+  r[M - 1] = rcp_f64(d);
+#pragma unroll
+  for (int i = M - 2; i >= 0; --i) {
+    d = (L.a[i] + sh) - L.b2[i] * r[i + 1];
+    ok = ok && d >= floor_;
+    r[i] = rcp_f64(d);
+  }
+  if (t == 0) L.ok = ok && isfinite(r[0]);   // the smallest shift: the pivots of T
+  double x = r[0] * cw;
+  r[0] = x;
+#pragma unroll
+  for (int i = 1; i < M; ++i) {
+    x *= -L.b[i - 1] * r[i];
+    r[i] = x;
+  }
+  // 16 rows at a time: transposed through LDS, four lanes per row add 16 nodes each
+  double *p = pool + wave * 16 * 65;
+#pragma unroll
+  for (int i0 = 0; i0 < M; i0 += 16) {
+    constexpr int R = M < 16 ? M : 16;
+#pragma unroll
+    for (int i = 0; i < R; ++i) p[i * 65 + lane] = r[i0 + i];
+    wave_sync();
+    const int row = lane >> 2, q = lane & 3;
+    double v = 0.0;
+    if (row < R)
+#pragma unroll
+      for (int j = 0; j < 16; ++j) v += p[row * 65 + q * 16 + j];
+    v += __shfl_xor(v, 1, 64);
+    v += __shfl_xor(v, 2, 64);
+    if (q == 0 && row < R) L.sum[wave][i0 + row] = v;
+    wave_sync();
+  }
+}
+
+__device__ int root_quadrature(int m, const LzState *__restrict__ st, RootLds &L,
+                               double *__restrict__ pool, double &y) {
+  const int t = threadIdx.x, lane = t & 63;
+  const double ai = lane < m ? st->alpha[lane] : 0.0;
+  const double bi = lane < m - 1 ? st->beta[lane] : 0.0;
+  const double bp = __shfl_up(bi, 1, 64);
+  double G = fabs(ai) + fabs(bi) + (lane > 0 ? fabs(bp) : 0.0);
+  for (int off = 32; off > 0; off >>= 1) G = fmax(G, __shfl_xor(G, off, 64));
+  if (!(G > 1e-100 && G < 1e100)) return 0;   // the same on every thread; t^3 stays in range
+  if (t < 64) {
+    L.a[lane] = lane < m ? ai : G;
+    L.b[lane] = bi;
+    L.b2[lane] = bi * bi;
+  }
+  __syncthreads();
+  if (m <= 8)
+    root_nodes<8>(G, L, pool);
+  else if (m <= 16)
+    root_nodes<16>(G, L, pool);
+  else if (m <= 32)
+    root_nodes<32>(G, L, pool);
+  else
+    root_nodes<64>(G, L, pool);
+  __syncthreads();
+  if (!L.ok) return 0;
+  if (t < 64) {
+    const double eh = exp(-kRootStep), tail = 1.0 / (1.0 - eh), sG = sqrt(G);
+    // sum of every node below sqrt(G) down to 0, and of 1/t beyond the last node
+    const double low = sG * exp(-0.5 * kRootStep) * tail;
+    const double high = tail * exp(-(kThreads - kRootLow + 0.5) * kRootStep) / sG;
+    const double A = (L.sum[0][lane] + L.sum[1][lane]) + L.sum[2][lane];
+    const double B = L.sum[3][lane] + (lane == 0 ? high : 0.0);
+    const double z = lane < m ? B : 0.0;
+    L.z[lane + 1] = z;
+    if (lane == 0) L.z[0] = L.z[kMaxKrylov + 1] = 0.0;
+    wave_sync();
+    const double Tz = (lane > 0 ? L.b[lane - 1] * L.z[lane] : 0.0) + ai * z +
+                      (lane < m - 1 ? bi * L.z[lane + 2] : 0.0);
+    y = (2.0 * kRootStep / M_PI) * (((lane == 0 ? low : 0.0) - A) + Tz);
+  }
+  return 1;
+}
+
+// y_m = |w| T_m^{1/2} e_1 (root_quadrature, or the eigendecomposition of T_m brought up from the
+// order it was left at, negative eigenvalues taken as zero), eps_m and the stop test.  Every
+// thread of the workgroup (kThreads) calls this; the first wavefront forms y_m and the status.
 __device__ void tridiag_body(int m, double tol, LzState *__restrict__ st, LzEig *__restrict__ eig) {
+  static_assert(kThreads == 256, "one quadrature node per thread");
+  __shared__ RootLds L;
+  __shared__ double pool[kRootPool];
   __shared__ double Rz[kMaxKrylov];   // sqrt(lambda_k) q_k[0]
-  const int failed = eig_update(m, st, eig);
+  double yr = 0.0;
+  const int fast = root_quadrature(m, st, L, pool, yr);
+  int failed = 0;
+  bool indefinite = false;
   const int lane = threadIdx.x;
+  if (!fast) {
+    const int have = st->eig_m;
+    __syncthreads();   // every thread has read eig_m and is done with the pool
+    for (int k = have + 1; k <= m; ++k) {
+      failed |= eig_update(k, st, eig, pool);
+      __syncthreads();
+    }
+    if (lane < 64) {
+      const double *Q = eig->Q[m & 1];
+      const double lmin = eig->lam[0], lmax = eig->lam[m - 1];
+      indefinite = lmin < -1e-12 * fmax(lmax, 0.0);
+      // lane k forms sqrt(lambda_k) q_k[0], then lane r sums row r
+      if (lane < m) Rz[lane] = sqrt(fmax(eig->lam[lane], 0.0)) * Q[lane * kMaxKrylov];
+      yr = 0.0;
+      if (lane < m) {
+#pragma unroll 4
+        for (int k = 0; k < m; ++k) yr += Rz[k] * Q[k * kMaxKrylov + lane];
+      }
+      if (lane == 0) st->eig_m = m;
+    }
+  }
   if (lane >= 64) return;
-  const double lmin = eig->lam[0], lmax = eig->lam[m - 1];
   double amax = lane < m ? fabs(st->alpha[lane]) : 0.0;
   for (int off = 32; off > 0; off >>= 1) amax = fmax(amax, __shfl_xor(amax, off, 64));
-  // y_m = |w| Q L^{1/2} Q^T e_1: lane k forms sqrt(lambda_k) q_k[0], then lane r sums row r
-  if (lane < m) Rz[lane] = sqrt(fmax(eig->lam[lane], 0.0)) * eig->Q[lane * kMaxKrylov];
-  const double wn = st->wnorm;
-  double yr = 0.0;
-  if (lane < m) {
-#pragma unroll 4
-    for (int k = 0; k < m; ++k) yr += Rz[k] * eig->Q[k * kMaxKrylov + lane];
-    yr *= wn;
-  }
+  yr = lane < m ? yr * st->wnorm : 0.0;
   // eps_m in the orthonormal Krylov basis
   const double yp = (lane < m - 1) ? st->yprev[lane] : 0.0;
   const double diff = (lane < m) ? (yr - yp) : 0.0;
@@ -597,7 +734,7 @@ __device__ void tridiag_body(int m, double tol, LzState *__restrict__ st, LzEig 
     int reason = 0;
     if (failed)
       reason = 4;
-    else if (lmin < -1e-12 * fmax(lmax, 0.0))
+    else if (indefinite)
       reason = 3;
     else if (m >= 2 && eps < tol)
       reason = 1;
@@ -630,6 +767,7 @@ __global__ void lz_reset(LzState *st) {
   if (t == 0) {
     st->wnorm = 0.0;
     st->halt = 0;
+    st->eig_m = 0;
     st->eps = 0.0;
     st->m = 0;
     st->reason = 0;
@@ -1098,7 +1236,7 @@ __global__ __launch_bounds__(kThreads) void seg_reorth_update_sq(
 
 // beta_k = sqrt(sum of the system's kSegBlocks partials, in order), then the eigensolve of T_k
 // with its stop test; a stopped system is frozen.
-__global__ __launch_bounds__(64) void seg_beta_eig(SegView v, int m, double tol,
+__global__ __launch_bounds__(kThreads) void seg_beta_eig(SegView v, int m, double tol,
                                                    const double *__restrict__ part) {
   const int s = blockIdx.x;
   if (v.done[s]) return;
@@ -1115,7 +1253,7 @@ __global__ __launch_bounds__(64) void seg_beta_eig(SegView v, int m, double tol,
 // The eigensolve of T_1, T_2, ..., T_m in turn (as a Krylov process meets them), row k - 1 of
 // ys (m doubles) receiving y_k = |w| T_k^{1/2} e_1 (entries k..m-1 zero); fail[0] = 1 when an
 // eigensolve fails.  The stop tests are evaluated but do not stop the sequence.
-__global__ __launch_bounds__(64) void tridiag_sequence(int m, LzState *__restrict__ st,
+__global__ __launch_bounds__(kThreads) void tridiag_sequence(int m, LzState *__restrict__ st,
                                                        LzEig *__restrict__ eig,
                                                        double *__restrict__ ys,
                                                        int *__restrict__ fail) {
@@ -1167,6 +1305,7 @@ __global__ void lz_reset_batched(SegView v, int nsys) {
   }
   if (t == 0) {
     st->wnorm = 0.0;
+    st->eig_m = 0;
     st->eps = 0.0;
     st->m = 0;
     st->reason = 0;
@@ -1612,7 +1751,7 @@ int lanczos_segments(rpb_ctx *ctx, const Batch &b, const double *L, double *t, c
       seg_reorth_update_sq<<<dim3{unsigned(kSegBlocks), ns, 1u}, kThreads, 0, stream>>>(
           v, m3, k, V, u, vk, vprev, part);
       RPB_LAUNCHED(ctx);
-      seg_beta_eig<<<ns, 64, 0, stream>>>(v, k, tol, part);
+      seg_beta_eig<<<ns, kThreads, 0, stream>>>(v, k, tol, part);
       RPB_LAUNCHED(ctx);
       seg_all_done<<<1, 256, 0, stream>>>(v, nsys);
       RPB_LAUNCHED(ctx);
@@ -1857,7 +1996,7 @@ extern "C" int lanczos_tridiag_sqrt(rpb_ctx *ctx, int32_t m, const double *alpha
   if (!buf) return st;
   int *flag = reinterpret_cast<int *>(buf + ybytes);
   RPB_HIP(ctx, hipMemcpyAsync(ls, &h, sizeof(LzState), hipMemcpyHostToDevice, stream));
-  tridiag_sequence<<<1, 64, 0, stream>>>(m, ls, eig, reinterpret_cast<double *>(buf), flag);
+  tridiag_sequence<<<1, kThreads, 0, stream>>>(m, ls, eig, reinterpret_cast<double *>(buf), flag);
   RPB_LAUNCHED(ctx);
   int failed = 0;
   RPB_HIP(ctx, hipMemcpyAsync(y_out, buf, ybytes, hipMemcpyDeviceToHost, stream));
