@@ -160,6 +160,7 @@ int rpb_create(int hip_device, rpb_ctx **out) {
     delete c;
     return RPB_ENOMEM;
   }
+  std::memset(c->host_pinned, 0, kHostScratchBytes);   // no word equals a solve's epoch yet
   if (hipHostGetDevicePointer(&c->host_pinned_dev, c->host_pinned, 0) != hipSuccess) {
     (void)hipHostFree(c->host_pinned);
     delete c;

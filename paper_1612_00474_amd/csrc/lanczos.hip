@@ -20,6 +20,7 @@
 #include <deque>
 #include <mutex>
 #include <thread>
+#include <type_traits>
 #include <vector>
 
 #include "rpb_internal.h"
@@ -29,7 +30,6 @@ namespace rpb {
 namespace {
 
 constexpr int kMaxKrylov = 64;      // largest m (the eigensolve keeps T_m in one wavefront)
-constexpr int kRedBlocks = 256;     // partial sums per reduction
 constexpr int kThreads = 256;
 
 // Device-side Lanczos scalars (lives at the start of the WS_SMALL slot).
@@ -102,52 +102,6 @@ int lz_ring_wait(rpb_ctx *ctx, int q) {
   ctx->lz_live[q] = false;
   return RPB_OK;
 }
-
-__device__ __forceinline__ double block_sum(double v, double *sh) {
-  const int t = threadIdx.x;
-  sh[t] = v;
-  __syncthreads();
-  for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-    if (t < s) sh[t] += sh[t + s];
-    __syncthreads();
-  }
-  const double r = sh[0];
-  __syncthreads();
-  return r;
-}
-
-
-
-__global__ void scale_by_inverse(int64_t m, const double *__restrict__ x,
-                                 const double *__restrict__ d, double *__restrict__ y,
-                                 const LzState *__restrict__ st) {
-  if (st && st->reason != 0) return;
-  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= m) return;
-  const double s = d[0];
-  y[i] = s > 0.0 ? x[i] / s : 0.0;
-}
-
-// scale_by_inverse for v_{k+1} = u / beta_k that also writes it into the next product's
-// packed sources, as that product's own packing would: src[c n + s] = Real(H_s y[3 s + c]).
-template <typename Real>
-__global__ void scale_by_inverse_packed(int64_t m, const double *__restrict__ x,
-                                        const double *__restrict__ d, double *__restrict__ y,
-                                        const LzState *__restrict__ st,
-                                        const double *__restrict__ hw, Real *__restrict__ src) {
-  if (st->reason != 0) return;
-  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= m) return;
-  const double s = d[0];
-  const double v = s > 0.0 ? x[i] / s : 0.0;
-  y[i] = v;
-  const int64_t n = m / 3, sp = i / 3;
-  src[(i - 3 * sp) * n + sp] = Real(hw[sp] * v);
-}
-
-
-
-
 
 // out = V y (first nvec rows of V)
 __global__ void basis_combine(int64_t m, int nvec, const double *__restrict__ V,
@@ -755,132 +709,513 @@ __device__ __forceinline__ void post_status(const LzState *__restrict__ st, LzRi
   __threadfence_system();
 }
 
-__global__ void lz_reset(LzState *st) {
+// ---- Krylov processes on segments of concatenated vectors -------------------------------------
+//
+// Process s owns elements [3 offs[s], 3 offs[s + 1]) of every vector (offs NULL: one process, all
+// m3 elements) and its own LzState.  done[s] != 0 (done NULL for a single process) freezes a
+// process: every kernel skips it, so it stops changing once its own tolerance or breakdown test
+// is met, whatever the others do.
+//
+// After the product u = M v_k, an iteration is two kernels, and the sum alpha_k = v_k . u is taken
+// with the product's own reduction, one partial per 64 rows:
+//   lz_dots    u <- u - alpha_k v_k - beta_{k-1} v_{k-1} (every workgroup sums the partials of
+//              alpha), h_j = V_j . u for j <= k and |u|^2, one partial per workgroup; each
+//              workgroup keeps its elements in registers over all basis vectors;
+//   lz_update  every workgroup sums h and |u|^2, so beta_k^2 = |u - V_k h|^2 = |u|^2 - |h|^2 (the h_j
+//              are rounding errors, so nothing cancels unless the Krylov space is exhausted, where
+//              beta_k is a rounding error either way) needs no third pass, and
+//              v_{k+1} = (u - V_k h) / beta_k goes to the basis and, weighted, into the next
+//              product's sources; the process's first workgroup then takes T_k^{1/2} e_1 and the
+//              stop test.
+// The work is a few reads of vectors that fit the caches; what bounds it is the ~4.4 us that each
+// dependent launch costs, so the count is what matters: six kernels per iteration before (two
+// for alpha, dots, their sum, update, beta and root, scaling), 42 -> 25 us per iteration at 2,100
+// spheres.
+
+constexpr int kPartRows = 64;   // rows per partial of alpha
+
+struct SegView {
+  const int64_t *offs;    // nsys + 1 (device); NULL: one process
+  const int *sys_of;      // sphere -> system (device)
+  LzState *st;            // nsys states
+  int *done;              // nsys flags, the all-done flag, the count of finished processes
+  LzEig *eig;             // nsys eigendecompositions
+  int nsys;
+  int64_t m3;             // elements of a vector
+};
+
+__device__ __forceinline__ void seg_range(const SegView &v, int s, int64_t &e0, int64_t &e1) {
+  e0 = v.offs ? 3 * v.offs[s] : 0;
+  e1 = v.offs ? 3 * v.offs[s + 1] : v.m3;
+}
+
+__device__ __forceinline__ double wave_sum(double v) {
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+  return v;
+}
+
+// Sum of np partials by the whole workgroup, the same value on every thread (sh: kThreads / 64).
+__device__ __forceinline__ double sum_partials(const double *__restrict__ part, int64_t np,
+                                               double *sh) {
+  double a = 0.0;
+  for (int64_t i = threadIdx.x; i < np; i += kThreads) a += part[i];
+  a = wave_sum(a);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = a;
+  __syncthreads();
+  double r = sh[0];
+#pragma unroll
+  for (int w = 1; w < kThreads / 64; ++w) r += sh[w];
+  __syncthreads();
+  return r;
+}
+
+// One partial per 64 elements of a . b over each live process (grid: elements / kThreads, nsys);
+// partial q of process s at part[s * stride + q].
+__global__ __launch_bounds__(kThreads) void lz_dot(SegView v, const double *__restrict__ a,
+                                                   const double *__restrict__ b, int check_done,
+                                                   double *__restrict__ part, int64_t stride) {
+  const int s = blockIdx.y;
+  if (check_done && v.done && v.done[s]) return;
+  int64_t e0, e1;
+  seg_range(v, s, e0, e1);
+  const int64_t i = e0 + int64_t(blockIdx.x) * kThreads + threadIdx.x;
+  const double x = wave_sum(i < e1 ? a[i] * b[i] : 0.0);
+  const int64_t q = int64_t(blockIdx.x) * (kThreads / 64) + (threadIdx.x >> 6);
+  if ((threadIdx.x & 63) == 0 && e0 + q * kPartRows < e1) part[s * stride + q] = x;
+}
+
+// The state of process s at its start, by one workgroup.
+__device__ __forceinline__ void reset_state(const SegView &v, int s, double wn) {
+  LzState *st = v.st + s;
   const int t = threadIdx.x;
-  if (t < kMaxKrylov) {
-    st->alpha[t] = 0.0;
-    st->beta[t] = 0.0;
-    st->y[t] = 0.0;
-    st->yprev[t] = 0.0;
-    st->h[t] = 0.0;
-  }
+  if (t < kMaxKrylov) st->alpha[t] = st->beta[t] = st->y[t] = st->yprev[t] = st->h[t] = 0.0;
   if (t == 0) {
-    st->wnorm = 0.0;
+    st->wnorm = wn;
     st->halt = 0;
     st->eig_m = 0;
     st->eps = 0.0;
     st->m = 0;
     st->reason = 0;
+    if (v.done) v.done[s] = 0;
   }
 }
 
-// ---- one Lanczos iteration of a single system in six kernels (segments > kFusedSegment) ----
+// Start of every process: |w| from the partials of w . w, the state reset, v_1 = w / |w| into the
+// basis and, with src, into the first product's packed sources; with mw = M w also u = mw / |w| and
+// the partials of alpha_1 = v_1 . u.  counter (nullable): a persistent kernel's work counter, zeroed.
+template <typename Real>
+__global__ __launch_bounds__(kThreads) void lz_start(
+    SegView v, const double *__restrict__ w, const double *__restrict__ npart,
+    double *__restrict__ V, const double *__restrict__ hw, Real *__restrict__ src,
+    const double *__restrict__ mw, double *__restrict__ u, double *__restrict__ apart,
+    int64_t stride, int *counter) {
+  __shared__ double sh[kThreads / 64];
+  const int s = blockIdx.y, t = threadIdx.x;
+  if (s == 0 && blockIdx.x == 0 && t == 0) {
+    if (counter) counter[0] = 0;
+    if (v.done) v.done[v.nsys] = v.done[v.nsys + 1] = 0;
+  }
+  int64_t e0, e1;
+  seg_range(v, s, e0, e1);
+  if (blockIdx.x > 0 && e0 + int64_t(blockIdx.x) * kThreads >= e1) return;
+  const double wn =
+      sqrt(sum_partials(npart + s * stride, (e1 - e0 + kPartRows - 1) / kPartRows, sh));
+  if (blockIdx.x == 0) reset_state(v, s, wn);
+  const int64_t i = e0 + int64_t(blockIdx.x) * kThreads + t;
+  double a = 0.0;
+  if (i < e1) {
+    const double x = wn > 0.0 ? w[i] / wn : 0.0;
+    V[i] = x;
+    if (src) {
+      const int64_t sp = i / 3;
+      src[(i - 3 * sp) * (v.m3 / 3) + sp] = Real(hw[sp] * x);
+    }
+    if (mw) {
+      const double y = wn > 0.0 ? mw[i] / wn : 0.0;
+      u[i] = y;
+      a = x * y;
+    }
+  }
+  if (!mw) return;
+  a = wave_sum(a);
+  const int64_t q = int64_t(blockIdx.x) * (kThreads / 64) + (t >> 6);
+  if ((t & 63) == 0 && e0 + q * kPartRows < e1) apart[s * stride + q] = a;
+}
+
+// Workgroups of a process of `len` elements in lz_dots and lz_update.
+template <int EPT>
+__device__ __forceinline__ int seg_groups(int64_t len) {
+  const int64_t g = (len + kThreads * EPT - 1) / (kThreads * EPT);
+  return g > 0 ? int(g) : 1;
+}
+
+template <int EPT>
+__global__ __launch_bounds__(kThreads) void lz_dots(SegView v, int k,
+                                                    const double *__restrict__ V,
+                                                    double *__restrict__ u,
+                                                    const double *__restrict__ apart,
+                                                    int64_t stride, double *__restrict__ part,
+                                                    int nb) {
+  constexpr int W = kThreads / 64;
+  __shared__ double sh[W];
+  __shared__ double hsh[(kMaxKrylov + 1) * W];   // wavefront sums: [j * W + wave]
+  const int s = blockIdx.y, t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  if (v.done && v.done[s]) return;
+  int64_t e0, e1;
+  seg_range(v, s, e0, e1);
+  if (int(blockIdx.x) >= seg_groups<EPT>(e1 - e0)) return;
+  LzState *st = v.st + s;
+  const double *vk = V + int64_t(k - 1) * v.m3;
+  const double *vp = V + int64_t(k > 1 ? k - 2 : 0) * v.m3;
+  const double be = k > 1 ? st->beta[k - 2] : 0.0;
+  bool in[EPT];
+  int64_t ix[EPT];
+  double x[EPT], xv[EPT], xp[EPT];
+#pragma unroll
+  for (int r = 0; r < EPT; ++r) {
+    const int64_t i = e0 + (int64_t(blockIdx.x) * EPT + r) * kThreads + t;
+    in[r] = i < e1;
+    ix[r] = in[r] ? i : 0;
+    x[r] = in[r] ? u[ix[r]] : 0.0;
+    xv[r] = in[r] ? vk[ix[r]] : 0.0;
+    xp[r] = in[r] && k > 1 ? vp[ix[r]] : 0.0;
+  }
+  const double al = sum_partials(apart + s * stride, (e1 - e0 + kPartRows - 1) / kPartRows, sh);
+  if (blockIdx.x == 0 && t == 0) st->alpha[k - 1] = al;
+  double nrm = 0.0;
+#pragma unroll
+  for (int r = 0; r < EPT; ++r) {
+    x[r] -= al * xv[r];
+    x[r] -= be * xp[r];
+    if (in[r]) u[ix[r]] = x[r];
+    nrm += x[r] * x[r];
+  }
+  for (int j0 = 0; j0 < k; j0 += 8) {   // eight basis vectors' loads at a time
+    double vq[8][EPT], a[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+#pragma unroll
+      for (int r = 0; r < EPT; ++r) vq[q][r] = V[int64_t(min(j0 + q, k - 1)) * v.m3 + ix[r]];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      a[q] = 0.0;
+#pragma unroll
+      for (int r = 0; r < EPT; ++r) a[q] += vq[q][r] * x[r];
+    }
+#pragma unroll
+    for (int q = 0; q < 8; ++q) a[q] = wave_sum(a[q]);
+    if (lane == 0)
+#pragma unroll
+      for (int q = 0; q < 8; ++q)
+        if (j0 + q < k) hsh[(j0 + q) * W + wave] = a[q];
+  }
+  nrm = wave_sum(nrm);
+  if (lane == 0) hsh[k * W + wave] = nrm;
+  __syncthreads();
+  if (t <= k) {
+    double r = hsh[t * W];
+#pragma unroll
+    for (int w = 1; w < W; ++w) r += hsh[t * W + w];
+    part[(int64_t(s) * (kMaxKrylov + 1) + t) * nb + blockIdx.x] = r;
+  }
+}
+
+// The root of T_k and the stop test of process s by one workgroup, beta_k being in the state.  ring
+// (single process, nullable): the host's slot of status words.  host_done (batches, nullable):
+// pinned words that receive `epoch` when a process stops.
+__device__ __forceinline__ void root_and_stop(const SegView &v, int s, int k, double tol,
+                                              LzRingSlot *ring, int *host_done, int epoch) {
+  LzState *st = v.st + s;
+  // every thread reads the same reason: only this workgroup writes it, after the barriers
+  if (v.done || st->reason == 0) tridiag_body(k, tol, st, v.eig + s);
+  if (threadIdx.x != 0) return;
+  if (ring) post_status(st, ring);
+  if (v.done && st->reason != 0) {
+    v.done[s] = 1;
+    if (atomicAdd(v.done + v.nsys + 1, 1) + 1 == v.nsys) v.done[v.nsys] = 1;
+    if (host_done) {
+      host_done[s] = epoch;
+      __threadfence_system();
+    }
+  }
+}
+
+// The same in a launch of its own, one workgroup per process.
+__global__ __launch_bounds__(kThreads) void lz_root(SegView v, int k, double tol, LzRingSlot *ring,
+                                                    int *host_done, int epoch) {
+  if (v.done && v.done[blockIdx.x]) return;
+  root_and_stop(v, blockIdx.x, k, tol, ring, host_done, epoch);
+}
+
+// ROOT: the process's first workgroup takes the root too.  Its registers and LDS leave two
+// workgroups per CU, so a grid beyond that (large batches: 1,536 workgroups took 36 us) leaves
+// the root to lz_root.
+template <int EPT, typename Real, bool ROOT>
+__global__ __launch_bounds__(kThreads, 2) void lz_update(
+    SegView v, int k, double tol, double *__restrict__ V, const double *__restrict__ u,
+    const double *__restrict__ part, int nb, int write_next, const double *__restrict__ hw,
+    Real *__restrict__ src, int *counter, LzRingSlot *ring, int *host_done, int epoch) {
+  __shared__ double hs[kMaxKrylov + 1];
+  const int s = blockIdx.y, t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  if (counter && s == 0 && blockIdx.x == 0 && t == 0) counter[0] = 0;
+  if (v.done && v.done[s]) return;
+  int64_t e0, e1;
+  seg_range(v, s, e0, e1);
+  const int ng = seg_groups<EPT>(e1 - e0);
+  if (int(blockIdx.x) >= ng) return;
+  LzState *st = v.st + s;
+  for (int j = wave; j <= k; j += kThreads / 64) {
+    const double *p = part + (int64_t(s) * (kMaxKrylov + 1) + j) * nb;
+    double a = 0.0;
+    for (int b = lane; b < ng; b += 64) a += p[b];
+    a = wave_sum(a);
+    if (lane == 0) hs[j] = a;
+  }
+  __syncthreads();
+  const double hj = lane < k ? hs[lane] : 0.0;
+  const double b2 = hs[k] - wave_sum(hj * hj);
+  const double beta = sqrt(b2 > 0.0 ? b2 : (b2 == b2 ? 0.0 : b2));
+  if (write_next) {
+    int64_t ix[EPT];
+    bool in[EPT];
+    double x[EPT], proj[EPT];
+#pragma unroll
+    for (int r = 0; r < EPT; ++r) {
+      const int64_t i = e0 + (int64_t(blockIdx.x) * EPT + r) * kThreads + t;
+      in[r] = i < e1;
+      ix[r] = in[r] ? i : 0;
+      x[r] = in[r] ? u[ix[r]] : 0.0;
+      proj[r] = 0.0;
+    }
+    for (int j0 = 0; j0 < k; j0 += 8) {
+      double vq[8][EPT];
+#pragma unroll
+      for (int q = 0; q < 8; ++q)
+#pragma unroll
+        for (int r = 0; r < EPT; ++r) vq[q][r] = V[int64_t(min(j0 + q, k - 1)) * v.m3 + ix[r]];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const double h = j0 + q < k ? hs[j0 + q] : 0.0;
+#pragma unroll
+        for (int r = 0; r < EPT; ++r) proj[r] += h * vq[q][r];
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < EPT; ++r)
+      if (in[r]) {
+        const double y = x[r] - proj[r];
+        const double z = beta > 0.0 ? y / beta : 0.0;
+        V[int64_t(k) * v.m3 + ix[r]] = z;
+        if (src) {
+          const int64_t sp = ix[r] / 3;
+          src[(ix[r] - 3 * sp) * (v.m3 / 3) + sp] = Real(hw[sp] * z);
+        }
+      }
+  }
+  if (blockIdx.x != 0) return;
+  if (t == 0) st->beta[k - 1] = beta;
+  if (t < k) st->h[t] = hs[t];
+  if constexpr (ROOT) {
+    __syncthreads();
+    root_and_stop(v, s, k, tol, ring, host_done, epoch);
+  }
+}
+
+// ---- the same iteration with its sums in a fixed grouping (mixed precision) ---------------------
 //
-// Sums in two stages, kRedBlocks workgroup partials and their sum in a fixed order by one
-// workgroup (a last-arriving workgroup could take the second stage, but its device-scope
-// release fence writes back its XCD's L2 and cost more than the launch it saved).  The
-// three-term recurrence is applied where its result is read; alpha's second stage is taken by
-// every workgroup of the re-orthogonalisation dots (the same sum in each), and the second
-// stage of |u| shares its workgroup with the eigensolve.  The arithmetic and its order are
-// those of one kernel per step.
+// A mixed product rounds v_k to float32, so another rounding of alpha, h or beta, 1e-16 of v_k, now
+// and then carries one of its elements across a float32 rounding boundary (a few per cent of the
+// solves of 282,000 spheres), which moves a position by 1e-10 and a velocity of the next step by up
+// to 7e-8.  Mixed processes therefore keep one grouping of every sum, whatever the launches: NB
+// workgroups of strided elements, a tree over the workgroup's threads, then the NB partials by a
+// tree (single process, NB = 256) or in order (segments, NB = 16), and beta as the norm of the
+// re-orthogonalised u.  Each finishing sum is taken by every workgroup that needs it instead of a
+// launch of its own: four kernels per iteration after the product, against six (eight in
+// batches, with the packing of v_k and the all-done flag).
 
-__global__ __launch_bounds__(kThreads) void dot_partial(int64_t m, const double *__restrict__ a,
-                                                        const double *__restrict__ b,
-                                                        double *__restrict__ part) {
+template <bool TREE>
+constexpr int ord_blocks() { return TREE ? 256 : 16; }
+
+// Sum of the workgroup's 256 values by a tree, on thread 0.
+__device__ __forceinline__ double tree_sum(double v, double *sh) {
+  const int t = threadIdx.x;
+  sh[t] = v;
+  __syncthreads();
+  double r = 0.0;
+  if (t < 64) {
+    r = (sh[t] + sh[t + 128]) + (sh[t + 64] + sh[t + 192]);
+    r = wave_sum(r);
+  }
+  __syncthreads();
+  return r;
+}
+
+// Sum of a quantity's partials, the same on every lane (every lane of a wavefront calls this).
+template <bool TREE>
+__device__ __forceinline__ double finish_sum(const double *__restrict__ p) {
+  if constexpr (TREE) {
+    const int l = threadIdx.x & 63;
+    return wave_sum((p[l] + p[l + 128]) + (p[l + 64] + p[l + 192]));
+  } else {
+    double acc = 0.0;
+    for (int b = 0; b < ord_blocks<TREE>(); ++b) acc += p[b];
+    return acc;
+  }
+}
+
+// part[s * NB + b]: partial of a . b over process s.
+template <bool TREE>
+__global__ __launch_bounds__(kThreads) void ord_dot(SegView v, const double *__restrict__ a,
+                                                    const double *__restrict__ b, int check_done,
+                                                    double *__restrict__ part) {
   __shared__ double sh[kThreads];
+  constexpr int NB = ord_blocks<TREE>();
+  const int s = blockIdx.y;
+  if (check_done && v.done && v.done[s]) return;
+  int64_t e0, e1;
+  seg_range(v, s, e0, e1);
   double acc = 0.0;
-  for (int64_t i = int64_t(blockIdx.x) * kThreads + threadIdx.x; i < m;
-       i += int64_t(gridDim.x) * kThreads)
+  for (int64_t i = e0 + int64_t(blockIdx.x) * kThreads + threadIdx.x; i < e1;
+       i += int64_t(NB) * kThreads)
     acc += a[i] * b[i];
-  const double s = block_sum(acc, sh);
-  if (threadIdx.x == 0) part[blockIdx.x] = s;
+  const double r = tree_sum(acc, sh);
+  if (threadIdx.x == 0) part[int64_t(s) * NB + blockIdx.x] = r;
 }
 
-// out = sum(part) (mode 0) or sqrt(sum(part)) (mode 1)
-__global__ __launch_bounds__(kThreads) void dot_finish(const double *__restrict__ part, int np,
-                                                       double *__restrict__ out, int mode) {
-  __shared__ double sh[kThreads];
-  double acc = 0.0;
-  for (int i = threadIdx.x; i < np; i += kThreads) acc += part[i];
-  const double s = block_sum(acc, sh);
-  if (threadIdx.x == 0) out[0] = mode == 1 ? sqrt(s) : s;
+// lz_start from the partials of w . w (alpha_1 is left to ord_dot).
+template <bool TREE, typename Real>
+__global__ __launch_bounds__(kThreads) void ord_start(SegView v, const double *__restrict__ w,
+                                                      const double *__restrict__ npart,
+                                                      double *__restrict__ V,
+                                                      const double *__restrict__ hw,
+                                                      Real *__restrict__ src,
+                                                      const double *__restrict__ mw,
+                                                      double *__restrict__ u, int *counter) {
+  const int s = blockIdx.y, t = threadIdx.x;
+  if (s == 0 && blockIdx.x == 0 && t == 0) {
+    if (counter) counter[0] = 0;
+    if (v.done) v.done[v.nsys] = v.done[v.nsys + 1] = 0;
+  }
+  int64_t e0, e1;
+  seg_range(v, s, e0, e1);
+  if (blockIdx.x > 0 && e0 + int64_t(blockIdx.x) * kThreads >= e1) return;
+  const double wn = sqrt(finish_sum<TREE>(npart + int64_t(s) * ord_blocks<TREE>()));
+  if (blockIdx.x == 0) reset_state(v, s, wn);
+  const int64_t i = e0 + int64_t(blockIdx.x) * kThreads + t;
+  if (i >= e1) return;
+  const double x = wn > 0.0 ? w[i] / wn : 0.0;
+  V[i] = x;
+  if (src) {
+    const int64_t sp = i / 3;
+    src[(i - 3 * sp) * (v.m3 / 3) + sp] = Real(hw[sp] * x);
+  }
+  if (mw) u[i] = wn > 0.0 ? mw[i] / wn : 0.0;
 }
 
-// part[j * gridDim.x + b] = partial of V_j . (u - alpha_k v_k - beta_{k-1} v_{k-1}) over
-// workgroup b's share (grid y: j < k); u is not modified.  alpha_k is the sum of the np
-// partials of v_k . u in apart, which every workgroup forms as dot_finish would (the same
-// value in each), and the first workgroup stores (alpha_out).
-__global__ __launch_bounds__(kThreads) void reorth_dots_3t(
-    int64_t m, const double *__restrict__ V, const double *__restrict__ u,
-    const double *__restrict__ vk, const double *__restrict__ vprev,
-    const double *__restrict__ apart, int np, double *__restrict__ alpha_out,
-    const double *__restrict__ beta, double *__restrict__ part) {
+// part[(s * kMaxKrylov + j) * NB + b] = partial of V_j . (u - alpha_k v_k - beta_{k-1} v_{k-1}), j =
+// blockIdx.z < k; u is not modified.
+template <bool TREE>
+__global__ __launch_bounds__(kThreads) void ord_dots(SegView v, int k,
+                                                     const double *__restrict__ V,
+                                                     const double *__restrict__ u,
+                                                     const double *__restrict__ apart,
+                                                     double *__restrict__ part) {
   __shared__ double sh[kThreads];
-  double a0 = 0.0;
-  for (int i = threadIdx.x; i < np; i += kThreads) a0 += apart[i];
-  const double al = block_sum(a0, sh);
-  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) alpha_out[0] = al;
-  const int j = blockIdx.y;
-  const double *vj = V + int64_t(j) * m;
-  const double be = vprev ? beta[0] : 0.0;
+  constexpr int NB = ord_blocks<TREE>();
+  const int s = blockIdx.y, j = blockIdx.z;
+  if (v.done && v.done[s]) return;
+  int64_t e0, e1;
+  seg_range(v, s, e0, e1);
+  LzState *st = v.st + s;
+  const double al = finish_sum<TREE>(apart + int64_t(s) * NB);
+  if (blockIdx.x == 0 && j == 0 && threadIdx.x == 0) st->alpha[k - 1] = al;
+  const double *vj = V + int64_t(j) * v.m3, *vk = V + int64_t(k - 1) * v.m3;
+  const double *vprev = k > 1 ? V + int64_t(k - 2) * v.m3 : nullptr;
+  const double be = vprev ? st->beta[k - 2] : 0.0;
   double acc = 0.0;
-  for (int64_t i = int64_t(blockIdx.x) * kThreads + threadIdx.x; i < m;
-       i += int64_t(gridDim.x) * kThreads) {
+  for (int64_t i = e0 + int64_t(blockIdx.x) * kThreads + threadIdx.x; i < e1;
+       i += int64_t(NB) * kThreads) {
     double x = u[i] - al * vk[i];
     if (vprev) x -= be * vprev[i];
     acc += vj[i] * x;
   }
-  const double s = block_sum(acc, sh);
-  if (threadIdx.x == 0) part[int64_t(j) * gridDim.x + blockIdx.x] = s;
+  const double r = tree_sum(acc, sh);
+  if (threadIdx.x == 0) part[(int64_t(s) * kMaxKrylov + j) * NB + blockIdx.x] = r;
 }
 
-// h[j] = sum of the np partials of V_j . u; one workgroup per basis vector j
-__global__ __launch_bounds__(kThreads) void reorth_finish(int np, const double *__restrict__ part,
-                                                          double *__restrict__ h) {
+// u <- u - alpha_k v_k - beta_{k-1} v_{k-1} - sum_j h_j V_j, and the partials of |u|^2.
+template <bool TREE>
+__global__ __launch_bounds__(kThreads) void ord_update(SegView v, int k,
+                                                       const double *__restrict__ V,
+                                                       double *__restrict__ u,
+                                                       const double *__restrict__ part,
+                                                       double *__restrict__ bpart) {
   __shared__ double sh[kThreads];
-  const int j = blockIdx.x;
-  double acc = 0.0;
-  for (int i = threadIdx.x; i < np; i += kThreads) acc += part[int64_t(j) * np + i];
-  const double s = block_sum(acc, sh);
-  if (threadIdx.x == 0) h[j] = s;
-}
-
-// u <- u - alpha_k v_k - beta_{k-1} v_{k-1} - sum_j h_j V_j, and the workgroup partials of |u|^2
-__global__ __launch_bounds__(kThreads) void reorth_update_sq(
-    int64_t m, int k, const double *__restrict__ V, double *__restrict__ u,
-    const double *__restrict__ vk, const double *__restrict__ vprev,
-    const LzState *__restrict__ st, double *__restrict__ part) {
-  __shared__ double sh[kThreads];
+  __shared__ double hs[kMaxKrylov];
+  constexpr int NB = ord_blocks<TREE>();
+  const int s = blockIdx.y, t = threadIdx.x;
+  if (v.done && v.done[s]) return;
+  int64_t e0, e1;
+  seg_range(v, s, e0, e1);
+  LzState *st = v.st + s;
+  const double *p = part + int64_t(s) * kMaxKrylov * NB;
+  if constexpr (TREE) {
+    for (int j = t >> 6; j < k; j += kThreads / 64) {
+      const double h = finish_sum<TREE>(p + int64_t(j) * NB);
+      if ((t & 63) == 0) hs[j] = h;
+    }
+  } else {
+    if (t < k) hs[t] = finish_sum<TREE>(p + int64_t(t) * NB);
+  }
+  __syncthreads();
+  if (blockIdx.x == 0 && t < k) st->h[t] = hs[t];
+  const double *vk = V + int64_t(k - 1) * v.m3;
+  const double *vprev = k > 1 ? V + int64_t(k - 2) * v.m3 : nullptr;
   const double al = st->alpha[k - 1], be = vprev ? st->beta[k - 2] : 0.0;
   double acc = 0.0;
-  for (int64_t i = int64_t(blockIdx.x) * kThreads + threadIdx.x; i < m;
-       i += int64_t(gridDim.x) * kThreads) {
+  for (int64_t i = e0 + int64_t(blockIdx.x) * kThreads + t; i < e1;
+       i += int64_t(NB) * kThreads) {
     double x = u[i] - al * vk[i];
     if (vprev) x -= be * vprev[i];
     double proj = 0.0;
-    for (int j = 0; j < k; ++j) proj += st->h[j] * V[int64_t(j) * m + i];
+    for (int j = 0; j < k; ++j) proj += hs[j] * V[int64_t(j) * v.m3 + i];
     x -= proj;
     u[i] = x;
     acc += x * x;
   }
-  const double s = block_sum(acc, sh);
-  if (threadIdx.x == 0) part[blockIdx.x] = s;
+  const double r = tree_sum(acc, sh);
+  if (t == 0) bpart[int64_t(s) * NB + blockIdx.x] = r;
 }
 
-// beta_k = sqrt(sum of the np partials), then the eigensolve of T_k with its stop test (unless
-// the process has stopped) and the status words into the host's ring slot.
-__global__ __launch_bounds__(kThreads) void beta_eig(int np, const double *__restrict__ part,
-                                                     int k, double tol, LzState *__restrict__ st,
-                                                     LzEig *__restrict__ eig, LzRingSlot *slot) {
-  __shared__ double sh[kThreads];
-  double acc = 0.0;
-  for (int i = threadIdx.x; i < np; i += kThreads) acc += part[i];
-  const double s = block_sum(acc, sh);
-  if (threadIdx.x == 0) st->beta[k - 1] = sqrt(s);
-  __syncthreads();
-  // every thread reads the same reason: only tridiag_body writes it, after its barriers
-  if (st->reason == 0) tridiag_body(k, tol, st, eig);
-  if (threadIdx.x == 0) post_status(st, slot);
+// beta_k, v_{k+1} = u / beta_k (when write_next) into the basis and the packed sources and, with
+// ROOT, the root and stop test by the process's first workgroup (see lz_update).
+template <bool TREE, typename Real, bool ROOT>
+__global__ __launch_bounds__(kThreads, ROOT ? 2 : 4) void ord_scale(
+    SegView v, int k, double tol, double *__restrict__ V, const double *__restrict__ u,
+    const double *__restrict__ bpart, int write_next, const double *__restrict__ hw,
+    Real *__restrict__ src, int *counter, LzRingSlot *ring, int *host_done, int epoch) {
+  const int s = blockIdx.y, t = threadIdx.x;
+  if (counter && s == 0 && blockIdx.x == 0 && t == 0) counter[0] = 0;
+  if (v.done && v.done[s]) return;
+  int64_t e0, e1;
+  seg_range(v, s, e0, e1);
+  if (blockIdx.x > 0 && e0 + int64_t(blockIdx.x) * kThreads >= e1) return;
+  const double beta = sqrt(finish_sum<TREE>(bpart + int64_t(s) * ord_blocks<TREE>()));
+  const int64_t i = e0 + int64_t(blockIdx.x) * kThreads + t;
+  if (write_next && i < e1) {
+    const double x = beta > 0.0 ? u[i] / beta : 0.0;
+    V[int64_t(k) * v.m3 + i] = x;
+    if (src) {
+      const int64_t sp = i / 3;
+      src[(i - 3 * sp) * (v.m3 / 3) + sp] = Real(hw[sp] * x);
+    }
+  }
+  if (blockIdx.x != 0) return;
+  if (t == 0) v.st[s].beta[k - 1] = beta;
+  if constexpr (ROOT) {
+    __syncthreads();
+    root_and_stop(v, s, k, tol, ring, host_done, epoch);
+  }
 }
 
 // Longest segment (3 n values of one system) that one workgroup takes through a whole Lanczos
@@ -1121,135 +1456,6 @@ __global__ __launch_bounds__(kThreads) void lanczos_eig(LzState *__restrict__ st
   if (threadIdx.x == 0) post_status(st, slot);
 }
 
-// ---- batched Lanczos: one Krylov process per system, segments of the concatenated vectors ----
-//
-// System s owns elements [3 offs[s], 3 offs[s+1]) of every 3n vector and its own LzState.
-// done[s] != 0 freezes a system: every kernel skips it, so a system stops changing once its
-// own tolerance or breakdown test is met, whatever the others do.
-
-constexpr int kSegBlocks = 16;      // partial sums per system segment
-
-struct SegView {
-  const int64_t *offs;    // nsys + 1 (device)
-  const int *sys_of;      // sphere -> system (device)
-  LzState *st;            // nsys states
-  int *done;              // nsys flags
-  LzEig *eig;             // nsys eigendecompositions
-};
-
-// part[s * kSegBlocks + b] = partial dot of a and b over system s
-__global__ __launch_bounds__(kThreads) void seg_dot_partial(SegView v, const double *__restrict__ a,
-                                                            const double *__restrict__ b,
-                                                            double *__restrict__ part) {
-  __shared__ double sh[kThreads];
-  const int s = blockIdx.y;
-  if (v.done[s]) return;
-  const int64_t e0 = 3 * v.offs[s], e1 = 3 * v.offs[s + 1];
-  double acc = 0.0;
-  for (int64_t i = e0 + int64_t(blockIdx.x) * kThreads + threadIdx.x; i < e1;
-       i += int64_t(kSegBlocks) * kThreads)
-    acc += a[i] * b[i];
-  const double r = block_sum(acc, sh);
-  if (threadIdx.x == 0) part[int64_t(s) * kSegBlocks + blockIdx.x] = r;
-}
-
-// st[s].<field at double offset `field`> = sum (mode 0) or sqrt(sum) (mode 1)
-__global__ __launch_bounds__(64) void seg_dot_finish(SegView v, const double *__restrict__ part,
-                                                     int field, int mode) {
-  const int s = blockIdx.x;
-  if (v.done[s] || threadIdx.x != 0) return;
-  double acc = 0.0;
-  for (int b = 0; b < kSegBlocks; ++b) acc += part[int64_t(s) * kSegBlocks + b];
-  reinterpret_cast<double *>(v.st + s)[field] = mode == 1 ? sqrt(acc) : acc;
-}
-
-// y = x / st[s].<field> on every live system (zero when the divisor is not positive)
-__global__ void seg_scale_by_inverse(SegView v, int64_t m, const double *__restrict__ x, int field,
-                                     double *__restrict__ y) {
-  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= m) return;
-  const int s = v.sys_of[i / 3];
-  if (v.done[s]) return;
-  const double d = reinterpret_cast<const double *>(v.st + s)[field];
-  y[i] = d > 0.0 ? x[i] / d : 0.0;
-}
-
-// part[(s * nvec + j) * kSegBlocks + b] = partial dot of V_j and u - alpha_k v_k -
-// beta_{k-1} v_{k-1} over system s (the three-term recurrence applied where it is read; u is
-// not modified), nvec = k
-__global__ __launch_bounds__(kThreads) void seg_reorth_dots_3t(
-    SegView v, int64_t m, int nvec, const double *__restrict__ V, const double *__restrict__ u,
-    const double *__restrict__ vk, const double *__restrict__ vprev, double *__restrict__ part) {
-  __shared__ double sh[kThreads];
-  const int s = blockIdx.z, j = blockIdx.y;
-  if (v.done[s]) return;
-  const int64_t e0 = 3 * v.offs[s], e1 = 3 * v.offs[s + 1];
-  const double *vj = V + int64_t(j) * m;
-  const double al = v.st[s].alpha[nvec - 1], be = vprev ? v.st[s].beta[nvec - 2] : 0.0;
-  double acc = 0.0;
-  for (int64_t i = e0 + int64_t(blockIdx.x) * kThreads + threadIdx.x; i < e1;
-       i += int64_t(kSegBlocks) * kThreads) {
-    double x = u[i] - al * vk[i];
-    if (vprev) x -= be * vprev[i];
-    acc += vj[i] * x;
-  }
-  const double r = block_sum(acc, sh);
-  if (threadIdx.x == 0) part[(int64_t(s) * nvec + j) * kSegBlocks + blockIdx.x] = r;
-}
-
-__global__ __launch_bounds__(64) void seg_reorth_finish(SegView v, int nvec,
-                                                        const double *__restrict__ part) {
-  const int s = blockIdx.x;
-  if (v.done[s]) return;
-  for (int j = threadIdx.x; j < nvec; j += blockDim.x) {
-    double acc = 0.0;
-    for (int b = 0; b < kSegBlocks; ++b) acc += part[(int64_t(s) * nvec + j) * kSegBlocks + b];
-    v.st[s].h[j] = acc;
-  }
-}
-
-// u <- u - alpha_k v_k - beta_{k-1} v_{k-1} - sum_j h_j V_j on every live system, and
-// part[s * kSegBlocks + b] = the partial of |u|^2 over system s
-__global__ __launch_bounds__(kThreads) void seg_reorth_update_sq(
-    SegView v, int64_t m, int k, const double *__restrict__ V, double *__restrict__ u,
-    const double *__restrict__ vk, const double *__restrict__ vprev, double *__restrict__ part) {
-  __shared__ double sh[kThreads];
-  const int s = blockIdx.y;
-  if (v.done[s]) return;
-  const int64_t e0 = 3 * v.offs[s], e1 = 3 * v.offs[s + 1];
-  const LzState &st = v.st[s];
-  const double al = st.alpha[k - 1], be = vprev ? st.beta[k - 2] : 0.0;
-  double acc = 0.0;
-  for (int64_t i = e0 + int64_t(blockIdx.x) * kThreads + threadIdx.x; i < e1;
-       i += int64_t(kSegBlocks) * kThreads) {
-    double x = u[i] - al * vk[i];
-    if (vprev) x -= be * vprev[i];
-    double proj = 0.0;
-    for (int j = 0; j < k; ++j) proj += st.h[j] * V[int64_t(j) * m + i];
-    x -= proj;
-    u[i] = x;
-    acc += x * x;
-  }
-  const double r = block_sum(acc, sh);
-  if (threadIdx.x == 0) part[int64_t(s) * kSegBlocks + blockIdx.x] = r;
-}
-
-// beta_k = sqrt(sum of the system's kSegBlocks partials, in order), then the eigensolve of T_k
-// with its stop test; a stopped system is frozen.
-__global__ __launch_bounds__(kThreads) void seg_beta_eig(SegView v, int m, double tol,
-                                                   const double *__restrict__ part) {
-  const int s = blockIdx.x;
-  if (v.done[s]) return;
-  if (threadIdx.x == 0) {
-    double acc = 0.0;
-    for (int b = 0; b < kSegBlocks; ++b) acc += part[int64_t(s) * kSegBlocks + b];
-    v.st[s].beta[m - 1] = sqrt(acc);
-  }
-  __syncthreads();
-  tridiag_body(m, tol, v.st + s, v.eig + s);
-  if (threadIdx.x == 0 && v.st[s].reason != 0) v.done[s] = 1;
-}
-
 // The eigensolve of T_1, T_2, ..., T_m in turn (as a Krylov process meets them), row k - 1 of
 // ys (m doubles) receiving y_k = |w| T_k^{1/2} e_1 (entries k..m-1 zero); fail[0] = 1 when an
 // eigensolve fails.  The stop tests are evaluated but do not stop the sequence.
@@ -1268,16 +1474,34 @@ __global__ __launch_bounds__(kThreads) void tridiag_sequence(int m, LzState *__r
   }
 }
 
-// lanczos_step_body for every live system, one workgroup each (segments <= kFusedSegment).
-__global__ __launch_bounds__(kThreads) void seg_lanczos_step(SegView v, double *__restrict__ V,
-                                                             double *__restrict__ u, int64_t m3,
-                                                             int k, double tol, int write_next) {
+// lanczos_step_body for every live system, one workgroup each (segments <= kFusedSegment); src,
+// counter, host_done and epoch as in lz_update.
+template <typename Real>
+__global__ __launch_bounds__(kThreads) void seg_lanczos_step(
+    SegView v, double *__restrict__ V, double *__restrict__ u, int k, double tol, int write_next,
+    const double *__restrict__ hw, Real *__restrict__ src, int *counter, int *host_done,
+    int epoch) {
   const int s = blockIdx.x;
+  if (counter && s == 0 && threadIdx.x == 0) counter[0] = 0;
   if (v.done[s]) return;
   LzState *st = v.st + s;
-  lanczos_step_body(st, v.eig + s, V, u, m3, 3 * v.offs[s], 3 * v.offs[s + 1], k, tol,
-                    write_next != 0);
-  if (threadIdx.x == 0 && st->reason != 0) v.done[s] = 1;
+  const int64_t e0 = 3 * v.offs[s], e1 = 3 * v.offs[s + 1];
+  lanczos_step_body(st, v.eig + s, V, u, v.m3, e0, e1, k, tol, write_next != 0);
+  if (src && write_next && st->reason == 0) {
+    const double *next = V + int64_t(k) * v.m3;
+    for (int64_t i = e0 + threadIdx.x; i < e1; i += kThreads) {   // this thread's own values
+      const int64_t sp = i / 3;
+      src[(i - 3 * sp) * (v.m3 / 3) + sp] = Real(hw[sp] * next[i]);
+    }
+  }
+  if (threadIdx.x == 0 && st->reason != 0) {
+    v.done[s] = 1;
+    if (atomicAdd(v.done + v.nsys + 1, 1) + 1 == v.nsys) v.done[v.nsys] = 1;
+    if (host_done) {
+      host_done[s] = epoch;
+      __threadfence_system();
+    }
+  }
 }
 
 // out = V_m y_m per system (m = the system's own iteration count)
@@ -1289,44 +1513,6 @@ __global__ void seg_basis_combine(SegView v, int64_t m, const double *__restrict
   double acc = 0.0;
   for (int j = 0; j < st.m; ++j) acc += st.y[j] * V[int64_t(j) * m + i];
   out[i] = acc;
-}
-
-__global__ void lz_reset_batched(SegView v, int nsys) {
-  const int s = blockIdx.x;
-  if (s >= nsys) return;
-  LzState *st = v.st + s;
-  const int t = threadIdx.x;
-  if (t < kMaxKrylov) {
-    st->alpha[t] = 0.0;
-    st->beta[t] = 0.0;
-    st->y[t] = 0.0;
-    st->yprev[t] = 0.0;
-    st->h[t] = 0.0;
-  }
-  if (t == 0) {
-    st->wnorm = 0.0;
-    st->eig_m = 0;
-    st->eps = 0.0;
-    st->m = 0;
-    st->reason = 0;
-    v.done[s] = 0;
-    if (s == 0) v.done[nsys] = 0;
-  }
-}
-
-// done[nsys] = 1 once every system is done: later launches of the persistent product kernel
-// return at once instead of walking their work list.
-__global__ __launch_bounds__(256) void seg_all_done(SegView v, int nsys) {
-  __shared__ int any[256];
-  int open = 0;
-  for (int s = threadIdx.x; s < nsys; s += 256) open |= v.done[s] == 0;
-  any[threadIdx.x] = open;
-  __syncthreads();
-  for (int off = 128; off > 0; off >>= 1) {
-    if (int(threadIdx.x) < off) any[threadIdx.x] |= any[threadIdx.x + off];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) v.done[nsys] = any[0] ? 0 : 1;
 }
 
 // compact status record per system: (m, reason, eps)
@@ -1353,13 +1539,132 @@ __global__ void multiply_by(int64_t m, double *x, const double *__restrict__ s) 
 inline unsigned nblk(int64_t m) { return unsigned((m + kThreads - 1) / kThreads); }
 
 
-int dot(rpb_ctx *ctx, int64_t m, const double *a, const double *b, double *part, double *out,
-        int mode, hipStream_t stream) {
-  dot_partial<<<kRedBlocks, kThreads, 0, stream>>>(m, a, b, part);
-  RPB_LAUNCHED(ctx);
-  dot_finish<<<1, kThreads, 0, stream>>>(part, kRedBlocks, out, mode);
-  RPB_LAUNCHED(ctx);
+// Elements per thread of lz_dots and lz_update: one while the grid then fits the device at once (two
+// workgroups per CU, by the registers of the root), else four.
+inline int ept_of(int nsys, int64_t longest) {
+  return int64_t(nsys) * nblk(longest) <= 512 ? 1 : 4;
+}
+inline int groups_of(int64_t longest, int ept) {
+  return int(std::max<int64_t>(1, (longest + kThreads * ept - 1) / (int64_t(kThreads) * ept)));
+}
+
+// Partial sums of the processes' scalars: float64 processes take one partial of |w|^2 and of
+// alpha per 64 rows and one of each basis product per workgroup of lz_dots, mixed ones the
+// grouping of the ord_ kernels.
+struct LzPartials {
+  double *norm, *alpha, *dots;   // dots: basis products, then |u|^2
+  int64_t stride;                // partials of alpha per process
+  int nb;                        // workgroups of lz_dots
+};
+inline bool one_process(const SegView &v) { return v.offs == nullptr; }
+
+int lz_partials(rpb_ctx *ctx, int nsys, int64_t longest, LzPartials *out) {
+  out->stride = std::max<int64_t>({1, (longest + kPartRows - 1) / kPartRows, 256});
+  out->nb = groups_of(longest, ept_of(nsys, longest));
+  const int64_t dots = int64_t(kMaxKrylov + 1) * std::max(out->nb, 256);
+  int st;
+  out->norm = static_cast<double *>(workspace(
+      ctx, WS_REDUCE, size_t(nsys) * size_t(2 * out->stride + dots) * sizeof(double), &st));
+  if (!out->norm) return st;
+  out->alpha = out->norm + int64_t(nsys) * out->stride;
+  out->dots = out->alpha + int64_t(nsys) * out->stride;
   return RPB_OK;
+}
+
+// Whether every process's sums keep the grouping of the ord_ kernels.
+template <typename Real>
+constexpr bool ordered_sums() { return std::is_same<Real, float>::value; }
+
+// |w|, v_1 and the state of every process.
+template <typename Real>
+int start_processes(rpb_ctx *ctx, const SegView &v, int64_t longest, const double *w,
+                    const LzPartials &P, double *V, const double *hw, Real *src, const double *mw,
+                    double *u, int *counter, hipStream_t stream) {
+  const dim3 grid{std::max(1u, nblk(longest)), unsigned(v.nsys), 1u};
+  if constexpr (ordered_sums<Real>()) {
+    auto run = [&](auto T) -> int {
+      constexpr bool kT = decltype(T)::value;
+      const dim3 dg{unsigned(ord_blocks<kT>()), unsigned(v.nsys), 1u};
+      ord_dot<kT><<<dg, kThreads, 0, stream>>>(v, w, w, 0, P.norm);
+      RPB_LAUNCHED(ctx);
+      ord_start<kT, Real><<<grid, kThreads, 0, stream>>>(v, w, P.norm, V, hw, src, mw, u, counter);
+      RPB_LAUNCHED(ctx);
+      return RPB_OK;
+    };
+    return one_process(v) ? run(std::true_type{}) : run(std::false_type{});
+  } else {
+    lz_dot<<<grid, kThreads, 0, stream>>>(v, w, w, 0, P.norm, P.stride);
+    RPB_LAUNCHED(ctx);
+    lz_start<Real><<<grid, kThreads, 0, stream>>>(v, w, P.norm, V, hw, src, mw, u, P.alpha,
+                                                  P.stride, counter);
+    RPB_LAUNCHED(ctx);
+    return RPB_OK;
+  }
+}
+
+// The vector work, root and stop test of iteration k of every process after u = M v_k; dotted:
+// alpha's partials are there already.
+template <typename Real>
+int iterate_processes(rpb_ctx *ctx, const SegView &v, int64_t longest, int k, double tol,
+                      double *V, double *u, bool dotted, const LzPartials &P, bool write_next,
+                      const double *hw, Real *src, int *counter, LzRingSlot *ring, int *host_done,
+                      int epoch, hipStream_t stream) {
+  const double *vk = V + int64_t(k - 1) * v.m3;
+  const unsigned ns = unsigned(v.nsys);
+  const dim3 all{std::max(1u, nblk(longest)), ns, 1u};
+  auto root = [&]() -> int {
+    lz_root<<<ns, kThreads, 0, stream>>>(v, k, tol, ring, host_done, epoch);
+    RPB_LAUNCHED(ctx);
+    return RPB_OK;
+  };
+  if constexpr (ordered_sums<Real>()) {
+    auto run = [&](auto T) -> int {
+      constexpr bool kT = decltype(T)::value;
+      constexpr unsigned NB = unsigned(ord_blocks<kT>());
+      double *bpart = P.dots + int64_t(v.nsys) * kMaxKrylov * NB;
+      ord_dot<kT><<<dim3{NB, ns, 1u}, kThreads, 0, stream>>>(v, vk, u, 1, P.alpha);
+      RPB_LAUNCHED(ctx);
+      ord_dots<kT><<<dim3{NB, ns, unsigned(k)}, kThreads, 0, stream>>>(v, k, V, u, P.alpha,
+                                                                       P.dots);
+      RPB_LAUNCHED(ctx);
+      ord_update<kT><<<dim3{NB, ns, 1u}, kThreads, 0, stream>>>(v, k, V, u, P.dots, bpart);
+      RPB_LAUNCHED(ctx);
+      if (int64_t(all.x) * ns <= 512) {
+        ord_scale<kT, Real, true><<<all, kThreads, 0, stream>>>(
+            v, k, tol, V, u, bpart, write_next, hw, src, counter, ring, host_done, epoch);
+        RPB_LAUNCHED(ctx);
+        return RPB_OK;
+      }
+      ord_scale<kT, Real, false><<<all, kThreads, 0, stream>>>(
+          v, k, tol, V, u, bpart, write_next, hw, src, counter, ring, host_done, epoch);
+      RPB_LAUNCHED(ctx);
+      return root();
+    };
+    return one_process(v) ? run(std::true_type{}) : run(std::false_type{});
+  } else {
+    if (!dotted) {
+      lz_dot<<<all, kThreads, 0, stream>>>(v, vk, u, 1, P.alpha, P.stride);
+      RPB_LAUNCHED(ctx);
+    }
+    const int ept = ept_of(v.nsys, longest);
+    const dim3 grid{unsigned(P.nb), ns, 1u};
+    auto run = [&](auto E, auto R) -> int {
+      constexpr int kE = decltype(E)::value;
+      constexpr bool kR = decltype(R)::value;
+      lz_dots<kE><<<grid, kThreads, 0, stream>>>(v, k, V, u, P.alpha, P.stride, P.dots, P.nb);
+      RPB_LAUNCHED(ctx);
+      lz_update<kE, Real, kR><<<grid, kThreads, 0, stream>>>(v, k, tol, V, u, P.dots, P.nb,
+                                                             write_next, hw, src, counter, ring,
+                                                             host_done, epoch);
+      RPB_LAUNCHED(ctx);
+      return kR ? RPB_OK : root();
+    };
+    using E1 = std::integral_constant<int, 1>;
+    using E4 = std::integral_constant<int, 4>;
+    if (ept == 1) return run(E1{}, std::true_type{});
+    if (int64_t(P.nb) * v.nsys <= 512) return run(E4{}, std::true_type{});
+    return run(E4{}, std::false_type{});
+  }
 }
 
 }  // namespace
@@ -1510,9 +1815,8 @@ int lanczos_run(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const double
   if (!V) return st;
   double *u = static_cast<double *>(workspace(ctx, WS_VEC_A, size_t(m3) * sizeof(double), &st));
   if (!u) return st;
-  double *part = static_cast<double *>(
-      workspace(ctx, WS_REDUCE, size_t(kRedBlocks) * (kMaxKrylov + 1) * sizeof(double), &st));
-  if (!part) return st;
+  LzPartials P;
+  RPB_TRY(lz_partials(ctx, 1, m3, &P));
   LzState *ls = static_cast<LzState *>(workspace(ctx, WS_SMALL, kSmallBytes, &st));
   if (!ls) return st;
   LzEig *eig = static_cast<LzEig *>(workspace(ctx, WS_LZEIG, sizeof(LzEig), &st));
@@ -1530,8 +1834,8 @@ int lanczos_run(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const double
   LzRing *ring = lz_ring(ctx);
   LzRing *ring_dev = lz_ring_dev(ctx);
   const bool fused = m3 <= kFusedSegment;
-  // without the preconditioner the kernel that forms v_{k+1} also packs it for the next product
-  // (lanczos_vec, or scale_by_inverse_packed for larger systems)
+  // without the preconditioner the kernels that form v_1 and v_{k+1} also pack them for the next
+  // product (lz_start; lanczos_vec, or lz_update for larger systems)
   const bool prepack = !precond;
   void *src = nullptr;
   if (prepack) {
@@ -1548,11 +1852,13 @@ int lanczos_run(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const double
   const int lag = fused ? 2 : 1;
   const int *stopped = fused ? &ls->halt : &ls->reason;
 
-  lz_reset<<<1, 64, 0, stream>>>(ls);
-  RPB_LAUNCHED(ctx);
-  RPB_TRY(dot(ctx, m3, w, w, part, &ls->wnorm, 1, stream));
-  scale_by_inverse<<<nblk(m3), kThreads, 0, stream>>>(m3, w, &ls->wnorm, V, nullptr);
-  RPB_LAUNCHED(ctx);
+  const SegView view{nullptr, nullptr, ls, nullptr, eig, 1, m3};
+  if (f64)
+    RPB_TRY(start_processes(ctx, view, m3, w, P, V, hw, static_cast<double *>(src), mw, u, nullptr,
+                            stream));
+  else
+    RPB_TRY(start_processes(ctx, view, m3, w, P, V, hw, static_cast<float *>(src), mw, u, nullptr,
+                            stream));
 
   int m = 0;           // iterations whose result counts
   int reason = 0;
@@ -1565,20 +1871,19 @@ int lanczos_run(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const double
       const int slot = k % kLzRing;
       mark[slot] = ctx->ev_start.size();
       double *vm = V + int64_t(k - 1) * m3;
-      const double *vprev = k > 1 ? V + int64_t(k - 2) * m3 : nullptr;
+      bool dotted = false;   // alpha's partials are in apart
       if (precond) {   // u = L^-1 M L^-1 vm
         divide_by<<<nblk(m3), kThreads, 0, stream>>>(m3, vm, L, t);
         RPB_LAUNCHED(ctx);
         RPB_TRY(matvec_packed(ctx, p, g, t, nullptr, 0, n, u, stream, stopped));
         divide_by<<<nblk(m3), kThreads, 0, stream>>>(m3, u, L, u);
         RPB_LAUNCHED(ctx);
-      } else if (k == 1 && mw) {   // M v_1 = (M w) / |w| from the caller's product
-        scale_by_inverse<<<nblk(m3), kThreads, 0, stream>>>(m3, mw, &ls->wnorm, u, nullptr);
-        RPB_LAUNCHED(ctx);
-      } else if (prepack && k > 1) {   // v_k packed by the previous iteration's lanczos_vec
-        RPB_TRY(matvec_prepacked(ctx, p, g, src, u, stream, stopped));
-      } else {
-        RPB_TRY(matvec_packed(ctx, p, g, vm, nullptr, 0, n, u, stream, stopped));
+      } else if (k == 1 && mw) {   // M v_1 = (M w) / |w| from the caller's product (lz_start)
+        dotted = true;
+      } else {   // v_k packed where it was formed
+        DotOut dot{fused || !f64 ? nullptr : vm, P.alpha};
+        RPB_TRY(matvec_prepacked(ctx, p, g, src, u, stream, stopped, &dot));
+        dotted = dot.done;
       }
       if (fused) {   // the vector work in one workgroup; the eigensolve on the second stream
         if (f64)
@@ -1592,35 +1897,15 @@ int lanczos_run(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const double
         ctx->lz_live[slot] = true;   // the helper records lz_ev[slot] after its eigensolve
         seq[slot] = last_seq =
             lz_helper_push(helper, LzJob{ls, eig, &ring_dev->slot[slot], k, tol, slot});
-      } else {   // six kernels (see dot_partial)
-        double *apart = part + int64_t(kRedBlocks) * kMaxKrylov;   // partials of v_k . u
-        dot_partial<<<kRedBlocks, kThreads, 0, stream>>>(m3, vm, u, apart);
-        RPB_LAUNCHED(ctx);
-        const dim3 grid{unsigned(kRedBlocks), unsigned(k), 1u};
-        reorth_dots_3t<<<grid, kThreads, 0, stream>>>(m3, V, u, vm, vprev, apart, kRedBlocks,
-                                                       &ls->alpha[k - 1],
-                                                       k > 1 ? &ls->beta[k - 2] : nullptr, part);
-        RPB_LAUNCHED(ctx);
-        reorth_finish<<<unsigned(k), kThreads, 0, stream>>>(kRedBlocks, part, ls->h);
-        RPB_LAUNCHED(ctx);
-        reorth_update_sq<<<kRedBlocks, kThreads, 0, stream>>>(m3, k, V, u, vm, vprev, ls, part);
-        RPB_LAUNCHED(ctx);
-        beta_eig<<<1, kThreads, 0, stream>>>(kRedBlocks, part, k, tol, ls, eig,
-                                             &ring_dev->slot[slot]);
-        RPB_LAUNCHED(ctx);
-        if (k < max_iter) {
-          double *next = V + int64_t(k) * m3;
-          if (!prepack)
-            scale_by_inverse<<<nblk(m3), kThreads, 0, stream>>>(m3, u, &ls->beta[k - 1], next,
-                                                                 ls);
-          else if (f64)
-            scale_by_inverse_packed<double><<<nblk(m3), kThreads, 0, stream>>>(
-                m3, u, &ls->beta[k - 1], next, ls, hw, static_cast<double *>(src));
-          else
-            scale_by_inverse_packed<float><<<nblk(m3), kThreads, 0, stream>>>(
-                m3, u, &ls->beta[k - 1], next, ls, hw, static_cast<float *>(src));
-          RPB_LAUNCHED(ctx);
-        }
+      } else {
+        if (f64)
+          RPB_TRY(iterate_processes(ctx, view, m3, k, tol, V, u, dotted, P, k < max_iter, hw,
+                                    static_cast<double *>(src), nullptr, &ring_dev->slot[slot],
+                                    nullptr, 0, stream));
+        else
+          RPB_TRY(iterate_processes(ctx, view, m3, k, tol, V, u, dotted, P, k < max_iter, hw,
+                                    static_cast<float *>(src), nullptr, &ring_dev->slot[slot],
+                                    nullptr, 0, stream));
         RPB_TRY(lz_ring_post(ctx, slot, stream));
       }
       // the statuses up to iteration k - lag (all of them after the last iteration)
@@ -1670,105 +1955,134 @@ int lanczos_run(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const double
 
 namespace {
 
-// One Krylov process per segment (system) of `b`; product(src, done_dev, done_host, dst) writes
-// dst = M src for every segment not yet done (done_host: the flags as of the last host read,
-// NULL when unknown).  L (nullable): preconditioner scale, 3 b.n entries, with scratch t.
-// mw (nullable, not with L): M w computed by the caller, used for the first iteration.
+// Layout of the batched state: LzState records, the flags of SegView::done, then the status.
+inline size_t lz_status_offset(int nsys) {
+  return (size_t(nsys) * sizeof(LzState) + size_t(nsys + 2) * sizeof(int) + 255) / 256 * 256;
+}
+
+// A product of lanczos_segments: u = M v_k for every process not yet done.
+struct SegProduct {
+  const double *vk;        // the basis vectors ([3 n] of all processes)
+  const void *src;         // v_k packed (NULL: not packed)
+  const int *done_dev;     // device flags
+  const int *done_host;    // the flags as of the last host read, NULL when unknown
+  DotOut dot;              // alpha's partials, when the product can take them
+};
+
+// One Krylov process per segment (system) of `b`; product(SegProduct &, u) writes u = M v_k for
+// every segment not yet done.  hw (nullable): weights with which v_k is packed for the product where
+// it is formed (into `src`, of the precision `f64` names); counter (nullable): the product's work
+// counter, zeroed with it.  L (nullable): preconditioner scale, 3 b.n entries, with scratch t.
+// mw (nullable, not with L): M w computed by the caller, used for the first iteration.  With
+// sync_each the host reads the flags of iteration k after it has enqueued iteration k + lag.
 template <typename Product>
 int lanczos_segments(rpb_ctx *ctx, const Batch &b, const double *L, double *t, const double *w,
-                     double tol, int max_iter, Product &&product, double *out, bool sync_each,
+                     double tol, int max_iter, Product &&product, const double *hw, void *src,
+                     bool f64, int *counter, double *out, bool sync_each, int lag,
                      LzStatus *status_host, hipStream_t stream, const double *mw = nullptr) {
   const int64_t m3 = 3 * b.n;
   const int nsys = b.nsys;
+  int64_t longest = 0;
+  bool fused = true;            // every system small enough for one workgroup per iteration
+  for (int s = 0; s < nsys; ++s) {
+    const int64_t len = 3 * (b.host_offs[s + 1] - b.host_offs[s]);
+    longest = std::max(longest, len);
+    fused = fused && len <= kFusedSegment;
+  }
   int st;
   double *V = static_cast<double *>(
       workspace(ctx, WS_KRYLOV, size_t(max_iter) * size_t(m3) * sizeof(double), &st));
   if (!V) return st;
   double *u = static_cast<double *>(workspace(ctx, WS_VEC_A, size_t(m3) * sizeof(double), &st));
   if (!u) return st;
-  double *part = static_cast<double *>(workspace(
-      ctx, WS_REDUCE, size_t(nsys) * kMaxKrylov * kSegBlocks * sizeof(double), &st));
-  if (!part) return st;
+  LzPartials P;
+  RPB_TRY(lz_partials(ctx, nsys, longest, &P));
   const size_t states_bytes = size_t(nsys) * sizeof(LzState);
-  const size_t status_off = (states_bytes + size_t(nsys + 1) * sizeof(int) + 255) / 256 * 256;
+  const size_t status_off = lz_status_offset(nsys);
   char *lz = static_cast<char *>(
       workspace(ctx, WS_LZBATCH, status_off + size_t(nsys) * sizeof(LzStatus), &st));
   if (!lz) return st;
   LzEig *eig = static_cast<LzEig *>(workspace(ctx, WS_LZEIG, size_t(nsys) * sizeof(LzEig), &st));
   if (!eig) return st;
-  SegView v{b.offs, b.sys_of, reinterpret_cast<LzState *>(lz),
-            reinterpret_cast<int *>(lz + states_bytes), eig};
+  const SegView v{b.offs, b.sys_of, reinterpret_cast<LzState *>(lz),
+                  reinterpret_cast<int *>(lz + states_bytes), eig, nsys, m3};
   LzStatus *status_dev = reinterpret_cast<LzStatus *>(lz + status_off);
   const unsigned ns = unsigned(nsys);
-  const int f_alpha = int(offsetof(LzState, alpha) / sizeof(double));
-  const int f_beta = int(offsetof(LzState, beta) / sizeof(double));
-  const int f_wnorm = int(offsetof(LzState, wnorm) / sizeof(double));
-  auto seg_dot = [&](const double *a, const double *c, int field, int mode) -> int {
-    seg_dot_partial<<<dim3{unsigned(kSegBlocks), ns, 1u}, kThreads, 0, stream>>>(v, a, c, part);
-    RPB_LAUNCHED(ctx);
-    seg_dot_finish<<<ns, 64, 0, stream>>>(v, part, field, mode);
-    RPB_LAUNCHED(ctx);
-    return RPB_OK;
-  };
+  // a process that stops writes this call's epoch (from 1, unique in the context, whose pinned
+  // buffer starts zeroed) into its word of the pinned buffer
+  int *host_done = nullptr, *host_done_dev = nullptr;
+  const int epoch = ++ctx->lz_epoch;
+  if (sync_each) {
+    RPB_TRY(lz_ring_fence(ctx));
+    host_done = reinterpret_cast<int *>(static_cast<char *>(host_scratch(ctx)) + kHostDoneOffset);
+    host_done_dev =
+        reinterpret_cast<int *>(static_cast<char *>(host_scratch_dev(ctx)) + kHostDoneOffset);
+  }
+  std::vector<int> known;   // host copy of the flags, once read
 
-  lz_reset_batched<<<ns, 64, 0, stream>>>(v, nsys);
-  RPB_LAUNCHED(ctx);
-  RPB_TRY(seg_dot(w, w, f_wnorm, 1));
-  seg_scale_by_inverse<<<nblk(m3), kThreads, 0, stream>>>(v, m3, w, f_wnorm, V);
-  RPB_LAUNCHED(ctx);
-  int *host_done = static_cast<int *>(host_scratch(ctx));
-  const int *known = nullptr;   // host copy of the flags, once read
-  bool fused = true;            // every system small enough for one workgroup per iteration
-  for (int s = 0; s < nsys; ++s)
-    fused = fused && 3 * (b.host_offs[s + 1] - b.host_offs[s]) <= kFusedSegment;
-  for (int k = 1; k <= max_iter; ++k) {
+  if (f64)
+    RPB_TRY(start_processes(ctx, v, longest, w, P, V, hw, static_cast<double *>(src), mw, u,
+                            counter, stream));
+  else
+    RPB_TRY(start_processes(ctx, v, longest, w, P, V, hw, static_cast<float *>(src), mw, u, counter,
+                            stream));
+  size_t mark[kLzRing] = {};   // first timing record of each iteration in flight
+  int next_q = 1;              // first iteration whose flags the host has not read
+  bool stop = false;
+  for (int k = 1; k <= max_iter && !stop; ++k) {
+    const int slot = k % kLzRing;
+    mark[slot] = ctx->ev_start.size();
     double *vk = V + int64_t(k - 1) * m3;
-    const double *vprev = k > 1 ? V + int64_t(k - 2) * m3 : nullptr;
+    SegProduct job{vk, src, v.done, known.empty() ? nullptr : known.data(),
+                   DotOut{fused || !f64 ? nullptr : vk, P.alpha, P.stride}};
     if (L) {   // u = L^-1 M L^-1 vk (rows of finished systems are not used)
       divide_by<<<nblk(m3), kThreads, 0, stream>>>(m3, vk, L, t);
       RPB_LAUNCHED(ctx);
-      RPB_TRY(product(t, v.done, known, u));
+      job.vk = t;
+      job.dot.v = nullptr;
+      RPB_TRY(product(job, u));
       divide_by<<<nblk(m3), kThreads, 0, stream>>>(m3, u, L, u);
       RPB_LAUNCHED(ctx);
-    } else if (k == 1 && mw) {   // M v_1 = (M w) / |w| per system, from the caller's product
-      seg_scale_by_inverse<<<nblk(m3), kThreads, 0, stream>>>(v, m3, mw, f_wnorm, u);
-      RPB_LAUNCHED(ctx);
+    } else if (k == 1 && mw) {   // M v_1 = (M w) / |w| per system (lz_start)
+      job.dot.done = true;
     } else {
-      RPB_TRY(product(vk, v.done, known, u));
+      RPB_TRY(product(job, u));
     }
+    const bool next = k < max_iter;
     if (fused) {   // every system's iteration in one workgroup
-      seg_lanczos_step<<<ns, kThreads, 0, stream>>>(v, V, u, m3, k, tol, k < max_iter);
-      RPB_LAUNCHED(ctx);
-      seg_all_done<<<1, 256, 0, stream>>>(v, nsys);
+      if (f64)
+        seg_lanczos_step<double><<<ns, kThreads, 0, stream>>>(
+            v, V, u, k, tol, next, hw, static_cast<double *>(src), counter, host_done_dev, epoch);
+      else
+        seg_lanczos_step<float><<<ns, kThreads, 0, stream>>>(
+            v, V, u, k, tol, next, hw, static_cast<float *>(src), counter, host_done_dev, epoch);
       RPB_LAUNCHED(ctx);
     } else {
-      RPB_TRY(seg_dot(vk, u, f_alpha + k - 1, 0));
-      seg_reorth_dots_3t<<<dim3{unsigned(kSegBlocks), unsigned(k), ns}, kThreads, 0, stream>>>(
-          v, m3, k, V, u, vk, vprev, part);
-      RPB_LAUNCHED(ctx);
-      seg_reorth_finish<<<ns, 64, 0, stream>>>(v, k, part);
-      RPB_LAUNCHED(ctx);
-      seg_reorth_update_sq<<<dim3{unsigned(kSegBlocks), ns, 1u}, kThreads, 0, stream>>>(
-          v, m3, k, V, u, vk, vprev, part);
-      RPB_LAUNCHED(ctx);
-      seg_beta_eig<<<ns, kThreads, 0, stream>>>(v, k, tol, part);
-      RPB_LAUNCHED(ctx);
-      seg_all_done<<<1, 256, 0, stream>>>(v, nsys);
-      RPB_LAUNCHED(ctx);
-      if (k < max_iter) {
-        seg_scale_by_inverse<<<nblk(m3), kThreads, 0, stream>>>(v, m3, u, f_beta + k - 1,
-                                                                 V + int64_t(k) * m3);
-        RPB_LAUNCHED(ctx);
-      }
+      if (f64)
+        RPB_TRY(iterate_processes(ctx, v, longest, k, tol, V, u, job.dot.done, P, next, hw,
+                                  static_cast<double *>(src), counter, nullptr, host_done_dev,
+                                  epoch, stream));
+      else
+        RPB_TRY(iterate_processes(ctx, v, longest, k, tol, V, u, job.dot.done, P, next, hw,
+                                  static_cast<float *>(src), counter, nullptr, host_done_dev,
+                                  epoch, stream));
     }
-    if (sync_each) {
-      RPB_HIP(ctx, hipMemcpyAsync(host_done, v.done, size_t(nsys) * sizeof(int),
-                                  hipMemcpyDeviceToHost, stream));
-      RPB_HIP(ctx, hipStreamSynchronize(stream));
+    if (!sync_each) continue;
+    RPB_TRY(lz_ring_post(ctx, slot, stream));
+    const int qmax = next ? k - lag : next_q - 1;   // nothing to decide after the last iteration
+    for (; next_q <= qmax && !stop; ++next_q) {
+      RPB_TRY(lz_ring_wait(ctx, next_q % kLzRing));
+      known.resize(size_t(nsys));
       bool all = true;
-      for (int s = 0; s < nsys && all; ++s) all = host_done[s] != 0;
-      if (all) break;
-      known = host_done;
+      for (int s = 0; s < nsys; ++s) {
+        known[size_t(s)] = __atomic_load_n(host_done + s, __ATOMIC_RELAXED) == epoch;
+        all = all && known[size_t(s)];
+      }
+      if (all) {
+        // launches past the stop returned at once: drop their timing records
+        if (next_q < k) timing_discard(ctx, mark[(next_q + 1) % kLzRing]);
+        stop = true;
+      }
     }
   }
   seg_basis_combine<<<nblk(m3), kThreads, 0, stream>>>(v, m3, V, out);
@@ -1794,24 +2108,35 @@ int lanczos_batched_run(rpb_ctx *ctx, const rpb_params *p, const Batch &b, const
                         bool sync_each, LzStatus *status_host, hipStream_t stream,
                         const double *mw) {
   const int64_t m3 = 3 * b.n;
+  int st;
   double *L = nullptr, *t = nullptr;
   if (precond) {
-    int st;
     L = static_cast<double *>(workspace(ctx, WS_PRECOND, size_t(2 * m3) * sizeof(double), &st));
     if (!L) return st;
     t = L + m3;
     RPB_TRY(block_diag_scale(ctx, p, g, L, stream));
   }
-  auto product = [&](const double *src, const int *done_dev, const int *, double *dst) {
-    return matvec_batched(ctx, p, b, g, src, nullptr, done_dev, dst, stream);
+  const bool f64 = g.precision == RPB_FP64;
+  void *src = nullptr;
+  int *counter = nullptr;
+  if (!precond) {
+    src = source_buffer(ctx, g, &st);
+    if (!src) return st;
+    counter = work_counter(ctx, &st);
+    if (!counter) return st;
+  }
+  auto product = [&](SegProduct &job, double *u) {
+    if (!precond)
+      return matvec_batched_prepacked(ctx, p, b, g, job.src, job.done_dev, u, stream, &job.dot);
+    return matvec_batched(ctx, p, b, g, job.vk, nullptr, job.done_dev, u, stream);
   };
-  return lanczos_segments(ctx, b, L, t, w, tol, max_iter, product, out, sync_each, status_host,
-                          stream, precond ? nullptr : mw);
+  return lanczos_segments(ctx, b, L, t, w, tol, max_iter, product,
+                          precond ? nullptr : packed_weights(g), src, f64, counter, out, sync_each,
+                          1, status_host, stream, precond ? nullptr : mw);
 }
 
 int lanczos_batched_status_copy(rpb_ctx *ctx, int nsys, LzStatus *host, hipStream_t stream) {
-  const size_t states_bytes = size_t(nsys) * sizeof(LzState);
-  const size_t status_off = (states_bytes + size_t(nsys + 1) * sizeof(int) + 255) / 256 * 256;
+  const size_t status_off = lz_status_offset(nsys);
   const DevBuf &b = ctx->ws[WS_LZBATCH];
   if (!b.ptr || b.bytes < status_off + size_t(nsys) * sizeof(LzStatus))
     return fail(ctx, RPB_EINVAL, "no batched Lanczos state");
@@ -1954,12 +2279,18 @@ extern "C" int lanczos_sqrt_apply_multi(rpb_ctx *ctx, const rpb_params *p, int64
   RPB_TRY(prepare_batch(ctx, nvec, offs.data(), p->precision, &b, stream, false));
   Packed g;
   RPB_TRY(pack_geometry(ctx, p, n, pos, WS_GEOM, &g, stream));
-  auto product = [&](const double *src, const int *, const int *done_host, double *dst) {
-    return matvec_multi(ctx, p, g, nvec, done_host, src, dst, stream);
+  // Up to a few thousand spheres a product takes less than the host needs to read the flags and
+  // launch the next one, so the host reads them one iteration late; a vector that has just
+  // stopped then rides along in one more product (17 us of pair kernel for four vectors at 1,100
+  // spheres, against ~70 us of idle device), whose launches return at once when all have.
+  const int lag = n <= 4096 ? 1 : 0;
+  auto product = [&](SegProduct &job, double *u) {
+    return matvec_multi(ctx, p, g, nvec, job.done_host, job.vk, u, stream, &job.dot,
+                        job.done_dev + nvec);
   };
   LzStatus *stat = static_cast<LzStatus *>(host_scratch(ctx));
-  RPB_TRY(lanczos_segments(ctx, b, nullptr, nullptr, w, tol, max_iter, product, out, true, stat,
-                           stream));
+  RPB_TRY(lanczos_segments(ctx, b, nullptr, nullptr, w, tol, max_iter, product, nullptr, nullptr,
+                           p->precision == RPB_FP64, nullptr, out, true, lag, stat, stream));
   for (int s = 0; s < nvec; ++s) {
     if (iters_out) iters_out[s] = stat[s].m;
     if (eps_out) eps_out[s] = stat[s].eps;

@@ -59,13 +59,15 @@ __global__ void pack_geometry_mixed(int64_t n, const double *__restrict__ pos, d
 }
 
 // Source vectors, H-weighted, structure of arrays: [fx | fy | fz | tx | ty | tz] (n each); the
-// torques divided by a (lengths in units of a).
+// torques divided by a (lengths in units of a).  counter (nullable): a work counter to zero.
 template <typename Real>
 __global__ void pack_vectors(int64_t n, const double *__restrict__ h,
                              const double *__restrict__ force, const double *__restrict__ torque,
-                             double inv_a, Real *__restrict__ out, const int *__restrict__ skip) {
+                             double inv_a, Real *__restrict__ out, const int *__restrict__ skip,
+                             int *counter) {
   if (skip && *skip) return;
   const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (counter && i == 0) counter[0] = 0;
   if (i >= n) return;
   const double w = h[i];
   for (int c = 0; c < 3; ++c) {
@@ -911,11 +913,13 @@ __global__ __launch_bounds__(kBlock) void pair_kernel_f64_expanded(SymArgs a, Pa
 // kRedGroups threads per (component, row), 64 rows per workgroup (one wavefront per group):
 // the partials of the chunk [pm.L0, L1) dealt over the groups (chunk_row_sum_dealt) and the
 // group sums added in a fixed order, written to vel on the first chunk and added to it on the
-// others; after the last chunk the sum is scaled by H_i / (8 pi eta a).
+// others; after the last chunk the sum is scaled by H_i / (8 pi eta a) and, with dotv, the
+// workgroup's partial of dotv . vel goes to dpart.
 template <typename Part>
 __global__ __launch_bounds__(64 * kRedGroups) void reduce_sym_chunk(
     SymArgs a, PartMap pm, int64_t L1, int first, int last, const Part *__restrict__ partial,
-    const double *__restrict__ h, double scale, double *__restrict__ vel) {
+    const double *__restrict__ h, double scale, double *__restrict__ vel,
+    const double *__restrict__ dotv, double *__restrict__ dpart) {
   __shared__ double sh[kRedGroups * 64];
   if (a.skip && *a.skip) return;
   const int lane = threadIdx.x & 63, grp = threadIdx.x >> 6;
@@ -927,11 +931,15 @@ __global__ __launch_bounds__(64 * kRedGroups) void reduce_sym_chunk(
       live ? chunk_row_sum_dealt(partial, pm, a.nt, L1, r / a.ts, r % a.ts, 0, d, grp, kRedGroups)
            : 0.0;
   __syncthreads();
-  if (grp != 0 || !live) return;
+  if (grp != 0) return;
   double v = sh[lane];
   for (int q = 1; q < kRedGroups; ++q) v += sh[q * 64 + lane];
-  if (!first) v += vel[3 * r + d];
-  vel[3 * r + d] = last ? scale * h[r] * v : v;
+  if (live) {
+    if (!first) v += vel[3 * r + d];
+    if (last) v *= scale * h[r];
+    vel[3 * r + d] = v;
+  }
+  if (last && dotv) store_dot_partial(live, v, dotv, 3 * r + d, dpart + blockIdx.x);
 }
 
 // ---- batched systems: persistent workgroups over a cost-ordered item list -------------------
@@ -1092,24 +1100,48 @@ __global__ __launch_bounds__(kBlock) void pair_kernel_f64_sym_batched(
   }
 }
 
-// System s's partials start at part_base[s] and cover its whole triangle (one chunk).
-template <typename Part>
-__global__ void reduce_partials_sym_batched(SymBatchArgs b, const int *__restrict__ sys_of,
-                                            const Part *__restrict__ partial,
-                                            const double *__restrict__ h, double scale,
-                                            double *__restrict__ vel) {
-  const int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;   // (component, row)
-  if (e >= 3 * b.n) return;
-  const int d = int(e / b.n);
-  const int64_t r = e - int64_t(d) * b.n;
-  const int s = sys_of[r];
+// System s's partials start at part_base[s] and cover its whole triangle (one chunk).  As
+// reduce_sym_chunk with G threads per (component, row) and W wavefronts of 64 of them per
+// workgroup, all of system blockIdx.y; dpart: the system's partials of dotv . vel at
+// dpart[s * dstride].  Small batches take G = 8 (their few rows are many slots deep); a batch of
+// 282,705 spheres keeps the device full with one thread per row (34 us, 62 with eight).
+template <typename Part, int G, int W>
+__global__ __launch_bounds__(64 * G * W) void reduce_partials_sym_batched(
+    SymBatchArgs b, const Part *__restrict__ partial, const double *__restrict__ h, double scale,
+    double *__restrict__ vel, const double *__restrict__ dotv, double *__restrict__ dpart,
+    int64_t dstride) {
+  static_assert(G == 1 || W == 1, "the group sums of one set of rows");
+  __shared__ double sh[G * 64];
+  const int s = blockIdx.y;
   if (b.done && b.done[s]) return;
   const SymArgs a = sym_args_of(b, s);
-  const int64_t local = r - b.offs[s];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, grp = G > 1 ? wave : 0;
+  const int64_t set = int64_t(blockIdx.x) * W + (G > 1 ? 0 : wave);
+  if (set * 64 >= 3 * a.n) return;   // uniform over the workgroup when G > 1
+  const int64_t e = set * 64 + lane;
+  const bool live = e < 3 * a.n;
+  const int d = live ? int(e / a.n) : 0;
+  const int64_t r = live ? e - int64_t(d) * a.n : 0;
   const PartMap pm{0, b.nsplit, b.ts, 1};
-  vel[3 * r + d] = scale * h[r] *
-                   chunk_row_sum(partial + b.part_base[s], pm, a.nt, a.nt * (a.nt + 1) / 2,
-                                 local / a.ts, local % a.ts, 0, d);
+  const Part *p = partial + b.part_base[s];
+  const int64_t L1 = a.nt * (a.nt + 1) / 2;
+  double v = 0.0;
+  if constexpr (G == 1) {
+    if (live) v = chunk_row_sum(p, pm, a.nt, L1, r / a.ts, r % a.ts, 0, d);
+  } else {
+    sh[grp * 64 + lane] =
+        live ? chunk_row_sum_dealt(p, pm, a.nt, L1, r / a.ts, r % a.ts, 0, d, grp, G) : 0.0;
+    __syncthreads();
+    if (grp != 0) return;
+    v = sh[lane];
+    for (int q = 1; q < G; ++q) v += sh[q * 64 + lane];
+  }
+  const int64_t row = b.offs[s] + r;
+  if (live) {
+    v *= scale * h[row];
+    vel[3 * row + d] = v;
+  }
+  if (dotv) store_dot_partial(live, v, dotv, 3 * row + d, dpart + s * dstride + set);
 }
 
 __global__ void fill_sys_of(int nsys, const int64_t *__restrict__ offs, int *__restrict__ sys_of) {
@@ -1184,16 +1216,17 @@ inline bool periodic(const rpb_params *p) { return p->lx > 0.0; }
 
 // H-weighted sources of packed geometry `g` into `buf` (6 n values of the pair precision).
 int pack_sources_into(rpb_ctx *ctx, const Packed &g, const double *force, const double *torque,
-                      void *buf, hipStream_t stream, const int *skip = nullptr) {
+                      void *buf, hipStream_t stream, const int *skip = nullptr,
+                      int *counter = nullptr) {
   const int64_t n = g.n;
   const bool f64 = g.precision == RPB_FP64;
   const double *h = f64 ? geom_d(g).h : geom_f(g).h;
   if (f64)
     pack_vectors<double><<<blocks_for(n, 256), 256, 0, stream>>>(
-        n, h, force, torque, 1.0 / g.a, static_cast<double *>(buf), skip);
+        n, h, force, torque, 1.0 / g.a, static_cast<double *>(buf), skip, counter);
   else
     pack_vectors<float><<<blocks_for(n, 256), 256, 0, stream>>>(
-        n, h, force, torque, 1.0 / g.a, static_cast<float *>(buf), skip);
+        n, h, force, torque, 1.0 / g.a, static_cast<float *>(buf), skip, counter);
   RPB_LAUNCHED(ctx);
   return RPB_OK;
 }
@@ -1480,9 +1513,12 @@ void with_tile(TileShape t, Fn &&fn) {
 // whatever n.  The timing record spans the pair kernels of all chunks.
 int matvec_symmetric(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const void *src,
                      bool torque, const double *h, int tpt, double *vel, hipStream_t stream,
-                     const int *skip, bool expanded) {
+                     const int *skip, bool expanded, DotOut *dot = nullptr) {
   const int64_t n = g.n;
   const bool f64 = g.precision == RPB_FP64;
+  const double *dotv = dot ? dot->v : nullptr;
+  double *dpart = dot ? dot->part : nullptr;
+  if (dotv) dot->done = true;
   const bool tiles = f64 && !(expanded && !torque);
   const TileShape tile = sym64_shape(n, tpt);
   SymArgs a{n, tiles ? int64_t(64) * tile.wt * tile.tpt : int64_t(kBlock) * tpt, 0, n};
@@ -1536,10 +1572,10 @@ int matvec_symmetric(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const v
     const int first = L0 == 0, last = L1 == pairs;
     if (f64)
       reduce_sym_chunk<double><<<blocks_for(3 * n, 64), 64 * kRedGroups, 0, stream>>>(
-          a, pm, L1, first, last, static_cast<const double *>(part), h, scale, vel);
+          a, pm, L1, first, last, static_cast<const double *>(part), h, scale, vel, dotv, dpart);
     else
       reduce_sym_chunk<float><<<blocks_for(3 * n, 64), 64 * kRedGroups, 0, stream>>>(
-          a, pm, L1, first, last, static_cast<const float *>(part), h, scale, vel);
+          a, pm, L1, first, last, static_cast<const float *>(part), h, scale, vel, dotv, dpart);
     RPB_LAUNCHED(ctx);
   }
   return RPB_OK;
@@ -1555,14 +1591,14 @@ void *source_buffer(rpb_ctx *ctx, const Packed &g, int *status) {
 }
 
 int matvec_prepacked(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const void *src,
-                     double *vel, hipStream_t stream, const int *skip) {
+                     double *vel, hipStream_t stream, const int *skip, DotOut *dot) {
   const int64_t n = g.n;
   if (n <= 0) return RPB_OK;
   const bool f64 = g.precision == RPB_FP64;
   const Shape &shape = ctx->tune.s[f64 ? RPB_FP64 : RPB_MIXED];
   if (shape.symmetric)
     return matvec_symmetric(ctx, p, g, src, false, packed_weights(g), shape.tpt, vel, stream,
-                            skip, false);
+                            skip, false, dot);
   const int tpt = std::min(shape.tpt, 2);
   const int64_t chunk = ordered_chunk(n, tpt, shape.target_wgs, 65535);
   const int64_t nchunks = (n + chunk - 1) / chunk;
@@ -1758,7 +1794,8 @@ namespace {
 
 int matvec_batched_sym(rpb_ctx *ctx, const rpb_params *p, const Batch &b, const Packed &g,
                        const void *src, bool has_t, const int *done, int *counter, void *part,
-                       const double *h, double *vel, hipStream_t stream, bool expanded) {
+                       const double *h, double *vel, hipStream_t stream, bool expanded,
+                       DotOut *dot) {
   const int64_t n = g.n;
   const bool f64 = g.precision == RPB_FP64;
   const int tpt = b.tpt;
@@ -1791,27 +1828,41 @@ int matvec_batched_sym(rpb_ctx *ctx, const rpb_params *p, const Batch &b, const 
   RPB_LAUNCHED(ctx);
   RPB_TRY(timing_end(ctx, stream, t0, pairs, 4 + (f64 ? 0 : 2) + (has_t ? 1 : 0)));
   const double scale = 1.0 / (8.0 * M_PI * p->eta * p->a);
-  if (f64)
-    reduce_partials_sym_batched<double><<<blocks_for(3 * n, 256), 256, 0, stream>>>(
-        args, b.sys_of, static_cast<const double *>(part), h, scale, vel);
+  int64_t longest = 1;
+  for (int s = 0; s < b.nsys; ++s)
+    longest = std::max(longest, b.host_offs[s + 1] - b.host_offs[s]);
+  const double *dotv = dot ? dot->v : nullptr;
+  double *dpart = dot ? dot->part : nullptr;
+  const int64_t dstride = dot ? dot->stride : 0;
+  if (dotv) dot->done = true;
+  auto reduce = [&](auto G, auto W) {
+    constexpr int kG = decltype(G)::value, kW = decltype(W)::value;
+    const dim3 rgrid{blocks_for(3 * longest, 64 * kW), unsigned(b.nsys), 1u};
+    if (f64)
+      reduce_partials_sym_batched<double, kG, kW><<<rgrid, 64 * kG * kW, 0, stream>>>(
+          args, static_cast<const double *>(part), h, scale, vel, dotv, dpart, dstride);
+    else
+      reduce_partials_sym_batched<float, kG, kW><<<rgrid, 64 * kG * kW, 0, stream>>>(
+          args, static_cast<const float *>(part), h, scale, vel, dotv, dpart, dstride);
+  };
+  if (n < 65536)
+    reduce(std::integral_constant<int, kRedGroups>{}, std::integral_constant<int, 1>{});
   else
-    reduce_partials_sym_batched<float><<<blocks_for(3 * n, 256), 256, 0, stream>>>(
-        args, b.sys_of, static_cast<const float *>(part), h, scale, vel);
+    reduce(std::integral_constant<int, 1>{}, std::integral_constant<int, 4>{});
   RPB_LAUNCHED(ctx);
   return RPB_OK;
 }
 
 }  // namespace
 
-int matvec_batched(rpb_ctx *ctx, const rpb_params *p, const Batch &b, const Packed &g,
-                   const double *force, const double *torque, const int *done, double *vel,
-                   hipStream_t stream, bool expanded) {
+namespace {
+
+// The batched product of packed sources; the work counter is zero.
+int batched_product(rpb_ctx *ctx, const rpb_params *p, const Batch &b, const Packed &g,
+                    const void *src, bool has_t, const int *done, double *vel,
+                    hipStream_t stream, bool expanded, DotOut *dot) {
   const int64_t n = g.n;
-  if (n == 0 || b.nitems == 0) return RPB_OK;
-  const bool has_t = torque != nullptr;
   const bool f64 = g.precision == RPB_FP64;
-  void *src;
-  RPB_TRY(pack_sources(ctx, g, force, torque, &src, stream));
   const double *h = f64 ? geom_d(g).h : geom_f(g).h;
   int st;
   // symmetric items: float32 partials in mixed precision; ordered items: float64
@@ -1820,13 +1871,10 @@ int matvec_batched(rpb_ctx *ctx, const rpb_params *p, const Batch &b, const Pack
                                 : size_t(b.max_chunks) * 3 * size_t(n) * sizeof(double);
   void *part = workspace(ctx, WS_PART, std::max<size_t>(8, part_bytes), &st);
   if (!part) return st;
-  char *small = static_cast<char *>(workspace(ctx, WS_SMALL, kSmallBytes, &st));
-  if (!small) return st;
-  int *counter = reinterpret_cast<int *>(small + kSmallWorkCounter);
-  zero_int<<<1, 1, 0, stream>>>(counter);
-  RPB_LAUNCHED(ctx);
+  int *counter = work_counter(ctx, &st);
+  if (!counter) return st;
   if (b.symmetric) return matvec_batched_sym(ctx, p, b, g, src, has_t, done, counter, part, h,
-                                             vel, stream, expanded);
+                                             vel, stream, expanded, dot);
 
   BatchArgs args{b.offs, b.items, b.nitems, counter, n, b.chunk, done,
                  done ? done + b.nsys : nullptr};
@@ -1858,6 +1906,34 @@ int matvec_batched(rpb_ctx *ctx, const rpb_params *p, const Batch &b, const Pack
                                                                  done, dpart, h, scale, vel);
   RPB_LAUNCHED(ctx);
   return RPB_OK;
+}
+
+}  // namespace
+
+int *work_counter(rpb_ctx *ctx, int *status) {
+  char *small = static_cast<char *>(workspace(ctx, WS_SMALL, kSmallBytes, status));
+  return small ? reinterpret_cast<int *>(small + kSmallWorkCounter) : nullptr;
+}
+
+int matvec_batched(rpb_ctx *ctx, const rpb_params *p, const Batch &b, const Packed &g,
+                   const double *force, const double *torque, const int *done, double *vel,
+                   hipStream_t stream, bool expanded) {
+  if (g.n == 0 || b.nitems == 0) return RPB_OK;
+  int st;
+  int *counter = work_counter(ctx, &st);
+  if (!counter) return st;
+  void *src = source_buffer(ctx, g, &st);
+  if (!src) return st;
+  RPB_TRY(pack_sources_into(ctx, g, force, torque, src, stream, nullptr, counter));
+  return batched_product(ctx, p, b, g, src, torque != nullptr, done, vel, stream, expanded,
+                         nullptr);
+}
+
+int matvec_batched_prepacked(rpb_ctx *ctx, const rpb_params *p, const Batch &b, const Packed &g,
+                             const void *src, const int *done, double *vel, hipStream_t stream,
+                             DotOut *dot) {
+  if (g.n == 0 || b.nitems == 0) return RPB_OK;
+  return batched_product(ctx, p, b, g, src, false, done, vel, stream, false, dot);
 }
 
 int check_offsets(rpb_ctx *ctx, int32_t nsys, const int64_t *offs) {

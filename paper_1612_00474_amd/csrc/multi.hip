@@ -48,7 +48,10 @@ struct SrcPtrs {
 };
 template <int K>
 struct OutPtrs {
-  double *p[K];         // [n][3] result of each slot, NULL: not stored
+  double *p[K];         // [n][3] result of each slot
+  // partials of v[k] . p[k] per 64 rows at dot[k] (NULL: not wanted)
+  const double *v[K] = {};
+  double *dot[K] = {};
 };
 
 // src[e n + i]: e = 3 k + c holds H_i F_k(i, c); with a torque, e = 3 K + c holds H_i T(i, c)/a
@@ -232,6 +235,7 @@ __global__ __launch_bounds__(kBlock) void pair_kernel_mixed_multi(SymArgs a, Par
                                                                   PairConsts<float> k_arg,
                                                                   float *__restrict__ partial) {
   const PairConsts<float> k = vgpr_consts(k_arg);
+  if (a.skip && *a.skip) return;
   __shared__ MultiLdsF<K, TQ> L;
   int64_t I, J;
   const int64_t Lp = pm.L0 + int64_t(blockIdx.x);
@@ -239,34 +243,43 @@ __global__ __launch_bounds__(kBlock) void pair_kernel_mixed_multi(SymArgs a, Par
   multi_tile_pair<K, TQ, WALL>(a, g, src, k, partial, pm, Lp, I, J, L);
 }
 
-// kRedGroups threads per (vector slot, component, row), 64 rows per workgroup: the chunk's
-// partials dealt over the groups (chunk_row_sum_dealt), the group sums added in a fixed order,
-// written to out.p[v] ([n][3]) on the first chunk and added on the others, scaled by H_i / (8 pi
-// eta a) after the last.
+// kRedGroups threads per (component, row) of vector slot blockIdx.y, 64 rows per workgroup: the
+// chunk's partials dealt over the groups (chunk_row_sum_dealt), the group sums added in a fixed
+// order, written to out.p[v] ([n][3]) on the first chunk and added on the others, scaled by H_i /
+// (8 pi eta a) after the last (with which the slot's dot partials are taken).
 template <int K, typename Part>
 __global__ __launch_bounds__(64 * kRedGroups) void reduce_multi(
     SymArgs a, PartMap pm, int64_t L1, int first, int last, OutPtrs<K> out,
     const Part *__restrict__ partial, const double *__restrict__ h, double scale) {
   __shared__ double sh[kRedGroups * 64];
-  const int lane = threadIdx.x & 63, grp = threadIdx.x >> 6;
+  if (a.skip && *a.skip) return;
+  const int lane = threadIdx.x & 63, grp = threadIdx.x >> 6, v = blockIdx.y;
   const int64_t e = int64_t(blockIdx.x) * 64 + lane;
-  const int64_t per = 3 * a.n;
-  const bool in = e < K * per;
-  const int v = in ? int(e / per) : 0;
-  const int64_t rem = in ? e - int64_t(v) * per : 0;
-  const int d = int(rem / a.n);
-  const int64_t r = rem - int64_t(d) * a.n;
-  double *dst = out.p[v];
-  const bool live = in && dst;
+  const bool live = e < 3 * a.n;
+  const int d = live ? int(e / a.n) : 0;
+  const int64_t r = live ? e - int64_t(d) * a.n : 0;
   sh[grp * 64 + lane] =
       live ? chunk_row_sum_dealt(partial, pm, a.nt, L1, r / a.ts, r % a.ts, v, d, grp, kRedGroups)
            : 0.0;
   __syncthreads();
-  if (grp != 0 || !live) return;
+  if (grp != 0) return;
   double x = sh[lane];
   for (int q = 1; q < kRedGroups; ++q) x += sh[q * 64 + lane];
-  if (!first) x += dst[3 * r + d];
-  dst[3 * r + d] = last ? scale * h[r] * x : x;
+  double *dst = nullptr, *dot = nullptr;
+  const double *dv = nullptr;
+#pragma unroll
+  for (int q = 0; q < K; ++q)
+    if (q == v) {
+      dst = out.p[q];
+      dot = out.dot[q];
+      dv = out.v[q];
+    }
+  if (live) {
+    if (!first) x += dst[3 * r + d];
+    if (last) x *= scale * h[r];
+    dst[3 * r + d] = x;
+  }
+  if (last && dot) store_dot_partial(live, x, dv, 3 * r + d, dot + blockIdx.x);
 }
 
 // Wavefronts along the targets of the float64 tiles (64 of them each, one target per lane): small
@@ -283,12 +296,14 @@ inline int multi_wt(int64_t n) { return n < 7000 ? 1 : n < 28000 ? 2 : 4; }
 // bounded whatever n.  The timing record spans the pair kernels of all chunks.
 template <int K, bool TQ>
 int multi_launch(rpb_ctx *ctx, const rpb_params *p, const Packed &g, SrcPtrs<K> in,
-                 const double *torque, OutPtrs<K> out, hipStream_t stream) {
+                 const double *torque, OutPtrs<K> out, hipStream_t stream,
+                 const int *skip = nullptr) {
   const int64_t n = g.n;
   const bool f64 = g.precision == RPB_FP64;
   const int wt = multi_wt(n);
   const int64_t ts = f64 ? 64 * wt : kBlock;
   SymArgs a{n, ts, (n + ts - 1) / ts, n};
+  a.skip = skip;
   const int64_t pairs = a.nt * (a.nt + 1) / 2;
   const size_t esz = f64 ? sizeof(double) : sizeof(float);
   const int64_t per_chunk = chunk_pairs(pairs, 1, K, ts, esz, ctx->chunk_bytes);
@@ -353,7 +368,7 @@ int multi_launch(rpb_ctx *ctx, const rpb_params *p, const Packed &g, SrcPtrs<K> 
     if (L1 == pairs)
       RPB_TRY(timing_end(ctx, stream, t0, double(n) * double(n) * used, 8 + (f64 ? 0 : 2)));
     const int first = L0 == 0, last = L1 == pairs;
-    const unsigned rgrid = blocks_for(int64_t(K) * 3 * n, 64);
+    const dim3 rgrid{blocks_for(3 * n, 64), unsigned(K), 1u};
     if (f64)
       reduce_multi<K, double><<<rgrid, 64 * kRedGroups, 0, stream>>>(a, pm, L1, first, last, out,
                                                          static_cast<const double *>(part), h,
@@ -524,7 +539,8 @@ size_t multi_batch_partial_bytes(int K, const Batch &bt, size_t esz) {
 }  // namespace
 
 int matvec_multi(rpb_ctx *ctx, const rpb_params *p, const Packed &g, int nvec, const int *done,
-                 const double *force, double *vel, hipStream_t stream) {
+                 const double *force, double *vel, hipStream_t stream, DotOut *dot,
+                 const int *skip) {
   const int64_t n = g.n;
   if (n == 0 || nvec <= 0) return RPB_OK;
   if (p->lx > 0.0)
@@ -542,9 +558,14 @@ int matvec_multi(rpb_ctx *ctx, const rpb_params *p, const Packed &g, int nvec, c
       const size_t off = size_t(ids[g0 + s]) * 3 * n;
       in.p[s] = force + off;
       out.p[s] = vel + off;
+      if (dot && dot->v) {
+        out.v[s] = dot->v + off;
+        out.dot[s] = dot->part + int64_t(ids[g0 + s]) * dot->stride;
+      }
     }
-    return multi_launch<K, false>(ctx, p, g, in, nullptr, out, stream);
+    return multi_launch<K, false>(ctx, p, g, in, nullptr, out, stream, skip);
   };
+  if (dot && dot->v) dot->done = true;
   size_t g0 = 0;
   for (; g0 + kMulti <= ids.size(); g0 += kMulti)
     RPB_TRY(group(g0, std::integral_constant<int, kMulti>{}));

@@ -234,6 +234,14 @@ inline int64_t chunk_pairs(int64_t pairs, int64_t nsplit, int V, int64_t ts, siz
 // 64 rows per workgroup).
 constexpr int kRedGroups = 8;
 
+// Partial sum of the calling wavefront's 64 products x v[e] (lanes not live add nothing), by lane 0.
+__device__ __forceinline__ void store_dot_partial(bool live, double x, const double *v, int64_t e,
+                                                  double *part) {
+  double a = live ? v[e] * x : 0.0;
+  for (int off = 32; off > 0; off >>= 1) a += __shfl_xor(a, off, 64);
+  if ((threadIdx.x & 63) == 0) *part = a;
+}
+
 inline unsigned blocks_for(int64_t n, int threads) {
   return unsigned((n + threads - 1) / threads);
 }

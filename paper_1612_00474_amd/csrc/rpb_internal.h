@@ -109,6 +109,7 @@ struct rpb_ctx {
   // events that mark each slot's status as landed; `lz_live` is set while one may be in flight
   hipEvent_t lz_ev[rpb::kLzRing] = {};
   bool lz_live[rpb::kLzRing] = {};
+  int lz_epoch = 0;                     // batched solves so far (marks their host flags)
   // the second stream on which small systems run the Lanczos eigensolve and stop test beside
   // the vector recurrence, and the events that order the two streams
   hipStream_t lz_stream = nullptr;
@@ -136,6 +137,7 @@ void *workspace(rpb_ctx *ctx, Slot slot, size_t bytes, int *status);
 constexpr size_t kHostScratchBytes = 1 << 17;
 constexpr size_t kHostLzRingOffset = kHostScratchBytes / 2;
 constexpr size_t kHostFiniteOffset = kHostLzRingOffset + 1024;   // deferred position check
+constexpr size_t kHostDoneOffset = kHostLzRingOffset + 4096;     // batched Lanczos: a word per process
 inline void *host_scratch(rpb_ctx *ctx) { return ctx->host_pinned; }
 inline void *host_scratch_dev(rpb_ctx *ctx) { return ctx->host_pinned_dev; }
 
@@ -241,10 +243,19 @@ const double *packed_weights(const Packed &g);
 // H-weighted force, f[c * n + i] = H_i F_i,c (the product in float64, then rounded), rows
 // 3..5 the H-weighted torque divided by the radius.
 void *source_buffer(rpb_ctx *ctx, const Packed &g, int *status);
+// Partials of v . u that a product u = M v can take in its reduction: one per 64 rows of each
+// system, partial q of system s at part[s * stride + q].  `done` is set by the products that did.
+struct DotOut {
+  const double *v = nullptr;   // NULL: not wanted
+  double *part = nullptr;
+  int64_t stride = 0;
+  bool done = false;
+};
 // U = M F for the whole system from force sources already written into `src` (rows 0..2 of
 // source_buffer's layout; no torque), as matvec_packed would form them.
 int matvec_prepacked(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const void *src,
-                     double *vel, hipStream_t stream, const int *skip = nullptr);
+                     double *vel, hipStream_t stream, const int *skip = nullptr,
+                     DotOut *dot = nullptr);
 
 // ---- batched products (matvec.hip) -----------------------------------------------------
 
@@ -278,13 +289,23 @@ int prepare_batch(rpb_ctx *ctx, int32_t nsys, const int64_t *offs, int precision
 int matvec_batched(rpb_ctx *ctx, const rpb_params *p, const Batch &b, const Packed &g,
                    const double *force, const double *torque, const int *done, double *vel,
                    hipStream_t stream, bool expanded = false);
+// The work counter of the persistent batched kernels; matvec_batched zeroes it itself, the
+// prepacked form below takes it zeroed by an earlier kernel of the stream.
+int *work_counter(rpb_ctx *ctx, int *status);
+// Batched U = M F from force sources already in `src` (the layout of source_buffer).
+int matvec_batched_prepacked(rpb_ctx *ctx, const rpb_params *p, const Batch &b, const Packed &g,
+                             const void *src, const int *done, double *vel, hipStream_t stream,
+                             DotOut *dot);
 
 // ---- multi-vector products (multi.hip) --------------------------------------------------
 
 // vel[v] = M force[v] for the nvec vectors force[v] ([n][3] float64 each, v-major) of packed
-// geometry `g`; vectors with done[v] != 0 (host array, nullable) are skipped.
+// geometry `g`; vectors with done[v] != 0 (host array, nullable) are skipped.  dot (nullable):
+// partials of force[v] . vel[v] (v is its system); skip (nullable): a device flag, while it is
+// nonzero the launches return at once.
 int matvec_multi(rpb_ctx *ctx, const rpb_params *p, const Packed &g, int nvec, const int *done,
-                 const double *force, double *vel, hipStream_t stream);
+                 const double *force, double *vel, hipStream_t stream, DotOut *dot = nullptr,
+                 const int *skip = nullptr);
 // The products of a step at its own configuration in one launch (the pair coefficients shared):
 // u_force = M force + M_C torque, u_w = M w and, when w3 is not NULL, u_w3 = M w3; torque
 // nullable.  Available when matvec_first_supported(p, n) (no box, partials within the
