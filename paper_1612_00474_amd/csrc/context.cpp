@@ -160,7 +160,7 @@ int rpb_create(int hip_device, rpb_ctx **out) {
     delete c;
     return RPB_ENOMEM;
   }
-  std::memset(c->host_pinned, 0, kHostScratchBytes);   // no word equals a solve's epoch yet
+  std::memset(c->host_pinned, 0, kHostScratchBytes);   // no word holds a solve's tag yet
   if (hipHostGetDevicePointer(&c->host_pinned_dev, c->host_pinned, 0) != hipSuccess) {
     (void)hipHostFree(c->host_pinned);
     delete c;
@@ -171,21 +171,12 @@ int rpb_create(int hip_device, rpb_ctx **out) {
     delete c;
     return RPB_EDEVICE;
   }
-  bool ok = hipStreamCreateWithFlags(&c->lz_stream, hipStreamNonBlocking) == hipSuccess &&
-            hipEventCreateWithFlags(&c->lz_join_ev, hipEventDisableTiming) == hipSuccess;
-  for (auto &e : c->lz_vec_ev)
-    ok = ok && hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
-  if (!ok) {
-    rpb_destroy(c);
-    return RPB_EDEVICE;
-  }
   *out = c;
   return RPB_OK;
 }
 
 void rpb_destroy(rpb_ctx *ctx) {
   if (!ctx) return;
-  lz_helper_destroy(ctx);
   (void)hipSetDevice(ctx->device);
   (void)hipDeviceSynchronize();
   for (auto &b : ctx->ws)
@@ -193,12 +184,6 @@ void rpb_destroy(rpb_ctx *ctx) {
   for (auto e : ctx->ev_start) (void)hipEventDestroy(e);
   for (auto e : ctx->ev_stop) (void)hipEventDestroy(e);
   for (auto e : ctx->ev_pool) (void)hipEventDestroy(e);
-  for (auto e : ctx->lz_ev)
-    if (e) (void)hipEventDestroy(e);
-  for (auto e : ctx->lz_vec_ev)
-    if (e) (void)hipEventDestroy(e);
-  if (ctx->lz_join_ev) (void)hipEventDestroy(ctx->lz_join_ev);
-  if (ctx->lz_stream) (void)hipStreamDestroy(ctx->lz_stream);
   if (ctx->fin_ev) (void)hipEventDestroy(ctx->fin_ev);
   if (ctx->host_pinned) (void)hipHostFree(ctx->host_pinned);
   if (ctx->batch_host) (void)hipHostFree(ctx->batch_host);

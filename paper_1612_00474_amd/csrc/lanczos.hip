@@ -15,14 +15,12 @@
 #include <algorithm>
 #include <cfloat>
 #include <cmath>
-#include <condition_variable>
 #include <cstddef>
-#include <deque>
-#include <mutex>
 #include <thread>
 #include <type_traits>
 #include <vector>
 
+#include "pair_common.h"
 #include "rpb_internal.h"
 
 namespace rpb {
@@ -40,8 +38,8 @@ struct LzState {
   double yprev[kMaxKrylov];
   double h[kMaxKrylov];
   double wnorm;
-  int halt;       // set by the vector work once it has seen reason != 0 (read by the products)
   int eig_m;      // order of the eigendecomposition held in LzEig (0: none)
+  int pad_;
   // status (read by the host every iteration)
   double eps;
   int m;
@@ -52,20 +50,17 @@ static_assert(sizeof(LzState) <= kSmallWorkCounter, "LzState must fit the start 
 static_assert(size_t(kMaxBatchSystems) * sizeof(LzStatus) <= kHostLzRingOffset,
               "per-system records must stay below the status ring");
 
-// Host copies of the status words (eps, m, reason) of consecutive iterations, slot k mod
-// kLzRing for iteration k.
+// Host copies of the status words of consecutive iterations, slot k mod kLzRing for iteration k.
+// The kernel that ends an iteration's stop test stores them and then the tag that the host waits
+// for (an event after the kernel would cost the device ~5 us per iteration).
 struct LzRingSlot {
   double eps;
-  int m;
   int reason;
+  int tag;
 };
 struct LzRing {
   LzRingSlot slot[kLzRing];
 };
-static_assert(sizeof(LzRingSlot) == sizeof(double) + 2 * sizeof(int) &&
-                  offsetof(LzState, reason) - offsetof(LzState, eps) ==
-                      offsetof(LzRingSlot, reason) - offsetof(LzRingSlot, eps),
-              "the ring slot mirrors the status words of LzState");
 
 LzRing *lz_ring(rpb_ctx *ctx) {
   return reinterpret_cast<LzRing *>(static_cast<char *>(host_scratch(ctx)) + kHostLzRingOffset);
@@ -76,31 +71,34 @@ LzRing *lz_ring_dev(rpb_ctx *ctx) {
                                     kHostLzRingOffset);
 }
 
-// Waits for every ring copy still in flight (a previous call's last copy may target a slot
-// this call is about to reuse, possibly from another stream).
-int lz_ring_fence(rpb_ctx *ctx) {
-  for (int q = 0; q < kLzRing; ++q) {
-    if (!ctx->lz_live[q]) continue;
-    RPB_HIP(ctx, hipEventSynchronize(ctx->lz_ev[q]));
-    ctx->lz_live[q] = false;
+// Tags of a solve: its epoch (from 1, unique in the context until it wraps after 2^24 solves, whose
+// pinned buffer starts zeroed), the iteration and, for the processes of a batch, a stop bit.
+constexpr int kTagStop = 0x80;
+__host__ __device__ __forceinline__ int lz_tag(int epoch, int k) { return (epoch << 8) | k; }
+int next_epoch(rpb_ctx *ctx) {
+  ctx->lz_epoch = ctx->lz_epoch >= 0x7fffff ? 1 : ctx->lz_epoch + 1;
+  return ctx->lz_epoch;
+}
+
+// Blocks until ready(), which reads words that kernels of `stream` store in pinned memory.  The
+// stream is asked now and then, so the wait ends with an error if its work ends or fails without
+// storing them.
+template <typename Ready>
+int wait_pinned(rpb_ctx *ctx, hipStream_t stream, Ready &&ready) {
+  for (int spins = 1;; ++spins) {
+    if (ready()) return RPB_OK;
+    if (spins % 4096 != 0) continue;
+    const hipError_t e = hipStreamQuery(stream);
+    if (e == hipErrorNotReady) {
+      (void)hipGetLastError();
+      std::this_thread::yield();
+      continue;
+    }
+    if (e != hipSuccess)
+      return fail(ctx, RPB_EDEVICE, "hipStreamQuery failed: %s", hipGetErrorString(e));
+    if (ready()) return RPB_OK;
+    return fail(ctx, RPB_EDEVICE, "a Lanczos status did not arrive");
   }
-  return RPB_OK;
-}
-
-// Marks ring slot q with event q: the iteration's status-writing kernel (lanczos_eig or
-// beta_eig, which store the status words into the slot) precedes it on the stream.
-int lz_ring_post(rpb_ctx *ctx, int q, hipStream_t stream) {
-  if (!ctx->lz_ev[q]) RPB_HIP(ctx, hipEventCreateWithFlags(&ctx->lz_ev[q], hipEventDisableTiming));
-  RPB_HIP(ctx, hipEventRecord(ctx->lz_ev[q], stream));
-  ctx->lz_live[q] = true;
-  return RPB_OK;
-}
-
-// Blocks until the copy into ring slot q has landed.
-int lz_ring_wait(rpb_ctx *ctx, int q) {
-  RPB_HIP(ctx, hipEventSynchronize(ctx->lz_ev[q]));
-  ctx->lz_live[q] = false;
-  return RPB_OK;
 }
 
 // out = V y (first nvec rows of V)
@@ -163,7 +161,7 @@ __device__ void secular_roots(int p, const double *__restrict__ d, const double 
   const int w = int(threadIdx.x) / 64, i = int(threadIdx.x) & 63;
   // the terms are split over the wavefronts only when there are enough of them to pay for
   // the exchange (one barrier per step); otherwise the first wavefront takes them all
-  const int W = p >= 16 ? int(blockDim.x) / 64 : 1;
+  const int W = p >= 16 ? kMaxW : 1;
   if (w >= W) return;   // wavefront-uniform; the caller's next barrier joins them again
   const bool act = p > 0 && i <= p;
   int buf = 0;
@@ -327,7 +325,7 @@ __device__ int eig_update(int m, const LzState *__restrict__ st, LzEig *__restri
   __shared__ int fail_s[kMaxKrylov];
   __shared__ int rot_p[kMaxKrylov], rot_j[kMaxKrylov];
   __shared__ int info[4];   // p, number of deflated, number of rotations, failure
-  const int tid = threadIdx.x, nthr = blockDim.x;
+  const int tid = threadIdx.x, nthr = kThreads;
   const int lane = tid & 63;
   const bool w0 = tid < 64;
   if (m == 1) {
@@ -700,13 +698,18 @@ __device__ void tridiag_body(int m, double tol, LzState *__restrict__ st, LzEig 
   }
 }
 
-// Status words of the iteration into the host's ring slot (pinned host memory, written by the
-// kernel so that no copy needs enqueuing), by one thread after the state is final.
-__device__ __forceinline__ void post_status(const LzState *__restrict__ st, LzRingSlot *slot) {
-  slot->eps = st->eps;
-  slot->m = st->m;
-  slot->reason = st->reason;
+// A tag into pinned host memory, after everything the thread has stored before it.
+__device__ __forceinline__ void post_tag(int *word, int tag) {
   __threadfence_system();
+  __hip_atomic_store(word, tag, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// Status words of iteration k into the host's ring slot, by one thread after the state is final.
+__device__ __forceinline__ void post_status(const LzState *__restrict__ st, LzRingSlot *slot,
+                                            int tag) {
+  slot->eps = st->eps;
+  slot->reason = st->reason;
+  post_tag(&slot->tag, tag);
 }
 
 // ---- Krylov processes on segments of concatenated vectors -------------------------------------
@@ -791,7 +794,6 @@ __device__ __forceinline__ void reset_state(const SegView &v, int s, double wn) 
   if (t < kMaxKrylov) st->alpha[t] = st->beta[t] = st->y[t] = st->yprev[t] = st->h[t] = 0.0;
   if (t == 0) {
     st->wnorm = wn;
-    st->halt = 0;
     st->eig_m = 0;
     st->eps = 0.0;
     st->m = 0;
@@ -920,31 +922,38 @@ __global__ __launch_bounds__(kThreads) void lz_dots(SegView v, int k,
   }
 }
 
-// The root of T_k and the stop test of process s by one workgroup, beta_k being in the state.  ring
-// (single process, nullable): the host's slot of status words.  host_done (batches, nullable):
-// pinned words that receive `epoch` when a process stops.
+// Where a process reports to the host after iteration k (all nullable): a single process its ring
+// slot, the processes of a batch one word each.
+struct LzReport {
+  LzRingSlot *ring;
+  int *words;
+  int epoch;
+};
+
+__device__ __forceinline__ void report_stop(const SegView &v, int s, int k, bool stop,
+                                            const LzReport &rep) {
+  if (stop) {
+    v.done[s] = 1;
+    if (atomicAdd(v.done + v.nsys + 1, 1) + 1 == v.nsys) v.done[v.nsys] = 1;
+  }
+  if (rep.words) post_tag(rep.words + s, lz_tag(rep.epoch, k) | (stop ? kTagStop : 0));
+}
+
+// The root of T_k and the stop test of process s by one workgroup, beta_k being in the state.
 __device__ __forceinline__ void root_and_stop(const SegView &v, int s, int k, double tol,
-                                              LzRingSlot *ring, int *host_done, int epoch) {
+                                              const LzReport &rep) {
   LzState *st = v.st + s;
   // every thread reads the same reason: only this workgroup writes it, after the barriers
   if (v.done || st->reason == 0) tridiag_body(k, tol, st, v.eig + s);
   if (threadIdx.x != 0) return;
-  if (ring) post_status(st, ring);
-  if (v.done && st->reason != 0) {
-    v.done[s] = 1;
-    if (atomicAdd(v.done + v.nsys + 1, 1) + 1 == v.nsys) v.done[v.nsys] = 1;
-    if (host_done) {
-      host_done[s] = epoch;
-      __threadfence_system();
-    }
-  }
+  if (rep.ring) post_status(st, rep.ring, lz_tag(rep.epoch, k));
+  if (v.done) report_stop(v, s, k, st->reason != 0, rep);
 }
 
 // The same in a launch of its own, one workgroup per process.
-__global__ __launch_bounds__(kThreads) void lz_root(SegView v, int k, double tol, LzRingSlot *ring,
-                                                    int *host_done, int epoch) {
+__global__ __launch_bounds__(kThreads) void lz_root(SegView v, int k, double tol, LzReport rep) {
   if (v.done && v.done[blockIdx.x]) return;
-  root_and_stop(v, blockIdx.x, k, tol, ring, host_done, epoch);
+  root_and_stop(v, blockIdx.x, k, tol, rep);
 }
 
 // ROOT: the process's first workgroup takes the root too.  Its registers and LDS leave two
@@ -954,7 +963,7 @@ template <int EPT, typename Real, bool ROOT>
 __global__ __launch_bounds__(kThreads, 2) void lz_update(
     SegView v, int k, double tol, double *__restrict__ V, const double *__restrict__ u,
     const double *__restrict__ part, int nb, int write_next, const double *__restrict__ hw,
-    Real *__restrict__ src, int *counter, LzRingSlot *ring, int *host_done, int epoch) {
+    Real *__restrict__ src, int *counter, LzReport rep) {
   __shared__ double hs[kMaxKrylov + 1];
   const int s = blockIdx.y, t = threadIdx.x, lane = t & 63, wave = t >> 6;
   if (counter && s == 0 && blockIdx.x == 0 && t == 0) counter[0] = 0;
@@ -1017,7 +1026,7 @@ __global__ __launch_bounds__(kThreads, 2) void lz_update(
   if (t < k) st->h[t] = hs[t];
   if constexpr (ROOT) {
     __syncthreads();
-    root_and_stop(v, s, k, tol, ring, host_done, epoch);
+    root_and_stop(v, s, k, tol, rep);
   }
 }
 
@@ -1193,7 +1202,7 @@ template <bool TREE, typename Real, bool ROOT>
 __global__ __launch_bounds__(kThreads, ROOT ? 2 : 4) void ord_scale(
     SegView v, int k, double tol, double *__restrict__ V, const double *__restrict__ u,
     const double *__restrict__ bpart, int write_next, const double *__restrict__ hw,
-    Real *__restrict__ src, int *counter, LzRingSlot *ring, int *host_done, int epoch) {
+    Real *__restrict__ src, int *counter, LzReport rep) {
   const int s = blockIdx.y, t = threadIdx.x;
   if (counter && s == 0 && blockIdx.x == 0 && t == 0) counter[0] = 0;
   if (v.done && v.done[s]) return;
@@ -1214,7 +1223,7 @@ __global__ __launch_bounds__(kThreads, ROOT ? 2 : 4) void ord_scale(
   if (t == 0) v.st[s].beta[k - 1] = beta;
   if constexpr (ROOT) {
     __syncthreads();
-    root_and_stop(v, s, k, tol, ring, host_done, epoch);
+    root_and_stop(v, s, k, tol, rep);
   }
 }
 
@@ -1410,50 +1419,272 @@ __device__ void lanczos_step_body(LzState *__restrict__ st, LzEig *__restrict__ 
   if (write_next && st->reason == 0) lanczos_write_next(V, u, m3, e0, e1, k, beta);
 }
 
-// Single system, the whole vector (3 n <= kFusedSegment): the vector work of iteration k and
-// v_{k+1}, with the eigensolve and stop test left to lanczos_eig on a second stream, which
-// runs beside the next product.  Until that stream reports a stop the recurrence runs on (the
-// iterations past the stop are never used); once the workgroup sees reason != 0 it only sets
-// st->halt, on which the products of later iterations return at once.  (reason is written by
-// the other stream meanwhile: one thread reads it and the workgroup follows that read.)
-// With src (nullable), v_{k+1} also goes into the next product's packed sources, as that
-// product's own packing would write them: src[c n + s] = Real(H_s v_{k+1}[3 s + c]) (hw: H).
-template <typename Real>
-__global__ __launch_bounds__(kThreads) void lanczos_vec(LzState *__restrict__ st,
-                                                        double *__restrict__ V,
-                                                        double *__restrict__ u, int64_t m3, int k,
-                                                        int write_next,
-                                                        const double *__restrict__ hw,
-                                                        Real *__restrict__ src) {
-  __shared__ int stop_s;
-  if (threadIdx.x == 0) {
-    stop_s = __hip_atomic_load(&st->reason, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
-    if (stop_s) st->halt = 1;
+// ---- small systems (3 n <= kFusedSegment): one launch per iteration ------------------------------
+//
+// A few hundred spheres leave every kernel of an iteration at the cost of its launch, so one kernel
+// takes the iteration: launch k finishes iteration k - 1 (alpha, the recurrence, the
+// re-orthogonalisation, beta, v_k), forms u_k = M v_k, and takes the root and stop test of
+// T_{k-2}.  No workgroup waits for another: each one forms v_k for itself (the same sums in
+// the same order, from vectors that fit the L2) and then the rows of u_k that it owns, one
+// wavefront per row; the last workgroup takes the root, whose coefficients the launches before
+// have stored.  All basis vectors' values are loaded at once into registers (twelve wavefronts,
+// one or two values per thread), which the projection then reuses.  What bounds an iteration is the
+// latency of those loads and of the sums, and the root's chain beside them.  256 spheres, float64, 25
+// iterations to 1e-6: 790 -> 434 us per solve (four kernels per iteration on two streams before, the
+// root's issued by a helper thread).
+constexpr int kSmallThreads = 768;
+
+struct SmallArgs {
+  LzState *st;
+  LzEig *eig;
+  double *V;           // basis, max_iter rows
+  const double *w;
+  const double *mw;    // M w (nullable): u_1 is then M w / |w|
+  double *u0, *u1;     // u_k of even and odd k
+  int64_t n;
+  int k, max_iter;
+  int part;            // float32: sources summed in float32 before they are added in float64
+  double tol, scale;
+  LzReport rep;        // ring: status slot of T_{k-2}
+};
+
+// Rows of M F for one target per wavefront.  Float64 sources are dealt to the lanes in turn; float32
+// ones in runs of `part` (the runs, and the order within them, of the one-tile product of
+// sym_tile_pair, so both give the same float32 sums).
+template <bool WALL, bool PERIODIC>
+struct SmallRowsD {
+  double x[512], y[512], z[512], f[3][512];
+  __device__ __forceinline__ void stage(const GeomD &g, int j) {
+    x[j] = g.x[j];
+    y[j] = g.y[j];
+    z[j] = g.z[j];
   }
-  __syncthreads();
-  if (stop_s) return;
-  const double beta = lanczos_vec_body(st, V, u, m3, 0, m3, k);
-  if (!write_next) return;
-  double *next = V + int64_t(k) * m3;
-  const int64_t n = m3 / 3;
-  for (int64_t i = threadIdx.x; i < m3; i += kThreads) {
-    const double x = beta > 0.0 ? u[i] / beta : 0.0;
-    next[i] = x;
-    if (src) {
-      const int64_t s = i / 3;
-      src[(i - 3 * s) * n + s] = Real(hw[s] * x);
+  __device__ __forceinline__ void row(int n, int, int i, int lane, const PairConsts<double> &k,
+                                      double (&acc)[3]) const {
+    const double xi = x[i], yi = y[i], zi = z[i];
+#pragma unroll 2
+    for (int j = lane; j < n; j += 64)
+      for_images<PERIODIC>(xi - x[j], yi - y[j], k, [&](double dx, double dy) {
+        const double dz = zi - z[j];
+        SymCoef<double> c;
+        if (dx * dx + dy * dy + dz * dz < kFourA2) {
+          sym_coefficients<double, false, false, WALL>(dx, dy, zi, z[j], k, c);
+          sym_apply_one<double, WALL>(c, f[0][j], f[1][j], f[2][j], acc[0], acc[1], acc[2]);
+        } else {
+          sym_coefficients<double, true, false, WALL>(dx, dy, zi, z[j], k, c);
+          sym_apply_one<double, WALL>(c, f[0][j], f[1][j], f[2][j], acc[0], acc[1], acc[2]);
+        }
+      });
+  }
+};
+template <bool WALL, bool PERIODIC>
+struct SmallRowsF {
+  float xh[512], xl[512], yh[512], yl[512], z[512], f[3][512];
+  __device__ __forceinline__ void stage(const GeomF &g, int j) {
+    xh[j] = g.xh[j];
+    xl[j] = g.xl[j];
+    yh[j] = g.yh[j];
+    yl[j] = g.yl[j];
+    z[j] = g.z[j];
+  }
+  __device__ __forceinline__ void row(int n, int part, int i, int lane,
+                                      const PairConsts<float> &k, double (&acc)[3]) const {
+    const float xih = xh[i], xil = xl[i], yih = yh[i], yil = yl[i], zi = z[i];
+    for (int j0 = lane * part; j0 < n; j0 += 64 * part) {
+      float a[3] = {0.f, 0.f, 0.f};
+      const int j1 = min(n, j0 + part);
+#pragma unroll 2
+      for (int j = j0; j < j1; ++j) {
+        const float dx0 = (xih - xh[j]) + (xil - xl[j]);
+        const float dy0 = (yih - yh[j]) + (yil - yl[j]);
+        for_images<PERIODIC>(dx0, dy0, k, [&](float dx, float dy) {
+          const float dz = zi - z[j];
+          if (dx * dx + dy * dy + dz * dz < float(kFourA2))
+            pair_velocity<float, false, false, WALL>(dx, dy, zi, z[j], f[0][j], f[1][j], f[2][j],
+                                                     0.f, 0.f, 0.f, k, a[0], a[1], a[2]);
+          else
+            pair_velocity<float, false, true, WALL>(dx, dy, zi, z[j], f[0][j], f[1][j], f[2][j],
+                                                    0.f, 0.f, 0.f, k, a[0], a[1], a[2]);
+        });
+      }
+#pragma unroll
+      for (int c = 0; c < 3; ++c) acc[c] += double(a[c]);
     }
   }
-}
+};
 
-// The eigensolve of T_k and the stop test (skipped once the process has stopped: y, eps and
-// reason stay), then the status into the host's ring slot.  Only these kernels write reason,
-// one after another on their stream, so every thread reads the same value.
-__global__ __launch_bounds__(kThreads) void lanczos_eig(LzState *__restrict__ st,
-                                                        LzEig *__restrict__ eig, int k,
-                                                        double tol, LzRingSlot *slot) {
-  if (st->reason == 0) tridiag_body(k, tol, st, eig);
-  if (threadIdx.x == 0) post_status(st, slot);
+template <typename Real, int EPT, bool WALL, bool PERIODIC>
+__global__ __launch_bounds__(kSmallThreads) void lz_small(
+    SmallArgs A, typename std::conditional<std::is_same<Real, double>::value, GeomD, GeomF>::type g,
+    PairConsts<Real> kc) {
+  using Rows = typename std::conditional<std::is_same<Real, double>::value,
+                                         SmallRowsD<WALL, PERIODIC>,
+                                         SmallRowsF<WALL, PERIODIC>>::type;
+  constexpr int W = kSmallThreads / 64;
+  constexpr int KR = EPT == 1 ? 32 : 16;   // basis vectors kept in registers
+  __shared__ Rows R;
+  __shared__ double sh[W];
+  __shared__ double xs[kSmallThreads * EPT];
+  __shared__ double hs[kMaxKrylov + 1];
+  __shared__ int stop_s;
+  const int k = A.k, t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int n = int(A.n), m3 = 3 * n;
+  LzState *st = A.st;
+  if (blockIdx.x == gridDim.x - 1) {   // the root of T_{k-2}
+    if (k < 3 || t >= kThreads) return;
+    // every thread reads the same reason: only this workgroup writes it, after the barriers
+    if (st->reason == 0) tridiag_body(k - 2, A.tol, st, A.eig);
+    if (t == 0) post_status(st, A.rep.ring, lz_tag(A.rep.epoch, k - 2));
+    return;
+  }
+  if (k > A.max_iter + 1) return;   // the last launch takes a root only
+  if (k > 1) {   // reason is written by the root's workgroup meanwhile: one thread reads it
+    if (t == 0)
+      stop_s = __hip_atomic_load(&st->reason, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+    __syncthreads();
+    if (stop_s) return;
+  }
+  if (t < n) R.stage(g, t);
+  // workgroup sum of one value, the same on every thread
+  auto total = [&](double a) {
+    a = wave_sum(a);
+    if (lane == 0) sh[wave] = a;
+    __syncthreads();
+    double r = sh[0];
+#pragma unroll
+    for (int q = 1; q < W; ++q) r += sh[q];
+    return r;
+  };
+  bool in[EPT];
+  int ix[EPT];
+  double v[EPT];
+#pragma unroll
+  for (int r = 0; r < EPT; ++r) {
+    in[r] = t + r * kSmallThreads < m3;
+    ix[r] = in[r] ? t + r * kSmallThreads : 0;
+  }
+  if (k == 1) {
+    double s = 0.0;
+#pragma unroll
+    for (int r = 0; r < EPT; ++r) {
+      v[r] = in[r] ? A.w[ix[r]] : 0.0;
+      s += v[r] * v[r];
+    }
+    const double wn = sqrt(total(s));
+#pragma unroll
+    for (int r = 0; r < EPT; ++r) v[r] = wn > 0.0 ? v[r] / wn : 0.0;
+    if (blockIdx.x == 0) {
+      reset_state(SegView{nullptr, nullptr, st, nullptr, nullptr, 1, m3}, 0, wn);
+      if (A.mw)
+#pragma unroll
+        for (int r = 0; r < EPT; ++r)
+          if (in[r]) A.u1[ix[r]] = wn > 0.0 ? A.mw[ix[r]] / wn : 0.0;
+    }
+  } else {
+    const int nv = k - 1;   // basis vectors v_1 .. v_{k-1}
+    const double *u = (k & 1) ? A.u0 : A.u1;
+    const double *vk = A.V + int64_t(nv - 1) * m3;
+    const double *vp = A.V + int64_t(nv > 1 ? nv - 2 : 0) * m3;
+    const double be = nv > 1 ? st->beta[nv - 2] : 0.0;
+    double x[EPT], xv[EPT], xp[EPT], vq[KR][EPT];
+#pragma unroll
+    for (int r = 0; r < EPT; ++r) {
+      x[r] = in[r] ? u[ix[r]] : 0.0;
+      xv[r] = in[r] ? vk[ix[r]] : 0.0;
+      xp[r] = in[r] && nv > 1 ? vp[ix[r]] : 0.0;
+    }
+    auto load = [&](int j0) {
+#pragma unroll
+      for (int q = 0; q < KR; ++q)
+        if (j0 + q < nv)
+#pragma unroll
+          for (int r = 0; r < EPT; ++r) vq[q][r] = A.V[int64_t(j0 + q) * m3 + ix[r]];
+    };
+    load(0);
+    double s = 0.0;
+#pragma unroll
+    for (int r = 0; r < EPT; ++r) s += xv[r] * x[r];
+    const double alpha = total(s);
+#pragma unroll
+    for (int r = 0; r < EPT; ++r) {
+      x[r] -= alpha * xv[r];
+      x[r] -= be * xp[r];
+      xs[t + r * kSmallThreads] = x[r];   // zero past the last element
+    }
+    __syncthreads();
+    // one basis vector per wavefront at a time (and |u|^2 as one more), so that a product costs
+    // one sum over lanes instead of one in every wavefront
+    double xw[W * EPT];
+#pragma unroll
+    for (int r = 0; r < W * EPT; ++r) xw[r] = xs[lane + 64 * r];
+    for (int j = wave; j <= nv; j += W) {
+      double a = 0.0;
+      if (j < nv) {
+        const double *vj = A.V + int64_t(j) * m3;
+#pragma unroll
+        for (int r = 0; r < W * EPT; ++r) a += vj[min(lane + 64 * r, m3 - 1)] * xw[r];
+      } else {
+#pragma unroll
+        for (int r = 0; r < W * EPT; ++r) a += xw[r] * xw[r];
+      }
+      a = wave_sum(a);
+      if (lane == 0) hs[j] = a;
+    }
+    __syncthreads();
+    // beta^2 = |u|^2 - |h|^2, as in lz_update
+    const double hj = lane < nv ? hs[lane] : 0.0;
+    const double b2 = hs[nv] - wave_sum(hj * hj);
+    const double beta = sqrt(b2 > 0.0 ? b2 : (b2 == b2 ? 0.0 : b2));
+    double proj[EPT];
+#pragma unroll
+    for (int r = 0; r < EPT; ++r) proj[r] = 0.0;
+    for (int j0 = 0; j0 < nv; j0 += KR) {
+      if (nv > KR) load(j0);
+#pragma unroll
+      for (int q = 0; q < KR; ++q)
+        if (j0 + q < nv) {
+          const double h = hs[j0 + q];
+#pragma unroll
+          for (int r = 0; r < EPT; ++r) proj[r] += h * vq[q][r];
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < EPT; ++r) {
+      const double y = x[r] - proj[r];
+      v[r] = beta > 0.0 ? y / beta : 0.0;
+    }
+    if (blockIdx.x == 0) {
+      if (t == 0) {
+        st->alpha[nv - 1] = alpha;
+        st->beta[nv - 1] = beta;
+      }
+      if (t < nv) st->h[t] = hs[t];
+    }
+  }
+  if (k > A.max_iter) return;
+  if (blockIdx.x == 0)
+#pragma unroll
+    for (int r = 0; r < EPT; ++r)
+      if (in[r]) A.V[int64_t(k - 1) * m3 + ix[r]] = v[r];
+  if (k == 1 && A.mw) return;   // u_1 is there already
+#pragma unroll
+  for (int r = 0; r < EPT; ++r)
+    if (in[r]) {
+      const int sp = ix[r] / 3;
+      R.f[ix[r] - 3 * sp][sp] = Real(g.h[sp] * v[r]);
+    }
+  __syncthreads();
+  const int i = int(blockIdx.x) * W + wave;
+  if (i >= n) return;
+  double acc[3] = {0.0, 0.0, 0.0};
+  R.row(n, A.part, i, lane, kc, acc);
+#pragma unroll
+  for (int c = 0; c < 3; ++c) acc[c] = wave_sum(acc[c]);
+  if (lane == 0) {
+    double *u = (k & 1) ? A.u1 : A.u0;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) u[3 * i + c] = A.scale * g.h[i] * acc[c];
+  }
 }
 
 // The eigensolve of T_1, T_2, ..., T_m in turn (as a Krylov process meets them), row k - 1 of
@@ -1475,12 +1706,11 @@ __global__ __launch_bounds__(kThreads) void tridiag_sequence(int m, LzState *__r
 }
 
 // lanczos_step_body for every live system, one workgroup each (segments <= kFusedSegment); src,
-// counter, host_done and epoch as in lz_update.
+// counter and rep as in lz_update.
 template <typename Real>
 __global__ __launch_bounds__(kThreads) void seg_lanczos_step(
     SegView v, double *__restrict__ V, double *__restrict__ u, int k, double tol, int write_next,
-    const double *__restrict__ hw, Real *__restrict__ src, int *counter, int *host_done,
-    int epoch) {
+    const double *__restrict__ hw, Real *__restrict__ src, int *counter, LzReport rep) {
   const int s = blockIdx.x;
   if (counter && s == 0 && threadIdx.x == 0) counter[0] = 0;
   if (v.done[s]) return;
@@ -1494,14 +1724,7 @@ __global__ __launch_bounds__(kThreads) void seg_lanczos_step(
       src[(i - 3 * sp) * (v.m3 / 3) + sp] = Real(hw[sp] * next[i]);
     }
   }
-  if (threadIdx.x == 0 && st->reason != 0) {
-    v.done[s] = 1;
-    if (atomicAdd(v.done + v.nsys + 1, 1) + 1 == v.nsys) v.done[v.nsys] = 1;
-    if (host_done) {
-      host_done[s] = epoch;
-      __threadfence_system();
-    }
-  }
+  if (threadIdx.x == 0) report_stop(v, s, k, st->reason != 0, rep);
 }
 
 // out = V_m y_m per system (m = the system's own iteration count)
@@ -1607,13 +1830,13 @@ int start_processes(rpb_ctx *ctx, const SegView &v, int64_t longest, const doubl
 template <typename Real>
 int iterate_processes(rpb_ctx *ctx, const SegView &v, int64_t longest, int k, double tol,
                       double *V, double *u, bool dotted, const LzPartials &P, bool write_next,
-                      const double *hw, Real *src, int *counter, LzRingSlot *ring, int *host_done,
-                      int epoch, hipStream_t stream) {
+                      const double *hw, Real *src, int *counter, const LzReport &rep,
+                      hipStream_t stream) {
   const double *vk = V + int64_t(k - 1) * v.m3;
   const unsigned ns = unsigned(v.nsys);
   const dim3 all{std::max(1u, nblk(longest)), ns, 1u};
   auto root = [&]() -> int {
-    lz_root<<<ns, kThreads, 0, stream>>>(v, k, tol, ring, host_done, epoch);
+    lz_root<<<ns, kThreads, 0, stream>>>(v, k, tol, rep);
     RPB_LAUNCHED(ctx);
     return RPB_OK;
   };
@@ -1631,12 +1854,12 @@ int iterate_processes(rpb_ctx *ctx, const SegView &v, int64_t longest, int k, do
       RPB_LAUNCHED(ctx);
       if (int64_t(all.x) * ns <= 512) {
         ord_scale<kT, Real, true><<<all, kThreads, 0, stream>>>(
-            v, k, tol, V, u, bpart, write_next, hw, src, counter, ring, host_done, epoch);
+            v, k, tol, V, u, bpart, write_next, hw, src, counter, rep);
         RPB_LAUNCHED(ctx);
         return RPB_OK;
       }
       ord_scale<kT, Real, false><<<all, kThreads, 0, stream>>>(
-          v, k, tol, V, u, bpart, write_next, hw, src, counter, ring, host_done, epoch);
+          v, k, tol, V, u, bpart, write_next, hw, src, counter, rep);
       RPB_LAUNCHED(ctx);
       return root();
     };
@@ -1654,8 +1877,7 @@ int iterate_processes(rpb_ctx *ctx, const SegView &v, int64_t longest, int k, do
       lz_dots<kE><<<grid, kThreads, 0, stream>>>(v, k, V, u, P.alpha, P.stride, P.dots, P.nb);
       RPB_LAUNCHED(ctx);
       lz_update<kE, Real, kR><<<grid, kThreads, 0, stream>>>(v, k, tol, V, u, P.dots, P.nb,
-                                                             write_next, hw, src, counter, ring,
-                                                             host_done, epoch);
+                                                             write_next, hw, src, counter, rep);
       RPB_LAUNCHED(ctx);
       return kR ? RPB_OK : root();
     };
@@ -1669,133 +1891,86 @@ int iterate_processes(rpb_ctx *ctx, const SegView &v, int64_t longest, int k, do
 
 }  // namespace
 
-// One eigensolve of the second stream: wait for iteration k's vector work (event
-// lz_vec_ev[slot]), the eigensolve and stop test (lanczos_eig), then the status event of ring
-// slot `slot` (lz_ev[slot]).
-struct LzJob {
-  void *ls;          // LzState
-  void *eig;         // LzEig
-  void *ring_slot;   // LzRingSlot, device address
-  int k;
-  double tol;
-  int slot;
-};
-
-// The second stream's host calls of the small-system solves, issued by a thread of its own:
-// a cross-stream wait, a launch and an event record take ~15 us of host time per iteration,
-// which the calling thread spends on the next iteration's launches instead (the two threads'
-// calls overlap).  Jobs are issued in the order they are queued; `posted` counts those whose
-// calls have been issued (their status event then exists).
-struct LzHelper {
-  std::thread th;
-  std::mutex mu;
-  std::condition_variable cv_job, cv_done;
-  std::deque<LzJob> jobs;
-  int64_t pushed = 0, posted = 0;
-  bool stop = false;
-  hipError_t err = hipSuccess;   // the first failed call, reported to the caller by lz_helper_wait
-  const char *what = nullptr;
-};
-
 namespace {
 
-void lz_helper_run(rpb_ctx *ctx, LzHelper *h) {
-  (void)hipSetDevice(ctx->device);
-  for (;;) {
-    LzJob j;
-    {
-      std::unique_lock<std::mutex> lk(h->mu);
-      h->cv_job.wait(lk, [&] { return h->stop || !h->jobs.empty(); });
-      if (h->jobs.empty()) return;   // stopped with nothing left to issue
-      j = h->jobs.front();
-      h->jobs.pop_front();
-    }
-    const char *what = "hipStreamWaitEvent";
-    hipError_t e = hipStreamWaitEvent(ctx->lz_stream, ctx->lz_vec_ev[j.slot], 0);
-    if (e == hipSuccess) {
-      lanczos_eig<<<1, kThreads, 0, ctx->lz_stream>>>(static_cast<LzState *>(j.ls),
-                                                      static_cast<LzEig *>(j.eig), j.k, j.tol,
-                                                      static_cast<LzRingSlot *>(j.ring_slot));
-      e = hipGetLastError();
-      what = "lanczos_eig launch";
-    }
-    if (e == hipSuccess) {
-      e = hipEventRecord(ctx->lz_ev[j.slot], ctx->lz_stream);
-      what = "hipEventRecord";
-    }
-    {
-      std::lock_guard<std::mutex> lk(h->mu);
-      if (e != hipSuccess && h->err == hipSuccess) {
-        h->err = e;
-        h->what = what;
-      }
-      ++h->posted;
-    }
-    h->cv_done.notify_all();
-  }
-}
+// Outcome of a single-system solve, as the host read it.
+struct LzOutcome {
+  int m = 0;           // iterations whose result counts
+  int reason = 0;
+  double eps = 0.0;
+};
 
-// The context's helper, started on first use (with the ring's status events).
-int lz_helper_get(rpb_ctx *ctx, LzHelper **out) {
-  if (!ctx->lz_helper) {
-    for (auto &e : ctx->lz_ev)
-      if (!e) RPB_HIP(ctx, hipEventCreateWithFlags(&e, hipEventDisableTiming));
-    LzHelper *h = new (std::nothrow) LzHelper();
-    if (!h) return fail(ctx, RPB_ENOMEM, "no memory for the Lanczos helper");
-    try {
-      h->th = std::thread(lz_helper_run, ctx, h);
-    } catch (...) {
-      delete h;
-      return fail(ctx, RPB_EDEVICE, "could not start the Lanczos helper thread");
-    }
-    ctx->lz_helper = h;
+// Reads the statuses of the iterations up to qmax, in order, until one reports a stop.
+int read_statuses(rpb_ctx *ctx, int epoch, int qmax, int *next_q, LzOutcome *out,
+                  hipStream_t stream) {
+  LzRing *ring = lz_ring(ctx);
+  for (; *next_q <= qmax && out->reason == 0; ++*next_q) {
+    const int q = *next_q;
+    LzRingSlot &slot = ring->slot[q % kLzRing];
+    RPB_TRY(wait_pinned(ctx, stream, [&] {
+      return __atomic_load_n(&slot.tag, __ATOMIC_ACQUIRE) == lz_tag(epoch, q);
+    }));
+    out->m = q;
+    out->reason = slot.reason;
+    out->eps = slot.eps;
   }
-  *out = ctx->lz_helper;
   return RPB_OK;
 }
 
-// Queues a job; returns its sequence number.
-int64_t lz_helper_push(LzHelper *h, const LzJob &j) {
-  int64_t seq;
-  {
-    std::lock_guard<std::mutex> lk(h->mu);
-    h->jobs.push_back(j);
-    seq = ++h->pushed;
+// The small-system solve (lz_small).  The status of T_m comes from launch m + 2, and the host reads
+// it once launch m + 3 is enqueued, so the device always has one launch queued; launches past
+// the stop return at once.
+template <typename Real, typename Geom>
+int small_solve(rpb_ctx *ctx, const rpb_params *p, const Geom &geom, int part, SmallArgs A,
+                LzOutcome *out, hipStream_t stream) {
+  constexpr int W = kSmallThreads / 64;
+  const unsigned grid = unsigned((A.n + W - 1) / W) + 1u;
+  const auto kc = make_pair_consts<Real>(p->lx / p->a, p->ly / p->a);
+  A.part = part;
+  auto launch = [&](auto E) {
+    constexpr int kE = decltype(E)::value;
+    auto by_wall = [&](auto Wl) {
+      constexpr bool kW = decltype(Wl)::value;
+      if (p->lx > 0.0)
+        lz_small<Real, kE, kW, true><<<grid, kSmallThreads, 0, stream>>>(A, geom, kc);
+      else
+        lz_small<Real, kE, kW, false><<<grid, kSmallThreads, 0, stream>>>(A, geom, kc);
+    };
+    if (p->wall)
+      by_wall(std::true_type{});
+    else
+      by_wall(std::false_type{});
+  };
+  LzRing *ring_dev = lz_ring_dev(ctx);
+  int next_q = 1;
+  size_t mark[kLzRing] = {};
+  for (int k = 1; k <= A.max_iter + 2 && out->reason == 0; ++k) {
+    A.k = k;
+    const int m = k - 2;   // the status that this launch writes
+    A.rep.ring = m > 0 ? &ring_dev->slot[m % kLzRing] : nullptr;
+    mark[k % kLzRing] = ctx->ev_start.size();
+    const bool product = k <= A.max_iter && !(k == 1 && A.mw);
+    hipEvent_t t0 = nullptr;
+    if (product) RPB_TRY(timing_begin(ctx, stream, &t0));
+    if (3 * A.n <= kSmallThreads)
+      launch(std::integral_constant<int, 1>{});
+    else
+      launch(std::integral_constant<int, 2>{});
+    RPB_LAUNCHED(ctx);
+    if (product)
+      RPB_TRY(timing_end(ctx, stream, t0, double(A.n) * double(A.n),
+                         std::is_same<Real, double>::value ? 0 : 2));
+    if (m < 1) continue;
+    const int before = next_q;
+    RPB_TRY(read_statuses(ctx, A.rep.epoch, k < A.max_iter + 2 ? m - 1 : m, &next_q, out, stream));
+    // products past the stop count for nothing
+    if (out->reason != 0 && next_q > before && out->m + 1 <= k)
+      timing_discard(ctx, mark[(out->m + 1) % kLzRing]);
   }
-  h->cv_job.notify_one();
-  return seq;
-}
-
-// Blocks until the jobs up to sequence number `seq` are issued; reports a failed call.
-int lz_helper_wait(rpb_ctx *ctx, LzHelper *h, int64_t seq) {
-  hipError_t e;
-  const char *what;
-  {
-    std::unique_lock<std::mutex> lk(h->mu);
-    h->cv_done.wait(lk, [&] { return h->posted >= seq; });
-    e = h->err;
-    what = h->what;
-    h->err = hipSuccess;
-  }
-  if (e != hipSuccess)
-    return fail(ctx, RPB_EDEVICE, "%s failed: %s (Lanczos helper)", what, hipGetErrorString(e));
   return RPB_OK;
 }
 
 }  // namespace
-
-void lz_helper_destroy(rpb_ctx *ctx) {
-  LzHelper *h = ctx->lz_helper;
-  if (!h) return;
-  {
-    std::lock_guard<std::mutex> lk(h->mu);
-    h->stop = true;
-  }
-  h->cv_job.notify_all();
-  if (h->th.joinable()) h->th.join();
-  delete h;
-  ctx->lz_helper = nullptr;
-}
 
 int lanczos_run(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const double *w, double tol,
                 int max_iter, bool precond, double *out, int *iters, double *eps_out,
@@ -1821,57 +1996,49 @@ int lanczos_run(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const double
   if (!ls) return st;
   LzEig *eig = static_cast<LzEig *>(workspace(ctx, WS_LZEIG, sizeof(LzEig), &st));
   if (!eig) return st;
-  // The host reads the status of iteration m only after iterations up to m + lag have been
-  // enqueued, so the device never idles while the host decides.  Small systems (one workgroup
-  // per iteration) run the eigensolve and stop test of iteration k on a second stream beside
-  // the product of iteration k + 1 (lag 2); larger ones keep them in line on `stream` (lag 1),
-  // where an iteration the stop test has not yet cleared would cost a whole product.  Every
-  // kernel of an iteration past the stop leaves the result unchanged: it touches only u, h,
-  // V's next column, the packed sources of the next product, entries of alpha and beta past
-  // the last iteration and, once the stop is seen, the skip flag of the products (which then
-  // return at once); the eigensolve is skipped (y, eps and reason stay).
-  RPB_TRY(lz_ring_fence(ctx));
-  LzRing *ring = lz_ring(ctx);
-  LzRing *ring_dev = lz_ring_dev(ctx);
-  const bool fused = m3 <= kFusedSegment;
-  // without the preconditioner the kernels that form v_1 and v_{k+1} also pack them for the next
-  // product (lz_start; lanczos_vec, or lz_update for larger systems)
-  const bool prepack = !precond;
-  void *src = nullptr;
-  if (prepack) {
-    src = source_buffer(ctx, g, &st);
-    if (!src) return st;
-  }
-  const double *hw = prepack ? packed_weights(g) : nullptr;
+  const int epoch = next_epoch(ctx);
   const bool f64 = g.precision == RPB_FP64;
-  hipStream_t es = ctx->lz_stream;
-  LzHelper *helper = nullptr;   // issues the second stream's calls (small systems)
-  if (fused) RPB_TRY(lz_helper_get(ctx, &helper));
-  int64_t seq[kLzRing] = {};    // helper job of the iteration in each ring slot
-  int64_t last_seq = 0;
-  const int lag = fused ? 2 : 1;
-  const int *stopped = fused ? &ls->halt : &ls->reason;
-
-  const SegView view{nullptr, nullptr, ls, nullptr, eig, 1, m3};
-  if (f64)
-    RPB_TRY(start_processes(ctx, view, m3, w, P, V, hw, static_cast<double *>(src), mw, u, nullptr,
-                            stream));
-  else
-    RPB_TRY(start_processes(ctx, view, m3, w, P, V, hw, static_cast<float *>(src), mw, u, nullptr,
-                            stream));
-
-  int m = 0;           // iterations whose result counts
-  int reason = 0;
-  double eps = 0.0;
-  size_t mark[kLzRing] = {};   // first timing record of each iteration in flight
-  bool stop = false;
-  int next_q = 1;      // first iteration whose status the host has not read
-  auto iterate = [&]() -> int {
-    for (int k = 1; k <= max_iter && !stop; ++k) {
+  LzOutcome o;
+  const int part = precond || m3 > kFusedSegment ? 0 : one_tile_part(ctx, g);
+  if (part > 0) {   // one launch per iteration
+    double *u2 = static_cast<double *>(workspace(ctx, WS_LZ_U2, size_t(m3) * sizeof(double), &st));
+    if (!u2) return st;
+    const SmallArgs A{ls,   eig, V, w, mw, u, u2, n, 1, max_iter, part,
+                      tol, 1.0 / (8.0 * M_PI * p->eta * p->a), LzReport{nullptr, nullptr, epoch}};
+    if (f64)
+      RPB_TRY((small_solve<double>(ctx, p, geom_d(g), part, A, &o, stream)));
+    else
+      RPB_TRY((small_solve<float>(ctx, p, geom_f(g), part, A, &o, stream)));
+  } else {
+    // without the preconditioner the kernels that form v_1 and v_{k+1} also pack them for the
+    // next product
+    const bool prepack = !precond;
+    void *src = nullptr;
+    if (prepack) {
+      src = source_buffer(ctx, g, &st);
+      if (!src) return st;
+    }
+    const double *hw = prepack ? packed_weights(g) : nullptr;
+    const SegView view{nullptr, nullptr, ls, nullptr, eig, 1, m3};
+    if (f64)
+      RPB_TRY(start_processes(ctx, view, m3, w, P, V, hw, static_cast<double *>(src), mw, u,
+                              nullptr, stream));
+    else
+      RPB_TRY(start_processes(ctx, view, m3, w, P, V, hw, static_cast<float *>(src), mw, u,
+                              nullptr, stream));
+    LzRing *ring_dev = lz_ring_dev(ctx);
+    const int *stopped = &ls->reason;
+    size_t mark[kLzRing] = {};   // first timing record of each iteration in flight
+    int next_q = 1;              // first iteration whose status the host has not read
+    // The host reads the status of iteration m only after iteration m + 1 has been enqueued, so
+    // the device never idles while the host decides.  An iteration past the stop leaves the
+    // result unchanged: its product returns at once, and its vector work touches only u, h, V's
+    // next column, the packed sources and entries of alpha and beta past the last iteration.
+    for (int k = 1; k <= max_iter && o.reason == 0; ++k) {
       const int slot = k % kLzRing;
       mark[slot] = ctx->ev_start.size();
       double *vm = V + int64_t(k - 1) * m3;
-      bool dotted = false;   // alpha's partials are in apart
+      bool dotted = false;   // alpha's partials are in P
       if (precond) {   // u = L^-1 M L^-1 vm
         divide_by<<<nblk(m3), kThreads, 0, stream>>>(m3, vm, L, t);
         RPB_LAUNCHED(ctx);
@@ -1881,61 +2048,24 @@ int lanczos_run(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const double
       } else if (k == 1 && mw) {   // M v_1 = (M w) / |w| from the caller's product (lz_start)
         dotted = true;
       } else {   // v_k packed where it was formed
-        DotOut dot{fused || !f64 ? nullptr : vm, P.alpha};
+        DotOut dot{f64 ? vm : nullptr, P.alpha};
         RPB_TRY(matvec_prepacked(ctx, p, g, src, u, stream, stopped, &dot));
         dotted = dot.done;
       }
-      if (fused) {   // the vector work in one workgroup; the eigensolve on the second stream
-        if (f64)
-          lanczos_vec<double><<<1, kThreads, 0, stream>>>(
-              ls, V, u, m3, k, k < max_iter, hw, static_cast<double *>(src));
-        else
-          lanczos_vec<float><<<1, kThreads, 0, stream>>>(
-              ls, V, u, m3, k, k < max_iter, hw, static_cast<float *>(src));
-        RPB_LAUNCHED(ctx);
-        RPB_HIP(ctx, hipEventRecord(ctx->lz_vec_ev[slot], stream));
-        ctx->lz_live[slot] = true;   // the helper records lz_ev[slot] after its eigensolve
-        seq[slot] = last_seq =
-            lz_helper_push(helper, LzJob{ls, eig, &ring_dev->slot[slot], k, tol, slot});
-      } else {
-        if (f64)
-          RPB_TRY(iterate_processes(ctx, view, m3, k, tol, V, u, dotted, P, k < max_iter, hw,
-                                    static_cast<double *>(src), nullptr, &ring_dev->slot[slot],
-                                    nullptr, 0, stream));
-        else
-          RPB_TRY(iterate_processes(ctx, view, m3, k, tol, V, u, dotted, P, k < max_iter, hw,
-                                    static_cast<float *>(src), nullptr, &ring_dev->slot[slot],
-                                    nullptr, 0, stream));
-        RPB_TRY(lz_ring_post(ctx, slot, stream));
-      }
-      // the statuses up to iteration k - lag (all of them after the last iteration)
-      const int qmax = k < max_iter ? k - lag : k;
-      for (; next_q <= qmax; ++next_q) {
-        const int q = next_q;
-        if (fused) RPB_TRY(lz_helper_wait(ctx, helper, seq[q % kLzRing]));
-        RPB_TRY(lz_ring_wait(ctx, q % kLzRing));
-        m = q;
-        reason = ring->slot[q % kLzRing].reason;
-        eps = ring->slot[q % kLzRing].eps;
-        if (reason != 0) {
-          // the iterations after q did no work that counts: drop their pair-kernel timing
-          // records (some may have run in full before the stop was seen, others not at all)
-          if (q < k) timing_discard(ctx, mark[(q + 1) % kLzRing]);
-          stop = true;
-          break;
-        }
-      }
+      const LzReport rep{&ring_dev->slot[slot], nullptr, epoch};
+      if (f64)
+        RPB_TRY(iterate_processes(ctx, view, m3, k, tol, V, u, dotted, P, k < max_iter, hw,
+                                  static_cast<double *>(src), nullptr, rep, stream));
+      else
+        RPB_TRY(iterate_processes(ctx, view, m3, k, tol, V, u, dotted, P, k < max_iter, hw,
+                                  static_cast<float *>(src), nullptr, rep, stream));
+      RPB_TRY(read_statuses(ctx, epoch, k < max_iter ? k - 1 : k, &next_q, &o, stream));
+      // launches past the stop returned at once: drop their timing records
+      if (o.reason != 0 && o.m < k) timing_discard(ctx, mark[(o.m + 1) % kLzRing]);
     }
-    return RPB_OK;
-  };
-  int status = iterate();
-  if (fused) {   // the second stream's work, all of it, before anything later on `stream`
-    const int hs = lz_helper_wait(ctx, helper, last_seq);
-    if (status == RPB_OK) status = hs;
-    RPB_HIP(ctx, hipEventRecord(ctx->lz_join_ev, es));
-    RPB_HIP(ctx, hipStreamWaitEvent(stream, ctx->lz_join_ev, 0));
   }
-  if (status != RPB_OK) return status;
+  const int m = o.m, reason = o.reason;
+  const double eps = o.eps;
   basis_combine<<<nblk(m3), kThreads, 0, stream>>>(m3, m, V, ls->y, out);
   RPB_LAUNCHED(ctx);
   if (precond) {
@@ -2008,14 +2138,12 @@ int lanczos_segments(rpb_ctx *ctx, const Batch &b, const double *L, double *t, c
                   reinterpret_cast<int *>(lz + states_bytes), eig, nsys, m3};
   LzStatus *status_dev = reinterpret_cast<LzStatus *>(lz + status_off);
   const unsigned ns = unsigned(nsys);
-  // a process that stops writes this call's epoch (from 1, unique in the context, whose pinned
-  // buffer starts zeroed) into its word of the pinned buffer
-  int *host_done = nullptr, *host_done_dev = nullptr;
-  const int epoch = ++ctx->lz_epoch;
+  // every process reports each iteration into its word of the pinned buffer
+  LzReport rep{nullptr, nullptr, next_epoch(ctx)};
+  int *words = nullptr;
   if (sync_each) {
-    RPB_TRY(lz_ring_fence(ctx));
-    host_done = reinterpret_cast<int *>(static_cast<char *>(host_scratch(ctx)) + kHostDoneOffset);
-    host_done_dev =
+    words = reinterpret_cast<int *>(static_cast<char *>(host_scratch(ctx)) + kHostDoneOffset);
+    rep.words =
         reinterpret_cast<int *>(static_cast<char *>(host_scratch_dev(ctx)) + kHostDoneOffset);
   }
   std::vector<int> known;   // host copy of the flags, once read
@@ -2052,30 +2180,33 @@ int lanczos_segments(rpb_ctx *ctx, const Batch &b, const double *L, double *t, c
     if (fused) {   // every system's iteration in one workgroup
       if (f64)
         seg_lanczos_step<double><<<ns, kThreads, 0, stream>>>(
-            v, V, u, k, tol, next, hw, static_cast<double *>(src), counter, host_done_dev, epoch);
+            v, V, u, k, tol, next, hw, static_cast<double *>(src), counter, rep);
       else
         seg_lanczos_step<float><<<ns, kThreads, 0, stream>>>(
-            v, V, u, k, tol, next, hw, static_cast<float *>(src), counter, host_done_dev, epoch);
+            v, V, u, k, tol, next, hw, static_cast<float *>(src), counter, rep);
       RPB_LAUNCHED(ctx);
     } else {
       if (f64)
         RPB_TRY(iterate_processes(ctx, v, longest, k, tol, V, u, job.dot.done, P, next, hw,
-                                  static_cast<double *>(src), counter, nullptr, host_done_dev,
-                                  epoch, stream));
+                                  static_cast<double *>(src), counter, rep, stream));
       else
         RPB_TRY(iterate_processes(ctx, v, longest, k, tol, V, u, job.dot.done, P, next, hw,
-                                  static_cast<float *>(src), counter, nullptr, host_done_dev,
-                                  epoch, stream));
+                                  static_cast<float *>(src), counter, rep, stream));
     }
     if (!sync_each) continue;
-    RPB_TRY(lz_ring_post(ctx, slot, stream));
     const int qmax = next ? k - lag : next_q - 1;   // nothing to decide after the last iteration
     for (; next_q <= qmax && !stop; ++next_q) {
-      RPB_TRY(lz_ring_wait(ctx, next_q % kLzRing));
       known.resize(size_t(nsys));
       bool all = true;
       for (int s = 0; s < nsys; ++s) {
-        known[size_t(s)] = __atomic_load_n(host_done + s, __ATOMIC_RELAXED) == epoch;
+        // a stopped process keeps its last word; the others count up
+        int word = 0;
+        RPB_TRY(wait_pinned(ctx, stream, [&] {
+          word = __atomic_load_n(words + s, __ATOMIC_ACQUIRE);
+          return (word >> 8) == rep.epoch &&
+                 ((word & kTagStop) != 0 || (word & (kTagStop - 1)) >= next_q);
+        }));
+        known[size_t(s)] = (word & kTagStop) != 0 && (word & (kTagStop - 1)) <= next_q;
         all = all && known[size_t(s)];
       }
       if (all) {

@@ -1581,6 +1581,16 @@ int matvec_symmetric(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const v
   return RPB_OK;
 }
 
+int one_tile_part(const rpb_ctx *ctx, const Packed &g) {
+  const Shape &shape = ctx->tune.s[g.precision == RPB_FP64 ? RPB_FP64 : RPB_MIXED];
+  if (!shape.symmetric) return 0;
+  if (g.precision == RPB_FP64) return 1;
+  const int64_t ts = int64_t(kBlock) * shape.tpt;
+  if (g.n > ts) return 0;
+  const int64_t part = ts / sym_nsplit(g.n, ts);
+  return part < 64 ? int(part) : 0;   // parts of 64 or more take the 64-block form
+}
+
 const double *packed_weights(const Packed &g) {
   return g.precision == RPB_FP64 ? geom_d(g).h : geom_f(g).h;
 }

@@ -42,16 +42,12 @@ enum Slot {
   WS_CELLS,         // steric cell list: cells, buckets, sorted lists, bucket counts and starts
   WS_MBATCH,        // batched multi-vector products: per-system item and partial offsets
   WS_LZEIG,         // Lanczos: eigendecomposition of T_m per Krylov process
+  WS_LZ_U2,         // small-system Lanczos: the second u (launches alternate)
   WS_NSLOTS
 };
 
 // Slots of the Lanczos status ring: iterations whose status may be in flight at once.
 constexpr int kLzRing = 4;
-
-// The host thread that issues the second stream's work of small-system Lanczos solves
-// (lanczos.hip); created on first use, stopped by lz_helper_destroy.
-struct LzHelper;
-void lz_helper_destroy(rpb_ctx *ctx);
 
 // Default limit of the partial sums of one launch of the symmetric tile-pair kernels.
 constexpr size_t kMaxChunkBytes = size_t(512) << 20;
@@ -105,17 +101,7 @@ struct rpb_ctx {
   std::vector<double> ev_pairs;
   std::vector<int> ev_kind;             // 2 * (precision == mixed) + (torque present)
   std::vector<hipEvent_t> ev_pool;
-  // Lanczos status ring (rpb::kLzRing slots in the upper half of the pinned scratch) and the
-  // events that mark each slot's status as landed; `lz_live` is set while one may be in flight
-  hipEvent_t lz_ev[rpb::kLzRing] = {};
-  bool lz_live[rpb::kLzRing] = {};
-  int lz_epoch = 0;                     // batched solves so far (marks their host flags)
-  // the second stream on which small systems run the Lanczos eigensolve and stop test beside
-  // the vector recurrence, and the events that order the two streams
-  hipStream_t lz_stream = nullptr;
-  hipEvent_t lz_vec_ev[rpb::kLzRing] = {};
-  hipEvent_t lz_join_ev = nullptr;
-  rpb::LzHelper *lz_helper = nullptr;   // issues the second stream's calls from its own thread
+  int lz_epoch = 0;                     // Lanczos solves so far (tags their status words)
   // deferred position check (check_finite_begin / _end): its flag's copy and event
   hipEvent_t fin_ev = nullptr;
   bool fin_live = false;
@@ -133,7 +119,7 @@ void *workspace(rpb_ctx *ctx, Slot slot, size_t bytes, int *status);
 
 // Pinned host scratch (kHostScratchBytes).  The lower half holds device scalars and
 // per-system records copied back by one call and read before it returns; the upper half
-// holds the Lanczos status ring, whose last copy may still land after the call returns.
+// holds the Lanczos status words, which kernels of a solve may still store after the call returns.
 constexpr size_t kHostScratchBytes = 1 << 17;
 constexpr size_t kHostLzRingOffset = kHostScratchBytes / 2;
 constexpr size_t kHostFiniteOffset = kHostLzRingOffset + 1024;   // deferred position check
@@ -256,6 +242,10 @@ struct DotOut {
 int matvec_prepacked(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const void *src,
                      double *vel, hipStream_t stream, const int *skip = nullptr,
                      DotOut *dot = nullptr);
+
+// Sources that the whole-system force product of `g` sums in one run when it is a single tile of
+// the symmetric kernel (any positive number in float64, whose sums may be regrouped), else 0.
+int one_tile_part(const rpb_ctx *ctx, const Packed &g);
 
 // ---- batched products (matvec.hip) -----------------------------------------------------
 
