@@ -16,7 +16,6 @@
 #include <cfloat>
 #include <cmath>
 #include <cstddef>
-#include <thread>
 #include <type_traits>
 #include <vector>
 
@@ -78,27 +77,6 @@ __host__ __device__ __forceinline__ int lz_tag(int epoch, int k) { return (epoch
 int next_epoch(rpb_ctx *ctx) {
   ctx->lz_epoch = ctx->lz_epoch >= 0x7fffff ? 1 : ctx->lz_epoch + 1;
   return ctx->lz_epoch;
-}
-
-// Blocks until ready(), which reads words that kernels of `stream` store in pinned memory.  The
-// stream is asked now and then, so the wait ends with an error if its work ends or fails without
-// storing them.
-template <typename Ready>
-int wait_pinned(rpb_ctx *ctx, hipStream_t stream, Ready &&ready) {
-  for (int spins = 1;; ++spins) {
-    if (ready()) return RPB_OK;
-    if (spins % 4096 != 0) continue;
-    const hipError_t e = hipStreamQuery(stream);
-    if (e == hipErrorNotReady) {
-      (void)hipGetLastError();
-      std::this_thread::yield();
-      continue;
-    }
-    if (e != hipSuccess)
-      return fail(ctx, RPB_EDEVICE, "hipStreamQuery failed: %s", hipGetErrorString(e));
-    if (ready()) return RPB_OK;
-    return fail(ctx, RPB_EDEVICE, "a Lanczos status did not arrive");
-  }
 }
 
 // out = V y (first nvec rows of V)
@@ -2313,9 +2291,11 @@ int lanczos_entry(rpb_ctx *ctx, const rpb_params *p, int64_t n, const double *po
     return fail(ctx, RPB_EINVAL, "out overlaps an input");
   hipStream_t stream = static_cast<hipStream_t>(stream_);
   RPB_HIP(ctx, hipSetDevice(ctx->device));
-  RPB_TRY(check_finite(ctx, pos, n, stream));
+  Check check;
+  RPB_TRY(check_begin(ctx, &check, stream));
   Packed g;
-  RPB_TRY(pack_geometry(ctx, p, n, pos, WS_GEOM, &g, stream));
+  RPB_TRY(pack_checked(ctx, p, n, pos, WS_GEOM, &g, check, nullptr, nullptr, nullptr, stream));
+  RPB_TRY(check_end(ctx, check, stream));
   const int lz =
       lanczos_run(ctx, p, g, w, tol, max_iter, precond, out, iters_out, eps_out, stream);
   if (lz != RPB_OK && lz != RPB_ENOCONV) return lz;

@@ -710,8 +710,11 @@ extern "C" int rpb_mobility_matvec_multi(rpb_ctx *ctx, const rpb_params *p, int6
     return fail(ctx, RPB_EINVAL, "vel overlaps an input");
   hipStream_t stream = static_cast<hipStream_t>(stream_);
   RPB_HIP(ctx, hipSetDevice(ctx->device));
-  RPB_TRY(check_finite(ctx, pos, n, stream));
+  Check check;
+  RPB_TRY(check_begin(ctx, &check, stream));
   Packed g;
-  RPB_TRY(pack_geometry(ctx, p, n, pos, WS_GEOM, &g, stream));
-  return matvec_multi(ctx, p, g, nvec, nullptr, force, vel, stream);
+  RPB_TRY(pack_checked(ctx, p, n, pos, WS_GEOM, &g, check, nullptr, nullptr, nullptr, stream));
+  const int st = matvec_multi(ctx, p, g, nvec, nullptr, force, vel, stream, nullptr,
+                              check_skip(check));
+  return check_end(ctx, check, stream, st);
 }

@@ -7,6 +7,7 @@
 #include <cstdio>
 #include <map>
 #include <string>
+#include <thread>
 #include <tuple>
 #include <vector>
 
@@ -55,7 +56,7 @@ constexpr size_t kMaxChunkBytes = size_t(512) << 20;
 // Layout of the WS_SMALL slot.
 constexpr size_t kSmallBytes = 1 << 16;
 constexpr size_t kSmallWorkCounter = 8192;          // int: work counter of persistent kernels
-constexpr size_t kSmallFiniteFlag = kSmallBytes - 4; // int: non-finite input flag
+constexpr size_t kSmallCheck = 12288;               // CheckWords of the finite checks
 constexpr size_t kSmallStepState = 16384;           // int64 step, int have_prev (time step)
 
 struct DevBuf {
@@ -102,9 +103,8 @@ struct rpb_ctx {
   std::vector<int> ev_kind;             // 2 * (precision == mixed) + (torque present)
   std::vector<hipEvent_t> ev_pool;
   int lz_epoch = 0;                     // Lanczos solves so far (tags their status words)
-  // deferred position check (check_finite_begin / _end): its flag's copy and event
-  hipEvent_t fin_ev = nullptr;
-  bool fin_live = false;
+  int check_tag = 0;                    // finite checks so far (tags their host word)
+  bool check_clean = false;             // the check words are known to be reset
   // opt-in scan of each entry point's output for NaN / Inf (rpb_output_check_enable)
   bool check_output = false;
 };
@@ -122,7 +122,7 @@ void *workspace(rpb_ctx *ctx, Slot slot, size_t bytes, int *status);
 // holds the Lanczos status words, which kernels of a solve may still store after the call returns.
 constexpr size_t kHostScratchBytes = 1 << 17;
 constexpr size_t kHostLzRingOffset = kHostScratchBytes / 2;
-constexpr size_t kHostFiniteOffset = kHostLzRingOffset + 1024;   // deferred position check
+constexpr size_t kHostCheckOffset = kHostLzRingOffset + 1024;    // finite checks: tagged verdict
 constexpr size_t kHostDoneOffset = kHostLzRingOffset + 4096;     // batched Lanczos: a word per process
 inline void *host_scratch(rpb_ctx *ctx) { return ctx->host_pinned; }
 inline void *host_scratch_dev(rpb_ctx *ctx) { return ctx->host_pinned_dev; }
@@ -149,18 +149,59 @@ inline void *host_scratch_dev(rpb_ctx *ctx) { return ctx->host_pinned_dev; }
     if (s_ != RPB_OK) return s_;                                                        \
   } while (0)
 
+// Blocks until ready(), which reads words that kernels of `stream` store in pinned memory.  The
+// stream is asked now and then, so the wait ends with an error if its work ends or fails without
+// storing them.
+template <typename Ready>
+int wait_pinned(rpb_ctx *ctx, hipStream_t stream, Ready &&ready) {
+  for (int spins = 1;; ++spins) {
+    if (ready()) return RPB_OK;
+    if (spins % 4096 != 0) continue;
+    const hipError_t e = hipStreamQuery(stream);
+    if (e == hipErrorNotReady) {
+      (void)hipGetLastError();
+      std::this_thread::yield();
+      continue;
+    }
+    if (e != hipSuccess)
+      return fail(ctx, RPB_EDEVICE, "hipStreamQuery failed: %s", hipGetErrorString(e));
+    if (ready()) return RPB_OK;
+    return fail(ctx, RPB_EDEVICE, "a status word did not arrive");
+  }
+}
+
 // Common argument validation for the mobility entry points.
 int check_params(rpb_ctx *ctx, const rpb_params *p);
 // True when [a, a + abytes) and [b, b + bbytes) overlap (NULL never overlaps).
 bool overlaps(const void *a, size_t abytes, const void *b, size_t bbytes);
-// Checks that every position is finite (synchronises `stream`).
+// Finite checks.  A kernel that scans its input counts its workgroups, the offending ones in the
+// high half, in one atomic word; the last one resets the word, stores the verdict where later
+// kernels of the stream read it (a skip flag) and tags it into pinned host memory, which the host
+// polls: no launch to clear a flag, no copy and no synchronisation of the stream.
+struct CheckWords {
+  unsigned long long count;   // zero between checks
+  int bad;                    // verdict of the last check
+};
+struct Check {
+  CheckWords *w = nullptr;    // NULL: no check
+  int *host = nullptr;        // pinned word, device address
+  int tag = 0;
+};
+// A new check's descriptor (for one launch on `stream`).
+int check_begin(rpb_ctx *ctx, Check *c, hipStream_t stream);
+// The verdict word of checks, for kernels enqueued after the checking one.
+const int *check_skip(const Check &c);
+// Waits for the check's verdict (not for work enqueued after it): RPB_ENONFINITE naming `what`
+// if a value was NaN or Inf.  Work enqueued in between may see those values, so it must not index
+// memory by them, and must write only workspace or read check_skip.
+int check_end(rpb_ctx *ctx, const Check &c, hipStream_t stream, const char *what = "positions");
+// check_end after work enqueued in between returned `st`: the verdict comes first.
+inline int check_end(rpb_ctx *ctx, const Check &c, hipStream_t stream, int st) {
+  const int verdict = check_end(ctx, c, stream);
+  return verdict != RPB_OK ? verdict : st;
+}
+// The whole check at once: every position finite?
 int check_finite(rpb_ctx *ctx, const double *pos, int64_t n, hipStream_t stream);
-// The same check in two halves: _begin enqueues it and the copy of its flag to pinned host
-// memory; _end waits for that copy only (not for work enqueued after it) and returns
-// RPB_ENONFINITE if a position is NaN or Inf.  Work enqueued between the two may see those
-// values, so it must not index memory by position value, and must write only workspace.
-int check_finite_begin(rpb_ctx *ctx, const double *pos, int64_t n, hipStream_t stream);
-int check_finite_end(rpb_ctx *ctx);
 // With ctx->check_output set: scan m values at v for NaN / Inf on `stream`, synchronise, and
 // return RPB_ENONFINITE naming `what` if one is found; RPB_OK at once otherwise.
 int check_output(rpb_ctx *ctx, const double *v, int64_t m, hipStream_t stream, const char *what);
@@ -184,6 +225,11 @@ struct Packed {
 // Pack positions (clamp heights, weights H) into the geometry slot `slot`.
 int pack_geometry(rpb_ctx *ctx, const rpb_params *p, int64_t n, const double *pos, Slot slot,
                   Packed *out, hipStream_t stream);
+// The same in one launch with the check of the positions and, with src (the layout of
+// source_buffer), the packing of force and torque (nullable, not both).
+int pack_checked(rpb_ctx *ctx, const rpb_params *p, int64_t n, const double *pos, Slot slot,
+                 Packed *out, const Check &check, const double *force, const double *torque,
+                 void *src, hipStream_t stream);
 
 // The same packing into a caller-provided buffer of packed_geometry_bytes(n, precision).
 int pack_geometry_into(rpb_ctx *ctx, const rpb_params *p, int64_t n, const double *pos,
@@ -237,6 +283,10 @@ struct DotOut {
   int64_t stride = 0;
   bool done = false;
 };
+// matvec_packed from sources already in `src` (has_t: a torque among them).
+int matvec_sources(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const void *src, bool has_t,
+                   int64_t row0, int64_t nrows, double *vel, hipStream_t stream,
+                   const int *skip = nullptr, bool expanded = false, DotOut *dot = nullptr);
 // U = M F for the whole system from force sources already written into `src` (rows 0..2 of
 // source_buffer's layout; no torque), as matvec_packed would form them.
 int matvec_prepacked(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const void *src,

@@ -182,7 +182,8 @@ extern "C" int sab_step(rpb_ctx *ctx, const rpb_params *p, const rpb_sab_config 
   // are enqueued, so the device goes on from the previous call's work without a pause.
   // Those kernels index memory by sphere, tile and hashed (clamped) cell, never by a raw
   // position value, and write only workspace; the state changes after the check has passed.
-  RPB_TRY(check_finite_begin(ctx, state->pos, n, stream));
+  Check check;
+  RPB_TRY(check_begin(ctx, &check, stream));
   const int64_t m3 = 3 * n;
   int st;
   double *F = static_cast<double *>(workspace(ctx, WS_FORCE, nb, &st));
@@ -218,7 +219,8 @@ extern "C" int sab_step(rpb_ctx *ctx, const rpb_params *p, const rpb_sab_config 
   fill_torque<<<nblk(n), 256, 0, stream>>>(n, cfg->torque[0], cfg->torque[1], cfg->torque[2], T);
   RPB_LAUNCHED(ctx);
   Packed geo;
-  RPB_TRY(pack_geometry(ctx, p, n, state->pos, WS_GEOM, &geo, stream));
+  RPB_TRY(pack_checked(ctx, p, n, state->pos, WS_GEOM, &geo, check, nullptr, nullptr, nullptr,
+                       stream));
   // M F + M_C T, the first Lanczos product M W and, for the one-sided RFD in the step's own
   // precision, its product M W~ at q share the configuration: one launch evaluates each pair's
   // coefficients once for all of them.  In mixed precision that launch takes one workgroup per
@@ -228,19 +230,19 @@ extern "C" int sab_step(rpb_ctx *ctx, const rpb_params *p, const rpb_sab_config 
   const int64_t kJointMinN = p->precision == RPB_FP64 ? 0 : 4 * 256;
   double *mw = nullptr, *mwt = nullptr;
   const bool one_sided = cfg->rfd_scheme == 1;
-  if (cfg->lanczos_precond == 0 && n > kJointMinN && matvec_first_supported(p, n)) {
+  auto products = [&]() -> int {
+    if (cfg->lanczos_precond != 0 || n <= kJointMinN || !matvec_first_supported(p, n))
+      return matvec_packed(ctx, p, geo, F, T, 0, n, u, stream);
     mw = static_cast<double *>(workspace(ctx, WS_VEC_B, nb, &st));
     if (!mw) return st;
     if (one_sided && cfg->rfd_precision == p->precision) {
       mwt = static_cast<double *>(workspace(ctx, WS_VEC_E, nb, &st));   // rfd_run's q- product
       if (!mwt) return st;
     }
-    RPB_TRY(matvec_first(ctx, p, geo, F, T, W, mwt ? Wt : nullptr, u, mw, mwt, stream));
-  } else {
-    RPB_TRY(matvec_packed(ctx, p, geo, F, T, 0, n, u, stream));
-  }
-
-  RPB_TRY(check_finite_end(ctx));
+    return matvec_first(ctx, p, geo, F, T, W, mwt ? Wt : nullptr, u, mw, mwt, stream);
+  };
+  const int prod = products();
+  RPB_TRY(check_end(ctx, check, stream, prod));
 
   // Brownian increment (the last iterate is used if the tolerance is not met)
   int iters = 0;
