@@ -2294,7 +2294,7 @@ int lanczos_entry(rpb_ctx *ctx, const rpb_params *p, int64_t n, const double *po
   Check check;
   RPB_TRY(check_begin(ctx, &check, stream));
   Packed g;
-  RPB_TRY(pack_checked(ctx, p, n, pos, WS_GEOM, &g, check, nullptr, nullptr, nullptr, stream));
+  RPB_TRY(pack_checked(ctx, p, n, pos, WS_GEOM, &g, check, nullptr, Torque{}, nullptr, stream));
   RPB_TRY(check_end(ctx, check, stream));
   const int lz =
       lanczos_run(ctx, p, g, w, tol, max_iter, precond, out, iters_out, eps_out, stream);

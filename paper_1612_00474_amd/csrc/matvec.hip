@@ -32,49 +32,6 @@ namespace rpb {
 
 namespace {
 
-// Sphere i into the packed geometry, in units of a; returns H.  With a wall: z~ = max(z, a) and H =
-// clamp(z/a, 0, 1) (App. A); in free space: z~ = z, H = 1.
-__device__ __forceinline__ double pack_sphere(int64_t n, int64_t i, double px, double py,
-                                              double pz, double a, int wall,
-                                              double *__restrict__ out) {
-  const double z = pz / a, h = wall ? fmin(fmax(z, 0.0), 1.0) : 1.0;
-  out[i] = px / a;
-  out[n + i] = py / a;
-  out[2 * n + i] = wall ? fmax(z, 1.0) : z;
-  out[3 * n + i] = h;
-  return h;
-}
-
-__device__ __forceinline__ double pack_sphere(int64_t n, int64_t i, double px, double py,
-                                              double pz, double a, int wall,
-                                              double *__restrict__ hout, float *__restrict__ f) {
-  const double x = px / a, y = py / a, z = pz / a;
-  const double h = wall ? fmin(fmax(z, 0.0), 1.0) : 1.0;
-  const float xh = float(x), yh = float(y);
-  f[i] = xh;
-  f[n + i] = float(x - double(xh));
-  f[2 * n + i] = yh;
-  f[3 * n + i] = float(y - double(yh));
-  f[4 * n + i] = float(wall ? fmax(z, 1.0) : z);
-  hout[i] = h;
-  return h;
-}
-
-// Counts the workgroup in for a check (`bad`: on this thread; every thread calls this).  Relaxed
-// atomics do: the word carries the verdict itself.
-__device__ __forceinline__ void check_report(const Check &c, int bad) {
-  bad = __syncthreads_or(bad);
-  if (threadIdx.x != 0) return;
-  const unsigned long long add = 1ull + (bad ? 1ull << 32 : 0ull);
-  const unsigned long long now =
-      __hip_atomic_fetch_add(&c.w->count, add, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + add;
-  if ((now & 0xffffffffull) != gridDim.x) return;
-  const int any = (now >> 32) != 0;
-  __hip_atomic_store(&c.w->count, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  c.w->bad = any;
-  __hip_atomic_store(c.host, 2 * c.tag + any, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-}
-
 // Packed geometry of positions and, with src, the packed sources (as pack_vectors), with the
 // finite check of the positions when c.w is set.  One launch where three did this (clear, check,
 // copy of the flag, and a synchronisation, before the two packings), bound by its launch: a product
@@ -82,8 +39,7 @@ __device__ __forceinline__ void check_report(const Check &c, int bad) {
 template <typename Real>
 __global__ void pack_all(int64_t n, const double *__restrict__ pos, double a, int wall,
                          double *__restrict__ geom, const double *__restrict__ force,
-                         const double *__restrict__ torque, double inv_a, Real *__restrict__ src,
-                         Check c) {
+                         Torque torque, double inv_a, Real *__restrict__ src, Check c) {
   const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   int bad = 0;
   if (i < n) {
@@ -97,10 +53,41 @@ __global__ void pack_all(int64_t n, const double *__restrict__ pos, double a, in
     if (src)
       for (int q = 0; q < 3; ++q) {
         src[q * n + i] = force ? Real(w * force[3 * i + q]) : Real(0);
-        if (torque) src[(3 + q) * n + i] = Real(w * inv_a * torque[3 * i + q]);
+        if (torque.on) src[(3 + q) * n + i] = Real(w * inv_a * torque.at(i, q));
       }
   }
   if (c.w) check_report(c, bad);
+}
+
+// q + s w, the product rounded before the sum (no fused multiply-add): the shifted positions carry
+// the rounding of the difference as it is written, which the drift divides by delta.
+__device__ __forceinline__ double shifted(double q, double s, double w) {
+#pragma clang fp contract(off)
+  return q + s * w;
+}
+
+// Both configurations of a random finite difference, q + sp w and (with geom_m) q - sm w, packed
+// with their force sources w: one launch instead of five, bound by its launch on small systems.
+template <typename Real>
+__global__ void pack_shifted(int64_t n, const double *__restrict__ pos,
+                             const double *__restrict__ w, double sp, double sm, double a, int wall,
+                             double *__restrict__ geom_p, Real *__restrict__ src_p,
+                             double *__restrict__ geom_m, Real *__restrict__ src_m) {
+  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  const double q[3] = {pos[3 * i], pos[3 * i + 1], pos[3 * i + 2]};
+  const double v[3] = {w[3 * i], w[3 * i + 1], w[3 * i + 2]};
+  auto put = [&](double s, double *geom, Real *src) {
+    const double x = shifted(q[0], s, v[0]), y = shifted(q[1], s, v[1]), z = shifted(q[2], s, v[2]);
+    double h;
+    if constexpr (std::is_same<Real, double>::value)
+      h = pack_sphere(n, i, x, y, z, a, wall, geom);
+    else
+      h = pack_sphere(n, i, x, y, z, a, wall, geom, reinterpret_cast<float *>(geom + n));
+    for (int d = 0; d < 3; ++d) src[d * n + i] = Real(h * v[d]);
+  };
+  put(sp, geom_p, src_p);
+  if (geom_m) put(-sm, geom_m, src_m);
 }
 
 // Source vectors, H-weighted, structure of arrays: [fx | fy | fz | tx | ty | tz] (n each); the
@@ -937,15 +924,29 @@ __global__ __launch_bounds__(kBlock) void pair_kernel_mixed_sym(SymArgs a, PartM
                                              int64_t(blockIdx.x) % a.nsplit, L, col);
 }
 
+// The second product of a launch of two (blockIdx.y = 1): its own configuration, sources,
+// partials and result.
+struct SecondD {
+  GeomD g;
+  const double *src;
+  double *partial;
+  const double *h;
+  double *vel;
+};
+
 // Float64 forces with the expanded coefficients, for the drift of mixed-precision steps only (see
 // expanded_drift); every other float64 whole-system product takes pair_kernel_f64_tiles.
 template <int TPT, bool WALL, bool PERIODIC>
-__global__ __launch_bounds__(kBlock) void pair_kernel_f64_expanded(SymArgs a, PartMap pm, GeomD g,
-                                                                   const double *__restrict__ src,
-                                                                   PairConsts<double> k_arg,
-                                                                   double *__restrict__ partial) {
+__global__ __launch_bounds__(kBlock) void pair_kernel_f64_expanded(
+    SymArgs a, PartMap pm, GeomD g, const double *__restrict__ src, PairConsts<double> k_arg,
+    double *__restrict__ partial, SecondD second) {
   const PairConsts<double> k = vgpr_consts(k_arg);
   if (a.skip && *a.skip) return;
+  if (blockIdx.y) {
+    g = second.g;
+    src = second.src;
+    partial = second.partial;
+  }
   __shared__ LdsD<false> L;
   __shared__ double col[kWaves][kBlock][3];
   int64_t I, J;
@@ -953,6 +954,28 @@ __global__ __launch_bounds__(kBlock) void pair_kernel_f64_expanded(SymArgs a, Pa
   tri_decode(Lp, a.nt, I, J);
   sym_tile_pair<TPT, false, WALL, PERIODIC, SymCoefExpanded>(
       a, g, src, k, partial, pm, Lp, I, J, int64_t(blockIdx.x) % a.nsplit, L, col);
+}
+
+// pair_kernel_f64_tiles over two products: one alone leaves a small system's launch short of
+// workgroups, and every launch of a small system costs more than its work (about 4 us).  With the
+// packing of both configurations in one launch and the difference taken by its consumer, a step
+// of 2,100 spheres went from 521 to 496 us, of 256 from 567 to 557.
+template <int TPT, int WT, int W, bool WALL, bool PERIODIC>
+__global__ __launch_bounds__(64 * W) void pair_kernel_f64_two(SymArgs a, PartMap pm, GeomD g,
+                                                              const double *__restrict__ src,
+                                                              PairConsts<double> k,
+                                                              double *__restrict__ partial,
+                                                              SecondD second) {
+  if (blockIdx.y) {
+    g = second.g;
+    src = second.src;
+    partial = second.partial;
+  }
+  __shared__ Sym64Lds<1, false, TPT, WT, W> L;
+  int64_t I, J;
+  const int64_t Lp = pm.L0 + int64_t(blockIdx.x);
+  tri_decode(Lp, a.nt, I, J);
+  sym64_tile_pair<1, false, TPT, WT, W, WALL, PERIODIC>(a, g, src, k, partial, pm, Lp, I, J, L);
 }
 
 // kRedGroups threads per (component, row), 64 rows per workgroup (one wavefront per group):
@@ -964,9 +987,16 @@ template <typename Part>
 __global__ __launch_bounds__(64 * kRedGroups) void reduce_sym_chunk(
     SymArgs a, PartMap pm, int64_t L1, int first, int last, const Part *__restrict__ partial,
     const double *__restrict__ h, double scale, double *__restrict__ vel,
-    const double *__restrict__ dotv, double *__restrict__ dpart) {
+    const double *__restrict__ dotv, double *__restrict__ dpart, SecondD second) {
   __shared__ double sh[kRedGroups * 64];
   if (a.skip && *a.skip) return;
+  if constexpr (std::is_same<Part, double>::value) {
+    if (blockIdx.y) {
+      partial = second.partial;
+      h = second.h;
+      vel = second.vel;
+    }
+  }
   const int lane = threadIdx.x & 63, grp = threadIdx.x >> 6;
   const int64_t e = int64_t(blockIdx.x) * 64 + lane;
   const bool live = e < 3 * a.n;
@@ -1368,6 +1398,15 @@ int check_end(rpb_ctx *ctx, const Check &c, hipStream_t stream, const char *what
   return RPB_OK;
 }
 
+int check_end(rpb_ctx *ctx, const Check &c, hipStream_t stream, int st) {
+  if (st == RPB_OK) return check_end(ctx, c, stream);
+  if (hipStreamSynchronize(stream) != hipSuccess) return st;
+  const int word = __atomic_load_n(reinterpret_cast<const int *>(
+                                       static_cast<char *>(host_scratch(ctx)) + kHostCheckOffset),
+                                   __ATOMIC_ACQUIRE);
+  return word == 2 * c.tag + 1 ? check_end(ctx, c, stream) : st;
+}
+
 namespace {
 
 int scan_finite(rpb_ctx *ctx, const double *v, int64_t m, hipStream_t stream, Check *c) {
@@ -1399,8 +1438,9 @@ int check_output(rpb_ctx *ctx, const double *v, int64_t m, hipStream_t stream, c
 namespace {
 
 int pack_into(rpb_ctx *ctx, const rpb_params *p, int64_t n, const double *pos, void *buf,
-              Packed *out, const Check &check, const double *force, const double *torque,
+              Packed *out, const Check &check, const double *force, const Torque &torque,
               void *src, hipStream_t stream) {
+  *out = Packed{};
   out->n = n;
   out->a = p->a;
   out->precision = p->precision;
@@ -1430,11 +1470,11 @@ int pack_geometry(rpb_ctx *ctx, const rpb_params *p, int64_t n, const double *po
 
 int pack_geometry_into(rpb_ctx *ctx, const rpb_params *p, int64_t n, const double *pos,
                        void *buf, Packed *out, hipStream_t stream) {
-  return pack_into(ctx, p, n, pos, buf, out, Check{}, nullptr, nullptr, nullptr, stream);
+  return pack_into(ctx, p, n, pos, buf, out, Check{}, nullptr, Torque{}, nullptr, stream);
 }
 
 int pack_checked(rpb_ctx *ctx, const rpb_params *p, int64_t n, const double *pos, Slot slot,
-                 Packed *out, const Check &check, const double *force, const double *torque,
+                 Packed *out, const Check &check, const double *force, const Torque &torque,
                  void *src, hipStream_t stream) {
   int st;
   void *buf = workspace(ctx, slot, geom_bytes(n, p->precision), &st);
@@ -1561,9 +1601,13 @@ void with_tile(TileShape t, Fn &&fn) {
 // 150,000 spheres in mixed precision at 2 targets per lane and 75,000 in float64), each
 // chunk's pair kernel followed by its reduction into vel, so the workspace stays bounded
 // whatever n.  The timing record spans the pair kernels of all chunks.
+// With g2 (float64 forces) a second configuration's product of src2 into vel2 runs in the same
+// launches if the partials of both fit one chunk; *both says whether it did.
 int matvec_symmetric(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const void *src,
                      bool torque, const double *h, int tpt, double *vel, hipStream_t stream,
-                     const int *skip, bool expanded, DotOut *dot = nullptr) {
+                     const int *skip, bool expanded, DotOut *dot = nullptr,
+                     const Packed *g2 = nullptr, const void *src2 = nullptr,
+                     double *vel2 = nullptr, bool *both = nullptr) {
   const int64_t n = g.n;
   const bool f64 = g.precision == RPB_FP64;
   const double *dotv = dot ? dot->v : nullptr;
@@ -1578,23 +1622,45 @@ int matvec_symmetric(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const v
   const int64_t pairs = a.nt * (a.nt + 1) / 2;
   const size_t esz = f64 ? sizeof(double) : sizeof(float);
   const int64_t per = chunk_pairs(pairs, a.nsplit, 1, a.ts, esz, ctx->chunk_bytes);
+  const size_t pbytes = size_t(part_elems(per, a.nsplit, 1, a.ts)) * esz;
+  const bool two = g2 && per == pairs && 2 * pbytes <= ctx->chunk_bytes;
+  if (both) *both = two;
   int st;
-  void *part = workspace(ctx, WS_PART, size_t(part_elems(per, a.nsplit, 1, a.ts)) * esz, &st);
+  void *part = workspace(ctx, WS_PART, two ? 2 * pbytes : pbytes, &st);
   if (!part) return st;
+  SecondD second{};
+  if (two)
+    second = SecondD{geom_d(*g2), static_cast<const double *>(src2),
+                     reinterpret_cast<double *>(static_cast<char *>(part) + pbytes),
+                     geom_d(*g2).h, vel2};
+  const unsigned sets = two ? 2 : 1;
   const double scale = 1.0 / (8.0 * M_PI * p->eta * p->a);
   hipEvent_t t0;
   RPB_TRY(timing_begin(ctx, stream, &t0));
   for (int64_t L0 = 0; L0 < pairs; L0 += per) {
     const int64_t L1 = std::min(pairs, L0 + per);
     const PartMap pm{L0, a.nsplit, a.ts, 1, tiles ? 1 : 0};
-    const unsigned grid = unsigned((L1 - L0) * a.nsplit);
+    const dim3 grid{unsigned((L1 - L0) * a.nsplit), sets, 1u};
     if (f64 && !tiles)
       with_sym_variant(false, tpt, p->wall != 0, periodic(p), [&](auto, auto P, auto W, auto B) {
         constexpr bool kW = decltype(W)::value, kB = decltype(B)::value;
         constexpr int kP = decltype(P)::value;
         pair_kernel_f64_expanded<kP, kW, kB><<<grid, kBlock, 0, stream>>>(
             a, pm, geom_d(g), static_cast<const double *>(src),
-            make_pair_consts<double>(p->lx / p->a, p->ly / p->a), static_cast<double *>(part));
+            make_pair_consts<double>(p->lx / p->a, p->ly / p->a), static_cast<double *>(part),
+            second);
+      });
+    else if (two)
+      with_variant(false, 1, p->wall != 0, periodic(p), [&](auto, auto, auto W, auto B) {
+        constexpr bool kW = decltype(W)::value, kB = decltype(B)::value;
+        with_tile(tile, [&](auto P, auto Q, auto N) {
+          constexpr int kP = decltype(P)::value, kQ = decltype(Q)::value;
+          constexpr int kN = decltype(N)::value;
+          pair_kernel_f64_two<kP, kQ, kN, kW, kB><<<grid, 64 * kN, 0, stream>>>(
+              a, pm, geom_d(g), static_cast<const double *>(src),
+              make_pair_consts<double>(p->lx / p->a, p->ly / p->a), static_cast<double *>(part),
+              second);
+        });
       });
     else if (f64)
       with_variant(torque, 1, p->wall != 0, periodic(p), [&](auto T, auto, auto W, auto B) {
@@ -1617,15 +1683,18 @@ int matvec_symmetric(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const v
       });
     RPB_LAUNCHED(ctx);
     if (L1 == pairs)
-      RPB_TRY(timing_end(ctx, stream, t0, double(n) * double(n),
+      RPB_TRY(timing_end(ctx, stream, t0, sets * double(n) * double(n),
                          (f64 ? 0 : 2) + (torque ? 1 : 0)));
     const int first = L0 == 0, last = L1 == pairs;
+    const dim3 rgrid{blocks_for(3 * n, 64), sets, 1u};
     if (f64)
-      reduce_sym_chunk<double><<<blocks_for(3 * n, 64), 64 * kRedGroups, 0, stream>>>(
-          a, pm, L1, first, last, static_cast<const double *>(part), h, scale, vel, dotv, dpart);
+      reduce_sym_chunk<double><<<rgrid, 64 * kRedGroups, 0, stream>>>(
+          a, pm, L1, first, last, static_cast<const double *>(part), h, scale, vel, dotv, dpart,
+          second);
     else
-      reduce_sym_chunk<float><<<blocks_for(3 * n, 64), 64 * kRedGroups, 0, stream>>>(
-          a, pm, L1, first, last, static_cast<const float *>(part), h, scale, vel, dotv, dpart);
+      reduce_sym_chunk<float><<<rgrid, 64 * kRedGroups, 0, stream>>>(
+          a, pm, L1, first, last, static_cast<const float *>(part), h, scale, vel, dotv, dpart,
+          second);
     RPB_LAUNCHED(ctx);
   }
   return RPB_OK;
@@ -1673,6 +1742,49 @@ int matvec_sources(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const voi
 int matvec_prepacked(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const void *src,
                      double *vel, hipStream_t stream, const int *skip, DotOut *dot) {
   return matvec_sources(ctx, p, g, src, false, 0, g.n, vel, stream, skip, false, dot);
+}
+
+int matvec_shifted(rpb_ctx *ctx, const rpb_params *p, int64_t n, const double *pos,
+                   const double *w, double sp, double sm, bool minus, bool expanded, double *up,
+                   double *um, hipStream_t stream) {
+  const bool f64 = p->precision == RPB_FP64;
+  const size_t esz = f64 ? sizeof(double) : sizeof(float);
+  int st;
+  Packed g[2];
+  void *src[2];
+  for (int s = 0; s < 2; ++s) {
+    g[s].n = n;
+    g[s].a = p->a;
+    g[s].precision = p->precision;
+    if (s == 1 && !minus) break;
+    g[s].geom = workspace(ctx, s ? WS_GEOM2 : WS_GEOM, geom_bytes(n, p->precision), &st);
+    if (!g[s].geom) return st;
+  }
+  src[0] = source_buffer(ctx, g[0], &st);   // room for a force and a torque: here two forces
+  if (!src[0]) return st;
+  src[1] = static_cast<char *>(src[0]) + size_t(3 * n) * esz;
+  auto pack = [&](auto real) {
+    using Real = decltype(real);
+    pack_shifted<Real><<<blocks_for(n, 256), 256, 0, stream>>>(
+        n, pos, w, sp, sm, p->a, p->wall, static_cast<double *>(g[0].geom),
+        static_cast<Real *>(src[0]), minus ? static_cast<double *>(g[1].geom) : nullptr,
+        static_cast<Real *>(src[1]));
+  };
+  if (f64)
+    pack(double{});
+  else
+    pack(float{});
+  RPB_LAUNCHED(ctx);
+  bool both = false;
+  const Shape &shape = ctx->tune.s[f64 ? RPB_FP64 : RPB_MIXED];
+  if (f64 && minus && shape.symmetric)
+    RPB_TRY(matvec_symmetric(ctx, p, g[0], src[0], false, packed_weights(g[0]), shape.tpt, up,
+                             stream, nullptr, expanded, nullptr, &g[1], src[1], um, &both));
+  else
+    RPB_TRY(matvec_sources(ctx, p, g[0], src[0], false, 0, n, up, stream, nullptr, expanded));
+  if (minus && !both)
+    RPB_TRY(matvec_sources(ctx, p, g[1], src[1], false, 0, n, um, stream, nullptr, expanded));
+  return RPB_OK;
 }
 
 int matvec_packed(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const double *force,
@@ -2028,7 +2140,7 @@ int matvec_entry(rpb_ctx *ctx, const rpb_params *p, int64_t n, const double *pos
   int st;
   void *src = source_buffer(ctx, g, &st);
   if (!src) return st;
-  RPB_TRY(pack_checked(ctx, p, n, pos, WS_GEOM, &g, check, force, torque, src, stream));
+  RPB_TRY(pack_checked(ctx, p, n, pos, WS_GEOM, &g, check, force, Torque::of(torque), src, stream));
   // the product leaves vel alone when the check fails, and the host reads the verdict while it runs
   st = matvec_sources(ctx, p, g, src, torque != nullptr, row0, row1 - row0, vel, stream,
                       check_skip(check));

@@ -11,10 +11,11 @@
 // Layout: the symmetric tile-pair scheme of the single-vector product, one target per lane, K = 1
 // to 4 vectors per launch, the first optionally with a torque:
 //   pack_multi    O(N K)    AoS float64 vectors -> SoA H-weighted sources src[(k 3 + c) n + i]
-//   pair kernel   O(N^2)    float64: pair_kernel_f64_tiles (sym64.h).  Mixed: tile pair (I, J), I <= J, per workgroup: M_IJ F_J into the rows of
-//                           I (lane sums), M_JI F_I into the rows of J (rotating per-source sums
-//                           added across the workgroup's wavefronts in LDS); diagonal tiles as
-//                           ordered pairs.  Each pair's coefficients are computed once.  Batches
+//   pair kernel   O(N^2)    float64: pair_kernel_f64_tiles (sym64.h).  Mixed: tile pair (I, J),
+//                           I <= J, per workgroup: M_IJ F_J into the rows of I (lane sums),
+//                           M_JI F_I into the rows of J (rotating per-source sums added across
+//                           the workgroup's wavefronts in LDS); diagonal tiles as ordered
+//                           pairs.  Each pair's coefficients are computed once.  Batches
 //                           of systems: persistent workgroups map a work-item number to
 //                           (system, I, J).
 //   reduce_multi  O(N^2/tile) fixed-order sum of the tile partials, times H_i / (8 pi eta a).
@@ -73,6 +74,38 @@ __global__ void pack_multi(int64_t n, SrcPtrs<K> in, const double *__restrict__ 
 #pragma unroll
     for (int c = 0; c < 3; ++c) out[(3 * K + c) * n + i] = Real(w * inv_a * torque[3 * i + c]);
 }
+
+// The same with the geometry packing and the check of the positions: a step's first products.
+template <int K, typename Real>
+__global__ void pack_first(int64_t n, SrcPtrs<K> in, const double *__restrict__ pos, double a,
+                           int wall, double *__restrict__ geom, Torque torque, double inv_a,
+                           Real *__restrict__ out, Check check) {
+  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  int bad = 0;
+  if (i < n) {
+    const double x = pos[3 * i], y = pos[3 * i + 1], z = pos[3 * i + 2];
+    bad = !isfinite(x) || !isfinite(y) || !isfinite(z);
+    double w;
+    if constexpr (std::is_same<Real, double>::value)
+      w = pack_sphere(n, i, x, y, z, a, wall, geom);
+    else
+      w = pack_sphere(n, i, x, y, z, a, wall, geom, reinterpret_cast<float *>(geom + n));
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) out[(k * 3 + c) * n + i] = Real(w * in.p[k][3 * i + c]);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) out[(3 * K + c) * n + i] = Real(w * inv_a * torque.at(i, c));
+  }
+  check_report(check, bad);
+}
+
+// Arguments of pack_first beyond the vectors.
+struct FirstPack {
+  const double *pos;
+  Torque torque;
+  Check check;
+};
 
 template <int K, bool TQ>
 struct MultiLdsF {
@@ -289,14 +322,13 @@ __global__ __launch_bounds__(64 * kRedGroups) void reduce_multi(
 // (tiles of 256 on every size before: 110 us at 1,100; one to three vectors cross alike).
 inline int multi_wt(int64_t n) { return n < 7000 ? 1 : n < 28000 ? 2 : 4; }
 
-// One product of K vectors: sources in.p[k] (slot 0 with torque `torque` when TQ), results to
-// out.p[k].  The triangle of tile pairs is walked in chunks whose partials fit the context's
-// limit,
-// each chunk's pair kernel followed by its reduction into the results, so the workspace stays
+// One product of K vectors: sources in.p[k], results to out.p[k].  With TQ the geometry is packed
+// along, from first_pack, whose torque goes with slot 0.  The triangle of tile pairs is walked in chunks whose partials fit the context's
+// limit, each chunk's pair kernel followed by its reduction into the results, so the workspace stays
 // bounded whatever n.  The timing record spans the pair kernels of all chunks.
 template <int K, bool TQ>
 int multi_launch(rpb_ctx *ctx, const rpb_params *p, const Packed &g, SrcPtrs<K> in,
-                 const double *torque, OutPtrs<K> out, hipStream_t stream,
+                 const FirstPack *first_pack, OutPtrs<K> out, hipStream_t stream,
                  const int *skip = nullptr) {
   const int64_t n = g.n;
   const bool f64 = g.precision == RPB_FP64;
@@ -315,13 +347,21 @@ int multi_launch(rpb_ctx *ctx, const rpb_params *p, const Packed &g, SrcPtrs<K> 
   const double *h = f64 ? geom_d(g).h : geom_f(g).h;
   int used = 0;
   for (int s = 0; s < K; ++s) used += in.p[s] != nullptr || (s == 0 && TQ);
-  const double *tq = TQ ? torque : nullptr;
+  const unsigned pgrid = blocks_for(n, 256);
+  auto pack = [&](auto real) {
+    using Real = decltype(real);
+    if constexpr (TQ)
+      pack_first<K, Real><<<pgrid, 256, 0, stream>>>(
+          n, in, first_pack->pos, g.a, p->wall, static_cast<double *>(g.geom), first_pack->torque,
+          1.0 / g.a, static_cast<Real *>(src), first_pack->check);
+    else
+      pack_multi<K, Real><<<pgrid, 256, 0, stream>>>(n, in, h, nullptr, 1.0 / g.a,
+                                                    static_cast<Real *>(src));
+  };
   if (f64)
-    pack_multi<K, double><<<blocks_for(n, 256), 256, 0, stream>>>(n, in, h, tq, 1.0 / g.a,
-                                                                 static_cast<double *>(src));
+    pack(double{});
   else
-    pack_multi<K, float><<<blocks_for(n, 256), 256, 0, stream>>>(n, in, h, tq, 1.0 / g.a,
-                                                                static_cast<float *>(src));
+    pack(float{});
   RPB_LAUNCHED(ctx);
   const double scale = 1.0 / (8.0 * M_PI * p->eta * p->a);
   hipEvent_t t0;
@@ -579,21 +619,28 @@ int matvec_multi(rpb_ctx *ctx, const rpb_params *p, const Packed &g, int nvec, c
 
 bool matvec_first_supported(const rpb_params *p, int64_t n) { return p->lx <= 0.0 && n > 0; }
 
-int matvec_first(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const double *force,
-                 const double *torque, const double *w, const double *w3, double *u_force,
-                 double *u_w, double *u_w3, hipStream_t stream) {
-  if (!matvec_first_supported(p, g.n))
+int matvec_first(rpb_ctx *ctx, const rpb_params *p, int64_t n, const double *pos,
+                 const Check &check, Packed *g, const double *force, const Torque &torque,
+                 const double *w, const double *w3, double *u_force, double *u_w, double *u_w3,
+                 hipStream_t stream) {
+  if (!matvec_first_supported(p, n))
     return fail(ctx, RPB_EINVAL, "joint product not available for this configuration");
+  int st;
+  *g = Packed{};
+  g->n = n;
+  g->a = p->a;
+  g->precision = p->precision;
+  g->geom = workspace(ctx, WS_GEOM, packed_geometry_bytes(n, p->precision), &st);
+  if (!g->geom) return st;
+  const FirstPack fp{pos, torque, check};
   if (w3) {
     const SrcPtrs<3> in{{force, w, w3}};
     const OutPtrs<3> out{{u_force, u_w, u_w3}};
-    if (torque) return multi_launch<3, true>(ctx, p, g, in, torque, out, stream);
-    return multi_launch<3, false>(ctx, p, g, in, nullptr, out, stream);
+    return multi_launch<3, true>(ctx, p, *g, in, &fp, out, stream);
   }
   const SrcPtrs<2> in{{force, w}};
   const OutPtrs<2> out{{u_force, u_w}};
-  if (torque) return multi_launch<2, true>(ctx, p, g, in, torque, out, stream);
-  return multi_launch<2, false>(ctx, p, g, in, nullptr, out, stream);
+  return multi_launch<2, true>(ctx, p, *g, in, &fp, out, stream);
 }
 
 bool matvec_first_batched_supported(const rpb_params *p, const Batch &bt) {
@@ -713,7 +760,7 @@ extern "C" int rpb_mobility_matvec_multi(rpb_ctx *ctx, const rpb_params *p, int6
   Check check;
   RPB_TRY(check_begin(ctx, &check, stream));
   Packed g;
-  RPB_TRY(pack_checked(ctx, p, n, pos, WS_GEOM, &g, check, nullptr, nullptr, nullptr, stream));
+  RPB_TRY(pack_checked(ctx, p, n, pos, WS_GEOM, &g, check, nullptr, Torque{}, nullptr, stream));
   const int st = matvec_multi(ctx, p, g, nvec, nullptr, force, vel, stream, nullptr,
                               check_skip(check));
   return check_end(ctx, check, stream, st);

@@ -21,6 +21,49 @@ struct GeomF {         // mixed geometry: float32 hi/lo x, y, float32 z~, float6
   const double *h;
 };
 
+// Sphere i into the packed geometry, in units of a; returns H.  With a wall: z~ = max(z, a) and H =
+// clamp(z/a, 0, 1) (App. A); in free space: z~ = z, H = 1.
+__device__ __forceinline__ double pack_sphere(int64_t n, int64_t i, double px, double py,
+                                              double pz, double a, int wall,
+                                              double *__restrict__ out) {
+  const double z = pz / a, h = wall ? fmin(fmax(z, 0.0), 1.0) : 1.0;
+  out[i] = px / a;
+  out[n + i] = py / a;
+  out[2 * n + i] = wall ? fmax(z, 1.0) : z;
+  out[3 * n + i] = h;
+  return h;
+}
+
+__device__ __forceinline__ double pack_sphere(int64_t n, int64_t i, double px, double py,
+                                              double pz, double a, int wall,
+                                              double *__restrict__ hout, float *__restrict__ f) {
+  const double x = px / a, y = py / a, z = pz / a;
+  const double h = wall ? fmin(fmax(z, 0.0), 1.0) : 1.0;
+  const float xh = float(x), yh = float(y);
+  f[i] = xh;
+  f[n + i] = float(x - double(xh));
+  f[2 * n + i] = yh;
+  f[3 * n + i] = float(y - double(yh));
+  f[4 * n + i] = float(wall ? fmax(z, 1.0) : z);
+  hout[i] = h;
+  return h;
+}
+
+// Counts the workgroup in for a check (`bad`: on this thread; every thread calls this).  Relaxed
+// atomics do: the word carries the verdict itself.
+__device__ __forceinline__ void check_report(const Check &c, int bad) {
+  bad = __syncthreads_or(bad);
+  if (threadIdx.x != 0) return;
+  const unsigned long long add = 1ull + (bad ? 1ull << 32 : 0ull);
+  const unsigned long long now =
+      __hip_atomic_fetch_add(&c.w->count, add, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + add;
+  if ((now & 0xffffffffull) != gridDim.x) return;
+  const int any = (now >> 32) != 0;
+  __hip_atomic_store(&c.w->count, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  c.w->bad = any;
+  __hip_atomic_store(c.host, 2 * c.tag + any, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 inline GeomD geom_d(const Packed &g) {
   const double *b = static_cast<const double *>(g.geom);
   return {b, b + g.n, b + 2 * g.n, b + 3 * g.n};

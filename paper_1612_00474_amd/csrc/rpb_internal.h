@@ -195,11 +195,9 @@ const int *check_skip(const Check &c);
 // if a value was NaN or Inf.  Work enqueued in between may see those values, so it must not index
 // memory by them, and must write only workspace or read check_skip.
 int check_end(rpb_ctx *ctx, const Check &c, hipStream_t stream, const char *what = "positions");
-// check_end after work enqueued in between returned `st`: the verdict comes first.
-inline int check_end(rpb_ctx *ctx, const Check &c, hipStream_t stream, int st) {
-  const int verdict = check_end(ctx, c, stream);
-  return verdict != RPB_OK ? verdict : st;
-}
+// check_end after work enqueued in between returned `st` (an error before or after the check's
+// own launch): the verdict, if there is one, comes first.
+int check_end(rpb_ctx *ctx, const Check &c, hipStream_t stream, int st);
 // The whole check at once: every position finite?
 int check_finite(rpb_ctx *ctx, const double *pos, int64_t n, hipStream_t stream);
 // With ctx->check_output set: scan m values at v for NaN / Inf on `stream`, synchronise, and
@@ -225,10 +223,29 @@ struct Packed {
 // Pack positions (clamp heights, weights H) into the geometry slot `slot`.
 int pack_geometry(rpb_ctx *ctx, const rpb_params *p, int64_t n, const double *pos, Slot slot,
                   Packed *out, hipStream_t stream);
+// A product's torques: none, [n][3] at p, or the same c on every sphere.
+struct Torque {
+  bool on = false;
+  const double *p = nullptr;
+  double c[3] = {0.0, 0.0, 0.0};
+  static Torque of(const double *p) {
+    Torque t;
+    t.on = p != nullptr;
+    t.p = p;
+    return t;
+  }
+  static Torque constant(const double *c) {
+    Torque t;
+    t.on = true;
+    for (int q = 0; q < 3; ++q) t.c[q] = c[q];
+    return t;
+  }
+  __host__ __device__ double at(int64_t i, int q) const { return p ? p[3 * i + q] : c[q]; }
+};
 // The same in one launch with the check of the positions and, with src (the layout of
-// source_buffer), the packing of force and torque (nullable, not both).
+// source_buffer), the packing of force (nullable with a torque) and torque.
 int pack_checked(rpb_ctx *ctx, const rpb_params *p, int64_t n, const double *pos, Slot slot,
-                 Packed *out, const Check &check, const double *force, const double *torque,
+                 Packed *out, const Check &check, const double *force, const Torque &torque,
                  void *src, hipStream_t stream);
 
 // The same packing into a caller-provided buffer of packed_geometry_bytes(n, precision).
@@ -287,6 +304,12 @@ struct DotOut {
 int matvec_sources(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const void *src, bool has_t,
                    int64_t row0, int64_t nrows, double *vel, hipStream_t stream,
                    const int *skip = nullptr, bool expanded = false, DotOut *dot = nullptr);
+// up = M(pos + sp w) w and, with `minus`, um = M(pos - sm w) w: the products of a random finite
+// difference, in p->precision, without a position check.  Float64 products of a system whose
+// partials fit twice run in one launch.  Overwrites WS_GEOM and WS_GEOM2.
+int matvec_shifted(rpb_ctx *ctx, const rpb_params *p, int64_t n, const double *pos,
+                   const double *w, double sp, double sm, bool minus, bool expanded, double *up,
+                   double *um, hipStream_t stream);
 // U = M F for the whole system from force sources already written into `src` (rows 0..2 of
 // source_buffer's layout; no torque), as matvec_packed would form them.
 int matvec_prepacked(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const void *src,
@@ -347,13 +370,13 @@ int matvec_multi(rpb_ctx *ctx, const rpb_params *p, const Packed &g, int nvec, c
                  const double *force, double *vel, hipStream_t stream, DotOut *dot = nullptr,
                  const int *skip = nullptr);
 // The products of a step at its own configuration in one launch (the pair coefficients shared):
-// u_force = M force + M_C torque, u_w = M w and, when w3 is not NULL, u_w3 = M w3; torque
-// nullable.  Available when matvec_first_supported(p, n) (no box, partials within the
-// workspace limit).
+// u_force = M force + M_C torque, u_w = M w and, when w3 is not NULL, u_w3 = M w3.  Packs pos into
+// *g (WS_GEOM) on the way, under `check`.  Available when matvec_first_supported(p, n) (no box).
 bool matvec_first_supported(const rpb_params *p, int64_t n);
-int matvec_first(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const double *force,
-                 const double *torque, const double *w, const double *w3, double *u_force,
-                 double *u_w, double *u_w3, hipStream_t stream);
+int matvec_first(rpb_ctx *ctx, const rpb_params *p, int64_t n, const double *pos,
+                 const Check &check, Packed *g, const double *force, const Torque &torque,
+                 const double *w, const double *w3, double *u_force, double *u_w, double *u_w3,
+                 hipStream_t stream);
 
 // Batched form of matvec_first with two vectors (u_force = M force + M_C torque, u_w = M w per
 // system), one persistent launch; available when matvec_first_batched_supported(p, bt).
@@ -399,12 +422,20 @@ int lanczos_run(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const double
                 hipStream_t stream, const double *mw = nullptr);
 
 // ---- RFD / RNG / forces / step ----------------------------------------------------------
+// The drift scale (plus - minus) as its terms, in workspace (or `base`).
+struct RfdTerms {
+  const double *plus, *minus;
+  double scale;
+};
 // base (one-sided only, nullable): M(q) w~ already computed in rfd_precision by the caller.
+int rfd_terms(rpb_ctx *ctx, const rpb_params *p, int64_t n, const double *pos, const double *wt,
+              double delta, int rfd_precision, bool one_sided, hipStream_t stream,
+              const double *base, RfdTerms *out);
 int rfd_run(rpb_ctx *ctx, const rpb_params *p, int64_t n, const double *pos, const double *wt,
-            double delta, int rfd_precision, bool one_sided, double *drift, hipStream_t stream,
-            const double *base = nullptr);
+            double delta, int rfd_precision, bool one_sided, double *drift, hipStream_t stream);
+// out1 (nullable): the normals of stream_id + 1, in the same launch.
 int normals_run(rpb_ctx *ctx, int64_t count, uint64_t seed, uint64_t stream_id, uint64_t step,
-                double *out, hipStream_t stream);
+                double *out, hipStream_t stream, double *out1 = nullptr);
 int forces_run(rpb_ctx *ctx, const rpb_params *p, int64_t n, const double *pos, double f_grav_z,
                double u0, double b, double *force, hipStream_t stream);
 // Steric forces within each system of a batch (no interaction across systems).

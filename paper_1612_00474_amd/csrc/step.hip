@@ -28,13 +28,13 @@ __global__ void fill_torque(int64_t n, double tx, double ty, double tz, double *
 
 __global__ void combine_kernel(int64_t m, double *__restrict__ pos, double *__restrict__ u_prev,
                                const double *__restrict__ u, const double *__restrict__ g,
-                               const double *__restrict__ drift, double dt, double c0, double c1,
-                               double noise) {
+                               RfdTerms drift, double dt, double c0, double c1, double noise) {
   const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i >= m) return;
   const double ui = u[i];
   const double det = c1 != 0.0 ? c0 * ui - c1 * u_prev[i] : c0 * ui;
-  pos[i] = pos[i] + dt * det + noise * g[i] + dt * drift[i];
+  const double d = drift.scale * (drift.plus[i] - drift.minus[i]);
+  pos[i] = pos[i] + dt * det + noise * g[i] + dt * d;
   u_prev[i] = ui;
 }
 
@@ -188,39 +188,33 @@ extern "C" int sab_step(rpb_ctx *ctx, const rpb_params *p, const rpb_sab_config 
   int st;
   double *F = static_cast<double *>(workspace(ctx, WS_FORCE, nb, &st));
   if (!F) return st;
-  double *T = static_cast<double *>(workspace(ctx, WS_TORQUE, nb, &st));
-  if (!T) return st;
   double *u = static_cast<double *>(workspace(ctx, WS_VEC_F, nb, &st));
   if (!u) return st;
   double *g = static_cast<double *>(workspace(ctx, WS_VEC_G, nb, &st));
   if (!g) return st;
-  double *drift = static_cast<double *>(workspace(ctx, WS_VEC_H, nb, &st));
-  if (!drift) return st;
 
   // noise
   const double *W = w;
   const double *Wt = w_tilde;
+  double *made[2] = {nullptr, nullptr};
   if (!W) {
-    double *buf = static_cast<double *>(workspace(ctx, WS_NOISE_W, nb, &st));
-    if (!buf) return st;
-    RPB_TRY(normals_run(ctx, m3, cfg->seed, 0, uint64_t(state->step), buf, stream));
-    W = buf;
+    W = made[0] = static_cast<double *>(workspace(ctx, WS_NOISE_W, nb, &st));
+    if (!W) return st;
   }
   if (!Wt) {
-    double *buf = static_cast<double *>(workspace(ctx, WS_NOISE_WT, nb, &st));
-    if (!buf) return st;
-    RPB_TRY(normals_run(ctx, m3, cfg->seed, 1, uint64_t(state->step), buf, stream));
-    Wt = buf;
+    Wt = made[1] = static_cast<double *>(workspace(ctx, WS_NOISE_WT, nb, &st));
+    if (!Wt) return st;
   }
+  if (made[0])
+    RPB_TRY(normals_run(ctx, m3, cfg->seed, 0, uint64_t(state->step), made[0], stream, made[1]));
+  else if (made[1])
+    RPB_TRY(normals_run(ctx, m3, cfg->seed, 1, uint64_t(state->step), made[1], stream));
 
   // deterministic velocity
   RPB_TRY(forces_run(ctx, p, n, state->pos, cfg->f_grav_z, cfg->steric_u0, cfg->steric_b, F,
                      stream));
-  fill_torque<<<nblk(n), 256, 0, stream>>>(n, cfg->torque[0], cfg->torque[1], cfg->torque[2], T);
-  RPB_LAUNCHED(ctx);
+  const Torque T = Torque::constant(cfg->torque);
   Packed geo;
-  RPB_TRY(pack_checked(ctx, p, n, state->pos, WS_GEOM, &geo, check, nullptr, nullptr, nullptr,
-                       stream));
   // M F + M_C T, the first Lanczos product M W and, for the one-sided RFD in the step's own
   // precision, its product M W~ at q share the configuration: one launch evaluates each pair's
   // coefficients once for all of them.  In mixed precision that launch takes one workgroup per
@@ -231,15 +225,22 @@ extern "C" int sab_step(rpb_ctx *ctx, const rpb_params *p, const rpb_sab_config 
   double *mw = nullptr, *mwt = nullptr;
   const bool one_sided = cfg->rfd_scheme == 1;
   auto products = [&]() -> int {
-    if (cfg->lanczos_precond != 0 || n <= kJointMinN || !matvec_first_supported(p, n))
-      return matvec_packed(ctx, p, geo, F, T, 0, n, u, stream);
+    if (cfg->lanczos_precond != 0 || n <= kJointMinN || !matvec_first_supported(p, n)) {
+      geo.n = n;
+      geo.precision = p->precision;
+      void *src = source_buffer(ctx, geo, &st);
+      if (!src) return st;
+      RPB_TRY(pack_checked(ctx, p, n, state->pos, WS_GEOM, &geo, check, F, T, src, stream));
+      return matvec_sources(ctx, p, geo, src, true, 0, n, u, stream);
+    }
     mw = static_cast<double *>(workspace(ctx, WS_VEC_B, nb, &st));
     if (!mw) return st;
     if (one_sided && cfg->rfd_precision == p->precision) {
       mwt = static_cast<double *>(workspace(ctx, WS_VEC_E, nb, &st));   // rfd_run's q- product
       if (!mwt) return st;
     }
-    return matvec_first(ctx, p, geo, F, T, W, mwt ? Wt : nullptr, u, mw, mwt, stream);
+    return matvec_first(ctx, p, n, state->pos, check, &geo, F, T, W, mwt ? Wt : nullptr, u, mw, mwt,
+                        stream);
   };
   const int prod = products();
   RPB_TRY(check_end(ctx, check, stream, prod));
@@ -252,8 +253,9 @@ extern "C" int sab_step(rpb_ctx *ctx, const rpb_params *p, const rpb_sab_config 
   if (lz != RPB_OK && lz != RPB_ENOCONV) return lz;
 
   // stochastic drift
-  RPB_TRY(rfd_run(ctx, p, n, state->pos, Wt, cfg->delta, cfg->rfd_precision, one_sided, drift,
-                  stream, mwt));
+  RfdTerms drift;
+  RPB_TRY(rfd_terms(ctx, p, n, state->pos, Wt, cfg->delta, cfg->rfd_precision, one_sided, stream,
+                    mwt, &drift));
 
   const bool ab = cfg->scheme == 0 && state->have_prev;
   combine_kernel<<<nblk(m3), 256, 0, stream>>>(m3, state->pos, state->u_prev, u, g, drift,

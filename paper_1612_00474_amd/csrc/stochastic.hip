@@ -40,8 +40,13 @@ __device__ __forceinline__ double to_uniform(uint64_t w) {
   return (double(w >> 12) + 0.5) * 0x1p-52;
 }
 
+// blockIdx.y = 1: the next stream, into out1.
 __global__ void normals_kernel(int64_t count, uint64_t seed, uint64_t stream_id, uint64_t step,
-                               double *__restrict__ out) {
+                               double *__restrict__ out, double *__restrict__ out1) {
+  if (blockIdx.y) {
+    ++stream_id;
+    out = out1;
+  }
   const int64_t b = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (4 * b >= count) return;
   uint64_t x[4] = {uint64_t(b), step, 0ull, 0ull};
@@ -107,43 +112,39 @@ inline unsigned nblk(int64_t m) { return unsigned((m + 255) / 256); }
 }  // namespace
 
 int normals_run(rpb_ctx *ctx, int64_t count, uint64_t seed, uint64_t stream_id, uint64_t step,
-                double *out, hipStream_t stream) {
+                double *out, hipStream_t stream, double *out1) {
   if (count <= 0) return RPB_OK;
   const int64_t blocks = (count + 3) / 4;
-  normals_kernel<<<nblk(blocks), 256, 0, stream>>>(count, seed, stream_id, step, out);
+  normals_kernel<<<dim3{nblk(blocks), out1 ? 2u : 1u, 1u}, 256, 0, stream>>>(count, seed, stream_id,
+                                                                            step, out, out1);
   RPB_LAUNCHED(ctx);
   return RPB_OK;
 }
 
-int rfd_run(rpb_ctx *ctx, const rpb_params *p, int64_t n, const double *pos, const double *wt,
-            double delta, int rfd_precision, bool one_sided, double *drift, hipStream_t stream,
-            const double *base) {
-  const int64_t m = 3 * n;
-  const size_t vb = size_t(m) * sizeof(double);
+int rfd_terms(rpb_ctx *ctx, const rpb_params *p, int64_t n, const double *pos, const double *wt,
+              double delta, int rfd_precision, bool one_sided, hipStream_t stream,
+              const double *base, RfdTerms *out) {
+  const size_t vb = size_t(3 * n) * sizeof(double);
   int st;
-  double *qp = static_cast<double *>(workspace(ctx, WS_VEC_B, vb, &st));
-  if (!qp) return st;
-  double *qm = static_cast<double *>(workspace(ctx, WS_VEC_C, vb, &st));
-  if (!qm) return st;
   double *up = static_cast<double *>(workspace(ctx, WS_VEC_D, vb, &st));
   if (!up) return st;
   double *um = static_cast<double *>(workspace(ctx, WS_VEC_E, vb, &st));
   if (!um) return st;
-  shifted_pair<<<nblk(m), 256, 0, stream>>>(m, pos, wt, one_sided ? delta : 0.5 * delta,
-                                             one_sided ? 0.0 : 0.5 * delta, qp, qm);
-  RPB_LAUNCHED(ctx);
-  const bool ex = expanded_drift(p, rfd_precision);
+  const bool minus = !(one_sided && base);   // the product at q- (= q when one-sided)
   rpb_params q = *p;
   q.precision = rfd_precision;
-  Packed gp, gm;
-  RPB_TRY(pack_geometry(ctx, &q, n, qp, WS_GEOM, &gp, stream));
-  RPB_TRY(matvec_packed(ctx, &q, gp, wt, nullptr, 0, n, up, stream, nullptr, ex));
-  if (!(one_sided && base)) {   // the product at q- (= q when one-sided)
-    RPB_TRY(pack_geometry(ctx, &q, n, qm, WS_GEOM2, &gm, stream));
-    RPB_TRY(matvec_packed(ctx, &q, gm, wt, nullptr, 0, n, um, stream, nullptr, ex));
-    base = um;
-  }
-  scaled_difference<<<nblk(m), 256, 0, stream>>>(m, up, base, p->kT / delta, drift);
+  RPB_TRY(matvec_shifted(ctx, &q, n, pos, wt, one_sided ? delta : 0.5 * delta,
+                         one_sided ? 0.0 : 0.5 * delta, minus, expanded_drift(p, rfd_precision),
+                         up, um, stream));
+  *out = RfdTerms{up, minus ? um : base, p->kT / delta};
+  return RPB_OK;
+}
+
+int rfd_run(rpb_ctx *ctx, const rpb_params *p, int64_t n, const double *pos, const double *wt,
+            double delta, int rfd_precision, bool one_sided, double *drift, hipStream_t stream) {
+  RfdTerms t;
+  RPB_TRY(rfd_terms(ctx, p, n, pos, wt, delta, rfd_precision, one_sided, stream, nullptr, &t));
+  scaled_difference<<<nblk(3 * n), 256, 0, stream>>>(3 * n, t.plus, t.minus, t.scale, drift);
   RPB_LAUNCHED(ctx);
   return RPB_OK;
 }
