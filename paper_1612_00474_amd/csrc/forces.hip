@@ -5,11 +5,12 @@
 // the force is -grad U, magnitude U0/b or (U0/b) exp(-(r - d)/b), repulsive.  Gravity adds
 // f_g along z.  Pairs farther than d + 40 b are skipped (their force is below 4.3e-18 U0/b).
 // Float64 throughout, unclamped positions, minimum-image separations in a pseudo-periodic box
-// (App. B).  Two ways to find the pairs:
-//   * cell list (default): spheres binned into cubic cells of side >= d + 40 b, cells hashed
+// (App. B).  Three ways to find the pairs:
+//   * one wavefront per target over all sources (small systems): one launch;
+//   * cell list (larger systems and batches): spheres binned into cubic cells of side >= d + 40 b, cells hashed
 //     to buckets, buckets filled and then sorted by sphere index, each target visiting the 27
 //     neighbouring cells in a fixed order: O(N) work, deterministic sums;
-//   * all pairs over LDS tiles (a pseudo-periodic box with fewer than three cells per side):
+//   * all pairs over LDS tiles (a larger box with fewer than three cells per side):
 //     the sources split over workgroups and the chunk sums added in a fixed order.
 #include <algorithm>
 #include <cmath>
@@ -404,6 +405,57 @@ __global__ void steric_cells(int64_t n, const double *__restrict__ pos, CellArgs
   force[3 * i + 2] = fz;
 }
 
+// One wavefront per target over all sources, the lanes' sums added by a butterfly (a fixed order):
+// one launch for systems where the nine of the cell list cost more than the pairs.
+__global__ __launch_bounds__(kBlock) void steric_wave(int64_t n, const double *__restrict__ pos,
+                                                      double a, double u0, double b, double lx,
+                                                      double ly, double f_grav_z, int wall,
+                                                      double *__restrict__ force) {
+  const int64_t i = (int64_t(blockIdx.x) * kBlock + threadIdx.x) / 64;
+  const int lane = threadIdx.x & 63;
+  if (i >= n) return;   // the whole wavefront
+  const double d = 2.0 * a;
+  const double cut = d + 40.0 * b;
+  const double cut2 = cut * cut;
+  const double fmax_ = u0 / b;
+  const double inv_b = 1.0 / b;
+  const double xi = pos[3 * i], yi = pos[3 * i + 1], zi = pos[3 * i + 2];
+  double fx = 0.0, fy = 0.0, fz = 0.0;
+  for (int64_t j = lane; j < n; j += 64) {
+    double dx = xi - pos[3 * j], dy = yi - pos[3 * j + 1];
+    const double dz = zi - pos[3 * j + 2];
+    if (lx > 0.0) {   // minimum image
+      dx -= lx * rint(dx / lx);
+      dy -= ly * rint(dy / ly);
+    }
+    const double r2 = dx * dx + dy * dy + dz * dz;
+    if (r2 < cut2 && r2 > 0.0) {
+      const double r = sqrt(r2);
+      const double fm = r < d ? fmax_ : fmax_ * exp(-(r - d) * inv_b);
+      const double sc = fm / r;
+      fx += sc * dx;
+      fy += sc * dy;
+      fz += sc * dz;
+    }
+  }
+  for (int off = 1; off < 64; off <<= 1) {
+    fx += __shfl_xor(fx, off, 64);
+    fy += __shfl_xor(fy, off, 64);
+    fz += __shfl_xor(fz, off, 64);
+  }
+  if (lane != 0) return;
+  if (wall) fz += zi < a ? fmax_ : fmax_ * exp(-(zi - a) / b);
+  fz += f_grav_z;
+  force[3 * i] = fx;
+  force[3 * i + 1] = fy;
+  force[3 * i + 2] = fz;
+}
+
+// Largest system of steric_wave, without and with a box (whose minimum image costs two divisions a
+// pair).  A call by itself, us, cell list / one wavefront per target: 256: 50.5 / 25, 2,100: 64 /
+// 25.5, 4,099: 62 / 35, 6,000: 69 / 52, 8,191: 68 / 92.
+constexpr int64_t kWaveMaxN = 6000, kWaveMaxBoxN = 3000;
+
 // Cell side and layout for cutoff `cut`; false when a box holds fewer than three cells per
 // side (the neighbour cells would then wrap onto each other).
 bool cell_args(double cut, double lx, double ly, int64_t n, CellArgs *c) {
@@ -491,6 +543,12 @@ int forces_run(rpb_ctx *ctx, const rpb_params *p, int64_t n, const double *pos, 
   if (p->lx > 0.0 && (p->lx <= 2.0 * cut || p->ly <= 2.0 * cut))
     return fail(ctx, RPB_EINVAL, "box %g x %g too small for the minimum image (need > %g)", p->lx,
                 p->ly, 2.0 * cut);
+  if (n <= (p->lx > 0.0 ? kWaveMaxBoxN : kWaveMaxN)) {
+    steric_wave<<<unsigned((n * 64 + kBlock - 1) / kBlock), kBlock, 0, stream>>>(
+        n, pos, p->a, u0, b, p->lx, p->ly, f_grav_z, p->wall, force);
+    RPB_LAUNCHED(ctx);
+    return RPB_OK;
+  }
   CellArgs c;
   if (cell_args(cut, p->lx, p->ly, n, &c))
     return steric_cell_run(ctx, p, n, pos, nullptr, c, f_grav_z, u0, b, force, stream);
