@@ -11,7 +11,7 @@
 //     v_{m+1} = u / beta_m
 //   g = V_m y_m.
 // Reductions use a fixed number of blocks and a fixed tree, so results are bitwise
-// reproducible.  The host reads a 32-byte status record once per iteration.
+// reproducible.  Each iteration's stop test is tagged into pinned memory, which the host polls.
 #include <algorithm>
 #include <cfloat>
 #include <cmath>

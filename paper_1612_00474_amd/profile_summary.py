@@ -25,7 +25,7 @@ from collections import defaultdict
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 CALIB = "copyBuffer"
-PAIR_SOURCES = ("matvec.hip", "multi.hip", "pair_common.h", "pair_tensor.h")
+PAIR_SOURCES = ("matvec.hip", "multi.hip", "pair_common.h", "pair_tensor.h", "sym64.h")
 
 
 def kernel_source_hash() -> str:
