@@ -265,8 +265,9 @@ def read_kinds(ctx, shape_sym, sizes):
         if k:
             s = shape_sym["mixed" if mixed else "fp64"]
             t = ms * 1e-3
+            products = pairs / sum(n * n for n in sizes)   # a small drift launch takes two
             kinds[name] = {"launches": k, "ms_per_launch": ms / k, "pairs_per_s": pairs / t,
-                           "tflops_alg": k * alg_flops(sizes, s, torque) / t / 1e12,
+                           "tflops_alg": products * alg_flops(sizes, s, torque) / t / 1e12,
                            "tflops_logical": (FLOP_ORD_TORQUE if torque else FLOP_ORD_FORCE)
                            * pairs / t / 1e12}
     # the two-vector launch of each step: M F + M_C T together with the first Lanczos product

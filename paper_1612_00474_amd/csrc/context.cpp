@@ -160,7 +160,9 @@ int rpb_create(int hip_device, rpb_ctx **out) {
     delete c;
     return RPB_ENOMEM;
   }
-  std::memset(c->host_pinned, 0, kHostScratchBytes);   // no word holds a solve's tag yet
+  // no status word holds a tag yet
+  std::memset(static_cast<char *>(c->host_pinned) + kHostLzRingOffset, 0,
+              kHostDoneOffset - kHostLzRingOffset + kMaxBatchSystems * sizeof(int));
   if (hipHostGetDevicePointer(&c->host_pinned_dev, c->host_pinned, 0) != hipSuccess) {
     (void)hipHostFree(c->host_pinned);
     delete c;

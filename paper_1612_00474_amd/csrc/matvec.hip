@@ -1596,13 +1596,18 @@ void with_tile(TileShape t, Fn &&fn) {
     fn(C1{}, C1{}, C4{});
 }
 
+// Workgroups of one product up to which two share a launch: 16 a compute unit.  Above, each fills the
+// device by itself (16,384 spheres, 8,256 workgroups: the step's time did not change).
+constexpr int64_t kTwoMaxWorkgroups = 4096;
+
 // Whole-system product with one evaluation per unordered pair.  The triangle of tile pairs is
 // walked in chunks whose partials fit the context's limit (512 MiB: one chunk up to about
 // 150,000 spheres in mixed precision at 2 targets per lane and 75,000 in float64), each
 // chunk's pair kernel followed by its reduction into vel, so the workspace stays bounded
 // whatever n.  The timing record spans the pair kernels of all chunks.
 // With g2 (float64 forces) a second configuration's product of src2 into vel2 runs in the same
-// launches if the partials of both fit one chunk; *both says whether it did.
+// launches if the partials of both fit one chunk and one product alone is a small launch; *both says
+// whether it did.
 int matvec_symmetric(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const void *src,
                      bool torque, const double *h, int tpt, double *vel, hipStream_t stream,
                      const int *skip, bool expanded, DotOut *dot = nullptr,
@@ -1623,7 +1628,8 @@ int matvec_symmetric(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const v
   const size_t esz = f64 ? sizeof(double) : sizeof(float);
   const int64_t per = chunk_pairs(pairs, a.nsplit, 1, a.ts, esz, ctx->chunk_bytes);
   const size_t pbytes = size_t(part_elems(per, a.nsplit, 1, a.ts)) * esz;
-  const bool two = g2 && per == pairs && 2 * pbytes <= ctx->chunk_bytes;
+  const bool two = g2 && pairs * a.nsplit <= kTwoMaxWorkgroups && per == pairs &&
+                   2 * pbytes <= ctx->chunk_bytes;
   if (both) *both = two;
   int st;
   void *part = workspace(ctx, WS_PART, two ? 2 * pbytes : pbytes, &st);

@@ -305,8 +305,8 @@ int matvec_sources(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const voi
                    int64_t row0, int64_t nrows, double *vel, hipStream_t stream,
                    const int *skip = nullptr, bool expanded = false, DotOut *dot = nullptr);
 // up = M(pos + sp w) w and, with `minus`, um = M(pos - sm w) w: the products of a random finite
-// difference, in p->precision, without a position check.  Float64 products of a system whose
-// partials fit twice run in one launch.  Overwrites WS_GEOM and WS_GEOM2.
+// difference, in p->precision, without a position check.  Two small float64
+// products run in one launch.  Overwrites WS_GEOM and WS_GEOM2.
 int matvec_shifted(rpb_ctx *ctx, const rpb_params *p, int64_t n, const double *pos,
                    const double *w, double sp, double sm, bool minus, bool expanded, double *up,
                    double *um, hipStream_t stream);

@@ -19,7 +19,8 @@ using Key = std::tuple<int, int, int>;   // precision, batched, log2(n)
 std::map<Key, Tuning> &cache(rpb_ctx *ctx) { return ctx->tune_cache; }
 
 int time_candidate(rpb_ctx *ctx, const rpb_params *p, int32_t nsys, const int64_t *offs,
-                   const double *pos, int reps, hipStream_t stream, double *ms_out) {
+                   const double *pos, int reps, bool expanded, hipStream_t stream,
+                   double *ms_out) {
   const int64_t n = offs[nsys];
   int st;
   double *vel =
@@ -32,7 +33,7 @@ int time_candidate(rpb_ctx *ctx, const rpb_params *p, int32_t nsys, const int64_
   // the positions serve as a finite source vector: only the time matters here
   auto once = [&]() -> int {
     return nsys > 1 ? matvec_batched(ctx, p, b, g, pos, nullptr, nullptr, vel, stream)
-                    : matvec_packed(ctx, p, g, pos, nullptr, 0, n, vel, stream);
+                    : matvec_packed(ctx, p, g, pos, nullptr, 0, n, vel, stream, nullptr, expanded);
   };
   RPB_TRY(once());
   hipEvent_t e0, e1;
@@ -147,20 +148,28 @@ int rpb_autotune(rpb_ctx *ctx, const rpb_params *p, int32_t nsys, const int64_t 
         }
       }
     }
-    if (!batched && n >= 4 * 1024) {   // 4 targets per lane: tiles of 1,024 spheres, symmetric
-      // kernel only; on smaller systems most of a tile's lanes would idle
+    if (!batched && q == RPB_MIXED && n >= 4 * 1024) {   // 4 targets per lane: tiles of 1,024
+      // spheres, mixed symmetric kernel only (float64 products choose their tile by size, and the
+      // drift of mixed steps is 15 % slower with it); on smaller systems most lanes would idle
       Shape c = base;
       c.tpt = 4;
       c.symmetric = 1;
       cands.push_back(c);
     }
     int rc = RPB_OK;
+    double best_rank = -1.0;
     for (const Shape &sh : cands) {
       ctx->tune.s[q] = sh;
       double ms = 0.0;
-      rc = time_candidate(ctx, p, nsys, offs, pos, reps, stream, &ms);
+      rc = time_candidate(ctx, p, nsys, offs, pos, reps, false, stream, &ms);
       if (rc != RPB_OK) break;
-      if (best_ms < 0.0 || ms < best_ms) {
+      // a float64 shape also serves the drift of mixed steps, whose kernel follows it more closely
+      double drift_ms = ms;
+      if (q == RPB_FP64 && !batched && sh.symmetric)
+        rc = time_candidate(ctx, p, nsys, offs, pos, reps, true, stream, &drift_ms);
+      if (rc != RPB_OK) break;
+      if (best_rank < 0.0 || ms + drift_ms < best_rank) {
+        best_rank = ms + drift_ms;
         best_ms = ms;
         best = sh;
       }

@@ -32,3 +32,15 @@ def test_drift_is_the_difference_of_two_products(n, kib, rfd_precision, monkeypa
                          rfd_scheme="one_sided" if one_sided else "centred"))
         assert np.array_equal(got, (c.kT / delta) * (up - um)), (n, one_sided)
     c.close()
+
+
+def test_float64_tuning_keeps_to_shapes_that_serve_the_drift():
+    # four targets per lane are the float64 products' own choice by size already, and the
+    # slowest shape of the drift of mixed steps, so the tuner does not offer them
+    require_gpu()
+    from paper_1612_00474_amd import Context
+    c = Context(0)
+    pos = wl.sheet(4500, seed=1)
+    c.autotune(dev(pos), precision="fp64")
+    assert c.tuning()["fp64"]["tpt"] in (1, 2)
+    c.close()
