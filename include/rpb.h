@@ -14,8 +14,9 @@
  *    (x, y, z per sphere), 8-byte aligned, owned by the caller.  The library never
  *    frees or keeps them after the call returns.
  *  - Work is enqueued on `stream` (a hipStream_t; NULL = the default stream).  Calls
- *    that must read device scalars (Lanczos convergence, validation flags)
- *    synchronise `stream` before returning; host out-parameters are valid on return.
+ *    that must read device scalars (Lanczos convergence, validation flags) wait for
+ *    them, and so for the work on `stream` before them, before returning; host
+ *    out-parameters are valid on return, results in stream order.
  *  - Return value: RPB_OK (0) or a negative rpb_status.  rpb_last_error() then holds
  *    a message.  No C++ exception crosses this interface.
  *  - n == 0 is a no-op that returns RPB_OK.  RPB_EINVAL for n < 0, a NULL required
