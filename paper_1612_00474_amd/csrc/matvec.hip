@@ -1177,21 +1177,23 @@ __global__ __launch_bounds__(kBlock) void pair_kernel_f64_sym_batched(
 
 // System s's partials start at part_base[s] and cover its whole triangle (one chunk).  As
 // reduce_sym_chunk with G threads per (component, row) and W wavefronts of 64 of them per
-// workgroup, all of system blockIdx.y; dpart: the system's partials of dotv . vel at
+// workgroup, all of one system (blocks: a BlockList's list of 64 W values); dpart: the system's partials of dotv . vel at
 // dpart[s * dstride].  Small batches take G = 8 (their few rows are many slots deep); a batch of
 // 282,705 spheres keeps the device full with one thread per row (34 us, 62 with eight).
 template <typename Part, int G, int W>
 __global__ __launch_bounds__(64 * G * W) void reduce_partials_sym_batched(
-    SymBatchArgs b, const Part *__restrict__ partial, const double *__restrict__ h, double scale,
-    double *__restrict__ vel, const double *__restrict__ dotv, double *__restrict__ dpart,
+    SymBatchArgs b, const int2 *__restrict__ blocks, const Part *__restrict__ partial,
+    const double *__restrict__ h, double scale, double *__restrict__ vel,
+    const double *__restrict__ dotv, double *__restrict__ dpart,
     int64_t dstride) {
   static_assert(G == 1 || W == 1, "the group sums of one set of rows");
   __shared__ double sh[G * 64];
-  const int s = blockIdx.y;
+  int s, blk;
+  block_of(blocks, s, blk);
   if (b.done && b.done[s]) return;
   const SymArgs a = sym_args_of(b, s);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, grp = G > 1 ? wave : 0;
-  const int64_t set = int64_t(blockIdx.x) * W + (G > 1 ? 0 : wave);
+  const int64_t set = int64_t(blk) * W + (G > 1 ? 0 : wave);
   if (set * 64 >= 3 * a.n) return;   // uniform over the workgroup when G > 1
   const int64_t e = set * 64 + lane;
   const bool live = e < 3 * a.n;
@@ -1918,22 +1920,50 @@ int prepare_batch(rpb_ctx *ctx, int32_t nsys, const int64_t *offs, int precision
   b->nitems = int(items.size());
   b->max_chunks = max_chunks;
 
-  // device copies: offs (nsys + 1 int64), part_base (nsys int64), items, sys_of (n int32);
-  // staged through pinned memory
+  // workgroup lists of the kernels over rows
+  std::vector<int2> lists[kBlockKinds];
+  for (int q = 0; q < kBlockKinds; ++q) {
+    auto groups = [&](int s) {
+      return std::max<int64_t>(
+          1, (3 * (offs[s + 1] - offs[s]) + kBlockValues[q] - 1) / kBlockValues[q]);
+    };
+    int64_t longest = 1, total = 0;
+    for (int s = 0; s < nsys; ++s) {
+      longest = std::max(longest, groups(s));
+      total += groups(s);
+    }
+    BlockList &bl = b->blocks[q];
+    bl = BlockList{};
+    bl.total = total;
+    if (nsys <= kMaxGridY && longest * nsys <= 2 * total) {
+      bl.grid = dim3{unsigned(longest), unsigned(nsys), 1u};
+      continue;
+    }
+    bl.grid = dim3{unsigned(total), 1u, 1u};
+    lists[q].reserve(size_t(total));
+    for (int s = 0; s < nsys; ++s)
+      for (int64_t g = 0; g < groups(s); ++g) lists[q].push_back(int2{s, int(g)});
+  }
+
+  // device copies: offs (nsys + 1 int64), part_base (nsys int64), items, the workgroup lists,
+  // sys_of (n int32); all but the last staged through pinned memory
   const size_t offs_bytes = size_t(2 * nsys + 1) * sizeof(int64_t);
   const size_t items_bytes = std::max<size_t>(1, items.size()) * sizeof(int4);
   const size_t offs_pad = (offs_bytes + 255) / 256 * 256;
   const size_t items_pad = (items_bytes + 255) / 256 * 256;
+  size_t lists_at[kBlockKinds], host_bytes = offs_pad + items_pad;
+  for (int q = 0; q < kBlockKinds; ++q) {
+    lists_at[q] = host_bytes;
+    host_bytes += (lists[q].size() * sizeof(int2) + 255) / 256 * 256;
+  }
   const size_t sys_bytes = size_t(std::max<int64_t>(1, b->n)) * sizeof(int);
   int st;
-  char *dev = static_cast<char *>(
-      workspace(ctx, WS_BATCH, offs_pad + items_pad + sys_bytes, &st));
+  char *dev = static_cast<char *>(workspace(ctx, WS_BATCH, host_bytes + sys_bytes, &st));
   if (!dev) return st;
   b->offs = reinterpret_cast<int64_t *>(dev);
   b->part_base = b->offs + nsys + 1;
   b->items = reinterpret_cast<int4 *>(dev + offs_pad);
-  b->sys_of = reinterpret_cast<int *>(dev + offs_pad + items_pad);
-  const size_t host_bytes = offs_pad + items_pad;
+  b->sys_of = reinterpret_cast<int *>(dev + host_bytes);
   // the pinned staging buffer may still feed an earlier copy
   RPB_HIP(ctx, hipStreamSynchronize(stream));
   if (ctx->batch_host_bytes < host_bytes) {
@@ -1953,6 +1983,14 @@ int prepare_batch(rpb_ctx *ctx, int32_t nsys, const int64_t *offs, int precision
   if (!items.empty())
     RPB_HIP(ctx, hipMemcpyAsync(b->items, hi, items.size() * sizeof(int4), hipMemcpyHostToDevice,
                                 stream));
+  for (int q = 0; q < kBlockKinds; ++q) {
+    if (lists[q].empty()) continue;
+    const size_t bytes = lists[q].size() * sizeof(int2);
+    std::memcpy(hb + lists_at[q], lists[q].data(), bytes);
+    b->blocks[q].list = reinterpret_cast<const int2 *>(dev + lists_at[q]);
+    RPB_HIP(ctx, hipMemcpyAsync(dev + lists_at[q], hb + lists_at[q], bytes, hipMemcpyHostToDevice,
+                                stream));
+  }
   fill_sys_of<<<unsigned(nsys), 256, 0, stream>>>(nsys, b->offs, b->sys_of);
   RPB_LAUNCHED(ctx);
   return RPB_OK;
@@ -1996,22 +2034,21 @@ int matvec_batched_sym(rpb_ctx *ctx, const rpb_params *p, const Batch &b, const 
   RPB_LAUNCHED(ctx);
   RPB_TRY(timing_end(ctx, stream, t0, pairs, 4 + (f64 ? 0 : 2) + (has_t ? 1 : 0)));
   const double scale = 1.0 / (8.0 * M_PI * p->eta * p->a);
-  int64_t longest = 1;
-  for (int s = 0; s < b.nsys; ++s)
-    longest = std::max(longest, b.host_offs[s + 1] - b.host_offs[s]);
   const double *dotv = dot ? dot->v : nullptr;
   double *dpart = dot ? dot->part : nullptr;
   const int64_t dstride = dot ? dot->stride : 0;
   if (dotv) dot->done = true;
   auto reduce = [&](auto G, auto W) {
     constexpr int kG = decltype(G)::value, kW = decltype(W)::value;
-    const dim3 rgrid{blocks_for(3 * longest, 64 * kW), unsigned(b.nsys), 1u};
+    constexpr int kind = kW == 1 ? 0 : 1;
+    static_assert(kBlockValues[kind] == 64 * kW, "the list of this workgroup's values");
+    const BlockList &bl = b.blocks[kind];
     if (f64)
-      reduce_partials_sym_batched<double, kG, kW><<<rgrid, 64 * kG * kW, 0, stream>>>(
-          args, static_cast<const double *>(part), h, scale, vel, dotv, dpart, dstride);
+      reduce_partials_sym_batched<double, kG, kW><<<bl.grid, 64 * kG * kW, 0, stream>>>(
+          args, bl.list, static_cast<const double *>(part), h, scale, vel, dotv, dpart, dstride);
     else
-      reduce_partials_sym_batched<float, kG, kW><<<rgrid, 64 * kG * kW, 0, stream>>>(
-          args, static_cast<const float *>(part), h, scale, vel, dotv, dpart, dstride);
+      reduce_partials_sym_batched<float, kG, kW><<<bl.grid, 64 * kG * kW, 0, stream>>>(
+          args, bl.list, static_cast<const float *>(part), h, scale, vel, dotv, dpart, dstride);
   };
   if (n < 65536)
     reduce(std::integral_constant<int, kRedGroups>{}, std::integral_constant<int, 1>{});

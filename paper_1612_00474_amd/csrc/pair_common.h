@@ -273,6 +273,18 @@ inline int64_t chunk_pairs(int64_t pairs, int64_t nsplit, int V, int64_t ts, siz
   return (pairs + nchunks - 1) / nchunks;   // equal chunks
 }
 
+// The workgroup's system and its place among the system's workgroups (BlockList; list: its list).
+__device__ __forceinline__ void block_of(const int2 *__restrict__ list, int &s, int &blk) {
+  if (list) {
+    const int2 w = list[blockIdx.x];
+    s = w.x;
+    blk = w.y;
+  } else {
+    s = blockIdx.y;
+    blk = blockIdx.x;
+  }
+}
+
 // Threads per (component, row) of the reductions that deal a row's partials (one wavefront each,
 // 64 rows per workgroup).
 constexpr int kRedGroups = 8;

@@ -323,6 +323,22 @@ int one_tile_part(const rpb_ctx *ctx, const Packed &g);
 // ---- batched products (matvec.hip) -----------------------------------------------------
 
 // Work list of a batch of independent systems (built on the host, copied to the device).
+// Workgroups of a kernel over the 3 n values of every system of a batch, each workgroup within one
+// system (an empty system keeps one).  Systems of about one size take a two-dimensional grid
+// (workgroup of the system, system).  Where that would launch more than twice the workgroups that
+// have work, or the systems outnumber the grid's second dimension, the grid is one-dimensional over
+// a list of (system, workgroup of the system): one more dependent load per workgroup (so the even
+// grid stays), against the longest system's workgroups for every system (one system of 60,000
+// spheres among 4,000 of 16: 2.8 million workgroups of 256 values instead of 4,704).
+struct BlockList {
+  const int2 *list = nullptr;    // device; NULL: the two-dimensional grid
+  dim3 grid{1u, 1u, 1u};
+  int64_t total = 0;             // workgroups with work
+};
+constexpr int kBlockKinds = 2;
+constexpr int64_t kBlockValues[kBlockKinds] = {64, 256};   // values per workgroup
+constexpr int64_t kMaxGridY = 65535;
+
 struct Batch {
   int nsys = 0;
   int64_t n = 0;                 // total spheres
@@ -338,6 +354,7 @@ struct Batch {
   bool symmetric = false;        // items are (system, I, J, part) of the symmetric kernel
   int nsplit = 1;                // source parts per symmetric tile pair
   int64_t *part_base = nullptr;  // device, nsys entries: each system's first partial slot
+  BlockList blocks[kBlockKinds]; // by values per workgroup
   int64_t part_elems = 0;        // partial elements of the symmetric layout (float32 in mixed precision)
 };
 

@@ -1,0 +1,78 @@
+"""GPU: batches of very many and of very uneven systems, whose row kernels take a one-dimensional
+grid over a list of (system, workgroup) pairs, against single calls on each system's own rows."""
+import numpy as np
+import pytest
+
+from paper_1612_00474_amd import workloads as wl
+from tests.gpu_util import close, dev, host, require_gpu
+
+pytestmark = pytest.mark.gpu
+
+# A system of a batch and the same system alone differ in the order of their sums only: a few units
+# of rounding per pair in float64, of float32 rounding in mixed precision.
+TOL = {"fp64": 1e-13, "mixed": 1e-6}
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    require_gpu()
+    from paper_1612_00474_amd import Context
+    c = Context(0)
+    yield c
+    c.close()
+
+
+def _system(n, rng):
+    return wl.sample_positions(n, wl.side_for_area_fraction(max(n, 1), 0.4), 1.1, 2.5, rng=rng)
+
+
+def _offsets(sizes):
+    return np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+
+
+@pytest.mark.parametrize("torque", [False, True])
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_more_systems_than_a_grid_dimension(ctx, precision, torque):
+    rng = np.random.default_rng(11)
+    kinds, reps = 7, 10_000                      # 70,000 systems of 8 spheres
+    pos = [_system(8, rng) for _ in range(kinds)]
+    F, T = rng.standard_normal((2, kinds, 8, 3))
+    rep = lambda a: dev(np.tile(np.reshape(a, (kinds * 8, 3)), (reps, 1)))
+    u = host(ctx.matvec_batched(rep(pos), _offsets([8] * kinds * reps), rep(F),
+                                rep(T) if torque else None, precision))
+    ref = np.stack([host(ctx.matvec(dev(pos[k]), dev(F[k]), dev(T[k]) if torque else None,
+                                    precision)) for k in range(kinds)])
+    u = u.reshape(reps, kinds, 8, 3)
+    for k in range(kinds):
+        assert close(u[:, k], np.broadcast_to(ref[k], (reps, 8, 3)), TOL[precision]), k
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_mostly_empty_systems(ctx, precision):
+    # few spheres, but systems on both sides of the grid limit
+    rng = np.random.default_rng(12)
+    sizes = np.zeros(70_001, dtype=np.int64)
+    sizes[[0, 1, 65_534, 65_535, 65_536, 70_000]] = [5, 700, 1, 40, 300, 65]
+    offs = _offsets(sizes)
+    pos = np.vstack([_system(int(n), rng) for n in sizes if n])
+    F = rng.standard_normal(pos.shape)
+    u = host(ctx.matvec_batched(dev(pos), offs, dev(F), None, precision))
+    for s in np.flatnonzero(sizes):
+        a, b = offs[s], offs[s + 1]
+        ref = host(ctx.matvec(dev(pos[a:b]), dev(F[a:b]), None, precision))
+        assert close(u[a:b], ref, TOL[precision]), s
+
+
+@pytest.mark.parametrize("big", [3000, 40_000])   # both forms of the reduction (by total size)
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_uneven_systems(ctx, precision, big):
+    rng = np.random.default_rng(13)
+    sizes = [16, 85, big] + [16] * 2000 + [0, 1]
+    offs = _offsets(sizes)
+    pos = np.vstack([_system(n, rng) for n in sizes if n])
+    F, T = rng.standard_normal((2,) + pos.shape)
+    u = host(ctx.matvec_batched(dev(pos), offs, dev(F), dev(T), precision))
+    for s in (0, 1, 2, 3, 1000, len(sizes) - 3, len(sizes) - 1):
+        a, b = offs[s], offs[s + 1]
+        ref = host(ctx.matvec(dev(pos[a:b]), dev(F[a:b]), dev(T[a:b]), precision))
+        assert close(u[a:b], ref, TOL[precision]), s
