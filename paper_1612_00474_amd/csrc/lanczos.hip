@@ -723,6 +723,8 @@ struct SegView {
   LzEig *eig;             // nsys eigendecompositions
   int nsys;
   int64_t m3;             // elements of a vector
+  // workgroups of kThreads and of 4 kThreads values (BlockList's lists, nullable)
+  const int2 *list1, *list4;
 };
 
 __device__ __forceinline__ void seg_range(const SegView &v, int s, int64_t &e0, int64_t &e1) {
@@ -750,18 +752,26 @@ __device__ __forceinline__ double sum_partials(const double *__restrict__ part, 
   return r;
 }
 
-// One partial per 64 elements of a . b over each live process (grid: elements / kThreads, nsys);
+// The workgroup's process and its place among the process's workgroups of EPT kThreads values.
+template <int EPT>
+__device__ __forceinline__ void seg_block(const SegView &v, int &s, int &blk) {
+  static_assert(EPT == 1 || EPT == 4, "lists of these");
+  block_of(EPT == 1 ? v.list1 : v.list4, s, blk);
+}
+
+// One partial per 64 elements of a . b over each live process (workgroups of kThreads values);
 // partial q of process s at part[s * stride + q].
 __global__ __launch_bounds__(kThreads) void lz_dot(SegView v, const double *__restrict__ a,
                                                    const double *__restrict__ b, int check_done,
                                                    double *__restrict__ part, int64_t stride) {
-  const int s = blockIdx.y;
+  int s, blk;
+  seg_block<1>(v, s, blk);
   if (check_done && v.done && v.done[s]) return;
   int64_t e0, e1;
   seg_range(v, s, e0, e1);
-  const int64_t i = e0 + int64_t(blockIdx.x) * kThreads + threadIdx.x;
+  const int64_t i = e0 + int64_t(blk) * kThreads + threadIdx.x;
   const double x = wave_sum(i < e1 ? a[i] * b[i] : 0.0);
-  const int64_t q = int64_t(blockIdx.x) * (kThreads / 64) + (threadIdx.x >> 6);
+  const int64_t q = int64_t(blk) * (kThreads / 64) + (threadIdx.x >> 6);
   if ((threadIdx.x & 63) == 0 && e0 + q * kPartRows < e1) part[s * stride + q] = x;
 }
 
@@ -790,18 +800,20 @@ __global__ __launch_bounds__(kThreads) void lz_start(
     const double *__restrict__ mw, double *__restrict__ u, double *__restrict__ apart,
     int64_t stride, int *counter) {
   __shared__ double sh[kThreads / 64];
-  const int s = blockIdx.y, t = threadIdx.x;
-  if (s == 0 && blockIdx.x == 0 && t == 0) {
+  const int t = threadIdx.x;
+  int s, blk;
+  seg_block<1>(v, s, blk);
+  if (s == 0 && blk == 0 && t == 0) {
     if (counter) counter[0] = 0;
     if (v.done) v.done[v.nsys] = v.done[v.nsys + 1] = 0;
   }
   int64_t e0, e1;
   seg_range(v, s, e0, e1);
-  if (blockIdx.x > 0 && e0 + int64_t(blockIdx.x) * kThreads >= e1) return;
+  if (blk > 0 && e0 + int64_t(blk) * kThreads >= e1) return;
   const double wn =
       sqrt(sum_partials(npart + s * stride, (e1 - e0 + kPartRows - 1) / kPartRows, sh));
-  if (blockIdx.x == 0) reset_state(v, s, wn);
-  const int64_t i = e0 + int64_t(blockIdx.x) * kThreads + t;
+  if (blk == 0) reset_state(v, s, wn);
+  const int64_t i = e0 + int64_t(blk) * kThreads + t;
   double a = 0.0;
   if (i < e1) {
     const double x = wn > 0.0 ? w[i] / wn : 0.0;
@@ -818,7 +830,7 @@ __global__ __launch_bounds__(kThreads) void lz_start(
   }
   if (!mw) return;
   a = wave_sum(a);
-  const int64_t q = int64_t(blockIdx.x) * (kThreads / 64) + (t >> 6);
+  const int64_t q = int64_t(blk) * (kThreads / 64) + (t >> 6);
   if ((t & 63) == 0 && e0 + q * kPartRows < e1) apart[s * stride + q] = a;
 }
 
@@ -839,11 +851,13 @@ __global__ __launch_bounds__(kThreads) void lz_dots(SegView v, int k,
   constexpr int W = kThreads / 64;
   __shared__ double sh[W];
   __shared__ double hsh[(kMaxKrylov + 1) * W];   // wavefront sums: [j * W + wave]
-  const int s = blockIdx.y, t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  int s, blk;
+  seg_block<EPT>(v, s, blk);
   if (v.done && v.done[s]) return;
   int64_t e0, e1;
   seg_range(v, s, e0, e1);
-  if (int(blockIdx.x) >= seg_groups<EPT>(e1 - e0)) return;
+  if (blk >= seg_groups<EPT>(e1 - e0)) return;
   LzState *st = v.st + s;
   const double *vk = V + int64_t(k - 1) * v.m3;
   const double *vp = V + int64_t(k > 1 ? k - 2 : 0) * v.m3;
@@ -853,7 +867,7 @@ __global__ __launch_bounds__(kThreads) void lz_dots(SegView v, int k,
   double x[EPT], xv[EPT], xp[EPT];
 #pragma unroll
   for (int r = 0; r < EPT; ++r) {
-    const int64_t i = e0 + (int64_t(blockIdx.x) * EPT + r) * kThreads + t;
+    const int64_t i = e0 + (int64_t(blk) * EPT + r) * kThreads + t;
     in[r] = i < e1;
     ix[r] = in[r] ? i : 0;
     x[r] = in[r] ? u[ix[r]] : 0.0;
@@ -861,7 +875,7 @@ __global__ __launch_bounds__(kThreads) void lz_dots(SegView v, int k,
     xp[r] = in[r] && k > 1 ? vp[ix[r]] : 0.0;
   }
   const double al = sum_partials(apart + s * stride, (e1 - e0 + kPartRows - 1) / kPartRows, sh);
-  if (blockIdx.x == 0 && t == 0) st->alpha[k - 1] = al;
+  if (blk == 0 && t == 0) st->alpha[k - 1] = al;
   double nrm = 0.0;
 #pragma unroll
   for (int r = 0; r < EPT; ++r) {
@@ -896,7 +910,7 @@ __global__ __launch_bounds__(kThreads) void lz_dots(SegView v, int k,
     double r = hsh[t * W];
 #pragma unroll
     for (int w = 1; w < W; ++w) r += hsh[t * W + w];
-    part[(int64_t(s) * (kMaxKrylov + 1) + t) * nb + blockIdx.x] = r;
+    part[(int64_t(s) * (kMaxKrylov + 1) + t) * nb + blk] = r;
   }
 }
 
@@ -943,13 +957,15 @@ __global__ __launch_bounds__(kThreads, 2) void lz_update(
     const double *__restrict__ part, int nb, int write_next, const double *__restrict__ hw,
     Real *__restrict__ src, int *counter, LzReport rep) {
   __shared__ double hs[kMaxKrylov + 1];
-  const int s = blockIdx.y, t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  if (counter && s == 0 && blockIdx.x == 0 && t == 0) counter[0] = 0;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  int s, blk;
+  seg_block<EPT>(v, s, blk);
+  if (counter && s == 0 && blk == 0 && t == 0) counter[0] = 0;
   if (v.done && v.done[s]) return;
   int64_t e0, e1;
   seg_range(v, s, e0, e1);
   const int ng = seg_groups<EPT>(e1 - e0);
-  if (int(blockIdx.x) >= ng) return;
+  if (blk >= ng) return;
   LzState *st = v.st + s;
   for (int j = wave; j <= k; j += kThreads / 64) {
     const double *p = part + (int64_t(s) * (kMaxKrylov + 1) + j) * nb;
@@ -968,7 +984,7 @@ __global__ __launch_bounds__(kThreads, 2) void lz_update(
     double x[EPT], proj[EPT];
 #pragma unroll
     for (int r = 0; r < EPT; ++r) {
-      const int64_t i = e0 + (int64_t(blockIdx.x) * EPT + r) * kThreads + t;
+      const int64_t i = e0 + (int64_t(blk) * EPT + r) * kThreads + t;
       in[r] = i < e1;
       ix[r] = in[r] ? i : 0;
       x[r] = in[r] ? u[ix[r]] : 0.0;
@@ -999,7 +1015,7 @@ __global__ __launch_bounds__(kThreads, 2) void lz_update(
         }
       }
   }
-  if (blockIdx.x != 0) return;
+  if (blk != 0) return;
   if (t == 0) st->beta[k - 1] = beta;
   if (t < k) st->h[t] = hs[t];
   if constexpr (ROOT) {
@@ -1078,17 +1094,19 @@ __global__ __launch_bounds__(kThreads) void ord_start(SegView v, const double *_
                                                       Real *__restrict__ src,
                                                       const double *__restrict__ mw,
                                                       double *__restrict__ u, int *counter) {
-  const int s = blockIdx.y, t = threadIdx.x;
-  if (s == 0 && blockIdx.x == 0 && t == 0) {
+  const int t = threadIdx.x;
+  int s, blk;
+  seg_block<1>(v, s, blk);
+  if (s == 0 && blk == 0 && t == 0) {
     if (counter) counter[0] = 0;
     if (v.done) v.done[v.nsys] = v.done[v.nsys + 1] = 0;
   }
   int64_t e0, e1;
   seg_range(v, s, e0, e1);
-  if (blockIdx.x > 0 && e0 + int64_t(blockIdx.x) * kThreads >= e1) return;
+  if (blk > 0 && e0 + int64_t(blk) * kThreads >= e1) return;
   const double wn = sqrt(finish_sum<TREE>(npart + int64_t(s) * ord_blocks<TREE>()));
-  if (blockIdx.x == 0) reset_state(v, s, wn);
-  const int64_t i = e0 + int64_t(blockIdx.x) * kThreads + t;
+  if (blk == 0) reset_state(v, s, wn);
+  const int64_t i = e0 + int64_t(blk) * kThreads + t;
   if (i >= e1) return;
   const double x = wn > 0.0 ? w[i] / wn : 0.0;
   V[i] = x;
@@ -1181,14 +1199,16 @@ __global__ __launch_bounds__(kThreads, ROOT ? 2 : 4) void ord_scale(
     SegView v, int k, double tol, double *__restrict__ V, const double *__restrict__ u,
     const double *__restrict__ bpart, int write_next, const double *__restrict__ hw,
     Real *__restrict__ src, int *counter, LzReport rep) {
-  const int s = blockIdx.y, t = threadIdx.x;
-  if (counter && s == 0 && blockIdx.x == 0 && t == 0) counter[0] = 0;
+  const int t = threadIdx.x;
+  int s, blk;
+  seg_block<1>(v, s, blk);
+  if (counter && s == 0 && blk == 0 && t == 0) counter[0] = 0;
   if (v.done && v.done[s]) return;
   int64_t e0, e1;
   seg_range(v, s, e0, e1);
-  if (blockIdx.x > 0 && e0 + int64_t(blockIdx.x) * kThreads >= e1) return;
+  if (blk > 0 && e0 + int64_t(blk) * kThreads >= e1) return;
   const double beta = sqrt(finish_sum<TREE>(bpart + int64_t(s) * ord_blocks<TREE>()));
-  const int64_t i = e0 + int64_t(blockIdx.x) * kThreads + t;
+  const int64_t i = e0 + int64_t(blk) * kThreads + t;
   if (write_next && i < e1) {
     const double x = beta > 0.0 ? u[i] / beta : 0.0;
     V[int64_t(k) * v.m3 + i] = x;
@@ -1197,7 +1217,7 @@ __global__ __launch_bounds__(kThreads, ROOT ? 2 : 4) void ord_scale(
       src[(i - 3 * sp) * (v.m3 / 3) + sp] = Real(hw[sp] * x);
     }
   }
-  if (blockIdx.x != 0) return;
+  if (blk != 0) return;
   if (t == 0) v.st[s].beta[k - 1] = beta;
   if constexpr (ROOT) {
     __syncthreads();
@@ -1552,7 +1572,7 @@ __global__ __launch_bounds__(kSmallThreads) void lz_small(
 #pragma unroll
     for (int r = 0; r < EPT; ++r) v[r] = wn > 0.0 ? v[r] / wn : 0.0;
     if (blockIdx.x == 0) {
-      reset_state(SegView{nullptr, nullptr, st, nullptr, nullptr, 1, m3}, 0, wn);
+      reset_state(SegView{nullptr, nullptr, st, nullptr, nullptr, 1, m3, nullptr, nullptr}, 0, wn);
       if (A.mw)
 #pragma unroll
         for (int r = 0; r < EPT; ++r)
@@ -1740,11 +1760,27 @@ __global__ void multiply_by(int64_t m, double *x, const double *__restrict__ s) 
 inline unsigned nblk(int64_t m) { return unsigned((m + kThreads - 1) / kThreads); }
 
 
+// Grids of the kernels over every process's elements: workgroups of kThreads and of 4 kThreads values.
+struct SegGrids {
+  BlockList one, four;
+};
+SegGrids seg_grids(const Batch &b) {
+  static_assert(kBlockValues[1] == kThreads && kBlockValues[2] == 4 * kThreads, "their lists");
+  return SegGrids{b.blocks[1], b.blocks[2]};
+}
+SegGrids one_process_grids(int64_t m3) {
+  SegGrids g;
+  g.one.total = std::max(1u, nblk(m3));
+  g.one.grid.x = unsigned(g.one.total);
+  g.four.total = (g.one.total + 3) / 4;
+  g.four.grid.x = unsigned(g.four.total);
+  return g;
+}
+inline int64_t launched(const BlockList &b) { return int64_t(b.grid.x) * b.grid.y; }
+
 // Elements per thread of lz_dots and lz_update: one while the grid then fits the device at once (two
 // workgroups per CU, by the registers of the root), else four.
-inline int ept_of(int nsys, int64_t longest) {
-  return int64_t(nsys) * nblk(longest) <= 512 ? 1 : 4;
-}
+inline int ept_of(const SegGrids &g) { return launched(g.one) <= 512 ? 1 : 4; }
 inline int groups_of(int64_t longest, int ept) {
   return int(std::max<int64_t>(1, (longest + kThreads * ept - 1) / (int64_t(kThreads) * ept)));
 }
@@ -1759,9 +1795,9 @@ struct LzPartials {
 };
 inline bool one_process(const SegView &v) { return v.offs == nullptr; }
 
-int lz_partials(rpb_ctx *ctx, int nsys, int64_t longest, LzPartials *out) {
+int lz_partials(rpb_ctx *ctx, int nsys, int64_t longest, const SegGrids &g, LzPartials *out) {
   out->stride = std::max<int64_t>({1, (longest + kPartRows - 1) / kPartRows, 256});
-  out->nb = groups_of(longest, ept_of(nsys, longest));
+  out->nb = groups_of(longest, ept_of(g));
   const int64_t dots = int64_t(kMaxKrylov + 1) * std::max(out->nb, 256);
   int st;
   out->norm = static_cast<double *>(workspace(
@@ -1778,10 +1814,10 @@ constexpr bool ordered_sums() { return std::is_same<Real, float>::value; }
 
 // |w|, v_1 and the state of every process.
 template <typename Real>
-int start_processes(rpb_ctx *ctx, const SegView &v, int64_t longest, const double *w,
+int start_processes(rpb_ctx *ctx, const SegView &v, const SegGrids &g, const double *w,
                     const LzPartials &P, double *V, const double *hw, Real *src, const double *mw,
                     double *u, int *counter, hipStream_t stream) {
-  const dim3 grid{std::max(1u, nblk(longest)), unsigned(v.nsys), 1u};
+  const dim3 grid = g.one.grid;
   if constexpr (ordered_sums<Real>()) {
     auto run = [&](auto T) -> int {
       constexpr bool kT = decltype(T)::value;
@@ -1806,13 +1842,13 @@ int start_processes(rpb_ctx *ctx, const SegView &v, int64_t longest, const doubl
 // The vector work, root and stop test of iteration k of every process after u = M v_k; dotted:
 // alpha's partials are there already.
 template <typename Real>
-int iterate_processes(rpb_ctx *ctx, const SegView &v, int64_t longest, int k, double tol,
+int iterate_processes(rpb_ctx *ctx, const SegView &v, const SegGrids &g, int k, double tol,
                       double *V, double *u, bool dotted, const LzPartials &P, bool write_next,
                       const double *hw, Real *src, int *counter, const LzReport &rep,
                       hipStream_t stream) {
   const double *vk = V + int64_t(k - 1) * v.m3;
   const unsigned ns = unsigned(v.nsys);
-  const dim3 all{std::max(1u, nblk(longest)), ns, 1u};
+  const dim3 all = g.one.grid;
   auto root = [&]() -> int {
     lz_root<<<ns, kThreads, 0, stream>>>(v, k, tol, rep);
     RPB_LAUNCHED(ctx);
@@ -1830,7 +1866,7 @@ int iterate_processes(rpb_ctx *ctx, const SegView &v, int64_t longest, int k, do
       RPB_LAUNCHED(ctx);
       ord_update<kT><<<dim3{NB, ns, 1u}, kThreads, 0, stream>>>(v, k, V, u, P.dots, bpart);
       RPB_LAUNCHED(ctx);
-      if (int64_t(all.x) * ns <= 512) {
+      if (launched(g.one) <= 512) {
         ord_scale<kT, Real, true><<<all, kThreads, 0, stream>>>(
             v, k, tol, V, u, bpart, write_next, hw, src, counter, rep);
         RPB_LAUNCHED(ctx);
@@ -1847,11 +1883,11 @@ int iterate_processes(rpb_ctx *ctx, const SegView &v, int64_t longest, int k, do
       lz_dot<<<all, kThreads, 0, stream>>>(v, vk, u, 1, P.alpha, P.stride);
       RPB_LAUNCHED(ctx);
     }
-    const int ept = ept_of(v.nsys, longest);
-    const dim3 grid{unsigned(P.nb), ns, 1u};
+    const int ept = ept_of(g);
     auto run = [&](auto E, auto R) -> int {
       constexpr int kE = decltype(E)::value;
       constexpr bool kR = decltype(R)::value;
+      const dim3 grid = kE == 1 ? g.one.grid : g.four.grid;
       lz_dots<kE><<<grid, kThreads, 0, stream>>>(v, k, V, u, P.alpha, P.stride, P.dots, P.nb);
       RPB_LAUNCHED(ctx);
       lz_update<kE, Real, kR><<<grid, kThreads, 0, stream>>>(v, k, tol, V, u, P.dots, P.nb,
@@ -1862,7 +1898,7 @@ int iterate_processes(rpb_ctx *ctx, const SegView &v, int64_t longest, int k, do
     using E1 = std::integral_constant<int, 1>;
     using E4 = std::integral_constant<int, 4>;
     if (ept == 1) return run(E1{}, std::true_type{});
-    if (int64_t(P.nb) * v.nsys <= 512) return run(E4{}, std::true_type{});
+    if (launched(g.four) <= 512) return run(E4{}, std::true_type{});
     return run(E4{}, std::false_type{});
   }
 }
@@ -1969,7 +2005,8 @@ int lanczos_run(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const double
   double *u = static_cast<double *>(workspace(ctx, WS_VEC_A, size_t(m3) * sizeof(double), &st));
   if (!u) return st;
   LzPartials P;
-  RPB_TRY(lz_partials(ctx, 1, m3, &P));
+  const SegGrids grids = one_process_grids(m3);
+  RPB_TRY(lz_partials(ctx, 1, m3, grids, &P));
   LzState *ls = static_cast<LzState *>(workspace(ctx, WS_SMALL, kSmallBytes, &st));
   if (!ls) return st;
   LzEig *eig = static_cast<LzEig *>(workspace(ctx, WS_LZEIG, sizeof(LzEig), &st));
@@ -1997,12 +2034,12 @@ int lanczos_run(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const double
       if (!src) return st;
     }
     const double *hw = prepack ? packed_weights(g) : nullptr;
-    const SegView view{nullptr, nullptr, ls, nullptr, eig, 1, m3};
+    const SegView view{nullptr, nullptr, ls, nullptr, eig, 1, m3, nullptr, nullptr};
     if (f64)
-      RPB_TRY(start_processes(ctx, view, m3, w, P, V, hw, static_cast<double *>(src), mw, u,
+      RPB_TRY(start_processes(ctx, view, grids, w, P, V, hw, static_cast<double *>(src), mw, u,
                               nullptr, stream));
     else
-      RPB_TRY(start_processes(ctx, view, m3, w, P, V, hw, static_cast<float *>(src), mw, u,
+      RPB_TRY(start_processes(ctx, view, grids, w, P, V, hw, static_cast<float *>(src), mw, u,
                               nullptr, stream));
     LzRing *ring_dev = lz_ring_dev(ctx);
     const int *stopped = &ls->reason;
@@ -2032,10 +2069,10 @@ int lanczos_run(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const double
       }
       const LzReport rep{&ring_dev->slot[slot], nullptr, epoch};
       if (f64)
-        RPB_TRY(iterate_processes(ctx, view, m3, k, tol, V, u, dotted, P, k < max_iter, hw,
+        RPB_TRY(iterate_processes(ctx, view, grids, k, tol, V, u, dotted, P, k < max_iter, hw,
                                   static_cast<double *>(src), nullptr, rep, stream));
       else
-        RPB_TRY(iterate_processes(ctx, view, m3, k, tol, V, u, dotted, P, k < max_iter, hw,
+        RPB_TRY(iterate_processes(ctx, view, grids, k, tol, V, u, dotted, P, k < max_iter, hw,
                                   static_cast<float *>(src), nullptr, rep, stream));
       RPB_TRY(read_statuses(ctx, epoch, k < max_iter ? k - 1 : k, &next_q, &o, stream));
       // launches past the stop returned at once: drop their timing records
@@ -2104,7 +2141,8 @@ int lanczos_segments(rpb_ctx *ctx, const Batch &b, const double *L, double *t, c
   double *u = static_cast<double *>(workspace(ctx, WS_VEC_A, size_t(m3) * sizeof(double), &st));
   if (!u) return st;
   LzPartials P;
-  RPB_TRY(lz_partials(ctx, nsys, longest, &P));
+  const SegGrids grids = seg_grids(b);
+  RPB_TRY(lz_partials(ctx, nsys, longest, grids, &P));
   const size_t states_bytes = size_t(nsys) * sizeof(LzState);
   const size_t status_off = lz_status_offset(nsys);
   char *lz = static_cast<char *>(
@@ -2113,7 +2151,8 @@ int lanczos_segments(rpb_ctx *ctx, const Batch &b, const double *L, double *t, c
   LzEig *eig = static_cast<LzEig *>(workspace(ctx, WS_LZEIG, size_t(nsys) * sizeof(LzEig), &st));
   if (!eig) return st;
   const SegView v{b.offs, b.sys_of, reinterpret_cast<LzState *>(lz),
-                  reinterpret_cast<int *>(lz + states_bytes), eig, nsys, m3};
+                  reinterpret_cast<int *>(lz + states_bytes), eig, nsys, m3,
+                  grids.one.list, grids.four.list};
   LzStatus *status_dev = reinterpret_cast<LzStatus *>(lz + status_off);
   const unsigned ns = unsigned(nsys);
   // every process reports each iteration into its word of the pinned buffer
@@ -2127,10 +2166,10 @@ int lanczos_segments(rpb_ctx *ctx, const Batch &b, const double *L, double *t, c
   std::vector<int> known;   // host copy of the flags, once read
 
   if (f64)
-    RPB_TRY(start_processes(ctx, v, longest, w, P, V, hw, static_cast<double *>(src), mw, u,
+    RPB_TRY(start_processes(ctx, v, grids, w, P, V, hw, static_cast<double *>(src), mw, u,
                             counter, stream));
   else
-    RPB_TRY(start_processes(ctx, v, longest, w, P, V, hw, static_cast<float *>(src), mw, u, counter,
+    RPB_TRY(start_processes(ctx, v, grids, w, P, V, hw, static_cast<float *>(src), mw, u, counter,
                             stream));
   size_t mark[kLzRing] = {};   // first timing record of each iteration in flight
   int next_q = 1;              // first iteration whose flags the host has not read
@@ -2165,10 +2204,10 @@ int lanczos_segments(rpb_ctx *ctx, const Batch &b, const double *L, double *t, c
       RPB_LAUNCHED(ctx);
     } else {
       if (f64)
-        RPB_TRY(iterate_processes(ctx, v, longest, k, tol, V, u, job.dot.done, P, next, hw,
+        RPB_TRY(iterate_processes(ctx, v, grids, k, tol, V, u, job.dot.done, P, next, hw,
                                   static_cast<double *>(src), counter, rep, stream));
       else
-        RPB_TRY(iterate_processes(ctx, v, longest, k, tol, V, u, job.dot.done, P, next, hw,
+        RPB_TRY(iterate_processes(ctx, v, grids, k, tol, V, u, job.dot.done, P, next, hw,
                                   static_cast<float *>(src), counter, rep, stream));
     }
     if (!sync_each) continue;

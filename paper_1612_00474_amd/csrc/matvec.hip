@@ -1946,7 +1946,7 @@ int prepare_batch(rpb_ctx *ctx, int32_t nsys, const int64_t *offs, int precision
   }
 
   // device copies: offs (nsys + 1 int64), part_base (nsys int64), items, the workgroup lists,
-  // sys_of (n int32); all but the last staged through pinned memory
+  // sys_of (n int32); all but the last staged through pinned memory in one copy
   const size_t offs_bytes = size_t(2 * nsys + 1) * sizeof(int64_t);
   const size_t items_bytes = std::max<size_t>(1, items.size()) * sizeof(int4);
   const size_t offs_pad = (offs_bytes + 255) / 256 * 256;
@@ -1979,18 +1979,12 @@ int prepare_batch(rpb_ctx *ctx, int32_t nsys, const int64_t *offs, int precision
               size_t(nsys) * sizeof(int64_t));
   int4 *hi = reinterpret_cast<int4 *>(hb + offs_pad);
   for (size_t q = 0; q < order.size(); ++q) hi[q] = items[order[q]];
-  RPB_HIP(ctx, hipMemcpyAsync(b->offs, hb, offs_bytes, hipMemcpyHostToDevice, stream));
-  if (!items.empty())
-    RPB_HIP(ctx, hipMemcpyAsync(b->items, hi, items.size() * sizeof(int4), hipMemcpyHostToDevice,
-                                stream));
   for (int q = 0; q < kBlockKinds; ++q) {
     if (lists[q].empty()) continue;
-    const size_t bytes = lists[q].size() * sizeof(int2);
-    std::memcpy(hb + lists_at[q], lists[q].data(), bytes);
+    std::memcpy(hb + lists_at[q], lists[q].data(), lists[q].size() * sizeof(int2));
     b->blocks[q].list = reinterpret_cast<const int2 *>(dev + lists_at[q]);
-    RPB_HIP(ctx, hipMemcpyAsync(dev + lists_at[q], hb + lists_at[q], bytes, hipMemcpyHostToDevice,
-                                stream));
   }
+  RPB_HIP(ctx, hipMemcpyAsync(dev, hb, host_bytes, hipMemcpyHostToDevice, stream));
   fill_sys_of<<<unsigned(nsys), 256, 0, stream>>>(nsys, b->offs, b->sys_of);
   RPB_LAUNCHED(ctx);
   return RPB_OK;

@@ -344,8 +344,8 @@ struct BlockList {
   dim3 grid{1u, 1u, 1u};
   int64_t total = 0;             // workgroups with work
 };
-constexpr int kBlockKinds = 2;
-constexpr int64_t kBlockValues[kBlockKinds] = {64, 256};   // values per workgroup
+constexpr int kBlockKinds = 3;
+constexpr int64_t kBlockValues[kBlockKinds] = {64, 256, 1024};   // values per workgroup
 constexpr int64_t kMaxGridY = 65535;
 
 struct Batch {

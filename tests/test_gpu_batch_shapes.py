@@ -76,3 +76,56 @@ def test_uneven_systems(ctx, precision, big):
         a, b = offs[s], offs[s + 1]
         ref = host(ctx.matvec(dev(pos[a:b]), dev(F[a:b]), dev(T[a:b]), precision))
         assert close(u[a:b], ref, TOL[precision]), s
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("sizes", [[3000] + [16] * 600 + [0, 1], [700, 0, 900, 513, 1] * 3,
+                                   [2] * 700 + [9000]])
+def test_uneven_lanczos(ctx, precision, sizes):
+    rng = np.random.default_rng(14)
+    offs = _offsets(sizes)
+    pos = np.vstack([_system(n, rng) for n in sizes if n])
+    W = rng.standard_normal(pos.shape)
+    m = 6
+    g, it, eps, st = ctx.lanczos_batched(dev(pos), offs, dev(W), 1e-300, m, precision,
+                                         allow_noconv=True)
+    g = host(g)
+    for s in sorted({0, 1, 2, 3, len(sizes) // 2, len(sizes) - 2, len(sizes) - 1}):
+        a, b = offs[s], offs[s + 1]
+        if a == b:
+            continue
+        ref, mref, _, _ = ctx.lanczos(dev(pos[a:b]), dev(W[a:b]), 1e-300, m, precision,
+                                      allow_noconv=True)
+        # a Krylov space of 3 n < 6 vectors ends at a breakdown: the iterates past it are rounding
+        if 3 * (b - a) > m:
+            assert it[s] == mref
+        # the Lanczos recurrence passes a rounding on with the square root's condition: a decade
+        assert close(g[a:b], host(ref), 10 * TOL[precision]), s
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_uneven_batch_costs_its_parts(ctx, precision):
+    """One system of 30,000 spheres and 4,095 single ones in one captured step (no host work in the
+    time) take about what they take apart; with the longest system's workgroups launched for
+    every system they took three times that."""
+    import time
+    import torch
+    rng = np.random.default_rng(15)
+
+    def step_time(sizes):
+        pos = dev(np.vstack([_system(n, rng) for n in sizes]))
+        u = torch.zeros_like(pos)
+        graph = ctx.step_graph(pos, u, _offsets(sizes), dt=1e-4, delta=1e-4, lanczos_tol=1e-300,
+                               lanczos_max_iter=8, precision=precision)
+        times = []
+        for _ in range(5):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            graph.launch()
+            torch.cuda.synchronize()
+            times.append(time.perf_counter() - t)
+        graph.close()
+        return min(times)
+
+    parts = step_time([30_000]) + step_time([1] * 4095)
+    assert step_time([30_000] + [1] * 4095) < 1.5 * parts
