@@ -1765,7 +1765,7 @@ struct SegGrids {
   BlockList one, four;
 };
 SegGrids seg_grids(const Batch &b) {
-  static_assert(kBlockValues[1] == kThreads && kBlockValues[2] == 4 * kThreads, "their lists");
+  static_assert(1 << kBlockShift[1] == kThreads && 1 << kBlockShift[2] == 4 * kThreads, "their lists");
   return SegGrids{b.blocks[1], b.blocks[2]};
 }
 SegGrids one_process_grids(int64_t m3) {

@@ -1177,9 +1177,8 @@ __global__ __launch_bounds__(kBlock) void pair_kernel_f64_sym_batched(
 
 // System s's partials start at part_base[s] and cover its whole triangle (one chunk).  As
 // reduce_sym_chunk with G threads per (component, row) and W wavefronts of 64 of them per
-// workgroup, all of one system (blocks: a BlockList's list of 64 W values); dpart: the system's partials of dotv . vel at
-// dpart[s * dstride].  Small batches take G = 8 (their few rows are many slots deep); a batch of
-// 282,705 spheres keeps the device full with one thread per row (34 us, 62 with eight).
+// workgroup, all of one system (blocks: a BlockList's list of 64 W values); dpart: the system's
+// partials of dotv . vel at dpart[s * dstride].
 template <typename Part, int G, int W>
 __global__ __launch_bounds__(64 * G * W) void reduce_partials_sym_batched(
     SymBatchArgs b, const int2 *__restrict__ blocks, const Part *__restrict__ partial,
@@ -1219,6 +1218,59 @@ __global__ __launch_bounds__(64 * G * W) void reduce_partials_sym_batched(
     vel[3 * row + d] = v;
   }
   if (dotv) store_dot_partial(live, v, dotv, 3 * row + d, dpart + s * dstride + set);
+}
+
+// The same sums, bit for bit, by one thread per (component, row) of the whole batch, without dotv: no
+// lane without a row, however small the systems.
+template <typename Part, int G>
+__global__ void reduce_partials_sym_rows(SymBatchArgs b, const int *__restrict__ sys_of,
+                                         const Part *__restrict__ partial,
+                                         const double *__restrict__ h, double scale,
+                                         double *__restrict__ vel) {
+  const int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (e >= 3 * b.n) return;
+  const int d = int(e / b.n);
+  const int64_t row = e - int64_t(d) * b.n;
+  const int s = sys_of[row];
+  if (b.done && b.done[s]) return;
+  const SymArgs a = sym_args_of(b, s);
+  const int64_t r = row - b.offs[s];
+  const PartMap pm{0, b.nsplit, b.ts, 1};
+  const Part *p = partial + b.part_base[s];
+  const int64_t L1 = a.nt * (a.nt + 1) / 2;
+  double v;
+  if constexpr (G == 1) {
+    v = chunk_row_sum(p, pm, a.nt, L1, r / a.ts, r % a.ts, 0, d);
+  } else {
+    // slot q is in group q mod G, in its running sum (q / G) mod 4 (chunk_row_sum_dealt)
+    const int64_t T = r / a.ts, local = r % a.ts, st = tri_start(T, a.nt);
+    const int ns = int(b.nsplit), ncol = int(T), nslots = ncol + int(a.nt - T) * ns;
+    double sum[4][G];
+#pragma unroll
+    for (int q = 0; q < 4 * G; ++q) sum[q / G][q % G] = 0.0;
+    for (int q0 = 0; q0 < nslots; q0 += 4 * G)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        if (q0 + j * G >= nslots) break;
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+          const int q = q0 + j * G + g, t = q - ncol;
+          if (q >= nslots) continue;
+          const int64_t o = q < ncol
+                                ? part_elem(pm, tri_start(q, a.nt) + T - q, ns, 0, d, local)
+                                : part_elem(pm, st + t / ns, t % ns, 0, d, local);
+          sum[j][g] += double(p[o]);
+        }
+      }
+    v = 0.0;
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      const double x = (sum[0][g] + sum[1][g]) + (sum[2][g] + sum[3][g]);
+      v = g == 0 ? x : v + x;
+    }
+  }
+  v *= scale * h[row];
+  vel[3 * row + d] = v;
 }
 
 __global__ void fill_sys_of(int nsys, const int64_t *__restrict__ offs, int *__restrict__ sys_of) {
@@ -1917,20 +1969,26 @@ int prepare_batch(rpb_ctx *ctx, int32_t nsys, const int64_t *offs, int precision
   int64_t max_chunks = 1;
   for (int s = 0; s < nsys; ++s)
     max_chunks = std::max<int64_t>(max_chunks, (offs[s + 1] - offs[s] + chunk - 1) / chunk);
+  int64_t longest_sys = 0;
+  for (int s = 0; s < nsys; ++s) longest_sys = std::max(longest_sys, offs[s + 1] - offs[s]);
+  b->max_slots = (longest_sys + per - 1) / per * b->nsplit;
   b->nitems = int(items.size());
   b->max_chunks = max_chunks;
 
   // workgroup lists of the kernels over rows
   std::vector<int2> lists[kBlockKinds];
   for (int q = 0; q < kBlockKinds; ++q) {
+    // (a shift: a batch of thousands of systems would notice the divisions)
+    const int shift = kBlockShift[q];
     auto groups = [&](int s) {
       return std::max<int64_t>(
-          1, (3 * (offs[s + 1] - offs[s]) + kBlockValues[q] - 1) / kBlockValues[q]);
+          1, (3 * (offs[s + 1] - offs[s]) + (int64_t(1) << shift) - 1) >> shift);
     };
     int64_t longest = 1, total = 0;
     for (int s = 0; s < nsys; ++s) {
-      longest = std::max(longest, groups(s));
-      total += groups(s);
+      const int64_t g = groups(s);
+      longest = std::max(longest, g);
+      total += g;
     }
     BlockList &bl = b->blocks[q];
     bl = BlockList{};
@@ -1942,7 +2000,7 @@ int prepare_batch(rpb_ctx *ctx, int32_t nsys, const int64_t *offs, int precision
     bl.grid = dim3{unsigned(total), 1u, 1u};
     lists[q].reserve(size_t(total));
     for (int s = 0; s < nsys; ++s)
-      for (int64_t g = 0; g < groups(s); ++g) lists[q].push_back(int2{s, int(g)});
+      for (int64_t g = 0, ng = groups(s); g < ng; ++g) lists[q].push_back(int2{s, int(g)});
   }
 
   // device copies: offs (nsys + 1 int64), part_base (nsys int64), items, the workgroup lists,
@@ -2035,7 +2093,7 @@ int matvec_batched_sym(rpb_ctx *ctx, const rpb_params *p, const Batch &b, const 
   auto reduce = [&](auto G, auto W) {
     constexpr int kG = decltype(G)::value, kW = decltype(W)::value;
     constexpr int kind = kW == 1 ? 0 : 1;
-    static_assert(kBlockValues[kind] == 64 * kW, "the list of this workgroup's values");
+    static_assert(1 << kBlockShift[kind] == 64 * kW, "the list of this workgroup's values");
     const BlockList &bl = b.blocks[kind];
     if (f64)
       reduce_partials_sym_batched<double, kG, kW><<<bl.grid, 64 * kG * kW, 0, stream>>>(
@@ -2044,10 +2102,37 @@ int matvec_batched_sym(rpb_ctx *ctx, const rpb_params *p, const Batch &b, const 
       reduce_partials_sym_batched<float, kG, kW><<<bl.grid, 64 * kG * kW, 0, stream>>>(
           args, bl.list, static_cast<const float *>(part), h, scale, vel, dotv, dpart, dstride);
   };
-  if (n < 65536)
-    reduce(std::integral_constant<int, kRedGroups>{}, std::integral_constant<int, 1>{});
-  else
-    reduce(std::integral_constant<int, 1>{}, std::integral_constant<int, 4>{});
+  auto rows = [&](auto G) {
+    constexpr int kG = decltype(G)::value;
+    const unsigned rgrid = blocks_for(3 * n, 256);
+    if (f64)
+      reduce_partials_sym_rows<double, kG><<<rgrid, 256, 0, stream>>>(
+          args, b.sys_of, static_cast<const double *>(part), h, scale, vel);
+    else
+      reduce_partials_sym_rows<float, kG><<<rgrid, 256, 0, stream>>>(
+          args, b.sys_of, static_cast<const float *>(part), h, scale, vel);
+  };
+  using One = std::integral_constant<int, 1>;
+  using Eight = std::integral_constant<int, kRedGroups>;
+  // Below 65,536 spheres a row's partials are summed in eight groups, by eight threads or by one:
+  // eight hide the latency of deep rows, but launch eight wavefronts for every 64 rows.  us, eight /
+  // one, with the sets of 64 rows and the slots of a row: 60,000 (2,813 sets, 472 slots) 59 / 105,
+  // 3 x 16,000 (2,250, 128) 30 / 49, 8 x 4,000 (1,504, 32) 12 / 15, 15 x 4,000 (2,820, 32) 19 / 17,
+  // 50 x 1,100 (2,600, 12) 14 / 9, 16 x 1,100 (832, 12) 7.0 / 7.6, 200 x 256 (2,400, 4) 9 / 5,
+  // 4,000 x 16 (4,000, 4) 12.5 / 6.  Larger batches keep the device full with one thread and sum
+  // in one group (282,705 spheres: 34 us, 62 in eight); where their systems are small, sets of
+  // 64 rows leave most lanes idle (60,000 among 4,000 x 16: 88 us in sets, 59 by rows).
+  const bool deep = b.blocks[0].total <= 48 * (16 + b.max_slots);
+  if (n >= 65536) {
+    if (dotv)
+      reduce(One{}, std::integral_constant<int, 4>{});
+    else
+      rows(One{});
+  } else if (dotv || deep) {
+    reduce(Eight{}, One{});
+  } else {
+    rows(Eight{});
+  }
   RPB_LAUNCHED(ctx);
   return RPB_OK;
 }

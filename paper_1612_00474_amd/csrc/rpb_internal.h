@@ -345,7 +345,7 @@ struct BlockList {
   int64_t total = 0;             // workgroups with work
 };
 constexpr int kBlockKinds = 3;
-constexpr int64_t kBlockValues[kBlockKinds] = {64, 256, 1024};   // values per workgroup
+constexpr int kBlockShift[kBlockKinds] = {6, 8, 10};   // 64, 256 and 1,024 values per workgroup
 constexpr int64_t kMaxGridY = 65535;
 
 struct Batch {
@@ -362,6 +362,7 @@ struct Batch {
   int *sys_of = nullptr;         // device, n entries
   bool symmetric = false;        // items are (system, I, J, part) of the symmetric kernel
   int nsplit = 1;                // source parts per symmetric tile pair
+  int64_t max_slots = 0;         // symmetric partials of a row of the largest system
   int64_t *part_base = nullptr;  // device, nsys entries: each system's first partial slot
   BlockList blocks[kBlockKinds]; // by values per workgroup
   int64_t part_elems = 0;        // partial elements of the symmetric layout (float32 in mixed precision)

@@ -79,6 +79,19 @@ def test_uneven_systems(ctx, precision, big):
 
 
 @pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("n,few,many", [(1100, 16, 50), (256, 20, 200), (1030, 8, 55)])
+def test_reduction_forms_agree_bitwise(ctx, precision, n, few, many):
+    """Eight threads per row (few systems) and one (many) add a row's partials in the same order; both
+    batches split their tile pairs alike."""
+    rng = np.random.default_rng(16)
+    pos = np.vstack([_system(n, rng) for _ in range(many)])
+    F = rng.standard_normal(pos.shape)
+    u = [host(ctx.matvec_batched(dev(pos[:k * n]), _offsets([n] * k), dev(F[:k * n]), None, precision))
+         for k in (few, many)]
+    assert np.array_equal(u[0], u[1][:few * n])
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
 @pytest.mark.parametrize("sizes", [[3000] + [16] * 600 + [0, 1], [700, 0, 900, 513, 1] * 3,
                                    [2] * 700 + [9000]])
 def test_uneven_lanczos(ctx, precision, sizes):
