@@ -676,18 +676,13 @@ __device__ void tridiag_body(int m, double tol, LzState *__restrict__ st, LzEig 
   }
 }
 
-// A tag into pinned host memory, after everything the thread has stored before it.
-__device__ __forceinline__ void post_tag(int *word, int tag) {
-  __threadfence_system();
-  __hip_atomic_store(word, tag, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-}
-
-// Status words of iteration k into the host's ring slot, by one thread after the state is final.
+// Status words of iteration k into the host's ring slot, by one thread after the state is final; the
+// release orders the tag after the two words before it.
 __device__ __forceinline__ void post_status(const LzState *__restrict__ st, LzRingSlot *slot,
                                             int tag) {
   slot->eps = st->eps;
   slot->reason = st->reason;
-  post_tag(&slot->tag, tag);
+  __hip_atomic_store(&slot->tag, tag, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // ---- Krylov processes on segments of concatenated vectors -------------------------------------
@@ -928,7 +923,10 @@ __device__ __forceinline__ void report_stop(const SegView &v, int s, int k, bool
     v.done[s] = 1;
     if (atomicAdd(v.done + v.nsys + 1, 1) + 1 == v.nsys) v.done[v.nsys] = 1;
   }
-  if (rep.words) post_tag(rep.words + s, lz_tag(rep.epoch, k) | (stop ? kTagStop : 0));
+  // the word says all that the host reads, so it need not wait for earlier stores
+  if (rep.words)
+    __hip_atomic_store(rep.words + s, lz_tag(rep.epoch, k) | (stop ? kTagStop : 0),
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // The root of T_k and the stop test of process s by one workgroup, beta_k being in the state.

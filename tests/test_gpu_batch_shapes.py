@@ -142,3 +142,39 @@ def test_uneven_batch_costs_its_parts(ctx, precision):
 
     parts = step_time([30_000]) + step_time([1] * 4095)
     assert step_time([30_000] + [1] * 4095) < 1.5 * parts
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_status_words_cost_little(ctx, precision):
+    """An iteration of a solve whose 4,096 processes report to the host takes about what it takes in a
+    captured step, which reports nothing (with a system-wide fence before each word it took 1.4
+    times that)."""
+    import time
+    import torch
+    rng = np.random.default_rng(17)
+    nsys = 4096
+    pos = dev(np.vstack([_system(8, rng) for _ in range(8)] * (nsys // 8)))
+    offs, w = _offsets([8] * nsys), dev(rng.standard_normal((8 * nsys, 3)))
+
+    def best(call):
+        times = []
+        for _ in range(7):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            call()
+            torch.cuda.synchronize()
+            times.append(time.perf_counter() - t)
+        return min(times)
+
+    def eager(m):
+        return best(lambda: ctx.lanczos_batched(pos, offs, w, 1e-300, m, precision,
+                                                allow_noconv=True))
+
+    def captured(m):
+        graph = ctx.step_graph(pos.clone(), torch.zeros_like(pos), offs, dt=1e-6, delta=1e-4,
+                               lanczos_tol=1e-300, lanczos_max_iter=m, precision=precision)
+        t = best(graph.launch)
+        graph.close()
+        return t
+
+    assert eager(14) - eager(2) < 1.2 * (captured(14) - captured(2))
