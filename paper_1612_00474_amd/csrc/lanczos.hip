@@ -89,12 +89,17 @@ __global__ void basis_combine(int64_t m, int nvec, const double *__restrict__ V,
   out[i] = acc;
 }
 
+// Orders a wavefront's own accesses before its later accesses to other lanes' words.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // Eigendecomposition of T_m kept from one order to the next (the eigensolve of T_{m+1} updates
-// it): eigenvalues in increasing order and the eigenvector matrix of T_m in Q[m & 1],
-// column-major.
+// it): eigenvalues in increasing order and the eigenvector matrix of T_m, column-major.
 struct LzEig {
   double lam[kMaxKrylov];
-  double Q[2][kMaxKrylov * kMaxKrylov];   // Q[..][col * kMaxKrylov + row]
+  double Q[kMaxKrylov * kMaxKrylov];   // Q[col * kMaxKrylov + row]
 };
 
 // LDS of the root of T_m: the quadrature's transposed sums or the arrowhead's eigenvectors.
@@ -294,8 +299,8 @@ __device__ int eig_update(int m, const LzState *__restrict__ st, LzEig *__restri
                           double *__restrict__ U) {
   // column-major (entry [row or component] fastest), so that the lanes of a wavefront, which
   // take consecutive rows, touch consecutive words; U (LDS, kRootPool): eigenvectors of the
-  // arrowhead, [j * 64 + i].  The old Q is rotated in place, the new one goes to the other buffer.
-  double *Qs = eig->Q[(m - 1) & 1], *Qn = eig->Q[m & 1];
+  // arrowhead, [j * 64 + i].  Q is rotated and then replaced in place.
+  double *Q = eig->Q;
   __shared__ double dd[kMaxKrylov], zz[kMaxKrylov], dn[kMaxKrylov], z2n[kMaxKrylov];
   __shared__ double zh[kMaxKrylov], tau_s[kMaxKrylov], dK_s[kMaxKrylov], val[kMaxKrylov];
   __shared__ double rot_c[kMaxKrylov], rot_s[kMaxKrylov];
@@ -309,7 +314,7 @@ __device__ int eig_update(int m, const LzState *__restrict__ st, LzEig *__restri
   if (m == 1) {
     if (tid == 0) {
       eig->lam[0] = st->alpha[0];
-      Qn[0] = 1.0;
+      Q[0] = 1.0;
     }
     __syncthreads();
     return 0;
@@ -319,7 +324,7 @@ __device__ int eig_update(int m, const LzState *__restrict__ st, LzEig *__restri
   if (w0) {
     if (lane < n1) {
       dd[lane] = eig->lam[lane];
-      zz[lane] = beta * Qs[lane * kMaxKrylov + (n1 - 1)];
+      zz[lane] = beta * Q[lane * kMaxKrylov + (n1 - 1)];
     }
     // deflation tolerance from |T_m| <= max(|lambda|, |alpha|) + |beta|
     double amax = lane < n1 ? fabs(eig->lam[lane]) : 0.0;
@@ -396,9 +401,9 @@ __device__ int eig_update(int m, const LzState *__restrict__ st, LzEig *__restri
     const int a = rot_p[q], b = rot_j[q];
     const double c = rot_c[q], sn = rot_s[q];
     for (int r = tid; r < n1; r += nthr) {
-      const double qa = Qs[a * 64 + r], qb = Qs[b * 64 + r];
-      Qs[a * 64 + r] = c * qa - sn * qb;
-      Qs[b * 64 + r] = sn * qa + c * qb;
+      const double qa = Q[a * 64 + r], qb = Q[b * 64 + r];
+      Q[a * 64 + r] = c * qa - sn * qb;
+      Q[b * 64 + r] = sn * qa + c * qb;
     }
     __syncthreads();
   }
@@ -462,10 +467,11 @@ __device__ int eig_update(int m, const LzState *__restrict__ st, LzEig *__restri
     if (lane == 0) info[3] = bad;
   }
   __syncthreads();
-  // new eigenvectors: column rank(e) of Q_m, rows 0..m-1
-  for (int x = tid; x < m * m; x += nthr) {
-    const int e = x / m, r = x - e * m;
-    double v;
+  // new eigenvectors: column rank(e) of Q_m, rows 0..m-1.  A row of the new Q needs the same row of
+  // the old one only, so a wavefront takes a row (lane e its entry e) and overwrites it.
+  for (int r = tid >> 6; r < m; r += nthr / 64) {
+    const int e = lane;
+    double v = 0.0;
     if (e <= p) {
       if (r < n1) {
         // four running sums keep several loads in flight
@@ -473,16 +479,17 @@ __device__ int eig_update(int m, const LzState *__restrict__ st, LzEig *__restri
         int j = 0;
         for (; j + 4 <= p; j += 4)
 #pragma unroll
-          for (int q = 0; q < 4; ++q) v4[q] += Qs[nd_s[j + q] * 64 + r] * U[(j + q) * 64 + e];
-        for (; j < p; ++j) v4[0] += Qs[nd_s[j] * 64 + r] * U[j * 64 + e];
+          for (int q = 0; q < 4; ++q) v4[q] += Q[nd_s[j + q] * 64 + r] * U[(j + q) * 64 + e];
+        for (; j < p; ++j) v4[0] += Q[nd_s[j] * 64 + r] * U[j * 64 + e];
         v = (v4[0] + v4[1]) + (v4[2] + v4[3]);
       } else {
         v = U[p * 64 + e];
       }
-    } else {
-      v = r < n1 ? Qs[df_s[e - p - 1] * 64 + r] : 0.0;
+    } else if (e < m && r < n1) {
+      v = Q[df_s[e - p - 1] * 64 + r];
     }
-    Qn[rank_s[e] * kMaxKrylov + r] = v;
+    wave_sync();
+    if (e < m) Q[rank_s[e] * kMaxKrylov + r] = v;
   }
   __syncthreads();
   return info[3];
@@ -512,12 +519,6 @@ struct RootLds {
   double z[kMaxKrylov + 2];                // padded, z[i + 1]
   int ok;
 };
-
-// Orders a wavefront's own LDS writes before its later reads of other lanes' words.
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
 
 // The weighted solutions of this thread's node for the leading M rows (rows past m are decoupled),
 // summed over each wavefront into L.sum.
@@ -630,7 +631,7 @@ __device__ void tridiag_body(int m, double tol, LzState *__restrict__ st, LzEig 
       __syncthreads();
     }
     if (lane < 64) {
-      const double *Q = eig->Q[m & 1];
+      const double *Q = eig->Q;
       const double lmin = eig->lam[0], lmax = eig->lam[m - 1];
       indefinite = lmin < -1e-12 * fmax(lmax, 0.0);
       // lane k forms sqrt(lambda_k) q_k[0], then lane r sums row r
@@ -755,10 +756,10 @@ __device__ __forceinline__ void seg_block(const SegView &v, int &s, int &blk) {
 }
 
 // One partial per 64 elements of a . b over each live process (workgroups of kThreads values);
-// partial q of process s at part[s * stride + q].
+// partials of process s from part[first_partial(its first element, s, kPartRows)].
 __global__ __launch_bounds__(kThreads) void lz_dot(SegView v, const double *__restrict__ a,
                                                    const double *__restrict__ b, int check_done,
-                                                   double *__restrict__ part, int64_t stride) {
+                                                   double *__restrict__ part) {
   int s, blk;
   seg_block<1>(v, s, blk);
   if (check_done && v.done && v.done[s]) return;
@@ -767,7 +768,8 @@ __global__ __launch_bounds__(kThreads) void lz_dot(SegView v, const double *__re
   const int64_t i = e0 + int64_t(blk) * kThreads + threadIdx.x;
   const double x = wave_sum(i < e1 ? a[i] * b[i] : 0.0);
   const int64_t q = int64_t(blk) * (kThreads / 64) + (threadIdx.x >> 6);
-  if ((threadIdx.x & 63) == 0 && e0 + q * kPartRows < e1) part[s * stride + q] = x;
+  if ((threadIdx.x & 63) == 0 && e0 + q * kPartRows < e1)
+    part[first_partial(e0, s, kPartRows) + q] = x;
 }
 
 // The state of process s at its start, by one workgroup.
@@ -793,7 +795,7 @@ __global__ __launch_bounds__(kThreads) void lz_start(
     SegView v, const double *__restrict__ w, const double *__restrict__ npart,
     double *__restrict__ V, const double *__restrict__ hw, Real *__restrict__ src,
     const double *__restrict__ mw, double *__restrict__ u, double *__restrict__ apart,
-    int64_t stride, int *counter) {
+    int *counter) {
   __shared__ double sh[kThreads / 64];
   const int t = threadIdx.x;
   int s, blk;
@@ -806,7 +808,8 @@ __global__ __launch_bounds__(kThreads) void lz_start(
   seg_range(v, s, e0, e1);
   if (blk > 0 && e0 + int64_t(blk) * kThreads >= e1) return;
   const double wn =
-      sqrt(sum_partials(npart + s * stride, (e1 - e0 + kPartRows - 1) / kPartRows, sh));
+      sqrt(sum_partials(npart + first_partial(e0, s, kPartRows),
+                        (e1 - e0 + kPartRows - 1) / kPartRows, sh));
   if (blk == 0) reset_state(v, s, wn);
   const int64_t i = e0 + int64_t(blk) * kThreads + t;
   double a = 0.0;
@@ -826,7 +829,8 @@ __global__ __launch_bounds__(kThreads) void lz_start(
   if (!mw) return;
   a = wave_sum(a);
   const int64_t q = int64_t(blk) * (kThreads / 64) + (t >> 6);
-  if ((t & 63) == 0 && e0 + q * kPartRows < e1) apart[s * stride + q] = a;
+  if ((t & 63) == 0 && e0 + q * kPartRows < e1)
+    apart[first_partial(e0, s, kPartRows) + q] = a;
 }
 
 // Workgroups of a process of `len` elements in lz_dots and lz_update.
@@ -836,13 +840,19 @@ __device__ __forceinline__ int seg_groups(int64_t len) {
   return g > 0 ? int(g) : 1;
 }
 
+// Process s's partials of h_j (j < k) and |u|^2 (j = k): one per workgroup, those of j from dots_at + j
+// times its workgroups.
+template <int EPT>
+__device__ __forceinline__ int64_t dots_at(int64_t e0, int s) {
+  return (kMaxKrylov + 1) * first_partial(e0, s, kThreads * EPT);
+}
+
 template <int EPT>
 __global__ __launch_bounds__(kThreads) void lz_dots(SegView v, int k,
                                                     const double *__restrict__ V,
                                                     double *__restrict__ u,
                                                     const double *__restrict__ apart,
-                                                    int64_t stride, double *__restrict__ part,
-                                                    int nb) {
+                                                    double *__restrict__ part) {
   constexpr int W = kThreads / 64;
   __shared__ double sh[W];
   __shared__ double hsh[(kMaxKrylov + 1) * W];   // wavefront sums: [j * W + wave]
@@ -852,7 +862,8 @@ __global__ __launch_bounds__(kThreads) void lz_dots(SegView v, int k,
   if (v.done && v.done[s]) return;
   int64_t e0, e1;
   seg_range(v, s, e0, e1);
-  if (blk >= seg_groups<EPT>(e1 - e0)) return;
+  const int ng = seg_groups<EPT>(e1 - e0);
+  if (blk >= ng) return;
   LzState *st = v.st + s;
   const double *vk = V + int64_t(k - 1) * v.m3;
   const double *vp = V + int64_t(k > 1 ? k - 2 : 0) * v.m3;
@@ -869,7 +880,8 @@ __global__ __launch_bounds__(kThreads) void lz_dots(SegView v, int k,
     xv[r] = in[r] ? vk[ix[r]] : 0.0;
     xp[r] = in[r] && k > 1 ? vp[ix[r]] : 0.0;
   }
-  const double al = sum_partials(apart + s * stride, (e1 - e0 + kPartRows - 1) / kPartRows, sh);
+  const double al = sum_partials(apart + first_partial(e0, s, kPartRows),
+                                 (e1 - e0 + kPartRows - 1) / kPartRows, sh);
   if (blk == 0 && t == 0) st->alpha[k - 1] = al;
   double nrm = 0.0;
 #pragma unroll
@@ -905,7 +917,7 @@ __global__ __launch_bounds__(kThreads) void lz_dots(SegView v, int k,
     double r = hsh[t * W];
 #pragma unroll
     for (int w = 1; w < W; ++w) r += hsh[t * W + w];
-    part[(int64_t(s) * (kMaxKrylov + 1) + t) * nb + blk] = r;
+    part[dots_at<EPT>(e0, s) + int64_t(t) * ng + blk] = r;
   }
 }
 
@@ -952,7 +964,7 @@ __global__ __launch_bounds__(kThreads) void lz_root(SegView v, int k, double tol
 template <int EPT, typename Real, bool ROOT>
 __global__ __launch_bounds__(kThreads, 2) void lz_update(
     SegView v, int k, double tol, double *__restrict__ V, const double *__restrict__ u,
-    const double *__restrict__ part, int nb, int write_next, const double *__restrict__ hw,
+    const double *__restrict__ part, int write_next, const double *__restrict__ hw,
     Real *__restrict__ src, int *counter, LzReport rep) {
   __shared__ double hs[kMaxKrylov + 1];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
@@ -966,7 +978,7 @@ __global__ __launch_bounds__(kThreads, 2) void lz_update(
   if (blk >= ng) return;
   LzState *st = v.st + s;
   for (int j = wave; j <= k; j += kThreads / 64) {
-    const double *p = part + (int64_t(s) * (kMaxKrylov + 1) + j) * nb;
+    const double *p = part + dots_at<EPT>(e0, s) + int64_t(j) * ng;
     double a = 0.0;
     for (int b = lane; b < ng; b += 64) a += p[b];
     a = wave_sum(a);
@@ -1779,30 +1791,29 @@ inline int64_t launched(const BlockList &b) { return int64_t(b.grid.x) * b.grid.
 // Elements per thread of lz_dots and lz_update: one while the grid then fits the device at once (two
 // workgroups per CU, by the registers of the root), else four.
 inline int ept_of(const SegGrids &g) { return launched(g.one) <= 512 ? 1 : 4; }
-inline int groups_of(int64_t longest, int ept) {
-  return int(std::max<int64_t>(1, (longest + kThreads * ept - 1) / (int64_t(kThreads) * ept)));
-}
 
 // Partial sums of the processes' scalars: float64 processes take one partial of |w|^2 and of
 // alpha per 64 rows and one of each basis product per workgroup of lz_dots, mixed ones the
 // grouping of the ord_ kernels.
 struct LzPartials {
   double *norm, *alpha, *dots;   // dots: basis products, then |u|^2
-  int64_t stride;                // partials of alpha per process
-  int nb;                        // workgroups of lz_dots
 };
 inline bool one_process(const SegView &v) { return v.offs == nullptr; }
 
-int lz_partials(rpb_ctx *ctx, int nsys, int64_t longest, const SegGrids &g, LzPartials *out) {
-  out->stride = std::max<int64_t>({1, (longest + kPartRows - 1) / kPartRows, 256});
-  out->nb = groups_of(longest, ept_of(g));
-  const int64_t dots = int64_t(kMaxKrylov + 1) * std::max(out->nb, 256);
+// vectors: the separate kernels of an iteration run (no fused workgroup per process).
+int lz_partials(rpb_ctx *ctx, const SegView &v, const SegGrids &g, bool f64, bool vectors,
+                LzPartials *out) {
+  const int64_t ns = v.nsys;
+  const int64_t nb = one_process(v) ? ord_blocks<true>() : ord_blocks<false>();
+  const int64_t scalar = f64 ? first_partial(v.m3, ns, kPartRows) + 1 : ns * nb;
+  const int64_t groups = f64 ? first_partial(v.m3, ns, kThreads * ept_of(g)) + 1 : ns * nb;
+  const int64_t dots = vectors ? (kMaxKrylov + 1) * groups : 0;
   int st;
-  out->norm = static_cast<double *>(workspace(
-      ctx, WS_REDUCE, size_t(nsys) * size_t(2 * out->stride + dots) * sizeof(double), &st));
+  out->norm = static_cast<double *>(
+      workspace(ctx, WS_REDUCE, size_t(2 * scalar + dots) * sizeof(double), &st));
   if (!out->norm) return st;
-  out->alpha = out->norm + int64_t(nsys) * out->stride;
-  out->dots = out->alpha + int64_t(nsys) * out->stride;
+  out->alpha = out->norm + scalar;
+  out->dots = out->alpha + scalar;
   return RPB_OK;
 }
 
@@ -1828,10 +1839,10 @@ int start_processes(rpb_ctx *ctx, const SegView &v, const SegGrids &g, const dou
     };
     return one_process(v) ? run(std::true_type{}) : run(std::false_type{});
   } else {
-    lz_dot<<<grid, kThreads, 0, stream>>>(v, w, w, 0, P.norm, P.stride);
+    lz_dot<<<grid, kThreads, 0, stream>>>(v, w, w, 0, P.norm);
     RPB_LAUNCHED(ctx);
     lz_start<Real><<<grid, kThreads, 0, stream>>>(v, w, P.norm, V, hw, src, mw, u, P.alpha,
-                                                  P.stride, counter);
+                                                  counter);
     RPB_LAUNCHED(ctx);
     return RPB_OK;
   }
@@ -1878,7 +1889,7 @@ int iterate_processes(rpb_ctx *ctx, const SegView &v, const SegGrids &g, int k, 
     return one_process(v) ? run(std::true_type{}) : run(std::false_type{});
   } else {
     if (!dotted) {
-      lz_dot<<<all, kThreads, 0, stream>>>(v, vk, u, 1, P.alpha, P.stride);
+      lz_dot<<<all, kThreads, 0, stream>>>(v, vk, u, 1, P.alpha);
       RPB_LAUNCHED(ctx);
     }
     const int ept = ept_of(g);
@@ -1886,10 +1897,10 @@ int iterate_processes(rpb_ctx *ctx, const SegView &v, const SegGrids &g, int k, 
       constexpr int kE = decltype(E)::value;
       constexpr bool kR = decltype(R)::value;
       const dim3 grid = kE == 1 ? g.one.grid : g.four.grid;
-      lz_dots<kE><<<grid, kThreads, 0, stream>>>(v, k, V, u, P.alpha, P.stride, P.dots, P.nb);
+      lz_dots<kE><<<grid, kThreads, 0, stream>>>(v, k, V, u, P.alpha, P.dots);
       RPB_LAUNCHED(ctx);
-      lz_update<kE, Real, kR><<<grid, kThreads, 0, stream>>>(v, k, tol, V, u, P.dots, P.nb,
-                                                             write_next, hw, src, counter, rep);
+      lz_update<kE, Real, kR><<<grid, kThreads, 0, stream>>>(v, k, tol, V, u, P.dots, write_next,
+                                                             hw, src, counter, rep);
       RPB_LAUNCHED(ctx);
       return kR ? RPB_OK : root();
     };
@@ -2002,9 +2013,6 @@ int lanczos_run(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const double
   if (!V) return st;
   double *u = static_cast<double *>(workspace(ctx, WS_VEC_A, size_t(m3) * sizeof(double), &st));
   if (!u) return st;
-  LzPartials P;
-  const SegGrids grids = one_process_grids(m3);
-  RPB_TRY(lz_partials(ctx, 1, m3, grids, &P));
   LzState *ls = static_cast<LzState *>(workspace(ctx, WS_SMALL, kSmallBytes, &st));
   if (!ls) return st;
   LzEig *eig = static_cast<LzEig *>(workspace(ctx, WS_LZEIG, sizeof(LzEig), &st));
@@ -2033,6 +2041,9 @@ int lanczos_run(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const double
     }
     const double *hw = prepack ? packed_weights(g) : nullptr;
     const SegView view{nullptr, nullptr, ls, nullptr, eig, 1, m3, nullptr, nullptr};
+    const SegGrids grids = one_process_grids(m3);
+    LzPartials P;
+    RPB_TRY(lz_partials(ctx, view, grids, f64, true, &P));
     if (f64)
       RPB_TRY(start_processes(ctx, view, grids, w, P, V, hw, static_cast<double *>(src), mw, u,
                               nullptr, stream));
@@ -2125,11 +2136,9 @@ int lanczos_segments(rpb_ctx *ctx, const Batch &b, const double *L, double *t, c
                      LzStatus *status_host, hipStream_t stream, const double *mw = nullptr) {
   const int64_t m3 = 3 * b.n;
   const int nsys = b.nsys;
-  int64_t longest = 0;
   bool fused = true;            // every system small enough for one workgroup per iteration
   for (int s = 0; s < nsys; ++s) {
     const int64_t len = 3 * (b.host_offs[s + 1] - b.host_offs[s]);
-    longest = std::max(longest, len);
     fused = fused && len <= kFusedSegment;
   }
   int st;
@@ -2138,9 +2147,7 @@ int lanczos_segments(rpb_ctx *ctx, const Batch &b, const double *L, double *t, c
   if (!V) return st;
   double *u = static_cast<double *>(workspace(ctx, WS_VEC_A, size_t(m3) * sizeof(double), &st));
   if (!u) return st;
-  LzPartials P;
   const SegGrids grids = seg_grids(b);
-  RPB_TRY(lz_partials(ctx, nsys, longest, grids, &P));
   const size_t states_bytes = size_t(nsys) * sizeof(LzState);
   const size_t status_off = lz_status_offset(nsys);
   char *lz = static_cast<char *>(
@@ -2151,6 +2158,8 @@ int lanczos_segments(rpb_ctx *ctx, const Batch &b, const double *L, double *t, c
   const SegView v{b.offs, b.sys_of, reinterpret_cast<LzState *>(lz),
                   reinterpret_cast<int *>(lz + states_bytes), eig, nsys, m3,
                   grids.one.list, grids.four.list};
+  LzPartials P;
+  RPB_TRY(lz_partials(ctx, v, grids, f64, !fused, &P));
   LzStatus *status_dev = reinterpret_cast<LzStatus *>(lz + status_off);
   const unsigned ns = unsigned(nsys);
   // every process reports each iteration into its word of the pinned buffer
@@ -2177,7 +2186,7 @@ int lanczos_segments(rpb_ctx *ctx, const Batch &b, const double *L, double *t, c
     mark[slot] = ctx->ev_start.size();
     double *vk = V + int64_t(k - 1) * m3;
     SegProduct job{vk, src, v.done, known.empty() ? nullptr : known.data(),
-                   DotOut{fused || !f64 ? nullptr : vk, P.alpha, P.stride}};
+                   DotOut{fused || !f64 ? nullptr : vk, P.alpha}};
     if (L) {   // u = L^-1 M L^-1 vk (rows of finished systems are not used)
       divide_by<<<nblk(m3), kThreads, 0, stream>>>(m3, vk, L, t);
       RPB_LAUNCHED(ctx);

@@ -1178,13 +1178,12 @@ __global__ __launch_bounds__(kBlock) void pair_kernel_f64_sym_batched(
 // System s's partials start at part_base[s] and cover its whole triangle (one chunk).  As
 // reduce_sym_chunk with G threads per (component, row) and W wavefronts of 64 of them per
 // workgroup, all of one system (blocks: a BlockList's list of 64 W values); dpart: the system's
-// partials of dotv . vel at dpart[s * dstride].
+// partials of dotv . vel from dpart[first_partial(3 offs[s], s, 64)].
 template <typename Part, int G, int W>
 __global__ __launch_bounds__(64 * G * W) void reduce_partials_sym_batched(
     SymBatchArgs b, const int2 *__restrict__ blocks, const Part *__restrict__ partial,
     const double *__restrict__ h, double scale, double *__restrict__ vel,
-    const double *__restrict__ dotv, double *__restrict__ dpart,
-    int64_t dstride) {
+    const double *__restrict__ dotv, double *__restrict__ dpart) {
   static_assert(G == 1 || W == 1, "the group sums of one set of rows");
   __shared__ double sh[G * 64];
   int s, blk;
@@ -1217,7 +1216,8 @@ __global__ __launch_bounds__(64 * G * W) void reduce_partials_sym_batched(
     v *= scale * h[row];
     vel[3 * row + d] = v;
   }
-  if (dotv) store_dot_partial(live, v, dotv, 3 * row + d, dpart + s * dstride + set);
+  if (dotv) store_dot_partial(live, v, dotv, 3 * row + d,
+                              dpart + first_partial(3 * b.offs[s], s, 64) + set);
 }
 
 // The same sums, bit for bit, by one thread per (component, row) of the whole batch, without dotv: no
@@ -2088,7 +2088,6 @@ int matvec_batched_sym(rpb_ctx *ctx, const rpb_params *p, const Batch &b, const 
   const double scale = 1.0 / (8.0 * M_PI * p->eta * p->a);
   const double *dotv = dot ? dot->v : nullptr;
   double *dpart = dot ? dot->part : nullptr;
-  const int64_t dstride = dot ? dot->stride : 0;
   if (dotv) dot->done = true;
   auto reduce = [&](auto G, auto W) {
     constexpr int kG = decltype(G)::value, kW = decltype(W)::value;
@@ -2097,10 +2096,10 @@ int matvec_batched_sym(rpb_ctx *ctx, const rpb_params *p, const Batch &b, const 
     const BlockList &bl = b.blocks[kind];
     if (f64)
       reduce_partials_sym_batched<double, kG, kW><<<bl.grid, 64 * kG * kW, 0, stream>>>(
-          args, bl.list, static_cast<const double *>(part), h, scale, vel, dotv, dpart, dstride);
+          args, bl.list, static_cast<const double *>(part), h, scale, vel, dotv, dpart);
     else
       reduce_partials_sym_batched<float, kG, kW><<<bl.grid, 64 * kG * kW, 0, stream>>>(
-          args, bl.list, static_cast<const float *>(part), h, scale, vel, dotv, dpart, dstride);
+          args, bl.list, static_cast<const float *>(part), h, scale, vel, dotv, dpart);
   };
   auto rows = [&](auto G) {
     constexpr int kG = decltype(G)::value;

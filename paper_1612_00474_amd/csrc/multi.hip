@@ -600,7 +600,7 @@ int matvec_multi(rpb_ctx *ctx, const rpb_params *p, const Packed &g, int nvec, c
       out.p[s] = vel + off;
       if (dot && dot->v) {
         out.v[s] = dot->v + off;
-        out.dot[s] = dot->part + int64_t(ids[g0 + s]) * dot->stride;
+        out.dot[s] = dot->part + first_partial(int64_t(off), ids[g0 + s], 64);
       }
     }
     return multi_launch<K, false>(ctx, p, g, in, nullptr, out, stream, skip);

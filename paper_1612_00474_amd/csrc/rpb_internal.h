@@ -301,12 +301,18 @@ const double *packed_weights(const Packed &g);
 // H-weighted force, f[c * n + i] = H_i F_i,c (the product in float64, then rounded), rows
 // 3..5 the H-weighted torque divided by the radius.
 void *source_buffer(rpb_ctx *ctx, const Packed &g, int *status);
+// Where the partials of system s start, one per `values` values, when its values start at e0: systems
+// of `len` values take ceil(len / values) of them (one if empty) and never overlap, since
+// floor(x) + ceil(y) <= floor(x + y) + 1.  In all, below 3 n / values + nsys + 1.
+__host__ __device__ inline int64_t first_partial(int64_t e0, int64_t s, int64_t values) {
+  return e0 / values + s;
+}
 // Partials of v . u that a product u = M v can take in its reduction: one per 64 rows of each
-// system, partial q of system s at part[s * stride + q].  `done` is set by the products that did.
+// system, partial q of system s at part[first_partial(3 offs[s], s, 64) + q].  `done` is set by the
+// products that did.
 struct DotOut {
   const double *v = nullptr;   // NULL: not wanted
   double *part = nullptr;
-  int64_t stride = 0;
   bool done = false;
 };
 // matvec_packed from sources already in `src` (has_t: a torque among them).

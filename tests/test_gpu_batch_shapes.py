@@ -178,3 +178,35 @@ def test_status_words_cost_little(ctx, precision):
         return t
 
     assert eager(14) - eager(2) < 1.2 * (captured(14) - captured(2))
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("sizes", [[8] * 4096, [20_000] + [16] * 2000])
+def test_lanczos_workspace(precision, sizes):
+    """A batched solve allocates what its processes need (an eigendecomposition and a state each, the
+    basis, and partial sums), not the longest system's partial sums for each of them."""
+    import torch
+    require_gpu()
+    from paper_1612_00474_amd import Context
+    rng = np.random.default_rng(18)
+    parts = {n: _system(n, rng) for n in set(sizes)}
+    pos = dev(np.vstack([parts[n] for n in sizes]))
+    w = dev(rng.standard_normal(tuple(pos.shape)))
+    out = torch.empty_like(pos)
+    m = 16
+    c = Context(0)   # what the driver allocates for kernels on their first launch
+    c.lanczos_batched(pos, _offsets(sizes), w, 1e-3, m, precision, out=out, allow_noconv=True)
+    c.close()
+    c = Context(0)
+    c.matvec_batched(pos, _offsets(sizes), w, precision=precision)   # the product's workspace
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    c.lanczos_batched(pos, _offsets(sizes), w, 1e-3, m, precision, out=out, allow_noconv=True)
+    torch.cuda.synchronize()
+    grown = before - torch.cuda.mem_get_info()[0]
+    c.close()
+    # 64 x 64 eigenvectors, 64 eigenvalues and five 64-vectors of state per process; m + 2 vectors;
+    # 16 partials of 67 sums per process (the mixed form); an eighth and 16 MiB for the vectors of
+    # the product that are counted before and for the pieces that the driver hands out
+    need = len(sizes) * 8 * (64 * 64 + 6 * 64 + 16 * 67) + 3 * 8 * pos.shape[0] * (m + 2)
+    assert grown <= 1.125 * need + (16 << 20), (grown / 2**20, need / 2**20)
