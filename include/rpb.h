@@ -343,7 +343,9 @@ void rpb_step_graph_destroy(rpb_graph *g);
  *
  * One shape per precision.  Single-system products: tpt, targets per lane of the pair kernels
  * (1, 2 or 4; 4 applies to the symmetric kernel, the ordered kernel then takes 2; in float64 the
- * symmetric kernel takes at most tpt, at most 2, and picks its tile by n); target_wgs,
+ * symmetric kernel takes at most tpt, at most 2, and picks its tile by n, and the tuner keeps a
+ * count of its own for the float64 drift of mixed steps, which setting another tpt resets to it);
+ * target_wgs,
  * workgroups the ordered kernel aims for when splitting the sources into chunks; symmetric,
  * whole-system products use the symmetric tile-pair kernel (M_ij = M_ji^T: each unordered pair
  * evaluated once, both directions applied; with torques both coupling directions come from the
@@ -358,7 +360,8 @@ void rpb_step_graph_destroy(rpb_graph *g);
  * p->precision on the given configuration (force-only products, `reps` launches each, HIP
  * events on `stream`); nsys = 1 tunes the single-system fields, nsys > 1 the batched ones.
  * The fastest is kept in the context and cached per (precision, single/batched,
- * floor(log2 n_total)); a cached shape is reused without timing (best_ms_out = -1 then).
+ * floor(log2 n_total) and, for single float64 systems, box or none and the size from which tpt
+ * limits the tile); a cached shape is reused without timing (best_ms_out = -1 then).
  * Results depend on the shape only through the order of the floating-point summation. */
 typedef struct {
   int tpt;

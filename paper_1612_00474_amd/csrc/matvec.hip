@@ -1629,6 +1629,8 @@ inline TileShape sym64_shape(int64_t n, int tpt) {
   return n < 96000 ? TileShape{2, 2, 4} : TileShape{2, 4, 4};
 }
 
+bool f64_tile_follows_tpt(int64_t n) { return sym64_shape(n, 1).tpt != sym64_shape(n, 2).tpt; }
+
 // Calls fn(tpt, wt, waves) with the three as std::integral_constant values.
 template <typename Fn>
 void with_tile(TileShape t, Fn &&fn) {
@@ -1673,6 +1675,7 @@ int matvec_symmetric(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const v
   double *dpart = dot ? dot->part : nullptr;
   if (dotv) dot->done = true;
   const bool tiles = f64 && !(expanded && !torque);
+  if (f64 && !tiles) tpt = ctx->tune.s[RPB_FP64].drift_tpt;
   const TileShape tile = sym64_shape(n, tpt);
   SymArgs a{n, tiles ? int64_t(64) * tile.wt * tile.tpt : int64_t(kBlock) * tpt, 0, n};
   a.skip = skip;

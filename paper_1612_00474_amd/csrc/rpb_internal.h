@@ -77,6 +77,7 @@ struct Shape {
   int symmetric;        // 1: whole-system products evaluate each unordered pair once
   int batch_tpt;        // targets per lane of the batched kernel
   int batch_symmetric;  // 1: batched products evaluate each unordered pair once
+  int drift_tpt = 2;    // float64: targets per lane of the drift of mixed steps (expanded_drift)
 };
 // One shape per precision, indexed by rpb_precision (RPB_FP64 = 0, RPB_MIXED = 1).
 struct Tuning {
@@ -90,7 +91,7 @@ struct rpb_ctx {
   // walked in chunks of at most this many bytes); RPB_CHUNK_KIB overrides it
   size_t chunk_bytes = rpb::kMaxChunkBytes;
   rpb::Tuning tune;
-  std::map<std::tuple<int, int, int>, rpb::Tuning> tune_cache;   // (precision, batched, log2 n)
+  std::map<std::tuple<int, int, int, int>, rpb::Tuning> tune_cache;   // keys: tune.cpp
   std::string err;
   rpb::DevBuf ws[rpb::WS_NSLOTS];
   void *host_pinned = nullptr;          // small pinned host buffer for device scalars
@@ -330,6 +331,10 @@ int matvec_shifted(rpb_ctx *ctx, const rpb_params *p, int64_t n, const double *p
 int matvec_prepacked(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const void *src,
                      double *vel, hipStream_t stream, const int *skip = nullptr,
                      DotOut *dot = nullptr);
+
+// Whether float64 whole-system products of n spheres take a smaller tile with one target per lane
+// than with two (sym64_shape).  Below that size the tile does not follow tpt.
+bool f64_tile_follows_tpt(int64_t n);
 
 // Sources that the whole-system force product of `g` sums in one run when it is a single tile of
 // the symmetric kernel (any positive number in float64, whose sums may be regrouped), else 0.

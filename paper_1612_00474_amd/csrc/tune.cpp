@@ -3,8 +3,9 @@
 // Candidates (targets per lane, symmetric or ordered evaluation, source split / work-item size,
 // workgroup count) are timed with HIP events on the caller's configuration and the fastest is
 // kept in the context; single-system and batched products have fields of their own.  Results
-// are cached per (precision, single or batched, log2 of the sphere count), so a later call
-// with a similar problem reuses the choice without timing.
+// are cached per (precision, single or batched, log2 of the sphere count and, for single float64
+// systems, whether the tile follows tpt and whether there is a box), so a later call with a similar problem reuses the choice
+// without timing.
 #include <cmath>
 #include <vector>
 
@@ -14,7 +15,7 @@ namespace rpb {
 
 namespace {
 
-using Key = std::tuple<int, int, int>;   // precision, batched, log2(n)
+using Key = std::tuple<int, int, int, int>;   // precision, batched, log2(n), float64 tile rule
 
 std::map<Key, Tuning> &cache(rpb_ctx *ctx) { return ctx->tune_cache; }
 
@@ -85,8 +86,9 @@ int rpb_set_tuning(rpb_ctx *ctx, const rpb_tuning *t) {
   }
   for (int q = 0; q < 2; ++q) {
     const rpb_shape &v = *src[q];
-    ctx->tune.s[q] = Shape{v.tpt,       v.target_wgs, v.batch_chunk,    v.batch_wgs,
-                           v.symmetric, v.batch_tpt,  v.batch_symmetric};
+    Shape &s = ctx->tune.s[q];
+    s = Shape{v.tpt,       v.target_wgs, v.batch_chunk,     v.batch_wgs,
+              v.symmetric, v.batch_tpt,  v.batch_symmetric, s.tpt == v.tpt ? s.drift_tpt : v.tpt};
   }
   return RPB_OK;
 }
@@ -107,7 +109,16 @@ int rpb_autotune(rpb_ctx *ctx, const rpb_params *p, int32_t nsys, const int64_t 
   RPB_TRY(check_finite(ctx, pos, n, stream));
   const bool batched = nsys > 1;
   const int q = p->precision == RPB_FP64 ? RPB_FP64 : RPB_MIXED;
-  const Key key{q, batched ? 1 : 0, int(std::floor(std::log2(double(n))))};
+  // Float64 products of single systems.  Where the tile follows tpt, one target per lane loses without
+  // a box (8,191 spheres: 135 us against 118, 16,384: 453 against 376; free space: 96 against 82,
+  // 298 against 230) and is not offered; in a box it wins at some sizes (8,191: 722 against 793,
+  // 12,000: 1,740 against 1,587), so it is.  Below that size both are the same launch, and two stands.
+  // The drift of mixed steps has its own count (4,099 spheres: 127 us with one, 148 with two; 8,191:
+  // 286 and 300; 16,384: 960 and 902).
+  const bool f64 = q == RPB_FP64 && !batched, box = p->lx > 0.0;
+  const bool follows = f64 && f64_tile_follows_tpt(n);
+  const Key key{q, batched ? 1 : 0, int(std::floor(std::log2(double(n)))),
+                f64 ? (follows ? 1 : 0) + (box ? 2 : 0) : 0};
   auto &tab = cache(ctx);
   double best_ms = -1.0;
   auto it = tab.find(key);
@@ -140,7 +151,7 @@ int rpb_autotune(rpb_ctx *ctx, const rpb_params *p, int32_t nsys, const int64_t 
         Shape c = base;
         c.tpt = tpt;
         c.symmetric = 1;
-        cands.push_back(c);
+        if (!f64 || tpt == 2 || n <= 256 || (follows && box)) cands.push_back(c);
         c.symmetric = 0;
         for (int wgs : {2048, 4096, 8192, 16384}) {
           c.target_wgs = wgs;
@@ -157,21 +168,30 @@ int rpb_autotune(rpb_ctx *ctx, const rpb_params *p, int32_t nsys, const int64_t 
       cands.push_back(c);
     }
     int rc = RPB_OK;
-    double best_rank = -1.0;
     for (const Shape &sh : cands) {
       ctx->tune.s[q] = sh;
       double ms = 0.0;
       rc = time_candidate(ctx, p, nsys, offs, pos, reps, false, stream, &ms);
       if (rc != RPB_OK) break;
-      // a float64 shape also serves the drift of mixed steps, whose kernel follows it more closely
-      double drift_ms = ms;
-      if (q == RPB_FP64 && !batched && sh.symmetric)
-        rc = time_candidate(ctx, p, nsys, offs, pos, reps, true, stream, &drift_ms);
-      if (rc != RPB_OK) break;
-      if (best_rank < 0.0 || ms + drift_ms < best_rank) {
-        best_rank = ms + drift_ms;
+      if (best_ms < 0.0 || ms < best_ms) {
         best_ms = ms;
         best = sh;
+      }
+    }
+    if (f64 && rc == RPB_OK) {
+      double best_drift = -1.0;
+      for (int tpt : {1, 2}) {
+        if (tpt == 2 && n <= 256) continue;
+        ctx->tune.s[q] = base;
+        ctx->tune.s[q].symmetric = 1;
+        ctx->tune.s[q].drift_tpt = tpt;
+        double ms = 0.0;
+        rc = time_candidate(ctx, p, nsys, offs, pos, reps, true, stream, &ms);
+        if (rc != RPB_OK) break;
+        if (best_drift < 0.0 || ms < best_drift) {
+          best_drift = ms;
+          best.drift_tpt = tpt;
+        }
       }
     }
     ctx->timing = timing;
