@@ -35,7 +35,6 @@ struct LzState {
   double beta[kMaxKrylov];
   double y[kMaxKrylov];
   double yprev[kMaxKrylov];
-  double h[kMaxKrylov];
   double wnorm;
   int eig_m;      // order of the eigendecomposition held in LzEig (0: none)
   int pad_;
@@ -776,7 +775,7 @@ __global__ __launch_bounds__(kThreads) void lz_dot(SegView v, const double *__re
 __device__ __forceinline__ void reset_state(const SegView &v, int s, double wn) {
   LzState *st = v.st + s;
   const int t = threadIdx.x;
-  if (t < kMaxKrylov) st->alpha[t] = st->beta[t] = st->y[t] = st->yprev[t] = st->h[t] = 0.0;
+  if (t < kMaxKrylov) st->alpha[t] = st->beta[t] = st->y[t] = st->yprev[t] = 0.0;
   if (t == 0) {
     st->wnorm = wn;
     st->eig_m = 0;
@@ -1027,7 +1026,6 @@ __global__ __launch_bounds__(kThreads, 2) void lz_update(
   }
   if (blk != 0) return;
   if (t == 0) st->beta[k - 1] = beta;
-  if (t < k) st->h[t] = hs[t];
   if constexpr (ROOT) {
     __syncthreads();
     root_and_stop(v, s, k, tol, rep);
@@ -1183,7 +1181,6 @@ __global__ __launch_bounds__(kThreads) void ord_update(SegView v, int k,
     if (t < k) hs[t] = finish_sum<TREE>(p + int64_t(t) * NB);
   }
   __syncthreads();
-  if (blockIdx.x == 0 && t < k) st->h[t] = hs[t];
   const double *vk = V + int64_t(k - 1) * v.m3;
   const double *vprev = k > 1 ? V + int64_t(k - 2) * v.m3 : nullptr;
   const double al = st->alpha[k - 1], be = vprev ? st->beta[k - 2] : 0.0;
@@ -1270,8 +1267,8 @@ __device__ __forceinline__ void group_sums(double (&v)[NV], double *sh) {
   __syncthreads();
 }
 
-// The vector work (alpha_k, the recurrence, the re-orthogonalisation, beta_k; alpha, beta and
-// the projections h stored in st), leaving the unnormalised u; returns beta_k to every thread.
+// The vector work (alpha_k, the recurrence, the re-orthogonalisation, beta_k; alpha and beta
+// stored in st), leaving the unnormalised u; returns beta_k to every thread.
 // The segment has at most kEpt values per thread (kFusedSegment in all), so each thread keeps
 // its values of u, v_k and v_{k-1} in registers, and each pass over the basis issues all its
 // loads at once; the sums and their order are those of one value at a time.
@@ -1384,7 +1381,6 @@ __device__ __forceinline__ double lanczos_vec_values(LzState *__restrict__ st,
     st->alpha[k - 1] = alpha;
     st->beta[k - 1] = beta;
   }
-  if (t < k) st->h[t] = hs[t];
   return beta;
 }
 
@@ -1666,7 +1662,6 @@ __global__ __launch_bounds__(kSmallThreads) void lz_small(
         st->alpha[nv - 1] = alpha;
         st->beta[nv - 1] = beta;
       }
-      if (t < nv) st->h[t] = hs[t];
     }
   }
   if (k > A.max_iter) return;
@@ -2056,7 +2051,7 @@ int lanczos_run(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const double
     int next_q = 1;              // first iteration whose status the host has not read
     // The host reads the status of iteration m only after iteration m + 1 has been enqueued, so
     // the device never idles while the host decides.  An iteration past the stop leaves the
-    // result unchanged: its product returns at once, and its vector work touches only u, h, V's
+    // result unchanged: its product returns at once, and its vector work touches only u, V's
     // next column, the packed sources and entries of alpha and beta past the last iteration.
     for (int k = 1; k <= max_iter && o.reason == 0; ++k) {
       const int slot = k % kLzRing;

@@ -502,11 +502,12 @@ __device__ __forceinline__ void sym_apply(const Coef &c, Real fx, Real fy, Real 
 // The coupling terms of both directions, (o) += M^C_ij T_j and (p) += M^C_ji T_i (tq: T_j,
 // uq: T_i).  M^C has no symmetry, but M^C_ji is the same expression with r -> -r and the image
 // height hh = z~_j/|R| replaced by z~_i/|R|, so everything else (|R|, e_z, X, the unbounded
-// coefficient) is shared.
+// coefficient) is shared.  Float64 with a wall takes sym_apply_both.
 template <typename Real, bool WALL>
 __device__ __forceinline__ void sym_apply_torque(const SymCoef<Real> &c, const PairConsts<Real> &k,
                                                  Real zi, const Real *tq, const Real *uq, Real &ox,
                                                  Real &oy, Real &oz, Real &px, Real &py, Real &pz) {
+  static_assert(!(WALL && std::is_same<Real, double>::value), "sym_apply_both's");
   const Real dx = c.dx, dy = c.dy, dz = c.dz, cT = c.cT;
   if (!WALL) {   // cT T_j x r into o, cT T_i x (-r) into p
     ox += cT * (tq[1] * dz - tq[2] * dy);
@@ -515,31 +516,6 @@ __device__ __forceinline__ void sym_apply_torque(const SymCoef<Real> &c, const P
     px -= cT * (uq[1] * dz - uq[2] * dy);
     py -= cT * (uq[2] * dx - uq[0] * dz);
     pz -= cT * (uq[0] * dy - uq[1] * dx);
-    return;
-  }
-  if constexpr (std::is_same<Real, double>::value) {
-    // per direction, k = (r_x, r_y, 0) x T = (r_y T_z, -r_x T_z, K):
-    //   u_x,y += al k_x,y + be (T_y, -T_x) - K ec (r_x, r_y),   u_z += K cz; r -> -r for j <- i
-    {
-      const Real K = dx * tq[1] - dy * tq[0], P = c.al * tq[2], ga = -K * c.ec[0];
-      ox += P * dy;
-      ox += c.be[0] * tq[1];
-      ox += ga * dx;
-      oy -= P * dx;
-      oy += ga * dy;
-      oy -= c.be[0] * tq[0];
-      oz += K * c.cz[0];
-    }
-    {
-      const Real K = dy * uq[0] - dx * uq[1], P = c.al * uq[2], ga = -K * c.ec[1];
-      px -= P * dy;
-      px += c.be[1] * uq[1];
-      px -= ga * dx;
-      py += P * dx;
-      py -= ga * dy;
-      py -= c.be[1] * uq[0];
-      pz += K * c.cz[1];
-    }
     return;
   }
   const Real iR = c.iR, iR2 = c.iR2, ez = c.ez, X = c.X, Rz = c.Rz;
@@ -669,10 +645,11 @@ __device__ __forceinline__ void pair_velocity_sym(Real dx, Real dy, Real zi, Rea
   sym_coefficients<Real, FAR_ONLY, TORQUE, WALL>(dx, dy, zi, zj, k, c);
   if constexpr (std::is_same<Real, double>::value && WALL && TORQUE) {
     sym_apply_both(c, fx, fy, fz, gx, gy, gz, tq, uq, ox, oy, oz, px, py, pz);
-    return;
+  } else {
+    sym_apply<Real, WALL>(c, fx, fy, fz, gx, gy, gz, ox, oy, oz, px, py, pz);
+    if constexpr (TORQUE)
+      sym_apply_torque<Real, WALL>(c, k, zi, tq, uq, ox, oy, oz, px, py, pz);
   }
-  sym_apply<Real, WALL>(c, fx, fy, fz, gx, gy, gz, ox, oy, oz, px, py, pz);
-  if (TORQUE) sym_apply_torque<Real, WALL>(c, k, zi, tq, uq, ox, oy, oz, px, py, pz);
 }
 
 __device__ __forceinline__ float round_nearest(float x) { return __builtin_rintf(x); }
