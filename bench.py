@@ -149,6 +149,14 @@ def force_kernel_name(prec: str, shape: dict) -> str:
     return f"pair_kernel_{kind}<false, {shape['tpt']}, true, false>"
 
 
+def lanczos_kernel_name(shape: dict, n: int) -> str:
+    """What the timing records of a float64 step's Lanczos products bracket: up to 512 spheres the
+    launch that takes a whole iteration (vector work and root with the product)."""
+    if n <= 512 and shape["symmetric"]:
+        return "lz_small<double, ...>, whole Lanczos iterations"
+    return force_kernel_name("fp64", shape) + ", force-only products"
+
+
 def parse():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -439,7 +447,7 @@ def run_fp64_sheet(ctx_cls, name, steps, warmup, budget):
             "roofline": None if dom is None else {
                 "bound": "alu", "achieved": dom["tflops_alg"], "peak": PEAK_FP64_TFLOPS,
                 "unit": "TFLOP/s", "frac": dom["tflops_alg"] / PEAK_FP64_TFLOPS,
-                "kernel": force_kernel_name("fp64", shape) + ", force-only products",
+                "kernel": lanczos_kernel_name(shape, w.n),
                 "ms_per_launch": dom["ms_per_launch"]}}
 
 

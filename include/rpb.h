@@ -397,14 +397,16 @@ int rpb_output_check_enable(rpb_ctx *ctx, int enable);
 /* Timing ------------------------------------------------------------------------------------
  *
  * When enabled, the library brackets every launch of the O(N^2) pair kernel with HIP
- * events on the stream it is launched on.  rpb_timing_read() synchronises, returns the
+ * events on the stream it is launched on.  (Unpreconditioned single-system Lanczos solves of up to
+ * 512 spheres take a whole iteration, vector work and root included, in the launch of its product:
+ * there the record is of those launches.)  rpb_timing_read() synchronises, returns the
  * summed kernel time in milliseconds, the number of launches and the number of ordered
  * pair interactions of the launches of kernel variant `kind`, and removes them from the
  * record.  kind = 2 * (precision == RPB_MIXED) + (torque present), plus 4 for the batched
  * kernel; 8 + 2 * (precision == RPB_MIXED) for the multi-vector kernel, whose pair count is
  * n^2 times the vectors of the launch; kind = -1 takes all.  A single-system Lanczos solve
- * enqueues one iteration past its stop before it reads the stop flag; that iteration's
- * launches return at once and are dropped from the record. */
+ * enqueues an iteration or two past its stop before it reads the stop flag; their launches
+ * are dropped from the record. */
 int rpb_timing_enable(rpb_ctx *ctx, int enable);
 int rpb_timing_read(rpb_ctx *ctx, int kind, double *ms_out, int64_t *launches_out,
                     double *pairs_out);

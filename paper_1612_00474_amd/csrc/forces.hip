@@ -452,8 +452,10 @@ __global__ __launch_bounds__(kBlock) void steric_wave(int64_t n, const double *_
 }
 
 // Largest system of steric_wave, without and with a box (whose minimum image costs two divisions a
-// pair).  A call by itself, us, cell list / one wavefront per target: 256: 50.5 / 25, 2,100: 64 /
-// 25.5, 4,099: 62 / 35, 6,000: 69 / 52, 8,191: 68 / 92.
+// pair).  Calls in a row, us, cell list / one wavefront per target:
+//   no box  256: 56 / 20   2,000: 78 / 22   4,000: 65 / 35   6,000: 69 / 54   8,191: 78 / 96
+//   box     256: 61 / 19   2,000: 85 / 26   3,000: 71 / 36   4,000: 76 / 50   6,000: 67 / 85
+// (in a box the two cross near 5,000; the line there stays below).
 constexpr int64_t kWaveMaxN = 6000, kWaveMaxBoxN = 3000;
 
 // Cell side and layout for cutoff `cut`; false when a box holds fewer than three cells per

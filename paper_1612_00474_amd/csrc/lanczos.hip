@@ -69,7 +69,7 @@ LzRing *lz_ring_dev(rpb_ctx *ctx) {
                                     kHostLzRingOffset);
 }
 
-// Tags of a solve: its epoch (from 1, unique in the context until it wraps after 2^24 solves, whose
+// Tags of a solve: its epoch (from 1, unique in the context until it wraps after 2^23 solves, whose
 // pinned buffer starts zeroed), the iteration and, for the processes of a batch, a stop bit.
 constexpr int kTagStop = 0x80;
 __host__ __device__ __forceinline__ int lz_tag(int epoch, int k) { return (epoch << 8) | k; }
@@ -496,7 +496,7 @@ __device__ int eig_update(int m, const LzState *__restrict__ st, LzEig *__restri
 
 // T^{1/2} e_1 without an eigendecomposition, from T^{1/2} = (2/pi) int_0^inf T (T + t^2)^{-1} dt with
 // t = e^x: the trapezoidal rule converges as exp(-pi^2/h) (the integrand's poles lie at
-// distance pi/2 from the real axis), 2e-21 at h = 0.2.  Thread k takes node t_k = sqrt(G) e^{(k -
+// distance pi/2 from the real axis), 4e-22 at h = 0.2.  Thread k takes node t_k = sqrt(G) e^{(k -
 // 191.5) h}, G >= |T| by Gershgorin, and solves (T + t_k^2) x = e_1 by elimination from the last
 // row; the solutions are independent chains of m reciprocals.  Nodes below sqrt(G) add t (e_1 -
 // t^2 x) and the others t T x (neither form cancels by more than |T|^{1/2}); what lies below t_0
@@ -705,8 +705,8 @@ __device__ __forceinline__ void post_status(const LzState *__restrict__ st, LzRi
 //              stop test.
 // The work is a few reads of vectors that fit the caches; what bounds it is the ~4.4 us that each
 // dependent launch costs, so the count is what matters: six kernels per iteration before (two
-// for alpha, dots, their sum, update, beta and root, scaling), 42 -> 25 us per iteration at 2,100
-// spheres.
+// for alpha, dots, their sum, update, beta and root, scaling), 93 -> 38 us per iteration at 2,100
+// spheres, product included (92 -> 67 with a mixed product, whose vector work has four kernels).
 
 constexpr int kPartRows = 64;   // rows per partial of alpha
 
@@ -1242,9 +1242,10 @@ constexpr int64_t kFusedSegment = 3 * 512;
 // vectors, by one workgroup, after the product u = M v_k: alpha_k = v_k . u; u -= alpha_k v_k +
 // beta_{k-1} v_{k-1}; the full re-orthogonalisation u -= V_k (V_k^T u); beta_k = |u|; the
 // eigensolve of T_k with its stop test (tridiag_body); and, unless the process stopped,
-// v_{k+1} = u / beta_k (when write_next).  The steps and their order are those of the separate
-// kernels; the sums are taken over the workgroup instead of in two stages, so small systems
-// need one launch per iteration instead of about ten.
+// v_{k+1} = u / beta_k (when write_next).  The steps are those of the separate kernels, beta
+// as the norm of the re-orthogonalised u (as the ord_ kernels take it, not lz_update); the sums
+// are taken over the workgroup instead of in two stages, so that the vector work, root and stop
+// test of small systems are one launch per iteration instead of two to five.
 // Sums over the workgroup of NV values per thread, each returned to every thread: a butterfly
 // over the wavefront's 64 lanes, then the kThreads/64 wavefront sums added in a fixed order.
 template <int NV>
@@ -1433,9 +1434,9 @@ __device__ void lanczos_step_body(LzState *__restrict__ st, LzEig *__restrict__ 
 // wavefront per row; the last workgroup takes the root, whose coefficients the launches before
 // have stored.  All basis vectors' values are loaded at once into registers (twelve wavefronts,
 // one or two values per thread), which the projection then reuses.  What bounds an iteration is the
-// latency of those loads and of the sums, and the root's chain beside them.  256 spheres, float64, 25
-// iterations to 1e-6: 790 -> 434 us per solve (four kernels per iteration on two streams before, the
-// root's issued by a helper thread).
+// latency of those loads and of the sums, and the root's chain beside them.  256 spheres, float64:
+// 31.6 -> 13.4 us per iteration, 25 of them to 1e-6 870 -> 345 us per solve (four kernels per
+// iteration on two streams before, the root's issued by a helper thread).
 constexpr int kSmallThreads = 768;
 
 struct SmallArgs {

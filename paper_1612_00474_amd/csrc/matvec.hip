@@ -34,8 +34,9 @@ namespace {
 
 // Packed geometry of positions and, with src, the packed sources (as pack_vectors), with the
 // finite check of the positions when c.w is set.  One launch where three did this (clear, check,
-// copy of the flag, and a synchronisation, before the two packings), bound by its launch: a product
-// of 256 float64 spheres 36.7 -> 20.0 us, of 4,099 74 -> 61 us.
+// copy of the flag, and a synchronisation, before the two packings), bound by its launch.  The host
+// reads the verdict while the product runs, so calls in a row no longer drain the stream in between:
+// a product of 256 float64 spheres 36.8 -> 18.8 us in a row, 59 -> 41 by itself on an idle device.
 template <typename Real>
 __global__ void pack_all(int64_t n, const double *__restrict__ pos, double a, int wall,
                          double *__restrict__ geom, const double *__restrict__ force,
@@ -1615,12 +1616,17 @@ struct TileShape {
 // partial sums (n / tile per row).  Force-only products, us, tiles of 64 / 128 / 256 / 512:
 //   2,100: 18.9 / 23.6 / 66 / 228      4,099: 40.5 / 44 / 68 / 228     8,191: 126 / 115 / 145 / 231
 //   16,384: 472 / 372 / 385 / 508      32,768: 1824 / 1395 / 1377 / 1484
-//   65,536: 6849 / 5620 / 5381 / 5431
+//   65,536: 6849 / 5620 / 5381 / 5431     96,001: - / - / 11,735 / 11,700
+//   200,000: - / - / 50,700 / 50,100     262,144: - / - / 87,090 / 86,500
 // With one target per lane, 64 / 256: 8,191: 126 / 176, 16,384: 472 / 449.  (Four targets per lane,
 // tiles of 1,024, were slower at every size: 6614 us at 65,536.)
 // Below 1,500 spheres (300 pairs of 64-sphere tiles) a pair's 64 rotation steps are dealt to eight
 // wavefronts instead of four (256: 10.9 -> 9.3 us, 1,024: 11.4 -> 10.1; 2,100: 17.9 and 17.5,
 // with torques 21.6 and 24.4).
+// The lines were drawn without a box.  In one, nine images per pair fill the device sooner and the
+// 64-sphere tile of one target per lane stays ahead (64 / 128 / 256: 6,000: 405 / 455 / 721, 8,191:
+// 722 / 793 / 1,038, 16,384: 2,779 / 2,881 / 3,063, 32,768: 10,950 / 11,159 / 11,253); the tuner can
+// choose it up to 12,000.
 inline TileShape sym64_shape(int64_t n, int tpt) {
   if (n < 1500) return TileShape{1, 1, 8};
   if (tpt == 1) return n < 12000 ? TileShape{1, 1, 4} : TileShape{1, 4, 4};
