@@ -618,7 +618,11 @@ __device__ void tridiag_body(int m, double tol, LzState *__restrict__ st, LzEig 
   __shared__ double pool[kRootPool];
   __shared__ double Rz[kMaxKrylov];   // sqrt(lambda_k) q_k[0]
   double yr = 0.0;
-  const int fast = root_quadrature(m, st, L, pool, yr);
+  // The pivots from the last row (the first entry of each trailing block's inverse) never grow with
+  // m and the bound on |T| never falls, so a T_m whose predecessor was left to the
+  // eigendecomposition is left to it too.
+  const bool left = m > 1 && st->eig_m == m - 1;
+  const int fast = left ? 0 : root_quadrature(m, st, L, pool, yr);
   int failed = 0;
   bool indefinite = false;
   const int lane = threadIdx.x;
