@@ -1713,17 +1713,19 @@ __global__ __launch_bounds__(kThreads) void tridiag_sequence(int m, LzState *__r
   }
 }
 
-// lanczos_step_body for every live system, one workgroup each (segments <= kFusedSegment); src,
-// counter and rep as in lz_update.
+// lanczos_step_body for every live process, one workgroup each (segments <= kFusedSegment); src,
+// counter and rep as in lz_update.  Batches, and the single solves that lz_small does not take
+// (preconditioned ones, shapes of more than one tile).
 template <typename Real>
 __global__ __launch_bounds__(kThreads) void seg_lanczos_step(
     SegView v, double *__restrict__ V, double *__restrict__ u, int k, double tol, int write_next,
     const double *__restrict__ hw, Real *__restrict__ src, int *counter, LzReport rep) {
   const int s = blockIdx.x;
   if (counter && s == 0 && threadIdx.x == 0) counter[0] = 0;
-  if (v.done[s]) return;
   LzState *st = v.st + s;
-  const int64_t e0 = 3 * v.offs[s], e1 = 3 * v.offs[s + 1];
+  if (v.done ? v.done[s] : st->reason) return;   // past its stop nobody reads a status
+  int64_t e0, e1;
+  seg_range(v, s, e0, e1);
   lanczos_step_body(st, v.eig + s, V, u, v.m3, e0, e1, k, tol, write_next != 0);
   if (src && write_next && st->reason == 0) {
     const double *next = V + int64_t(k) * v.m3;
@@ -1732,7 +1734,9 @@ __global__ __launch_bounds__(kThreads) void seg_lanczos_step(
       src[(i - 3 * sp) * (v.m3 / 3) + sp] = Real(hw[sp] * next[i]);
     }
   }
-  if (threadIdx.x == 0) report_stop(v, s, k, st->reason != 0, rep);
+  if (threadIdx.x != 0) return;
+  if (rep.ring) post_status(st, rep.ring, lz_tag(rep.epoch, k));
+  if (v.done) report_stop(v, s, k, st->reason != 0, rep);
 }
 
 // out = V_m y_m per system (m = the system's own iteration count)
@@ -2043,7 +2047,12 @@ int lanczos_run(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const double
     const SegView view{nullptr, nullptr, ls, nullptr, eig, 1, m3, nullptr, nullptr};
     const SegGrids grids = one_process_grids(m3);
     LzPartials P;
-    RPB_TRY(lz_partials(ctx, view, grids, f64, true, &P));
+    // Small systems: one launch of one workgroup for the vector work, root and stop test instead of
+    // three (float64) or four (mixed).  40 preconditioned iterations, us, separate / one: mixed 64
+    // spheres 1,925 / 1,590, 512: 1,985 / 2,005 (20 iterations 900 / 860); float64 64: 1,635 / 1,460,
+    // 256: 1,750 / 1,665, 512: 1,810 / 1,925.
+    const bool fused = m3 <= (f64 ? kFusedSegment / 2 : kFusedSegment);
+    RPB_TRY(lz_partials(ctx, view, grids, f64, !fused, &P));
     if (f64)
       RPB_TRY(start_processes(ctx, view, grids, w, P, V, hw, static_cast<double *>(src), mw, u,
                               nullptr, stream));
@@ -2072,12 +2081,20 @@ int lanczos_run(rpb_ctx *ctx, const rpb_params *p, const Packed &g, const double
       } else if (k == 1 && mw) {   // M v_1 = (M w) / |w| from the caller's product (lz_start)
         dotted = true;
       } else {   // v_k packed where it was formed
-        DotOut dot{f64 ? vm : nullptr, P.alpha};
+        DotOut dot{f64 && !fused ? vm : nullptr, P.alpha};
         RPB_TRY(matvec_prepacked(ctx, p, g, src, u, stream, stopped, &dot));
         dotted = dot.done;
       }
       const LzReport rep{&ring_dev->slot[slot], nullptr, epoch};
-      if (f64)
+      if (fused) {
+        if (f64)
+          seg_lanczos_step<double><<<1, kThreads, 0, stream>>>(
+              view, V, u, k, tol, k < max_iter, hw, static_cast<double *>(src), nullptr, rep);
+        else
+          seg_lanczos_step<float><<<1, kThreads, 0, stream>>>(
+              view, V, u, k, tol, k < max_iter, hw, static_cast<float *>(src), nullptr, rep);
+        RPB_LAUNCHED(ctx);
+      } else if (f64)
         RPB_TRY(iterate_processes(ctx, view, grids, k, tol, V, u, dotted, P, k < max_iter, hw,
                                   static_cast<double *>(src), nullptr, rep, stream));
       else
