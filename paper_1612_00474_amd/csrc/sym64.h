@@ -81,7 +81,8 @@ __device__ __forceinline__ void sym64_pair(double dx, double dy, double zi, doub
 // and tb = sb over rotation steps 0..32 (steps 1..31 meet each pair of the block once, step 32
 // meets the pairs (l, l + 32) twice and keeps lanes below 32, step 0 is the self pair, taken in
 // one direction), without the steps at which a last block of few spheres has no pair (a launch of
-// four vectors between two events: one sphere 17.1 -> 10.1 us, 64 spheres 16.5).  Every lane of the workgroup calls this (it synchronises).
+// four vectors between two events: one sphere 17.1 -> 10.1 us, 64 spheres 16.5).  Every lane of the
+// workgroup calls this (it synchronises).
 template <int K, bool TQ, int TPT, int WT, int W, bool WALL, bool PERIODIC>
 __device__ __forceinline__ void sym64_tile_pair(const SymArgs &a, const GeomD &g,
                                                 const double *__restrict__ src,
